@@ -31,7 +31,7 @@
 #define SRT_STACK_LDS 16
 #endif
 #ifndef SRT_TRACE_WAVES_PER_EU
-#define SRT_TRACE_WAVES_PER_EU 7
+#define SRT_TRACE_WAVES_PER_EU 8
 #endif
 
 namespace srt {
@@ -42,6 +42,7 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kStackLds = SRT_STACK_LDS;       // traversal stack entries per lane kept in LDS (power of two)
 constexpr int kStackGlobal = kStackMax - kStackLds;  // older entries spill to the workspace
 constexpr int kMaxTraceBlocks = 2048;
+static_assert(int64_t(kMaxTraceBlocks) * kBlock * kStackGlobal < (int64_t(1) << 32), "spill area index exceeds 32 bits");
 // Shading blocks are large: queue slots are reserved with one device-scope atomic per block
 // iteration and queue, and atomics on one address serialise.
 #ifndef SRT_SHADE_BLOCK
@@ -50,14 +51,19 @@ constexpr int kMaxTraceBlocks = 2048;
 constexpr int kShadeBlock = SRT_SHADE_BLOCK;
 constexpr int kShadeWaves = kShadeBlock / 64;
 static_assert((kStackLds & (kStackLds - 1)) == 0, "LDS stack size must be a power of two");
-// The builder emits the 4-wide tree level by level, so nodes 0 .. kLdsNodes-1 are its top levels,
-// which every ray crosses.  A single-scene traversal block copies them into LDS once per launch and
-// reads them from there, off the vector-memory path.  85 nodes are levels 0-3; a deeper copy
-// loses more to waves whose lanes split between LDS and global reads than it saves.
-#ifndef SRT_LDS_NODES
-#define SRT_LDS_NODES 85
+#ifndef SRT_COOP_RAYS
+#define SRT_COOP_RAYS 48
 #endif
-constexpr int kLdsNodes = kQuantNodes ? SRT_LDS_NODES : 0;
+constexpr int kCoopRays = SRT_COOP_RAYS;  // a wave with at most this many rays left shares them between its lanes
+static_assert(kCoopRays >= 0 && kCoopRays <= 64, "one slot per lane at most");
+#ifndef SRT_COOP_SHARE
+#define SRT_COOP_SHARE 8
+#endif
+constexpr int kCoopShare = SRT_COOP_SHARE;  // a hand-over needs at least 1/kCoopShare of the busy lanes in pairs
+#ifndef SRT_MIN_RAYS_LOG2
+#define SRT_MIN_RAYS_LOG2 3
+#endif
+constexpr int kMinRaysLog2 = SRT_MIN_RAYS_LOG2;  // smallest batch of rays a wave starts with
 
 // ---------------------------------------------------------------------------------------------
 // Small vector helpers
@@ -86,15 +92,31 @@ __device__ inline float safe_rcp(float x) {
 
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
-__device__ inline uint64_t lanemask_lt() {
-  const int lane = lane_id();
-  return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+// Number of lanes of `mask` below this one.
+__device__ inline int lanes_below(uint64_t mask) {
+  return int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
+}
+
+// The lane id, computed where it is called (its inputs are no registers, so it need not be kept until then).
+__device__ inline uint32_t fresh_lane() {
+  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+}
+
+// A pointer to global memory held in scalar registers.  The empty asm hides where it came from, so that it
+// is not loaded again, and the cast around it keeps accesses through it global ones (not flat).
+template <class T>
+__device__ __attribute__((always_inline)) inline T* global_scalar(T* p) {
+  typedef __attribute__((address_space(1))) T global_t;
+  global_t* g = (global_t*)p;
+  asm("" : "+s"(g));
+  return (T*)g;
 }
 
 // Next float above a non-negative x (+inf stays +inf): lets a `t < tmax` test admit t == x.
 __device__ inline float next_up(float x) { return x == INFINITY ? x : __int_as_float(__float_as_int(x) + 1); }
 
-__device__ inline uint32_t round64(uint32_t x) { return (x + 63u) & ~63u; }
+// x rounded up to a multiple of 2^log2n
+__device__ inline uint32_t round_up(uint32_t x, int log2n) { return ((x + (1u << log2n) - 1u) >> log2n) << log2n; }
 
 // ---------------------------------------------------------------------------------------------
 // Kernel arguments
@@ -237,28 +259,8 @@ __device__ inline float slab(float lox, float hix, float loy, float hiy, float l
 
 // Entry distances of the four children of BVH4 node `node` (+inf where the ray misses the child's
 // box inside [tmin, tmax]; with HITS_ONLY 0 instead of the distance of a hit child) and their references.
-// Reads node `node` of the LDS array `lnodes`.  Written as LDS instructions because the compiler
-// merges two plain reads of the same shape from LDS and global memory into one flat read, which
-// takes the vector-memory path for every lane.
-__device__ __attribute__((always_inline)) inline void lds_read_node(const float4* lnodes, int node, float4& a,
-                                                                    float4& b, float4& c, float4& d) {
-  typedef __attribute__((address_space(3))) const float4 lds_float4;
-  const uint32_t addr = uint32_t(uintptr_t((const lds_float4*)lnodes)) + uint32_t(node) * 64u;
-  asm volatile(
-      "ds_read_b128 %0, %4\n\t"
-      "ds_read_b128 %1, %4 offset:16\n\t"
-      "ds_read_b128 %2, %4 offset:32\n\t"
-      "ds_read_b128 %3, %4 offset:48\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-      : "v"(addr)
-      : "memory");
-}
-
-// Nodes below `kc` are read from the LDS copy `lnodes` of the top of the tree.
-template <bool HITS_ONLY, bool PERM_GRID>
-__device__ __attribute__((always_inline)) inline void node4_children(const float4* __restrict__ nodes,
-                                                                     const float4* lnodes, int kc, int node,
+template <bool HITS_ONLY>
+__device__ __attribute__((always_inline)) inline void node4_children(const float4* __restrict__ nodes, int node,
                                                                      float3 inv, float3 oi, float tmin, float tmax,
                                                                      float (&t)[4], int (&r)[4]) {
 #if SRT_QNODE
@@ -269,16 +271,12 @@ __device__ __attribute__((always_inline)) inline void node4_children(const float
   // node stores S = 2^24 s, so q 2^-24 (S / d) = q (s / d) exactly and each plane is the same fused
   // multiply-add, to the bit, as with q converted to FP32.  S / d is finite for every direction
   // because vertices lie within RT_MAX_COORD.
-  float4 n0, n1, n2, n3;
-  if (node < kc) {
-    lds_read_node(lnodes, node, n0, n1, n2, n3);
-  } else {
-    const float4* n = nodes + 4 * node;
-    n0 = n[0];
-    n1 = n[1];
-    n2 = n[2];
-    n3 = n[3];
-  }
+  const float4* n = nodes + 4 * node;
+  const float4 n0 = n[0], n2 = n[2], n3 = n[3];
+  float4 n1 = n[1];
+  // the references are used last; without this the compiler may load one of them a second time, later,
+  // where it turns out to be needed, and wait for memory twice
+  asm("" : "+v"(n1.x), "+v"(n1.y), "+v"(n1.z), "+v"(n1.w));
   const float ax = n0.w * inv.x, ay = n3.z * inv.y, az = n3.w * inv.z;  // 2^24 s / d; S is a power of two: exact
   const float bx = fmaf(n0.x, inv.x, -oi.x), by = fmaf(n0.y, inv.y, -oi.y), bz = fmaf(n0.z, inv.z, -oi.z);
   const bool px = inv.x >= 0.f, py = inv.y >= 0.f, pz = inv.z >= 0.f;
@@ -291,25 +289,16 @@ __device__ __attribute__((always_inline)) inline void node4_children(const float
     return __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(0u, w, j ? 0x0c030c02u : 0x0c010c00u));
   };
   half2_t hnx[2], hfx[2], hny[2], hfy[2], hnz[2], hfz[2];
-  if (PERM_GRID) {
-    for (int j = 0; j < 2; ++j) {
-      hnx[j] = grid_pair(nx, j), hfx[j] = grid_pair(fx, j), hny[j] = grid_pair(ny, j), hfy[j] = grid_pair(fy, j);
-      hnz[j] = grid_pair(nz, j), hfz[j] = grid_pair(fz, j);
-    }
+  for (int j = 0; j < 2; ++j) {
+    hnx[j] = grid_pair(nx, j), hfx[j] = grid_pair(fx, j), hny[j] = grid_pair(ny, j), hfy[j] = grid_pair(fy, j);
+    hnz[j] = grid_pair(nz, j), hfz[j] = grid_pair(fz, j);
   }
-  // Without PERM_GRID the bytes are converted to FP32 and scaled by s / d = 2^-24 (S / d), exact: the same
-  // planes to the bit with fewer live registers (the batch kernel also holds each lane's scene fields).
-  const float sx = ax * 0x1p-24f, sy = ay * 0x1p-24f, sz = az * 0x1p-24f;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     auto q = [k](const half2_t (&h)[2]) { return float((k & 1) ? h[k >> 1].y : h[k >> 1].x); };
-    auto b = [k](uint32_t w) { return float((w >> (8 * k)) & 0xffu); };
-    const float xn = PERM_GRID ? fmaf(q(hnx), ax, bx) : fmaf(b(nx), sx, bx);
-    const float xf = PERM_GRID ? fmaf(q(hfx), ax, bx) : fmaf(b(fx), sx, bx);
-    const float yn = PERM_GRID ? fmaf(q(hny), ay, by) : fmaf(b(ny), sy, by);
-    const float yf = PERM_GRID ? fmaf(q(hfy), ay, by) : fmaf(b(fy), sy, by);
-    const float zn = PERM_GRID ? fmaf(q(hnz), az, bz) : fmaf(b(nz), sz, bz);
-    const float zf = PERM_GRID ? fmaf(q(hfz), az, bz) : fmaf(b(fz), sz, bz);
+    const float xn = fmaf(q(hnx), ax, bx), xf = fmaf(q(hfx), ax, bx);
+    const float yn = fmaf(q(hny), ay, by), yf = fmaf(q(hfy), ay, by);
+    const float zn = fmaf(q(hnz), az, bz), zf = fmaf(q(hfz), az, bz);
     const float tn = fmaxf(fmaxf(xn, yn), fmaxf(zn, tmin));
     const float tf = fminf(fminf(xf, yf), fminf(zf, tmax));
     // HITS_ONLY: 0 for a hit child, +inf otherwise (an occlusion query needs no entry distance)
@@ -341,20 +330,24 @@ __device__ __attribute__((always_inline)) inline void node4_children(const float
 // ---------------------------------------------------------------------------------------------
 
 struct Stack {
-  uint32_t* lds;     // &lds_stack[threadIdx.x], stride kBlock
-  uint32_t* global;  // &gstack[global thread], stride gstride
-  int gstride;
+  uint32_t* lds;     // this thread's column: entry k of the ring at [k * kBlock]
+  uint32_t* global;  // the spill area: entry k of grid thread g at [k * gstride + g] (fits 32 bits)
+  uint32_t gblock;   // the grid thread of this block's thread 0
+  uint32_t gstride;
   int gcap;          // spill entries per lane
   int sp;
   bool overflow;
 
+  __device__ inline uint32_t& spill(int k) const {
+    return global[uint32_t(k) * gstride + (gblock + threadIdx.x)];
+  }
   __device__ inline void push(int v) {
     if (sp >= kStackLds) {
       if (sp - kStackLds >= gcap) {  // excluded by the depth checks on the host; never write out of bounds
         overflow = true;
         return;
       }
-      global[size_t(sp - kStackLds) * gstride] = lds[(sp & (kStackLds - 1)) * kBlock];
+      spill(sp - kStackLds) = lds[(sp & (kStackLds - 1)) * kBlock];
     }
     lds[(sp & (kStackLds - 1)) * kBlock] = uint32_t(v);
     ++sp;
@@ -379,7 +372,7 @@ struct Stack {
   __device__ inline int pop() {
     --sp;
     int v = int(lds[(sp & (kStackLds - 1)) * kBlock]);
-    if (sp >= kStackLds) lds[(sp & (kStackLds - 1)) * kBlock] = global[size_t(sp - kStackLds) * gstride];
+    if (sp >= kStackLds) lds[(sp & (kStackLds - 1)) * kBlock] = spill(sp - kStackLds);
     return v;
   }
 };
@@ -411,114 +404,247 @@ struct Best {
   int id;
 };
 
-// ANY = false: closest hit, minimum t, exact ties to the smaller original id; best.t starts at +inf.
-// ANY = true : occlusion, stops at the first primitive with t in (tmin, best.t); best.key >= 0 if found.
-// Candidates are tested against next_up(best.t) in the closest-hit case so that an exact tie in t
-// reaches the (t, id) comparison, and boxes entered exactly at best.t are not culled.
-template <bool ANY, bool COUNT, bool PERM_GRID>
-__device__ inline void traverse(const DevScene& sc, const float4* lnodes, int kc, float3 o, float3 d, float tmin,
-                                int exclude, bool brute, Best& best, Stack& st, uint32_t& nnodes, uint32_t& ntris) {
-  // upper end of the interval a candidate or a box must start in: best.t for an occlusion query, the
-  // next float above best.t for a closest hit; it changes only when a hit is accepted
-  float limit = ANY ? best.t : next_up(best.t);
-  auto accept = [&](float t, int key, int id) -> bool {  // returns true when the traversal can stop
-    if (key == exclude || !(t < INFINITY)) return false;
-    if (ANY) {
-      best.t = t;
-      best.key = key;
-      best.id = id;
-      return true;
-    }
-    if (t < best.t || (t == best.t && id < best.id)) {
-      best.t = t;
-      best.key = key;
-      best.id = id;
-      limit = __int_as_float(__float_as_int(t) + 1);  // t is finite here
-    }
-    return false;
-  };
+// The best hits of the rays a wave shares between its lanes, one slot per ray (LDS, this wave's part).
+// A slot's word is (limit bits << 32 | id): as an integer it orders hits by (t, id), limit being the next
+// float above t.  Within a wave LDS operations take effect in program order.
+struct Share {
+  unsigned long long* word;
+  int* key;
 
-  for (int s = 0; s < sc.S; ++s) {
-    const int key = sc.T + s;
-    if (accept(sphere_t(sc.spheres[s], o, d, tmin, limit), key, key)) return;
+  __device__ inline void open(int slot, uint32_t limit_bits, int id, int k) const {
+    __hip_atomic_store(&word[slot], (static_cast<unsigned long long>(limit_bits) << 32) | uint32_t(id),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(&key[slot], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  for (int p = 0; p < sc.P; ++p) {
-    const int key = sc.T + sc.S + p;
-    if (accept(plane_t(sc.planes[p], o, d, tmin, limit), key, key)) return;
+  __device__ inline float limit(int slot) const {
+    return __uint_as_float(
+        uint32_t(__hip_atomic_load(&word[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32));
   }
-  if (sc.T == 0) return;
-  if (brute || !sc.has_bvh) {
-    for (int r = 0; r < sc.T; ++r) {
-      int id;
-      const float t = tri_t(sc.tris, r, o, d, tmin, limit, &id);
-      if (COUNT) ++ntris;
-      if (accept(t, r, id)) return;
+  __device__ inline int key_of(int slot) const {
+    return __hip_atomic_load(&key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  // Takes a hit if it is the ray's best; no other lane offers the same (t, id).
+  __device__ inline void offer(int slot, uint32_t limit_bits, int id, int k) const {
+    const unsigned long long w = (static_cast<unsigned long long>(limit_bits) << 32) | uint32_t(id);
+    __hip_atomic_fetch_min(&word[slot], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__hip_atomic_load(&word[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == w)
+      __hip_atomic_store(&key[slot], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  // An occlusion query is answered: no candidate lies below a limit of 0.
+  __device__ inline void close(int slot) const {
+    __hip_atomic_store(&word[slot], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+};
+
+// A wave's working set of one kind of ray: lane l starts with ray l of the wave's batch (or none).
+struct Ray {
+  float3 o, d;
+  float tmin, limit;  // the interval [tmin, limit) a candidate must lie in
+  int exclude;        // key of the primitive the ray leaves (-1: none)
+};
+
+// Entry cap of a traversal loop; it only guards against a corrupt tree (T <= 2^29, so it fits 32 bits).
+__device__ inline int loop_guard(int T) { return 2 * T + 64; }
+
+__device__ inline float shfl_f(float v, int src) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+}
+__device__ inline int shfl_i(int v, int src) { return __builtin_amdgcn_ds_bpermute(src << 2, v); }
+
+// Traverses the rays of one wave (all lanes call it together; `mine` marks the lanes that hold a ray).
+// ANY = false: closest hit, minimum t, exact ties to the smaller original id; the limit starts at +inf.
+// ANY = true : occlusion, stops at the first primitive with t in (tmin, limit).
+// commit(key, t) is called once for every lane with a ray: the hit's key (-1: none) and distance.
+// Closest-hit candidates are tested against the next float above the best t, so that an exact tie in t
+// reaches the (t, id) comparison, and boxes entered exactly at the best t are not culled.
+//
+// One lane per ray while many rays are left.  A ray can need ten times the node visits of the average one,
+// so a wave's last rays would run alone (before, half of the VALU lanes were idle), and one ray's chain of
+// dependent node fetches (about 0.5 us each) sets the time of a small launch.  Once at most kCoopRays rays
+// are left, the wave's idle lanes help: each takes the top entry of a busy lane's stack, with a copy of its
+// ray, and traverses that subtree itself.  The lanes of one ray share its best hit through `share` (one slot
+// per shared ray); the result is the minimum (t, id) over everything they reach, which does not depend on
+// the order they reach it in.  Measured with the 8-wave budget on a 1080p frame of 3.4M triangles, depth 4,
+// 4 lights: the six launches took 538, 1324, 300, 166, 222 and 135 us and take 455, 1130, 230, 81, 53 and
+// 31; the frame went from 2844 to 2121 us.  kCoopRays 8 / 16 / 24 / 32 / 48 / 64: 2463 / 2376 / 2322 / 2278
+// / 2258 / 2310 us (at 7 waves).
+template <bool ANY, bool COUNT, class Commit>
+__device__ __attribute__((always_inline)) inline void traverse(const DevScene& sc, bool mine, Ray r,
+                                                               bool brute, Stack& st, const Share& share,
+                                                               uint32_t& nnodes, uint32_t& ntris, Commit commit) {
+  constexpr bool kCoop = !COUNT && kCoopRays > 0;  // work counts are those of one lane per ray
+  const int lane = lane_id();
+  // the fields the loop reads, held in scalar registers (the empty asm hides that they could be loaded again)
+  const float4* const nodes = global_scalar(sc.nodes);
+  const float4* const tris = global_scalar(sc.tris);
+  int num_nodes = sc.num_nodes, T = sc.T;
+  asm("" : "+s"(num_nodes), "+s"(T));
+  Best best{INFINITY, -1, 0x7fffffff};
+  bool found = false;    // ANY: the ray is occluded
+  int slot = 0;          // of the ray this lane works on, while the wave shares its rays
+  bool coop = false;     // the wave shares its rays (wave-uniform)
+  bool own_late = false; // this lane's own ray is one of them
+  uint64_t late = 0;     // the lanes whose rays it shares (wave-uniform)
+  auto accept = [&](float t, int key, int id) {
+    if (key == r.exclude || !(t < INFINITY)) return;
+    if (ANY) {
+      found = true;
+    } else if (kCoop && coop) {
+      share.offer(slot, __float_as_uint(t) + 1u, id, key);
+    } else if (t < best.t || (t == best.t && id < best.id)) {
+      best.t = t;
+      best.key = key;
+      best.id = id;
+      r.limit = __int_as_float(__float_as_int(t) + 1);  // the next float above t, finite here
     }
-    return;
-  }
-  const float3 inv = make_float3(safe_rcp(d.x), safe_rcp(d.y), safe_rcp(d.z));
-  const float3 oi = mul(o, inv);
-  // Each iteration takes one internal-node step and then, if the lane now holds a leaf, tests it,
-  // so the leaf step of a wave runs with every lane that reached a leaf in this iteration.
-  int node = sc.root;
+  };
+  int node = kDoneRef;
   st.sp = 0;
-  // A valid tree visits each node and leaf at most once; the cap only guards against a corrupt one
-  // (T <= 2^29, so it fits 32 bits).
-  for (int guard = 2 * sc.T + 64; guard > 0; --guard) {
-    if (node >= 0) {
-      if (node >= sc.num_nodes) {  // corrupt reference: stop this ray, never read out of bounds
-        st.overflow = true;
-        return;
+  if (mine) {
+    for (int s = 0; s < sc.S && !(ANY && found); ++s) {
+      const int key = sc.T + s;
+      accept(sphere_t(sc.spheres[s], r.o, r.d, r.tmin, r.limit), key, key);
+    }
+    for (int p = 0; p < sc.P && !(ANY && found); ++p) {
+      const int key = sc.T + sc.S + p;
+      accept(plane_t(sc.planes[p], r.o, r.d, r.tmin, r.limit), key, key);
+    }
+    if (brute || !sc.has_bvh) {
+      for (int k = 0; k < sc.T && !(ANY && found); ++k) {
+        int id;
+        const float t = tri_t(sc.tris, k, r.o, r.d, r.tmin, r.limit, &id);
+        if (COUNT) ++ntris;
+        accept(t, k, id);
       }
-      if (COUNT) ++nnodes;
-      const float tmax = limit;
-      float t[4];
-      int r[4];
-      node4_children<ANY, PERM_GRID>(sc.nodes, lnodes, kc, node, inv, oi, tmin, tmax, t, r);
-      if (ANY) {
-        // occlusion: the order of the hit children does not change the answer, so they are taken in
-        // slot order (the same for every lane of the wave) without sorting: the first hit child next,
-        // the later hit children pushed so that they pop in slot order
-        const bool h0 = t[0] == 0.0f, h1 = t[1] == 0.0f, h2 = t[2] == 0.0f, h3 = t[3] == 0.0f;
-        if (h0 || h1 || h2 || h3) {
-          node = h0 ? r[0] : (h1 ? r[1] : (h2 ? r[2] : r[3]));
-          const bool g1 = h1 && h0, g2 = h2 && (h0 || h1), g3 = h3 && (h0 || h1 || h2);  // hits after the first
-          const int np = int(g1) + int(g2) + int(g3);
-          if (np > 0) st.push_sorted(g1 ? r[1] : (g2 ? r[2] : r[3]), (g1 && g2) ? r[2] : r[3], r[3], np);
-        } else {
-          node = st.sp > 0 ? st.pop() : kDoneRef;
+    } else if (sc.T > 0 && !(ANY && found)) {
+      node = sc.root;
+    }
+  }
+  float3 inv = make_float3(safe_rcp(r.d.x), safe_rcp(r.d.y), safe_rcp(r.d.z));
+  float3 oi = mul(r.o, inv);
+  for (int guard = loop_guard(T); guard > 0; --guard) {
+    const uint64_t busy = __ballot(node != kDoneRef);
+    if (busy == 0) break;
+    if (kCoop) {
+      if (!coop && __popcll(busy) <= kCoopRays) {
+        coop = true;
+        late = busy;
+        own_late = node != kDoneRef;
+        if (own_late) {
+          slot = lanes_below(busy);
+          share.open(slot, __float_as_uint(r.limit), best.id, best.key);
+        } else if (mine) {
+          commit(ANY ? (found ? 0 : -1) : best.key, best.t);
         }
+      }
+      if (coop) {
+        // pair the k-th idle lane with the k-th busy lane that has a stack entry to give
+        const bool can_give = node != kDoneRef && st.sp > 0, is_idle = node == kDoneRef;
+        const uint64_t give = __ballot(can_give);
+        const int ngive = __popcll(give), nidle = 64 - __popcll(busy);
+        if (min(ngive, nidle) * kCoopShare >= 64 - nidle && give != 0) {
+          const int below = lanes_below(give), rank = lanes_below(~busy);
+          const bool gives = can_give && below < nidle, takes = is_idle && rank < ngive;
+          // a permutation of the lanes that lists the givers first
+          const int givers = __builtin_amdgcn_ds_permute((can_give ? below : ngive + lane - below) << 2, lane);
+          const int giver = shfl_i(givers, rank);
+          const int from = takes ? giver : lane;  // every other lane reads itself
+          int top = node;
+          if (gives) top = st.pop();
+          const int taken = shfl_i(top, from);
+          r.o.x = shfl_f(r.o.x, from), r.o.y = shfl_f(r.o.y, from), r.o.z = shfl_f(r.o.z, from);
+          r.d.x = shfl_f(r.d.x, from), r.d.y = shfl_f(r.d.y, from), r.d.z = shfl_f(r.d.z, from);
+          inv.x = shfl_f(inv.x, from), inv.y = shfl_f(inv.y, from), inv.z = shfl_f(inv.z, from);
+          oi.x = shfl_f(oi.x, from), oi.y = shfl_f(oi.y, from), oi.z = shfl_f(oi.z, from);
+          r.exclude = shfl_i(r.exclude, from);
+          slot = shfl_i(slot, from);
+          if (takes) {
+            node = taken;
+            found = false;
+          }
+        }
+        if (node != kDoneRef) {
+          r.limit = share.limit(slot);
+          if (ANY && r.limit == 0.0f) {  // another lane found an occluder
+            node = kDoneRef;
+            st.sp = 0;
+          }
+        }
+      }
+    }
+    // One internal-node step, then, if the lane now holds a leaf, its test, so the leaf step of a wave runs
+    // with every lane that reached a leaf in this iteration.
+    if (node >= 0 && node != kDoneRef) {
+      if (node >= num_nodes) {  // corrupt reference: stop this ray, never read out of bounds
+        st.overflow = true;
+        node = kDoneRef;
+        st.sp = 0;
       } else {
-        sort4(t, r);
-        if (t[0] < INFINITY) {
-          node = r[0];
-          const int np = int(t[1] < INFINITY) + int(t[2] < INFINITY) + int(t[3] < INFINITY);
-          if (np > 0) st.push_sorted(r[1], r[2], r[3], np);
+        if (COUNT) ++nnodes;
+        float t[4];
+        int c[4];
+        node4_children<ANY>(nodes, node, inv, oi, r.tmin, r.limit, t, c);
+        if (ANY) {
+          // occlusion: the order of the hit children does not change the answer, so they are taken in
+          // slot order (the same for every lane of the wave) without sorting: the first hit child next,
+          // the later hit children pushed so that they pop in slot order
+          const bool h0 = t[0] == 0.0f, h1 = t[1] == 0.0f, h2 = t[2] == 0.0f, h3 = t[3] == 0.0f;
+          if (h0 || h1 || h2 || h3) {
+            node = h0 ? c[0] : (h1 ? c[1] : (h2 ? c[2] : c[3]));
+            const bool g1 = h1 && h0, g2 = h2 && (h0 || h1), g3 = h3 && (h0 || h1 || h2);  // hits after the first
+            const int np = int(g1) + int(g2) + int(g3);
+            if (np > 0) st.push_sorted(g1 ? c[1] : (g2 ? c[2] : c[3]), (g1 && g2) ? c[2] : c[3], c[3], np);
+          } else {
+            node = st.sp > 0 ? st.pop() : kDoneRef;
+          }
         } else {
-          node = st.sp > 0 ? st.pop() : kDoneRef;
+          sort4(t, c);
+          if (t[0] < INFINITY) {
+            node = c[0];
+            const int np = int(t[1] < INFINITY) + int(t[2] < INFINITY) + int(t[3] < INFINITY);
+            if (np > 0) st.push_sorted(c[1], c[2], c[3], np);
+          } else {
+            node = st.sp > 0 ? st.pop() : kDoneRef;
+          }
         }
       }
     }
     if (node < 0) {
       const int code = ~node;
       const int first = code >> 2, count = (code & 3) + 1;
-      if (first + count > sc.T) {
+      if (first + count > T) {
         st.overflow = true;
-        return;
+        st.sp = 0;
+      } else {
+        for (int k = 0; k < count && !(ANY && found); ++k) {
+          const int i = first + k;
+          if (i == r.exclude) continue;  // the secondary ray's own primitive: not fetched
+          int id;
+          const float t = tri_t(tris, i, r.o, r.d, r.tmin, r.limit, &id);
+          if (COUNT) ++ntris;
+          accept(t, i, id);
+        }
       }
-      for (int k = 0; k < count; ++k) {
-        const int r = first + k;
-        if (r == exclude) continue;  // the secondary ray's own primitive: not fetched
-        int id;
-        const float t = tri_t(sc.tris, r, o, d, tmin, limit, &id);
-        if (COUNT) ++ntris;
-        if (accept(t, r, id)) return;
+      if (ANY && found) {
+        st.sp = 0;
+        if (kCoop && coop) share.close(slot);
       }
       node = st.sp > 0 ? st.pop() : kDoneRef;
     }
-    if (node == kDoneRef) return;
   }
-  st.overflow = true;
+  if (node != kDoneRef) st.overflow = true;
+  if (!kCoop || !coop) {
+    if (mine) commit(ANY ? (found ? 0 : -1) : best.key, best.t);
+  } else if (own_late) {
+    const int own = lanes_below(late);
+    const float limit = share.limit(own);
+    if (ANY) {
+      commit(limit == 0.0f ? 0 : -1, 0.0f);
+    } else {
+      const int key = share.key_of(own);
+      commit(key, key < 0 ? INFINITY : __uint_as_float(__float_as_uint(limit) - 1u));
+    }
+  }
 }
 
 __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
@@ -534,9 +660,9 @@ __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
 // ---------------------------------------------------------------------------------------------
 
 // Traversal occupancy: the traversal kernels are held to kTraceWaves waves per SIMD, a budget of
-// 72 VGPRs.  The single-scene kernel meets it without spilling; the batch kernel, whose scene fields
-// are per-lane values, spills two VGPRs and is still faster (2097 vs 1846 stereo frames/s on the
-// 64-pair batch).  The instrumented kernels are left free.
+// 64 VGPRs and 20 KB of LDS a block.  The single-scene kernel meets it without spilling, the batch kernel
+// with 8 registers spilled outside the node step.  7 waves: 2258 vs 2187 us for a 1080p frame of 3.4M
+// triangles, 7.68 vs 7.47 ms for 16 mixed pairs.  The instrumented kernels are left free.
 constexpr int kTraceWaves = SRT_TRACE_WAVES_PER_EU;
 #define SRT_TRACE_ATTR __attribute__((amdgpu_waves_per_eu(COUNT || kTraceWaves <= 0 ? 1 : kTraceWaves)))
 
@@ -551,38 +677,61 @@ __device__ __attribute__((always_inline)) inline const KArgs& kernel_args() {
   return *(const KArgs*)p;
 }
 
+// Calls body(item, mine) for each item that lanes of this wave hold, with `mine` marking its lanes; every
+// lane makes the call.  The item is the same for the whole wave, so its fields are scalar loads.  Queue
+// entries are in path order within a shading block's run, so nearly every wave holds one item.
+template <bool MULTI, class Body>
+__device__ __attribute__((always_inline)) inline void each_item(const KArgs& a, bool valid, int k, Body body) {
+  if (!MULTI) {
+    body(a.one, valid);
+    return;
+  }
+  typedef __attribute__((address_space(4))) const DevItem item_t;
+  for (uint64_t todo = __ballot(valid); todo != 0;) {
+    const int k0 = __builtin_amdgcn_readlane(k, __builtin_ctzll(todo));
+    const bool mine = valid && k == k0;
+    body(*(const DevItem*)((const item_t*)a.items + k0), mine);
+    todo &= ~__ballot(mine);
+  }
+}
+
 template <bool COUNT, bool MULTI>
 __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int depth) {
   __shared__ uint32_t lstack[kStackLds * kBlock];
-  __shared__ float4 lnodes[kLdsNodes > 0 ? 4 * kLdsNodes : 1];
+  __shared__ unsigned long long share_word[kWaves * std::max(kCoopRays, 1)];
+  __shared__ int share_key[kWaves * std::max(kCoopRays, 1)];
   const int lane = lane_id();
-  const int gtid = blockIdx.x * kBlock + threadIdx.x;
-  Stack st{&lstack[threadIdx.x], a.gstack + gtid, a.trace_threads, a.gstack_entries, 0, false};
+  const Share share{&share_word[(threadIdx.x >> 6) * kCoopRays], &share_key[(threadIdx.x >> 6) * kCoopRays]};
+  Stack st{&lstack[threadIdx.x], global_scalar(a.gstack), blockIdx.x * uint32_t(kBlock),
+           uint32_t(a.trace_threads), a.gstack_entries, 0, false};
   const int LS = a.lstride;
-  int kc = 0;  // nodes held in lnodes (the same for the whole block)
-  if (!MULTI && kLdsNodes > 0 && a.one.sc.has_bvh && a.one.sc.T > 0 && !a.brute) {
-    kc = min(kLdsNodes, a.one.sc.num_nodes);
-    for (int i = threadIdx.x; i < 4 * kc; i += kBlock) lnodes[i] = a.one.sc.nodes[i];
-    __syncthreads();
-  }
   const bool closest = depth <= a.dmax;
   const bool shadows = depth >= 1;
   const int q = depth & 1;
   const int sq = (depth + 1) & 1;  // parity of depth - 1
   const uint32_t nc = closest ? (depth == 0 ? uint32_t(a.path_count) : a.ctr->refl_count[depth]) : 0u;
-  const uint32_t nc_pad = round64(nc);
+  uint32_t rays = nc;
+  if (shadows)
+    for (int l = 0; l < LS; ++l) rays += a.ctr->shadow_count[depth - 1][l];
+  // Work comes in batches of 64 rays, one per lane, or fewer where that still gives every wave of the grid
+  // at most one batch: the wave's other lanes then share its rays from the start (see traverse).  A 641x479
+  // frame of 13k triangles takes 329 us that way and 436 us in batches of 64; batches of at least 4 or 16
+  // rays instead of 8 are within 1%.
+  const uint32_t nwaves = gridDim.x * uint32_t(kWaves);
+  int blog = 6;
+  if (!COUNT && kCoopRays > 0 && !a.brute && (MULTI || a.one.sc.has_bvh))
+    while (blog > kMinRaysLog2 && (rays >> (blog - 1)) < nwaves) --blog;
+  const uint32_t nc_pad = round_up(nc, blog);
   uint32_t total = nc_pad;
   if (shadows)
-    for (int l = 0; l < LS; ++l) total += round64(a.ctr->shadow_count[depth - 1][l]);
+    for (int l = 0; l < LS; ++l) total += round_up(a.ctr->shadow_count[depth - 1][l], blog);
   uint32_t c_nodes = 0, c_tris = 0, s_nodes = 0, s_tris = 0;
-  // Work comes in wave-wide batches of 64 items (larger grabs unbalance the launch's end, and
-  // refilling single lanes stalls the wave on every refill).  Device-scope atomics on one address
-  // serialise, so: wave w's first batch is batch w, with no atomic (a launch whose work fits in
+  // Larger grabs than one batch unbalance the launch's end, and refilling single lanes stalls the wave on
+  // every refill.  Device-scope atomics on one address serialise, so: wave w's first batch is batch w, with no atomic (a launch whose work fits in
   // the first round takes none); later batches b = nwaves + c + K k come from counter c = w mod K
   // of K = min(kWorkCounters, nwaves) interleaved counters, so K atomics proceed at once.
-  const uint32_t nwaves = gridDim.x * uint32_t(kWaves);
-  const uint32_t wid = blockIdx.x * uint32_t(kWaves) + uint32_t(threadIdx.x >> 6);
-  const uint32_t nbatches = total / 64u;  // total is a multiple of 64
+  const uint32_t wid = blockIdx.x * uint32_t(kWaves) + uint32_t(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const uint32_t nbatches = total >> blog;
   const uint32_t ncounters = nwaves < uint32_t(kWorkCounters) ? nwaves : uint32_t(kWorkCounters);  // each served
   const uint32_t home = wid % ncounters;
   uint32_t batch = wid;
@@ -591,74 +740,81 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
       if (nwaves + home >= nbatches) break;  // no batch left for this counter
       uint32_t k = 0;
       if (lane == 0) k = atomicAdd(&a.ctr->trace_work[depth][home][0], 1u);
-      batch = nwaves + home + ncounters * __shfl(k, 0);
+      batch = nwaves + home + ncounters * uint32_t(__builtin_amdgcn_readfirstlane(int(k)));
     }
     if (batch >= nbatches) break;
     const KArgs& a = kernel_args();  // the same values as the parameter, see kernel_args
-    const uint32_t base = batch * 64u;
+    const uint32_t base = batch << blog;
+    const bool filled = lane < (1 << blog);
     if (base < nc_pad) {
       // ---- closest-hit batch
       const uint32_t e = base + lane;
-      if (e < nc) {
-        float3 o, d;
-        int exclude = -1;
-        bool valid = true;
-        int k;
-        if (depth == 0) {
-          const int64_t p = a.path_begin + e;
-          k = item_of<MULTI>(a, p);
-          const DevItem& it = item_ref<MULTI>(a, k);
-          const DevCamera& cam = it.cam;
-          int eye, x, y;
-          valid = path_pixel(cam, p - it.path_offset, &eye, &x, &y);
-          if (valid) {
-            primary_ray(cam, eye, x, y, &o, &d);
-            a.ro[q][e] = make_float4(o.x, o.y, o.z, __int_as_float(int(e)));
-            a.rd[q][e] = make_float4(d.x, d.y, d.z, __int_as_float(-1));
+      bool valid = filled && e < nc;
+      int k = 0;
+      if (MULTI && valid)
+        k = item_of<MULTI>(a, a.path_begin + (depth == 0 ? e : uint32_t(__float_as_int(a.ro[q][e].w))));
+      each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
+        Ray r{};
+        r.limit = INFINITY;
+        r.tmin = depth == 0 ? 0.0f : kSecondaryTmin;
+        r.exclude = -1;
+        if (mine) {
+          if (depth == 0) {
+            int eye, x, y;
+            mine = path_pixel(it.cam, a.path_begin + e - it.path_offset, &eye, &x, &y);
+            if (mine) {
+              primary_ray(it.cam, eye, x, y, &r.o, &r.d);
+              a.ro[q][e] = make_float4(r.o.x, r.o.y, r.o.z, __int_as_float(int(e)));
+              a.rd[q][e] = make_float4(r.d.x, r.d.y, r.d.z, __int_as_float(-1));
+            } else {
+              a.ro[q][e].w = __int_as_float(-1);  // outside the image
+            }
           } else {
-            a.ro[q][e] = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
+            const float4 ro = a.ro[q][e], rd = a.rd[q][e];
+            r.o = f3(ro);
+            r.d = f3(rd);
+            r.exclude = __float_as_int(rd.w);
           }
-        } else {
-          const float4 ro = a.ro[q][e], rd = a.rd[q][e];
-          o = f3(ro);
-          d = f3(rd);
-          exclude = __float_as_int(rd.w);
-          k = item_of<MULTI>(a, a.path_begin + uint32_t(__float_as_int(ro.w)));
         }
-        if (valid) {
-          const DevScene sc = item_ref<MULTI>(a, k).sc;
-          Best b{INFINITY, -1, 0x7fffffff};
-          traverse<false, COUNT, !MULTI>(sc, lnodes, kc, o, d, depth == 0 ? 0.0f : kSecondaryTmin, exclude,
-                                         a.brute != 0, b, st, c_nodes, c_tris);
-          a.hit[e] = make_float2(b.t, __int_as_float(b.key));
-        }
-      }
+        traverse<false, COUNT>(it.sc, mine, r, a.brute != 0, st, share, c_nodes, c_tris,
+                                     [&](int key, float t) {
+                                       const uint32_t entry = e;
+                                       global_scalar(a.hit)[entry] = make_float2(t, __int_as_float(key));
+                                     });
+      });
     } else {
-      // ---- shadow batch: find the light whose (64-aligned) range holds this batch
+      // ---- shadow batch: find the light whose (padded) range holds this batch
       uint32_t start = nc_pad;
       int l = 0;
       uint32_t cnt = a.ctr->shadow_count[depth - 1][0];
-      while (l + 1 < LS && base >= start + round64(cnt)) {
-        start += round64(cnt);
+      while (l + 1 < LS && base >= start + round_up(cnt, blog)) {
+        start += round_up(cnt, blog);
         ++l;
         cnt = a.ctr->shadow_count[depth - 1][l];
       }
       const uint32_t i = base - start + lane;
-      if (i < cnt) {
-        const size_t slot = size_t(l) * a.cap + i;
-        const float4 rec = a.srec[sq][slot];
-        const uint32_t owner = a.sowner[sq][slot];
-        const int k = MULTI ? item_of<MULTI>(a, a.path_begin + a.resinfo[sq][owner].x) : 0;
-        const DevScene sc = item_ref<MULTI>(a, k).sc;
-        const float3 P = f3(rec);
-        const float3 Lv = f3(sc.lights[2 * l]) - P;
-        const float dist = sqrtf(dot(Lv, Lv));
-        const float3 Ld = (1.0f / dist) * Lv;
-        Best b{dist, -1, 0};
-        traverse<true, COUNT, !MULTI>(sc, lnodes, kc, P, Ld, kSecondaryTmin, __float_as_int(rec.w), a.brute != 0, b,
-                                      st, s_nodes, s_tris);
-        a.vis[sq][size_t(owner) * LS + l] = b.key < 0 ? 1 : 0;
-      }
+      const bool valid = filled && i < cnt;
+      const uint32_t owner = valid ? a.sowner[sq][size_t(l) * a.cap + i] : 0u;
+      int k = 0;
+      if (MULTI && valid) k = item_of<MULTI>(a, a.path_begin + a.resinfo[sq][owner].x);
+      each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
+        Ray r{};
+        r.tmin = kSecondaryTmin;
+        if (mine) {
+          const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
+          r.o = f3(rec);
+          r.exclude = __float_as_int(rec.w);
+          const float3 Lv = f3(it.sc.lights[2 * l]) - r.o;
+          r.limit = sqrtf(dot(Lv, Lv));
+          r.d = (1.0f / r.limit) * Lv;
+        }
+        traverse<true, COUNT>(it.sc, mine, r, a.brute != 0, st, share, s_nodes, s_tris,
+                                    [&](int key, float) {
+                                      uint32_t o = owner;
+                                      asm volatile("" : "+v"(o));  // the address is formed here, not before the loop
+                                      global_scalar(a.vis[sq])[size_t(o) * LS + l] = key < 0 ? 1 : 0;
+                                    });
+      });
     }
   }
   if (st.overflow) atomicOr(&a.ctr->error, 1u);
@@ -820,7 +976,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
       const bool mine = ((mask >> l) & 1u) != 0;
       const uint64_t bal = __ballot(mine);
       if (mine) {
-        const uint32_t slot = bbase[l] + wcnt[wave][l] + uint32_t(__popcll(bal & lanemask_lt()));
+        const uint32_t slot = bbase[l] + wcnt[wave][l] + uint32_t(lanes_below(bal));
         const float3 Lv = f3(lights[2 * l]) - P;
         const float dist = sqrtf(dot(Lv, Lv));
         const float3 Ld = (1.0f / dist) * Lv;
@@ -839,7 +995,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
     {
       const uint64_t bal = __ballot(spawn);
       if (spawn) {
-        const uint32_t slot = bbase[LS] + wcnt[wave][LS] + uint32_t(__popcll(bal & lanemask_lt()));
+        const uint32_t slot = bbase[LS] + wcnt[wave][LS] + uint32_t(lanes_below(bal));
         a.ro[nq][slot] = make_float4(P.x, P.y, P.z, ro.w);
         a.rd[nq][slot] = make_float4(rdir.x, rdir.y, rdir.z, __int_as_float(key));
         a.thr[nq][slot] = make_float4(thr.x * kr3.x, thr.y * kr3.y, thr.z * kr3.z, 0.f);
@@ -889,9 +1045,15 @@ __global__ __launch_bounds__(kBlock) void k_resolve(KArgs a, int depth) {
   }
 }
 
-__global__ void k_reset(Counters* ctr) {
+// One workgroup clears the counters (41 KB, most of it the spaced work cursors), 16 bytes a store.
+constexpr int kResetBlock = 1024;
+static_assert(sizeof(Counters) % 4 == 0, "Counters is cleared in words");
+__global__ __launch_bounds__(kResetBlock) void k_reset(Counters* ctr) {
+  constexpr int kQuads = int(sizeof(Counters) / 16), kWords = int(sizeof(Counters) / 4);
+  uint4* q = reinterpret_cast<uint4*>(ctr);  // the workspace is 256-byte aligned and the counters come first
+  for (int i = threadIdx.x; i < kQuads; i += kResetBlock) q[i] = make_uint4(0u, 0u, 0u, 0u);
   uint32_t* p = reinterpret_cast<uint32_t*>(ctr);
-  for (int i = threadIdx.x; i < int(sizeof(Counters) / 4); i += blockDim.x) p[i] = 0;
+  for (int i = 4 * kQuads + threadIdx.x; i < kWords; i += kResetBlock) p[i] = 0;
 }
 
 __global__ void k_finish(const Counters* ctr, int D, int L, int64_t* out) {
@@ -1049,25 +1211,32 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   a.gstack_entries = p.stack_entries;
   if (a.trace_threads > p.stack_threads) return hipErrorInvalidValue;  // the spill area is per grid thread
 
-  const unsigned gtrace = unsigned(p.grid_trace);
+  // The persistent grid, cut where the launch cannot hold that many batches (small frames: a workgroup
+  // without work still costs its dispatch).
+  const bool trees = multi || (ra.one.sc.has_bvh && !a.brute);
+  auto gtrace = [&](int d) {
+    const int64_t rays = ra.path_count * ((d <= ra.max_depth ? 1 : 0) + (d >= 1 ? ra.max_lights : 0));
+    const int64_t per_block = int64_t(kWaves) << (trees ? kMinRaysLog2 : 6);
+    return unsigned(std::max<int64_t>(1, std::min<int64_t>(p.grid_trace, (rays + per_block - 1) / per_block)));
+  };
   const unsigned gstream =
       unsigned(std::max<int64_t>(1, std::min<int64_t>((ra.path_count + kBlock - 1) / kBlock, ra.stream_blocks)));
   const unsigned gshade = unsigned(std::max<int64_t>(
       1, std::min<int64_t>((ra.path_count + kShadeBlock - 1) / kShadeBlock, ra.stream_blocks * kBlock / kShadeBlock)));
   hipError_t e;
   if (timer) timer_begin(timer, RT_STAGE_SETUP, s);
-  k_reset<<<1, 256, 0, s>>>(a.ctr);
+  k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
   e = hipGetLastError();
   if (timer) timer_end(timer, RT_STAGE_SETUP, s);
   if (e != hipSuccess) return e;
   const int D = a.dmax;
   for (int d = 0; d <= D + 1; ++d) {
     if (multi)
-      e = count ? launch(k_trace<true, true>, gtrace, a, d, s, timer, RT_STAGE_TRACE)
-                : launch(k_trace<false, true>, gtrace, a, d, s, timer, RT_STAGE_TRACE);
+      e = count ? launch(k_trace<true, true>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE)
+                : launch(k_trace<false, true>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE);
     else
-      e = count ? launch(k_trace<true, false>, gtrace, a, d, s, timer, RT_STAGE_TRACE)
-                : launch(k_trace<false, false>, gtrace, a, d, s, timer, RT_STAGE_TRACE);
+      e = count ? launch(k_trace<true, false>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE)
+                : launch(k_trace<false, false>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE);
     if (e != hipSuccess) return e;
     if (d <= D) {
       if (multi)

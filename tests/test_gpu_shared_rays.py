@@ -1,0 +1,86 @@
+"""The traversal's wave-wide ray sharing (a wave with few rays left spreads their stacks over its idle lanes) against
+brute force and against one-at-a-time renders, byte for byte: the closest hit and a shadow ray's answer do not depend
+on which lane visits a node, or in which order."""
+import pytest
+
+import scenegen as sg
+
+from tests.helpers import coincident_scene, corners_scene, flat_scene
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("radiance", "hit_t", "hit_prim", "path_prims", "shadow_state")
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1702_01530_amd import rt
+    rt.lib()
+    return torch
+
+
+def _same(torch, a, b, what):
+    for k in KEYS:
+        assert torch.equal(a[k], b[k]), (what, k)
+    assert torch.equal(a["ray_counts"][:3], b["ray_counts"][:3]) and int(b["ray_counts"][-1]) == 0, what
+
+
+# Paths per frame around the sizes where a launch's batches go from 8 to 16, 32 and 64 rays (8 x, 16 x and 32 x the
+# 8,192 waves of a full grid), and down to a single path of each eye.
+@pytest.mark.parametrize("size", [(1, 1), (3, 2), (8, 8), (17, 9), (179, 183), (181, 181), (255, 257), (363, 361), (420, 400)])
+def test_every_batch_width_equals_brute_force(torch_cuda, size):
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    scene, cam = sg.make_small_terrain(seed=31, grid=18, n_spheres=5, level=1, lights=4, depth=4)
+    cam = cam.resized(*size)
+    print(f"[shared rays] {size}", flush=True)
+    gs = GpuScene(scene)
+    tree, brute = render_stereo(gs, cam, path_ids=True), render_stereo(gs, cam, path_ids=True, brute_force=True)
+    torch.cuda.synchronize()
+    _same(torch, brute, tree, size)
+    # the kernels that count work trace one lane per ray
+    counted = render_stereo(gs, cam, path_ids=True, count_work=True)
+    torch.cuda.synchronize()
+    _same(torch, brute, counted, size)
+    gs.close()
+
+
+# Exact ties in t (the smaller id wins, whichever lane reaches it), zero-area triangles, boxes without height, grazing
+# and axis-parallel rays.
+@pytest.mark.parametrize("make", [coincident_scene, flat_scene, corners_scene])
+@pytest.mark.parametrize("size", [(48, 32), (190, 181)])
+def test_ties_and_flat_boxes_equal_brute_force(torch_cuda, make, size):
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    scene, cam = make()
+    cam = cam.resized(*size)
+    print(f"[shared rays] {make.__name__} {size}", flush=True)
+    gs = GpuScene(scene)
+    tree, brute = render_stereo(gs, cam, path_ids=True), render_stereo(gs, cam, path_ids=True, brute_force=True)
+    torch.cuda.synchronize()
+    _same(torch, brute, tree, make.__name__)
+    gs.close()
+
+
+def test_waves_that_hold_several_items(torch_cuda):
+    """A batch of tiny images: from the first mirror bounce on, one wave's rays belong to several items (and scenes),
+    which it traverses one after the other."""
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_batch, render_stereo
+    scenes = [sg.make_small_terrain(seed=40 + k, grid=10 + 3 * k, n_spheres=2 + k, level=1, lights=1 + k % 4, depth=3)
+              for k in range(4)] + [sg.make_spheres_scene(seed=9)]
+    built = [GpuScene(s) for s, _ in scenes]
+    pairs = [(built[i % 5], scenes[i % 5][1].with_(width=5 + i % 9, height=11 - i % 7, max_depth=1 + i % 4)) for i in range(40)]
+    print("[shared rays] batch of 40", flush=True)
+    outs = render_batch(pairs, path_ids=True)
+    torch.cuda.synchronize()
+    for i, (gs, cam) in enumerate(pairs):
+        one = render_stereo(gs, cam, path_ids=True)
+        torch.cuda.synchronize()
+        for k in KEYS:
+            assert torch.equal(one[k], outs[i][k]), (i, k)
+    for gs in built:
+        gs.close()
