@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kBlock) void k_tri_prep(const float* __restrict__ t
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_reduce_bounds(Bounds6* __restrict__ partial, int64_t n) {
+__global__ __launch_bounds__(kBlock) void k_reduce_bounds(const Bounds6* __restrict__ partial, int64_t n,
+                                                          Bounds6* __restrict__ out) {
   __shared__ float red[12][kBlock];
   float v[12];
   for (int a = 0; a < 3; ++a) {
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_bounds(Bounds6* __restrict__ 
       b.blo[a] = red[6 + a][0];
       b.bhi[a] = red[9 + a][0];
     }
-    partial[0] = b;
+    *out = b;
   }
 }
 
@@ -442,14 +443,8 @@ __device__ inline void dp_child_costs(int r, const float4* dp_cost, const float4
   }
 }
 
-// Fills the cost table entry of binary node n, whose box and children's entries are final.
-__device__ inline void dp_node(int64_t n, const int2* children, const float4* nodebox, const float4* leaf_lo,
-                               const float4* leaf_hi, const uint32_t* sorted_ids, float4* dp_cost,
-                               uint32_t* dp_choice) {
-  const int2 ch = children[n];
-  float ca[4], cb[4];
-  dp_child_costs(ch.x, dp_cost, leaf_lo, leaf_hi, sorted_ids, ca);
-  dp_child_costs(ch.y, dp_cost, leaf_lo, leaf_hi, sorted_ids, cb);
+// The costs C(n, 1..4) and choice bits of a node of half area `area` whose children cost ca and cb.
+__device__ inline float4 dp_costs(float area, const float (&ca)[4], const float (&cb)[4], uint32_t* choice_out) {
   float D[5];
   int K[5];
   for (int j = 2; j <= 4; ++j) {
@@ -463,21 +458,22 @@ __device__ inline void dp_node(int64_t n, const int2* children, const float4* no
       }
     }
   }
-  const float c1 = half_area(nodebox[2 * n], nodebox[2 * n + 1]) + D[4];
-  dp_cost[n] = make_float4(c1, fminf(c1, D[2]), fminf(c1, D[3]), fminf(c1, D[4]));
+  const float c1 = area + D[4];
   uint32_t choice = 0;
   for (int j = 2; j <= 4; ++j) choice |= (uint32_t(K[j]) | (D[j] < c1 ? 4u : 0u)) << (3 * (j - 2));
-  dp_choice[n] = choice;
+  *choice_out = choice;
+  return make_float4(c1, fminf(c1, D[2]), fminf(c1, D[3]), fminf(c1, D[4]));
 }
 
-// The clustering tree's nodes of one round (children were made in earlier rounds).
-__global__ __launch_bounds__(kBlock) void k_wide_dp(const int2* __restrict__ children, const float4* nodebox,
-                                                    const float4* leaf_lo, const float4* leaf_hi,
-                                                    const uint32_t* sorted_ids, float4* dp_cost,
-                                                    uint32_t* dp_choice, int64_t first, int64_t count) {
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= count) return;
-  dp_node(first + i, children, nodebox, leaf_lo, leaf_hi, sorted_ids, dp_cost, dp_choice);
+// Fills the cost table entry of binary node n, whose box and children's entries are final.
+__device__ inline void dp_node(int64_t n, const int2* children, const float4* nodebox, const float4* leaf_lo,
+                               const float4* leaf_hi, const uint32_t* sorted_ids, float4* dp_cost,
+                               uint32_t* dp_choice) {
+  const int2 ch = children[n];
+  float ca[4], cb[4];
+  dp_child_costs(ch.x, dp_cost, leaf_lo, leaf_hi, sorted_ids, ca);
+  dp_child_costs(ch.y, dp_cost, leaf_lo, leaf_hi, sorted_ids, cb);
+  dp_cost[n] = dp_costs(half_area(nodebox[2 * n], nodebox[2 * n + 1]), ca, cb, &dp_choice[n]);
 }
 
 __global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ children,
@@ -540,6 +536,14 @@ __global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ child
 // the survivors are compacted in order.  The globally best pair is always mutual, so every round
 // merges.  Node indices are handed out from T-2 downwards by prefix sums, so the root is node 0 and
 // the tree is the same on every run.
+//
+// A build has 40 (10k triangles) to 65 (3.4M) rounds, each leaving about 0.8 of the clusters, so it is
+// bound by the cost of a round that has little to do.  The number of clusters stays on the device: the
+// host launches as many rounds as the decay suggests, two kernels each, without waiting for any of them,
+// and one workgroup does every round from kPlocTail clusters down (about 30 of them) with the clusters in
+// LDS.  A cluster carries its row of the cost table, so a node's entry is made with the node.  With a host
+// read, two prefix sums and five launches a round, and a launch a round for the cost table, building and
+// showing a scene of 10k triangles took 2.99 ms and takes 0.80 (3.4M triangles: 8.2 and 3.3 ms).
 // ---------------------------------------------------------------------------------------------
 
 // Search radius: with the cost-table collapse, 32 gives the fewest node visits per frame on the
@@ -549,86 +553,349 @@ __global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ child
 #endif
 constexpr int kPlocRadius = SRT_PLOC_RADIUS;
 
+// What the build's kernels tell each other and, at its end, the host (the scratch's first words).
+struct BuildState {
+  uint32_t status;    // BuildResult::status_bits
+  int32_t max_depth;  // deepest leaf of the Karras tree
+  uint32_t error;     // a step that cannot happen: no merge in a round, more nodes than leaves
+  uint32_t pad;
+  struct Ploc {
+    uint32_t n;     // clusters left; 1 when the tree is complete, 0 after an error
+    uint32_t next;  // internal nodes not yet made: the next round's take the indices below this
+    uint32_t buf;   // the buffer that holds the clusters
+    uint32_t pad;
+  } ploc[2];  // round k reads slot k & 1 and writes the other
+  struct Wide {
+    uint32_t m;          // BVH4 nodes of the level to come
+    uint32_t allocated;  // BVH4 nodes down to that level
+    uint32_t level;
+    uint32_t pad;
+  } wide[2];  // level launch k reads slot k & 1 and writes the other
+  Bounds6 bounds;
+};
+static_assert(sizeof(BuildState) <= 256, "the plan sets 256 bytes aside");
+
+// Clusters in struct-of-arrays form: box corners with C(1) and C(2) beside them, then (C(3), C(4), reference).
+struct Clusters {
+  float4* lo[2];
+  float4* hi[2];
+  float4* ext[2];
+};
+
 __global__ __launch_bounds__(kBlock) void k_ploc_init(const uint32_t* __restrict__ sorted_ids,
                                                       const float4* __restrict__ leaf_lo,
-                                                      const float4* __restrict__ leaf_hi, int64_t n,
-                                                      float4* __restrict__ c_lo, float4* __restrict__ c_hi,
-                                                      int32_t* __restrict__ c_ref) {
+                                                      const float4* __restrict__ leaf_hi, int64_t n, Clusters c) {
   const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t id = sorted_ids[i];
-  c_lo[i] = leaf_lo[id];
-  c_hi[i] = leaf_hi[id];
-  c_ref[i] = ~int32_t(i);
+  const float4 lo = leaf_lo[id], hi = leaf_hi[id];
+  const float cost = SRT_DP_TRI_COST * half_area(lo, hi);
+  c.lo[0][i] = make_float4(lo.x, lo.y, lo.z, cost);
+  c.hi[0][i] = make_float4(hi.x, hi.y, hi.z, cost);
+  c.ext[0][i] = make_float4(cost, cost, __int_as_float(~int(i)), 0.f);
 }
 
-// nn[i] = the best merge partner of cluster i among positions i-R..i+R (n >= 2).
-__global__ __launch_bounds__(kBlock) void k_ploc_nn(const float4* __restrict__ c_lo, const float4* __restrict__ c_hi,
-                                                    int64_t n, int32_t* __restrict__ nn) {
-  __shared__ float4 s_lo[kBlock + 2 * kPlocRadius], s_hi[kBlock + 2 * kPlocRadius];
-  const int64_t start = int64_t(blockIdx.x) * kBlock;
-  for (int k = threadIdx.x; k < kBlock + 2 * kPlocRadius; k += kBlock) {
-    const int64_t g = start - kPlocRadius + k;
-    if (g >= 0 && g < n) {
-      s_lo[k] = c_lo[g];
-      s_hi[k] = c_hi[g];
+constexpr int kPlocBlock = 512;    // threads of a search block
+constexpr int kPlocBlocks = 1024;  // most blocks of a round: each sums the others' counts
+constexpr int kPlocTail = 1024;    // clusters that one workgroup takes over
+constexpr int kPackBlocks = 1024;  // workgroups that pack triangles beside it
+static_assert(kPlocBlock >= 4 * kPlocRadius, "a search block needs positions of its own");
+
+// The positions that block `b` of `blocks` handles in a round of n clusters: whole tiles of `own`.
+__device__ inline void ploc_range(uint32_t n, uint32_t own, uint32_t b, uint32_t blocks, uint32_t* begin,
+                                  uint32_t* end) {
+  const uint32_t tiles = (n + own - 1) / own, per = (tiles + blocks - 1) / blocks;
+  *begin = min(uint64_t(b) * per * own, uint64_t(n));
+  *end = min(uint64_t(b + 1) * per * own, uint64_t(n));
+}
+
+// Sum of v over the block (a multiple of 64 threads), in every thread; `tmp` holds one word per wave.
+__device__ inline uint32_t block_sum(uint32_t v, uint32_t* tmp) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint32_t t = 0;
+  for (int w = 0; w < int(blockDim.x) / 64; ++w) t += tmp[w];
+  return t;
+}
+
+// partner[i] = the position cluster i merges with this round, or -1; counts[block] = (merges, absorbed
+// clusters) of the block's positions.  A tile's mutual pairs need the choices of kPlocRadius positions on
+// either side too, so a block makes those as well (kPlocBlock choices for kPlocBlock - 2 kPlocRadius
+// positions).  LANES lanes share one position's search where a round has too few positions to fill the chip.
+template <int LANES>
+__global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* state, int slot,
+                                                        int32_t* __restrict__ partner, uint2* __restrict__ counts) {
+  constexpr int R = kPlocRadius, kPos = kPlocBlock / LANES, kOwn = kPos - 2 * R;
+  static_assert(kOwn > 0 && 2 * R % LANES == 0, "search split");
+  __shared__ float4 s_lo[kPos + 2 * R], s_hi[kPos + 2 * R];
+  __shared__ int s_nn[kPos];
+  __shared__ uint32_t tmp[kPlocBlock / 64];
+  const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
+  if (n <= kPlocTail) return;
+  const float4* __restrict__ lo = buf ? c.lo[1] : c.lo[0];
+  const float4* __restrict__ hi = buf ? c.hi[1] : c.hi[0];
+  uint32_t begin, end, merges = 0, absorbed = 0;
+  ploc_range(n, kOwn, blockIdx.x, gridDim.x, &begin, &end);
+  const int p = threadIdx.x / LANES, sub = threadIdx.x % LANES;
+  for (uint32_t base = begin; base < end; base += kOwn) {
+    __syncthreads();
+    for (int k = threadIdx.x; k < kPos + 2 * R; k += kPlocBlock) {
+      const int64_t g = int64_t(base) - 2 * R + k;
+      const bool in = g >= 0 && g < int64_t(n);
+      // a box at +inf: any merge with it has an infinite area and is never chosen
+      s_lo[k] = in ? lo[g] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+      s_hi[k] = in ? hi[g] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+    }
+    __syncthreads();
+    const int64_t g = int64_t(base) - R + p;  // this thread's position, at p + R in LDS
+    const bool valid = g >= 0 && g < int64_t(n);
+    const float4 alo = s_lo[p + R], ahi = s_hi[p + R];
+    float best = INFINITY;
+    int bk = 0;
+    // ascending positions: ties keep the smaller one
+#pragma unroll 8
+    for (int q = 0; q < R / LANES; ++q) {
+      const int k = -R + q * LANES + sub;
+      const float ar = merged_area(alo, ahi, s_lo[p + R + k], s_hi[p + R + k]);
+      if (ar < best) best = ar, bk = k;
+    }
+#pragma unroll 8
+    for (int q = 0; q < R / LANES; ++q) {
+      const int k = 1 + q * LANES + sub;
+      const float ar = merged_area(alo, ahi, s_lo[p + R + k], s_hi[p + R + k]);
+      if (ar < best) best = ar, bk = k;
+    }
+    for (int off = 1; off < LANES; off <<= 1) {
+      const float ob = __shfl_xor(best, off);
+      const int ok = __shfl_xor(bk, off);
+      if (ob < best || (ob == best && ok < bk)) best = ob, bk = ok;
+    }
+    if (valid) {
+      if (!(best < INFINITY)) bk = g > 0 ? -1 : 1;  // boxes of refused input only: keep the rounds well formed
+      const int toward = (g & 1) ? -1 : 1;  // g ^ 1
+      if (g + toward < int64_t(n) && ploc_takes_parity(best, alo, ahi, s_lo[p + R + toward], s_hi[p + R + toward]))
+        bk = toward;
+    }
+    if (sub == 0) s_nn[p] = valid ? p + bk : -1;
+    __syncthreads();
+    if (sub == 0 && p >= R && p < kPos - R && valid) {
+      const int j = s_nn[p];
+      const bool mutual = s_nn[j] == p;  // j lies within R of p
+      partner[g] = mutual ? int32_t(g + j - p) : -1;
+      merges += (mutual && j > p) ? 1u : 0u;    // the lower position of a mutual pair makes the node
+      absorbed += (mutual && j < p) ? 1u : 0u;  // the higher one goes
     }
   }
-  __syncthreads();
-  const int64_t i = start + threadIdx.x;
-  if (i >= n) return;
-  // the LDS arrays hold positions start - R .. start + kBlock + R - 1
-  nn[i] = int32_t(ploc_partner(s_lo, s_hi, start - kPlocRadius, i, n, kPlocRadius));
+  merges = block_sum(merges, tmp);
+  absorbed = block_sum(absorbed, tmp);
+  if (threadIdx.x == 0) counts[blockIdx.x] = make_uint2(merges, absorbed);
 }
 
-__global__ __launch_bounds__(kBlock) void k_ploc_flags(const int32_t* __restrict__ nn, int64_t n,
-                                                       uint32_t* __restrict__ keep, uint32_t* __restrict__ merge) {
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const int32_t j = nn[i];
-  const bool mutual = nn[j] == int32_t(i);
-  merge[i] = (mutual && int64_t(j) > i) ? 1u : 0u;  // the lower position of a mutual pair makes the node
-  keep[i] = (mutual && int64_t(j) < i) ? 0u : 1u;   // the higher one is absorbed
-}
-
-struct PlocCompactArgs {
-  const float4* c_lo;
-  const float4* c_hi;
-  const int32_t* c_ref;
-  const int32_t* nn;
-  const uint32_t* keep_pos;   // exclusive prefix sums of the keep flags
-  const uint32_t* merge_pos;  // ... and of the merge flags
-  int64_t n;
-  int64_t node_base;  // index of this round's first new node
-  float4* o_lo;
-  float4* o_hi;
-  int32_t* o_ref;
+struct PlocNodes {
   int2* children;
   float4* nodebox;
+  uint32_t* dp_choice;
 };
 
-__global__ __launch_bounds__(kBlock) void k_ploc_compact(PlocCompactArgs a) {
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= a.n) return;
-  const int32_t j = a.nn[i];
-  const bool mutual = a.nn[j] == int32_t(i);
-  if (mutual && int64_t(j) < i) return;  // absorbed by cluster j
-  const uint32_t p = a.keep_pos[i];
-  if (mutual) {
-    const int64_t node = a.node_base + a.merge_pos[i];
-    const float4 alo = a.c_lo[i], ahi = a.c_hi[i], blo = a.c_lo[j], bhi = a.c_hi[j];
-    const float4 ulo = make_float4(fminf(alo.x, blo.x), fminf(alo.y, blo.y), fminf(alo.z, blo.z), 0.f);
-    const float4 uhi = make_float4(fmaxf(ahi.x, bhi.x), fmaxf(ahi.y, bhi.y), fmaxf(ahi.z, bhi.z), 0.f);
-    a.children[node] = make_int2(a.c_ref[i], a.c_ref[j]);
-    a.nodebox[2 * node] = ulo;
-    a.nodebox[2 * node + 1] = uhi;
-    a.o_lo[p] = ulo;
-    a.o_hi[p] = uhi;
-    a.o_ref[p] = int32_t(node);
-  } else {
-    a.o_lo[p] = a.c_lo[i];
-    a.o_hi[p] = a.c_hi[i];
-    a.o_ref[p] = a.c_ref[i];
+// Merges clusters a (lower position) and b into node `node`.
+__device__ inline void ploc_merge(const PlocNodes& out, int node, float4 alo, float4 ahi, float4 aext, float4 blo,
+                                  float4 bhi, float4 bext, float4* lo, float4* hi, float4* ext) {
+  const float4 ulo = make_float4(fminf(alo.x, blo.x), fminf(alo.y, blo.y), fminf(alo.z, blo.z), 0.f);
+  const float4 uhi = make_float4(fmaxf(ahi.x, bhi.x), fmaxf(ahi.y, bhi.y), fmaxf(ahi.z, bhi.z), 0.f);
+  const float ca[4] = {alo.w, ahi.w, aext.x, aext.y}, cb[4] = {blo.w, bhi.w, bext.x, bext.y};
+  uint32_t choice;
+  const float4 cost = dp_costs(half_area(ulo, uhi), ca, cb, &choice);
+  out.children[node] = make_int2(__float_as_int(aext.z), __float_as_int(bext.z));
+  out.nodebox[2 * int64_t(node)] = ulo;
+  out.nodebox[2 * int64_t(node) + 1] = uhi;
+  out.dp_choice[node] = choice;
+  *lo = make_float4(ulo.x, ulo.y, ulo.z, cost.x);
+  *hi = make_float4(uhi.x, uhi.y, uhi.z, cost.y);
+  *ext = make_float4(cost.z, cost.w, __int_as_float(node), 0.f);
+}
+
+// Makes the round's nodes and compacts the survivors into the other buffer.  `own` and the grid are those of
+// the round's search, whose counts place each block's output.
+__global__ __launch_bounds__(kBlock) void k_ploc_compact(Clusters c, BuildState* state, int slot,
+                                                         const int32_t* __restrict__ partner,
+                                                         const uint2* __restrict__ counts, uint32_t own,
+                                                         PlocNodes out) {
+  __shared__ uint32_t tmp[kBlock / 64];
+  __shared__ uint32_t wkeep[2][kBlock / 64], wmerge[2][kBlock / 64];
+  const BuildState::Ploc st = state->ploc[slot];
+  BuildState::Ploc* next = &state->ploc[slot ^ 1];
+  if (st.n <= kPlocTail) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *next = st;
+    return;
+  }
+  uint32_t begin, end;
+  ploc_range(st.n, own, blockIdx.x, gridDim.x, &begin, &end);
+  uint32_t m0 = 0, a0 = 0, mall = 0, aall = 0;
+  for (uint32_t k = threadIdx.x; k < gridDim.x; k += kBlock) {
+    const uint2 v = counts[k];
+    mall += v.x, aall += v.y;
+    if (k < blockIdx.x) m0 += v.x, a0 += v.y;
+  }
+  m0 = block_sum(m0, tmp), a0 = block_sum(a0, tmp), mall = block_sum(mall, tmp), aall = block_sum(aall, tmp);
+  // every round merges a pair, each pair absorbs one cluster, and T - 1 nodes are made in all
+  const bool bad = mall == 0 || mall != aall || mall > st.next;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (bad) atomicOr(&state->error, 1u);
+    *next = BuildState::Ploc{bad ? 0u : st.n - mall, bad ? 0u : st.next - mall, st.buf ^ 1u, 0u};
+  }
+  if (bad) return;
+  const int src = int(st.buf), dst = src ^ 1;
+  const float4 *ilo = src ? c.lo[1] : c.lo[0], *ihi = src ? c.hi[1] : c.hi[0], *iext = src ? c.ext[1] : c.ext[0];
+  float4 *olo = dst ? c.lo[1] : c.lo[0], *ohi = dst ? c.hi[1] : c.hi[0], *oext = dst ? c.ext[1] : c.ext[0];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t pos0 = begin - a0, node0 = st.next - mall + m0;
+  int par = 0;
+  for (uint32_t base = begin; base < end; base += kBlock, par ^= 1) {
+    const uint32_t i = base + threadIdx.x;
+    const bool valid = i < end;
+    const int32_t j = valid ? partner[i] : -1;
+    const bool merge = valid && j > int32_t(i), keep = valid && (j < 0 || merge);
+    const uint64_t bk = __ballot(keep), bm = __ballot(merge);
+    if (lane == 0) wkeep[par][wave] = uint32_t(__popcll(bk)), wmerge[par][wave] = uint32_t(__popcll(bm));
+    __syncthreads();
+    uint32_t kb = 0, mb = 0, kt = 0, mt = 0;
+    for (int w = 0; w < kBlock / 64; ++w) {
+      const uint32_t x = wkeep[par][w], y = wmerge[par][w];
+      if (w < wave) kb += x, mb += y;
+      kt += x, mt += y;
+    }
+    const uint64_t lt = lanemask_lt();
+    const uint32_t pos = pos0 + kb + uint32_t(__popcll(bk & lt));
+    if (keep) {
+      float4 lo = ilo[i], hi = ihi[i], ext = iext[i];
+      if (merge) {
+        const uint32_t node = node0 + mb + uint32_t(__popcll(bm & lt));
+        ploc_merge(out, int(node), lo, hi, ext, ilo[j], ihi[j], iext[j], &lo, &hi, &ext);
+      }
+      olo[pos] = lo;
+      ohi[pos] = hi;
+      oext[pos] = ext;
+    }
+    pos0 += kt;
+    node0 += mt;
+  }
+}
+
+// Triangle records in leaf order, and zeros over the part of the node area that the tree may leave unused, so
+// that every build of a scene stores the same bytes.
+struct PackArgs {
+  const float* tris;
+  const uint32_t* mat;
+  const uint32_t* order;  // null: input order
+  int64_t T;
+  float4* recs;
+  float4* nodes;
+  int64_t node_float4;
+};
+
+__device__ inline void pack_scene(const PackArgs& a, int64_t first, int64_t step) {
+  for (int64_t i = first; i < a.T; i += step) {
+    const uint32_t id = a.order ? a.order[i] : uint32_t(i);
+    const float* p = a.tris + 9 * int64_t(id);
+    const float v0x = p[0], v0y = p[1], v0z = p[2];
+    a.recs[3 * i + 0] = make_float4(v0x, v0y, v0z, __int_as_float(int(id)));
+    a.recs[3 * i + 1] = make_float4(p[3] - v0x, p[4] - v0y, p[5] - v0z, __int_as_float(int(a.mat[id])));
+    a.recs[3 * i + 2] = make_float4(p[6] - v0x, p[7] - v0y, p[8] - v0z, 0.f);
+  }
+  for (int64_t i = first; i < a.node_float4; i += step) a.nodes[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+__global__ __launch_bounds__(kBlock) void k_pack(PackArgs a) {
+  pack_scene(a, int64_t(blockIdx.x) * kBlock + threadIdx.x, int64_t(gridDim.x) * kBlock);
+}
+
+// The remaining rounds of at most kPlocTail clusters, in one workgroup: a round costs a search whose 64
+// candidates are split over as many lanes as there are to spare, and three barriers (about 30 rounds, 116 us).
+// The launch's other workgroups pack the triangles meanwhile (77 us as a launch of its own, for 3.4M).
+__global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState* state, int slot, PlocNodes out,
+                                                         PackArgs pack) {
+  constexpr int R = kPlocRadius, kW = kPlocTail / 64;
+  __shared__ float4 s_lo[kPlocTail], s_hi[kPlocTail], s_ext[kPlocTail];
+  __shared__ int s_nn[kPlocTail];
+  __shared__ uint32_t wkeep[kW], wmerge[kW];
+  if (blockIdx.x > 0) {
+    pack_scene(pack, int64_t(blockIdx.x - 1) * kPlocTail + threadIdx.x, int64_t(gridDim.x - 1) * kPlocTail);
+    return;
+  }
+  BuildState::Ploc st = state->ploc[slot];
+  if (st.n > kPlocTail || st.n < 2) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < int(st.n)) {
+    s_lo[tid] = st.buf ? c.lo[1][tid] : c.lo[0][tid];
+    s_hi[tid] = st.buf ? c.hi[1][tid] : c.hi[0][tid];
+    s_ext[tid] = st.buf ? c.ext[1][tid] : c.ext[0][tid];
+  }
+  __syncthreads();
+  bool bad = false;
+  int n = int(st.n), next = int(st.next);
+  while (n > 1) {  // every round merges a pair, or ends the loop
+    int log2l = 0;
+    while (log2l < 5 && (n << (log2l + 1)) <= kPlocTail) ++log2l;
+    const int lanes = 1 << log2l, i = tid >> log2l, sub = tid & (lanes - 1);
+    float best = INFINITY;
+    int bk = 0;
+    if (i < n) {
+      const float4 alo = s_lo[i], ahi = s_hi[i];
+      const int first = max(-R, -i), last = min(R, n - 1 - i);
+      for (int k = first + sub; k <= last; k += lanes) {
+        const float ar = merged_area(alo, ahi, s_lo[i + k], s_hi[i + k]);
+        if (k != 0 && ar < best) best = ar, bk = k;
+      }
+    }
+    for (int off = 1; off < lanes; off <<= 1) {
+      const float ob = __shfl_xor(best, off);
+      const int ok = __shfl_xor(bk, off);
+      if (ob < best || (ob == best && ok < bk)) best = ob, bk = ok;
+    }
+    if (i < n && sub == 0) {
+      if (!(best < INFINITY)) bk = i > 0 ? -1 : 1;
+      const int p = i ^ 1;
+      if (p < n && ploc_takes_parity(best, s_lo[i], s_hi[i], s_lo[p], s_hi[p])) bk = p - i;
+      s_nn[i] = i + bk;
+    }
+    __syncthreads();
+    const int j = tid < n ? s_nn[tid] : -1;
+    const bool mutual = tid < n && s_nn[j] == tid;
+    const bool merge = mutual && j > tid, keep = tid < n && !(mutual && j < tid);
+    const uint64_t bkeep = __ballot(keep), bmerge = __ballot(merge);
+    if (lane == 0) wkeep[wave] = uint32_t(__popcll(bkeep)), wmerge[wave] = uint32_t(__popcll(bmerge));
+    float4 lo, hi, ext, blo, bhi, bext;
+    if (keep) lo = s_lo[tid], hi = s_hi[tid], ext = s_ext[tid];
+    if (merge) blo = s_lo[j], bhi = s_hi[j], bext = s_ext[j];
+    __syncthreads();
+    int kb = 0, mb = 0, mt = 0;
+    for (int w = 0; w < kW; ++w) {
+      const int x = int(wkeep[w]), y = int(wmerge[w]);
+      if (w < wave) kb += x, mb += y;
+      mt += y;
+    }
+    if (mt == 0 || mt > next) {
+      bad = true;
+      break;
+    }
+    next -= mt;
+    n -= mt;
+    const uint64_t lt = lanemask_lt();
+    if (merge) ploc_merge(out, next + mb + __popcll(bmerge & lt), lo, hi, ext, blo, bhi, bext, &lo, &hi, &ext);
+    if (keep) {
+      const int pos = kb + __popcll(bkeep & lt);
+      s_lo[pos] = lo;
+      s_hi[pos] = hi;
+      s_ext[pos] = ext;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    bad = bad || next != 0;
+    if (bad) atomicOr(&state->error, 1u);
+    state->ploc[0].n = state->ploc[1].n = bad ? 0u : 1u;
   }
 }
 
@@ -637,10 +904,13 @@ __global__ __launch_bounds__(kBlock) void k_ploc_compact(PlocCompactArgs a) {
 // children and opens some of them into their own children (keeping left-to-right order) where the
 // cost table says, so it holds up to four.  Internal children become the next level's nodes; their
 // indices come from a prefix sum, so the layout is deterministic and each level's nodes are
-// contiguous.
+// contiguous.  A tree has 11 (10k triangles) to 17 levels (3.4M); their sizes stay on the device, as the
+// clustering's do.
 // ---------------------------------------------------------------------------------------------
 
 constexpr int kWideEmpty = INT32_MIN;
+constexpr int kWideBlocks = 1024;  // most blocks of a level: each sums the others' counts
+constexpr int kWideTail = 1024;    // a level of at most this many nodes is done by the one-workgroup kernel
 
 struct WideArgs {
   const int2* children;
@@ -648,27 +918,24 @@ struct WideArgs {
   const float4* leaf_lo;
   const float4* leaf_hi;
   const uint32_t* sorted_ids;
-  const int2* frontier;  // (binary node, BVH4 index)
-  int64_t m;
-  int4* sel;             // chosen binary-tree references per frontier item
-  uint32_t* nint;        // internal children per item -> exclusive offsets (+ total at [m])
-  int2* next;            // next frontier
-  float4* nodes;         // 8 float4 per BVH4 node
-  int64_t level_base;    // BVH4 index of the next level's first node
-  float pad;
   const uint32_t* dp_choice;  // per binary node: the cost-optimal cut
+  int2* frontier[2];          // (binary node, BVH4 index) of level l's nodes in frontier[l & 1]
+  int4* sel;                  // chosen binary-tree references per frontier item
+  uint32_t* counts;           // internal children of a block's items
+  float4* nodes;
+  uint32_t max_nodes;         // T - 1
+  BuildState* state;
 };
 
-
-__global__ __launch_bounds__(kBlock) void k_wide_select(WideArgs a) {
-  int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= a.m) return;
-  const int2 ch = a.children[a.frontier[i].x];
+// The up to four binary-tree references that BVH4 node of binary node `bin` holds; returns how many are
+// internal.
+__device__ inline uint32_t wide_select(const WideArgs& a, int bin, int (&out)[4]) {
+  const int2 ch = a.children[bin];
   int r[4] = {ch.x, ch.y, kWideEmpty, kWideEmpty};
   int cnt = 2;
   // follow the cost-optimal cut: the node's four slots split k : 4 - k between its children, and a
   // child with j > 1 slots is opened when that is cheaper
-  int js[4] = {int((a.dp_choice[a.frontier[i].x] >> 6) & 3u), 0, 0, 0};
+  int js[4] = {int((a.dp_choice[bin] >> 6) & 3u), 0, 0, 0};
   js[1] = 4 - js[0];
   for (int step = 0; step < 2; ++step) {
     int p = -1;
@@ -698,24 +965,38 @@ __global__ __launch_bounds__(kBlock) void k_wide_select(WideArgs a) {
     }
     ++cnt;
   }
-  a.sel[i] = make_int4(r[0], r[1], r[2], r[3]);
   uint32_t n = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) n += (r[k] >= 0) ? 1u : 0u;
-  a.nint[i] = n;
+  for (int k = 0; k < 4; ++k) {
+    out[k] = r[k];
+    n += (r[k] >= 0) ? 1u : 0u;
+  }
+  return n;
 }
 
-__global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a) {
-  int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= a.m) return;
-  const int b4 = a.frontier[i].y;
-  const int4 s4 = a.sel[i];
-  const int r[4] = {s4.x, s4.y, s4.z, s4.w};
-  const uint32_t off = a.nint[i];
+// The next FP64 value above x >= 0, and below x >= 0 (0 stays 0).
+__device__ inline double next_double_up(double x) { return __longlong_as_double(__double_as_longlong(x) + 1); }
+__device__ inline double next_double_down(double x) {
+  return x == 0.0 ? 0.0 : __longlong_as_double(__double_as_longlong(x) - 1);
+}
+
+// The smallest e >= -126 with 255 * 2^e >= ext, for ext > 0: with ext = m 2^k, 1 <= m < 2, and
+// 255 = 1.9921875 * 2^7, it is k - 7, or k - 6 where m > 1.9921875.
+__device__ inline int grid_exponent(double ext) {
+  const uint64_t bits = uint64_t(__double_as_longlong(ext));
+  const int k = int(bits >> 52) - 1023;
+  const int e = k - 7 + ((bits & 0xfffffffffffffull) > 0xfe00000000000ull ? 1 : 0);
+  return e < -126 ? -126 : e;
+}
+
+// Writes BVH4 node `b4` with children r; its internal children are BVH4 nodes first, first + 1, ... and
+// entries slot, slot + 1, ... of the next level.
+__device__ inline void wide_emit(const WideArgs& a, float p, int b4, const int (&r)[4], uint32_t first, uint32_t slot,
+                                 int2* next) {
   float lo[3][4], hi[3][4];
   int ref[4];
   uint32_t k_int = 0;
-  const float p = a.pad;
+  
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     float4 l, h;
@@ -736,8 +1017,8 @@ __global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a) {
       h = a.nodebox[2 * r[k] + 1];
       l = make_float4(l.x - p, l.y - p, l.z - p, 0.f);
       h = make_float4(h.x + p, h.y + p, h.z + p, 0.f);
-      const int idx = int(a.level_base + off + k_int);
-      a.next[off + k_int] = make_int2(r[k], idx);
+      const int idx = int(first + k_int);
+      next[slot + k_int] = make_int2(r[k], idx);
       ++k_int;
       ref[k] = idx;
     }
@@ -765,24 +1046,15 @@ __global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a) {
   float steps[3];
   for (int ax = 0; ax < 3; ++ax) {
     const double base = double(plo[ax]);
-    const double ext = nextafter(double(phi[ax]) - base, INFINITY);
-    int e = -126;
-    if (ext > 0.0) {
-      int k2;
-      frexp(ext / 255.0, &k2);
-      e = k2;
-      while (e > -126 && ldexp(255.0, e - 1) >= ext) --e;
-      while (ldexp(255.0, e) < ext) ++e;
-    }
-    const double step = ldexp(1.0, e);
+    const double ext = next_double_up(double(phi[ax]) - base);
+    const int e = grid_exponent(ext);
     steps[ax] = __uint_as_float(uint32_t(e + 24 + 127) << 23);  // 2^(e + 24)
     for (int k = 0; k < 4; ++k) {
       uint32_t ql = 255u, qh = 0u;
       if (r[k] != kWideEmpty) {
-        const double dl = nextafter(double(lo[ax][k]) - base, -INFINITY);
-        const double dh = nextafter(double(hi[ax][k]) - base, INFINITY);
-        ql = uint32_t(fmin(fmax(floor(dl / step), 0.0), 255.0));
-        qh = uint32_t(fmin(fmax(ceil(dh / step), 0.0), 255.0));
+        const double dl = double(lo[ax][k]) - base, dh = double(hi[ax][k]) - base;  // both >= 0
+        ql = uint32_t(fmin(floor(ldexp(next_double_down(dl), -e)), 255.0));
+        qh = uint32_t(fmin(ceil(ldexp(next_double_up(dh), -e)), 255.0));
       }
       qlo[ax] |= ql << (8 * k);
       qhi[ax] |= qh << (8 * k);
@@ -808,19 +1080,152 @@ __global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a) {
 #endif
 }
 
-__global__ void k_set_int2(int2* p, int2 v) { *p = v; }
+// Conservative box growth (slab and triangle-test rounding).
+__device__ inline float wide_pad(const Bounds6& b) {
+  float m = 0.f;
+  for (int k = 0; k < 3; ++k) m = fmaxf(m, fmaxf(fabsf(b.blo[k]), fabsf(b.bhi[k])));
+  return m * 0x1p-18f + 1e-20f;
+}
 
-__global__ __launch_bounds__(kBlock) void k_pack_tris(const float* __restrict__ tris, const uint32_t* __restrict__ mat,
-                                                      const uint32_t* __restrict__ order, int64_t T,
-                                                      float4* __restrict__ recs) {
-  int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= T) return;
-  uint32_t id = order ? order[i] : uint32_t(i);
-  const float* p = tris + 9 * int64_t(id);
-  float v0x = p[0], v0y = p[1], v0z = p[2];
-  recs[3 * i + 0] = make_float4(v0x, v0y, v0z, __int_as_float(int(id)));
-  recs[3 * i + 1] = make_float4(p[3] - v0x, p[4] - v0y, p[5] - v0z, __int_as_float(int(mat[id])));
-  recs[3 * i + 2] = make_float4(p[6] - v0x, p[7] - v0y, p[8] - v0z, 0.f);
+// One level, first half: the cut of every node, and each block's count of the next level's nodes.
+__global__ __launch_bounds__(kBlock) void k_wide_select(WideArgs a, int slot) {
+  __shared__ uint32_t tmp[kBlock / 64];
+  const BuildState::Wide st = a.state->wide[slot];
+  if (st.m <= kWideTail) return;
+  const int2* frontier = (st.level & 1) ? a.frontier[1] : a.frontier[0];
+  uint32_t begin, end, n = 0;
+  ploc_range(st.m, kBlock, blockIdx.x, gridDim.x, &begin, &end);
+  for (uint32_t i = begin + threadIdx.x; i < end; i += kBlock) {
+    int r[4];
+    n += wide_select(a, frontier[i].x, r);
+    a.sel[i] = make_int4(r[0], r[1], r[2], r[3]);
+  }
+  n = block_sum(n, tmp);
+  if (threadIdx.x == 0) a.counts[blockIdx.x] = n;
+}
+
+// Second half: the nodes, and the next level's entries.
+__global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a, int slot) {
+  __shared__ uint32_t tmp[kBlock / 64];
+  __shared__ uint32_t wcnt[2][kBlock / 64];
+  const BuildState::Wide st = a.state->wide[slot];
+  BuildState::Wide* out = &a.state->wide[slot ^ 1];
+  if (st.m <= kWideTail) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *out = st;
+    return;
+  }
+  const int2* frontier = (st.level & 1) ? a.frontier[1] : a.frontier[0];
+  int2* next = (st.level & 1) ? a.frontier[0] : a.frontier[1];
+  uint32_t begin, end, before = 0, total = 0;
+  ploc_range(st.m, kBlock, blockIdx.x, gridDim.x, &begin, &end);
+  for (uint32_t k = threadIdx.x; k < gridDim.x; k += kBlock) {
+    const uint32_t v = a.counts[k];
+    total += v;
+    if (k < blockIdx.x) before += v;
+  }
+  before = block_sum(before, tmp), total = block_sum(total, tmp);
+  const bool bad = total > a.max_nodes - st.allocated;  // every level adds nodes: impossible for a valid tree
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (bad) atomicOr(&a.state->error, 2u);
+    *out = BuildState::Wide{bad ? 0u : total, st.allocated + (bad ? 0u : total), st.level + 1u, 0u};
+  }
+  if (bad) return;
+  const float pad = wide_pad(a.state->bounds);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int par = 0;
+  for (uint32_t base = begin; base < end; base += kBlock, par ^= 1) {
+    const uint32_t i = base + threadIdx.x;
+    const bool valid = i < end;
+    int r[4] = {kWideEmpty, kWideEmpty, kWideEmpty, kWideEmpty};
+    if (valid) {
+      const int4 s4 = a.sel[i];
+      r[0] = s4.x, r[1] = s4.y, r[2] = s4.z, r[3] = s4.w;
+    }
+    uint32_t n = 0;
+    for (int k = 0; k < 4; ++k) n += r[k] >= 0 ? 1u : 0u;
+    uint32_t scan = n;  // inclusive over the wave
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(scan, off);
+      if (lane >= off) scan += u;
+    }
+    if (lane == 63) wcnt[par][wave] = scan;
+    __syncthreads();
+    uint32_t wb = 0, all = 0;
+    for (int w = 0; w < kBlock / 64; ++w) {
+      if (w < wave) wb += wcnt[par][w];
+      all += wcnt[par][w];
+    }
+    const uint32_t off = before + wb + scan - n;
+    if (valid) wide_emit(a, pad, frontier[i].y, r, st.allocated + off, off, next);
+    before += all;
+  }
+}
+
+// Every level of at most kWideTail nodes from the state's level on, in one workgroup: the top of the tree
+// before the wide levels, and what is left after them.
+__global__ __launch_bounds__(kWideTail) void k_wide_levels(WideArgs a, int slot) {
+  constexpr int kW = kWideTail / 64;
+  __shared__ uint32_t wcnt[kW];
+  BuildState::Wide st = a.state->wide[slot];
+  if (a.state->ploc[0].n != 1 || a.state->ploc[1].n != 1) return;  // the binary tree is not complete yet
+  const float pad = wide_pad(a.state->bounds);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  bool bad = false;
+  while (st.m > 0 && st.m <= kWideTail) {  // allocated grows with every level and is bounded
+    const int2* frontier = (st.level & 1) ? a.frontier[1] : a.frontier[0];
+    int2* next = (st.level & 1) ? a.frontier[0] : a.frontier[1];
+    const bool valid = threadIdx.x < st.m;
+    int r[4] = {kWideEmpty, kWideEmpty, kWideEmpty, kWideEmpty};
+    int2 item = make_int2(0, 0);
+    uint32_t n = 0;
+    if (valid) {
+      item = frontier[threadIdx.x];
+      n = wide_select(a, item.x, r);
+    }
+    uint32_t scan = n;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(scan, off);
+      if (lane >= off) scan += u;
+    }
+    if (lane == 63) wcnt[wave] = scan;
+    __syncthreads();
+    uint32_t wb = 0, total = 0;
+    for (int w = 0; w < kW; ++w) {
+      if (w < wave) wb += wcnt[w];
+      total += wcnt[w];
+    }
+    if (total > a.max_nodes - st.allocated) {
+      bad = true;
+      break;
+    }
+    const uint32_t off = wb + scan - n;
+    if (valid) wide_emit(a, pad, item.y, r, st.allocated + off, off, next);
+    st.m = total;
+    st.allocated += total;
+    ++st.level;
+    __syncthreads();  // the next level's entries are written, wcnt is free
+  }
+  if (threadIdx.x == 0) {
+    if (bad) {
+      atomicOr(&a.state->error, 2u);
+      st.m = 0;
+    }
+    a.state->wide[slot] = st;
+  }
+}
+
+// The state a build starts from.  ploc_clusters: 1 with the Karras tree, whose nodes are made elsewhere.
+__global__ void k_build_init(BuildState* s, uint32_t ploc_clusters, int2* frontier0) {
+  if (threadIdx.x != 0) return;
+  s->status = 0;
+  s->max_depth = 0;
+  s->error = 0;
+  for (int k = 0; k < 2; ++k) {
+    s->ploc[k] = BuildState::Ploc{ploc_clusters, ploc_clusters - 1u, 0u, 0u};
+    s->wide[k] = BuildState::Wide{1u, 1u, 0u, 0u};
+  }
+  for (int k = 0; k < 3; ++k) s->bounds.clo[k] = s->bounds.chi[k] = s->bounds.blo[k] = s->bounds.bhi[k] = 0.f;
+  if (frontier0) *frontier0 = make_int2(0, 0);
 }
 
 template <typename T>
@@ -874,7 +1279,7 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
   off = 0;
   p.num_blocks_prep = (T + kBlock - 1) / kBlock;
   p.num_sort_blocks = (T + kSortTile - 1) / kSortTile;
-  p.status_off = take(64);
+  p.status_off = take(256);
   p.partial_off = take(size_t(p.num_blocks_prep > 0 ? p.num_blocks_prep : 1) * sizeof(Bounds6));
   if (T > 0) {
     p.lo_off = take(size_t(T) * 16);
@@ -893,22 +1298,21 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
       p.parent_off = take(size_t(2 * T) * 4);
       p.flags_off = take(size_t(T) * 4);
     }
-    p.dp_cost_off = take(size_t(T) * 16);
+    if (!ploc) p.dp_cost_off = take(size_t(T) * 16);
     p.dp_choice_off = take(size_t(T) * 4);
     p.frontier_off[0] = take(size_t(T) * 8);
     p.frontier_off[1] = take(size_t(T) * 8);
     p.sel_off = take(size_t(T) * 16);
-    p.nint_off = take(size_t(T + 1) * 4);
-    p.scan_tmp_off = take(size_t(scan_tmp_entries(std::max<int64_t>(T + 1, p.num_sort_blocks * kRadix))) * 4);
+    p.scan_tmp_off = take(size_t(scan_tmp_entries(p.num_sort_blocks * kRadix)) * 4);
+    p.counts_off = take(size_t(std::max(kPlocBlocks, kWideBlocks)) * 8);
     if (ploc) {
       for (int k = 0; k < 2; ++k) {
         p.ploc_lo_off[k] = take(size_t(T) * 16);
         p.ploc_hi_off[k] = take(size_t(T) * 16);
-        p.ploc_ref_off[k] = take(size_t(T) * 4);
       }
-      p.ploc_nn_off = take(size_t(T) * 4);
-      p.ploc_keep_off = take(size_t(T + 1) * 4);
-      p.ploc_merge_off = take(size_t(T + 1) * 4);
+      p.ploc_ext_off[0] = p.sel_off;  // free until the collapse
+      p.ploc_ext_off[1] = take(size_t(T) * 16);
+      p.ploc_partner_off = take(size_t(T) * 4);
     }
   }
   p.scratch_bytes = off;
@@ -919,7 +1323,8 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
                               hipStream_t stream, BuildResult* result) {
   const int64_t T = desc->num_triangles;
   const int S = desc->num_spheres, P = desc->num_planes, M = desc->num_materials, L = desc->num_lights;
-  uint32_t* status = reinterpret_cast<uint32_t*>(scratch + plan.status_off);
+  BuildState* state = reinterpret_cast<BuildState*>(scratch + plan.status_off);
+  uint32_t* status = &state->status;
   hipError_t e;
 #define SRT_CHECK(x)                   \
   do {                                 \
@@ -928,7 +1333,8 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
   } while (0)
 #define SRT_LAUNCH_CHECK() SRT_CHECK(hipGetLastError())
 
-  k_fill<uint32_t><<<1, 64, 0, stream>>>(status, 0u, 16);
+  k_build_init<<<1, 64, 0, stream>>>(state, plan.bvh && plan.ploc ? uint32_t(T) : 1u,
+                                     plan.bvh ? reinterpret_cast<int2*>(scratch + plan.frontier_off[0]) : nullptr);
   SRT_LAUNCH_CHECK();
 
   // spheres, planes, materials, lights
@@ -983,8 +1389,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
   for (int a = 0; a < 3; ++a) result->lo[a] = result->hi[a] = 0.f;
 
   float4* recs = reinterpret_cast<float4*>(storage + plan.tris_off);
-  Bounds6 bounds{};
-  int32_t depth = 0;
+  BuildState done{};
   if (T > 0) {
     float4* lo = reinterpret_cast<float4*>(scratch + plan.lo_off);
     float4* hi = reinterpret_cast<float4*>(scratch + plan.hi_off);
@@ -992,7 +1397,8 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
     k_tri_prep<<<blocks_for(T), kBlock, 0, stream>>>(desc->triangles, desc->tri_material, T, M, lo, hi, partial,
                                                      status);
     SRT_LAUNCH_CHECK();
-    k_reduce_bounds<<<1, kBlock, 0, stream>>>(partial, plan.num_blocks_prep);
+    PackArgs pack{desc->triangles, desc->tri_material, nullptr, T, recs, nullptr, 0};
+    k_reduce_bounds<<<1, kBlock, 0, stream>>>(partial, plan.num_blocks_prep, &state->bounds);
     SRT_LAUNCH_CHECK();
 
     if (plan.bvh) {
@@ -1002,7 +1408,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       uint32_t* i1 = reinterpret_cast<uint32_t*>(scratch + plan.ids1_off);
       uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + plan.hist_off);
       uint32_t* scan_tmp = reinterpret_cast<uint32_t*>(scratch + plan.scan_tmp_off);
-      k_morton<<<blocks_for(T), kBlock, 0, stream>>>(lo, hi, partial, T, k0, i0);
+      k_morton<<<blocks_for(T), kBlock, 0, stream>>>(lo, hi, &state->bounds, T, k0, i0);
       SRT_LAUNCH_CHECK();
       const int64_t nb = plan.num_sort_blocks;
       for (int pass = 0; pass < 8; ++pass) {
@@ -1016,143 +1422,128 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         std::swap(i0, i1);
       }
       // after 8 passes the sorted data is back in the *0 buffers
+      pack.order = i0;
+      // a node has at most four children, so the tree has at least (T - 1) / 3 of the T - 1 nodes
+      const size_t zero_from = plan.nodes_off + size_t((T - 1) / 3) * kNodeBytes;
+      pack.nodes = reinterpret_cast<float4*>(storage + zero_from);
+      pack.node_float4 = int64_t((plan.tris_off - zero_from) / 16);
       int2* children = reinterpret_cast<int2*>(scratch + plan.children_off);
       int2* range = reinterpret_cast<int2*>(scratch + plan.range_off);
       int32_t* parent = reinterpret_cast<int32_t*>(scratch + plan.parent_off);
       uint32_t* flags = reinterpret_cast<uint32_t*>(scratch + plan.flags_off);
       float4* nodebox = reinterpret_cast<float4*>(scratch + plan.nodebox_off);
-      float4* dp_cost = reinterpret_cast<float4*>(scratch + plan.dp_cost_off);
       uint32_t* dp_choice = reinterpret_cast<uint32_t*>(scratch + plan.dp_choice_off);
+      uint2* counts = reinterpret_cast<uint2*>(scratch + plan.counts_off);
+      Clusters cl{};
+      int32_t* partner = nullptr;
+      const PlocNodes made{children, nodebox, dp_choice};
+      bool packed = false;
+      int round = 0;
+      double expected = double(T);  // clusters left, were every round to leave the usual share
+      // `rounds` clustering rounds and the one-workgroup rest.  A round leaves 0.57 of the clusters at first
+      // and 0.81 to 0.83 later; a grid made for too few clusters takes more tiles a block, and a round that
+      // finds at most kPlocTail clusters does nothing.
+      auto cluster = [&](int rounds) -> hipError_t {
+        for (int k = 0; k < rounds; ++k, ++round) {
+          const bool few = expected < 65536;  // tiles of one lane a position would leave most of the chip idle
+          const unsigned own = kPlocBlock / (few ? 4 : 1) - 2 * kPlocRadius;
+          const unsigned grid = unsigned(std::min<double>(kPlocBlocks, std::max(1.0, std::ceil(expected / own))));
+          if (few)
+            k_ploc_nn<4><<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
+          else
+            k_ploc_nn<1><<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+          k_ploc_compact<<<grid, kBlock, 0, stream>>>(cl, state, round & 1, partner, counts, own, made);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+          expected = std::max(double(kPlocTail), expected * (round == 0 ? 0.6 : 0.83));
+        }
+        const int64_t blocks = packed ? 0 : std::min<int64_t>(kPackBlocks, (T + kPlocTail - 1) / kPlocTail);
+        packed = true;
+        k_ploc_tail<<<unsigned(1 + blocks), kPlocTail, 0, stream>>>(cl, state, round & 1, made, pack);
+        return hipGetLastError();
+      };
       if (plan.ploc) {
-        float4* c_lo[2] = {reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[0]),
-                           reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[1])};
-        float4* c_hi[2] = {reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[0]),
-                           reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[1])};
-        int32_t* c_ref[2] = {reinterpret_cast<int32_t*>(scratch + plan.ploc_ref_off[0]),
-                             reinterpret_cast<int32_t*>(scratch + plan.ploc_ref_off[1])};
-        int32_t* nn = reinterpret_cast<int32_t*>(scratch + plan.ploc_nn_off);
-        uint32_t* keep = reinterpret_cast<uint32_t*>(scratch + plan.ploc_keep_off);
-        uint32_t* merge = reinterpret_cast<uint32_t*>(scratch + plan.ploc_merge_off);
-        k_ploc_init<<<blocks_for(T), kBlock, 0, stream>>>(i0, lo, hi, T, c_lo[0], c_hi[0], c_ref[0]);
+        for (int k = 0; k < 2; ++k) {
+          cl.lo[k] = reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[k]);
+          cl.hi[k] = reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[k]);
+          cl.ext[k] = reinterpret_cast<float4*>(scratch + plan.ploc_ext_off[k]);
+        }
+        partner = reinterpret_cast<int32_t*>(scratch + plan.ploc_partner_off);
+        k_ploc_init<<<blocks_for(T), kBlock, 0, stream>>>(i0, lo, hi, T, cl);
         SRT_LAUNCH_CHECK();
-        std::vector<std::pair<int64_t, int64_t>> round_nodes;  // nodes each round created, in merge order
-        int64_t n = T, next = T - 1;
-        int cur = 0;
-        for (int round = 0; n > 1; ++round) {
-          if (round >= T) return hipErrorUnknown;  // every round merges at least one pair
-          k_ploc_nn<<<blocks_for(n), kBlock, 0, stream>>>(c_lo[cur], c_hi[cur], n, nn);
-          SRT_LAUNCH_CHECK();
-          k_ploc_flags<<<blocks_for(n), kBlock, 0, stream>>>(nn, n, keep, merge);
-          SRT_LAUNCH_CHECK();
-          SRT_CHECK(scan_exclusive(keep, n, keep + n, scan_tmp, stream));
-          SRT_CHECK(scan_exclusive(merge, n, merge + n, scan_tmp, stream));
-          uint32_t totals[2] = {0u, 0u};
-          SRT_CHECK(hipMemcpyAsync(&totals[0], keep + n, 4, hipMemcpyDeviceToHost, stream));
-          SRT_CHECK(hipMemcpyAsync(&totals[1], merge + n, 4, hipMemcpyDeviceToHost, stream));
-          SRT_CHECK(hipStreamSynchronize(stream));
-          const int64_t merges = totals[1];
-          if (merges < 1 || merges > next || int64_t(totals[0]) != n - merges) return hipErrorUnknown;
-          PlocCompactArgs ca;
-          ca.c_lo = c_lo[cur];
-          ca.c_hi = c_hi[cur];
-          ca.c_ref = c_ref[cur];
-          ca.nn = nn;
-          ca.keep_pos = keep;
-          ca.merge_pos = merge;
-          ca.n = n;
-          ca.node_base = next - merges;
-          ca.o_lo = c_lo[cur ^ 1];
-          ca.o_hi = c_hi[cur ^ 1];
-          ca.o_ref = c_ref[cur ^ 1];
-          ca.children = children;
-          ca.nodebox = nodebox;
-          k_ploc_compact<<<blocks_for(n), kBlock, 0, stream>>>(ca);
-          SRT_LAUNCH_CHECK();
-          round_nodes.emplace_back(next - merges, merges);
-          next -= merges;
-          n -= merges;
-          cur ^= 1;
-        }
-        if (next != 0) return hipErrorUnknown;  // T - 1 merges make a binary tree rooted at node 0
-        for (const auto& rn : round_nodes) {  // children were created in earlier rounds
-          k_wide_dp<<<blocks_for(rn.second), kBlock, 0, stream>>>(children, nodebox, lo, hi, i0, dp_cost, dp_choice,
-                                                                  rn.first, rn.second);
-          SRT_LAUNCH_CHECK();
-        }
-        SRT_CHECK(hipMemcpyAsync(&bounds, partial, sizeof(bounds), hipMemcpyDeviceToHost, stream));
-        SRT_CHECK(hipStreamSynchronize(stream));
+        SRT_CHECK(cluster(T <= kPlocTail ? 0 : 2 + int(std::ceil(std::log(double(T) / kPlocTail) / 0.2))));
       } else {
-        int32_t* dmax = reinterpret_cast<int32_t*>(status + 4);
+        k_pack<<<blocks_for(T), kBlock, 0, stream>>>(pack);
+        SRT_LAUNCH_CHECK();
+        float4* dp_cost = reinterpret_cast<float4*>(scratch + plan.dp_cost_off);
         k_karras<<<blocks_for(T - 1), kBlock, 0, stream>>>(k0, T, children, parent, range);
         SRT_LAUNCH_CHECK();
         k_fill<uint32_t><<<blocks_for(T - 1), kBlock, 0, stream>>>(flags, 0u, T - 1);
         SRT_LAUNCH_CHECK();
-        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(children, parent, lo, hi, i0, nodebox, flags, T, dmax, status,
-                                                      dp_cost, dp_choice);
+        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(children, parent, lo, hi, i0, nodebox, flags, T,
+                                                      &state->max_depth, status, dp_cost, dp_choice);
         SRT_LAUNCH_CHECK();
-        // read back the scene bounds for the padding
-        SRT_CHECK(hipMemcpyAsync(&bounds, partial, sizeof(bounds), hipMemcpyDeviceToHost, stream));
-        SRT_CHECK(hipMemcpyAsync(&depth, dmax, sizeof(depth), hipMemcpyDeviceToHost, stream));
-        SRT_CHECK(hipStreamSynchronize(stream));
       }
-      float coord_max = 0.f;
-      for (int a = 0; a < 3; ++a)
-        coord_max = std::max(coord_max, std::max(std::fabs(bounds.blo[a]), std::fabs(bounds.bhi[a])));
-      WideArgs wa;
+      WideArgs wa{};
       wa.children = children;
       wa.nodebox = nodebox;
       wa.leaf_lo = lo;
       wa.leaf_hi = hi;
       wa.sorted_ids = i0;
-      wa.sel = reinterpret_cast<int4*>(scratch + plan.sel_off);
-      wa.nint = reinterpret_cast<uint32_t*>(scratch + plan.nint_off);
-      wa.nodes = reinterpret_cast<float4*>(storage + plan.nodes_off);
-      wa.pad = coord_max * 0x1p-18f + 1e-20f;  // conservative box growth (slab and triangle-test rounding)
       wa.dp_choice = dp_choice;
-      int2* fr[2] = {reinterpret_cast<int2*>(scratch + plan.frontier_off[0]),
-                     reinterpret_cast<int2*>(scratch + plan.frontier_off[1])};
-      k_set_int2<<<1, 1, 0, stream>>>(fr[0], make_int2(0, 0));
-      SRT_LAUNCH_CHECK();
-      int64_t m = 1, allocated = 1;
-      int levels = 0;
-      while (m > 0) {
-        wa.frontier = fr[levels & 1];
-        wa.next = fr[(levels + 1) & 1];
-        wa.m = m;
-        wa.level_base = allocated;
-        k_wide_select<<<blocks_for(m), kBlock, 0, stream>>>(wa);
-        SRT_LAUNCH_CHECK();
-        SRT_CHECK(scan_exclusive(wa.nint, m, wa.nint + m, scan_tmp, stream));
-        k_wide_emit<<<blocks_for(m), kBlock, 0, stream>>>(wa);
-        SRT_LAUNCH_CHECK();
-        uint32_t next_m = 0;
-        SRT_CHECK(hipMemcpyAsync(&next_m, wa.nint + m, sizeof(next_m), hipMemcpyDeviceToHost, stream));
+      wa.sel = reinterpret_cast<int4*>(scratch + plan.sel_off);
+      wa.counts = reinterpret_cast<uint32_t*>(counts);
+      wa.nodes = reinterpret_cast<float4*>(storage + plan.nodes_off);
+      wa.max_nodes = uint32_t(T - 1);
+      wa.state = state;
+      for (int k = 0; k < 2; ++k) wa.frontier[k] = reinterpret_cast<int2*>(scratch + plan.frontier_off[k]);
+      int level = 0;
+      // the top of the tree, `levels` wide levels and what is left
+      auto collapse = [&](int levels) -> hipError_t {
+        k_wide_levels<<<1, kWideTail, 0, stream>>>(wa, level & 1);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const unsigned grid = unsigned(std::min<int64_t>(kWideBlocks, (T + kBlock - 1) / kBlock));
+        for (int k = 0; k < levels; ++k, ++level) {
+          k_wide_select<<<grid, kBlock, 0, stream>>>(wa, level & 1);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+          k_wide_emit<<<grid, kBlock, 0, stream>>>(wa, level & 1);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        if (levels > 0) k_wide_levels<<<1, kWideTail, 0, stream>>>(wa, level & 1);
+        return hipGetLastError();
+      };
+      // levels of more than kWideTail nodes: none for a small tree, 10 of 17 for 3.4M triangles
+      const int wide_levels = T <= kWideTail ? 0 : 4 + int(std::ceil(std::log2(double(T) / kWideTail) / 2));
+      SRT_CHECK(collapse(wide_levels));
+      for (;;) {
+        SRT_CHECK(hipMemcpyAsync(&done, state, sizeof(done), hipMemcpyDeviceToHost, stream));
         SRT_CHECK(hipStreamSynchronize(stream));
-        allocated += next_m;
-        m = next_m;
-        ++levels;
-        if (allocated > T - 1) return hipErrorUnknown;  // every level adds nodes: impossible for a valid hierarchy
+        if (done.status) break;  // refused input: its tree is of no use
+        if (done.error) return hipErrorUnknown;
+        const bool tree = done.ploc[round & 1].n == 1;
+        if (tree && done.wide[level & 1].m == 0) break;
+        // an unusual tree: more rounds or levels than the launches above.  Every round merges a pair and
+        // every level adds a node, so this ends.
+        if (!tree) SRT_CHECK(cluster(16));
+        SRT_CHECK(collapse(std::max(wide_levels, 4)));
       }
-      result->num_nodes = allocated;
-      depth = levels;
-      k_pack_tris<<<blocks_for(T), kBlock, 0, stream>>>(desc->triangles, desc->tri_material, i0, T, recs);
-      SRT_LAUNCH_CHECK();
+      result->num_nodes = done.wide[level & 1].allocated;
+      result->depth = int32_t(done.wide[level & 1].level);
       result->root = 0;
     } else {
-      k_pack_tris<<<blocks_for(T), kBlock, 0, stream>>>(desc->triangles, desc->tri_material, nullptr, T, recs);
+      k_pack<<<blocks_for(T), kBlock, 0, stream>>>(pack);
       SRT_LAUNCH_CHECK();
-      SRT_CHECK(hipMemcpyAsync(&bounds, partial, sizeof(bounds), hipMemcpyDeviceToHost, stream));
       result->root = ~0;  // a single leaf holding record 0 (used only when T == 1)
     }
   }
-  uint32_t st = 0;
-  SRT_CHECK(hipMemcpyAsync(&st, status, sizeof(st), hipMemcpyDeviceToHost, stream));
-  SRT_CHECK(hipStreamSynchronize(stream));
-  result->status_bits = st;
-  result->depth = depth;
+  if (!plan.bvh) {
+    SRT_CHECK(hipMemcpyAsync(&done, state, sizeof(done), hipMemcpyDeviceToHost, stream));
+    SRT_CHECK(hipStreamSynchronize(stream));
+  }
+  result->status_bits = done.status;
   for (int a = 0; a < 3; ++a) {
-    result->lo[a] = T > 0 ? bounds.blo[a] : 0.f;
-    result->hi[a] = T > 0 ? bounds.bhi[a] : 0.f;
+    result->lo[a] = T > 0 ? done.bounds.blo[a] : 0.f;
+    result->hi[a] = T > 0 ? done.bounds.bhi[a] : 0.f;
   }
   return hipSuccess;
 #undef SRT_CHECK

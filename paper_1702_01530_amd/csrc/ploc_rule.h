@@ -39,6 +39,12 @@ SRT_HD inline float merged_area(V alo, V ahi, V blo, V bhi) {
 // its smallest cheapest partner, which picks it back.  Either way every round has a mutual pair
 // and merges.
 template <class V>
+SRT_HD inline bool ploc_takes_parity(float best, V alo, V ahi, V plo, V phi) {
+  return best == merged_area(alo, ahi, alo, ahi) && best == merged_area(plo, phi, plo, phi) &&
+         best == merged_area(alo, ahi, plo, phi);
+}
+
+template <class V>
 SRT_HD inline int64_t ploc_partner(const V* lo, const V* hi, int64_t base, int64_t i, int64_t n, int radius) {
   const V alo = lo[i - base], ahi = hi[i - base];
   float best = __builtin_huge_valf();
@@ -53,12 +59,7 @@ SRT_HD inline int64_t ploc_partner(const V* lo, const V* hi, int64_t base, int64
     }
   }
   const int64_t p = i ^ 1;
-  if (p < n) {
-    const V plo = lo[p - base], phi = hi[p - base];
-    if (best == merged_area(alo, ahi, alo, ahi) && best == merged_area(plo, phi, plo, phi) &&
-        best == merged_area(alo, ahi, plo, phi))
-      bj = p;
-  }
+  if (p < n && ploc_takes_parity(best, alo, ahi, lo[p - base], hi[p - base])) bj = p;
   return bj;
 }
 
