@@ -42,8 +42,9 @@ int leaf_size() { return 1; }  // every leaf of the collapsed tree is one triang
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kSortItems = 16;                      // keys per thread per sort tile
-constexpr int kSortTile = kBlock * kSortItems;      // 4096 keys per block
+constexpr int kSortItems = 16;                      // keys per thread of a sort tile (4,096 keys a block)
+constexpr int kSortItemsFew = 4;                    // ... where that would leave most of the chip idle
+constexpr int64_t kSortFew = 1 << 18;               // (fewer triangles than this)
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 
@@ -222,15 +223,23 @@ __global__ __launch_bounds__(kBlock) void k_morton(const float4* __restrict__ lo
 // 4. Stable LSD radix sort, 8 bits per pass
 // ---------------------------------------------------------------------------------------------
 
+// A pass is bound by its traffic (12 bytes read and written a key, 8 read for the histogram) once its writes
+// are runs: a block orders its tile in LDS first, so that a digit's keys leave it side by side.  Written one
+// by one from the registers they took 60 us a pass for 3.4M keys; ordered, 28.  The prefix over the blocks is
+// one launch with a workgroup a digit (three launches, 14 us, as a general prefix sum), or none: below
+// kScanInScatter blocks each scatter block sums its own.
+constexpr int kScanInScatter = 32;
+
 // Per-block digit histogram, stored digit-major: hist[digit * nblocks + block].
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_digit_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
                                                        uint32_t* __restrict__ hist, int64_t nblocks) {
   __shared__ uint32_t h[kRadix];
   h[threadIdx.x] = 0;
   __syncthreads();
-  int64_t base = int64_t(blockIdx.x) * kSortTile;
+  int64_t base = int64_t(blockIdx.x) * (ITEMS * kBlock);
 #pragma unroll 4
-  for (int k = 0; k < kSortItems; ++k) {
+  for (int k = 0; k < ITEMS; ++k) {
     int64_t i = base + int64_t(k) * kBlock + threadIdx.x;
     if (i < n) atomicAdd(&h[(keys[i] >> shift) & (kRadix - 1)], 1u);
   }
@@ -238,82 +247,41 @@ __global__ __launch_bounds__(kBlock) void k_digit_hist(const uint64_t* __restric
   hist[int64_t(threadIdx.x) * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of hist (length m) in place, one block.
-__global__ __launch_bounds__(1024) void k_scan_exclusive(uint32_t* __restrict__ data, int64_t m,
-                                                          uint32_t* __restrict__ total_out) {
-  __shared__ uint32_t part[1024];
-  const int tid = threadIdx.x;
-  int64_t per = (m + 1023) / 1024;
-  int64_t begin = tid * per, end = begin + per < m ? begin + per : m;
-  uint32_t s = 0;
-  for (int64_t i = begin; i < end; ++i) s += data[i];
-  part[tid] = s;
+// Exclusive sum of v over the block's kBlock threads; the total in *total.  `tmp` holds one word per wave.
+__device__ inline uint32_t block_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t x = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t u = __shfl_up(x, off);
+    if (lane >= off) x += u;
+  }
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    uint32_t v = tid >= off ? part[tid - off] : 0u;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+  if (lane == 63) tmp[wave] = x;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+  for (int w = 0; w < kBlock / 64; ++w) {
+    if (w < wave) before += tmp[w];
+    all += tmp[w];
   }
-  uint32_t run = part[tid] - s;
-  for (int64_t i = begin; i < end; ++i) {
-    uint32_t x = data[i];
-    data[i] = run;
-    run += x;
-  }
-  if (total_out && tid == 1023) *total_out = part[1023];
+  *total = all;
+  return before + x - v;
 }
 
-// Multi-block exclusive scan for long arrays: per-tile sums, a scan of the sums, then each tile
-// scans itself from its offset.  Tiles are kScanTile consecutive elements, 4 per thread.
-constexpr int kScanThreads = 1024, kScanPer = 4, kScanTile = kScanThreads * kScanPer;
-
-__global__ __launch_bounds__(kScanThreads) void k_tile_sums(const uint32_t* __restrict__ data, int64_t m,
-                                                             uint32_t* __restrict__ sums) {
-  __shared__ uint32_t red[kScanThreads / 64];
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  uint32_t s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    const int64_t i = base + threadIdx.x + int64_t(k) * kScanThreads;
-    if (i < m) s += data[i];
+// Block d: the exclusive prefix of digit d's counts over the blocks, in place; their sum to totals[d].
+__global__ __launch_bounds__(kBlock) void k_digit_scan(uint32_t* __restrict__ hist, int64_t nblocks,
+                                                       uint32_t* __restrict__ totals) {
+  __shared__ uint32_t tmp[kBlock / 64];
+  uint32_t* row = hist + int64_t(blockIdx.x) * nblocks;
+  uint32_t run = 0;
+  for (int64_t base = 0; base < nblocks; base += kBlock) {
+    const int64_t i = base + threadIdx.x;
+    const uint32_t v = i < nblocks ? row[i] : 0u;
+    uint32_t total;
+    const uint32_t x = block_scan(v, tmp, &total);
+    if (i < nblocks) row[i] = run + x;
+    run += total;
   }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) t += red[w];
-    sums[blockIdx.x] = t;
-  }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_tile_scan(uint32_t* __restrict__ data, int64_t m,
-                                                             const uint32_t* __restrict__ offsets) {
-  __shared__ uint32_t part[kScanThreads];
-  const int tid = threadIdx.x;
-  const int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(tid) * kScanPer;
-  uint32_t v[kScanPer];
-  uint32_t s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = base + k < m ? data[base + k] : 0u;
-    s += v[k];
-  }
-  part[tid] = s;
-  __syncthreads();
-  for (int off = 1; off < kScanThreads; off <<= 1) {
-    const uint32_t x = tid >= off ? part[tid - off] : 0u;
-    __syncthreads();
-    part[tid] += x;
-    __syncthreads();
-  }
-  uint32_t run = offsets[blockIdx.x] + part[tid] - s;
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    if (base + k < m) data[base + k] = run;
-    run += v[k];
-  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = run;
 }
 
 __device__ inline uint64_t lanemask_lt() {
@@ -321,52 +289,114 @@ __device__ inline uint64_t lanemask_lt() {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Stable scatter: element order inside the tile is (round, thread), i.e. index order.
+// Stable scatter of one tile: wave w holds the tile's keys w * 64 * ITEMS on, 64 a round, so the order is
+// (wave, round, lane).  SCAN: hist holds raw counts (k_digit_scan was not run).
+template <int ITEMS, bool SCAN>
 __global__ __launch_bounds__(kBlock) void k_scatter(const uint64_t* __restrict__ keys_in,
                                                     const uint32_t* __restrict__ ids_in, int64_t n, int shift,
-                                                    const uint32_t* __restrict__ offsets, int64_t nblocks,
+                                                    const uint32_t* __restrict__ hist,
+                                                    const uint32_t* __restrict__ totals, int64_t nblocks,
                                                     uint64_t* __restrict__ keys_out, uint32_t* __restrict__ ids_out) {
-  __shared__ uint32_t running[kRadix];
-  __shared__ uint32_t wave_cnt[kBlock / 64][kRadix];
+  constexpr int kTile = ITEMS * kBlock, kW = kBlock / 64;
+  static_assert(kRadix == kBlock, "a thread a digit");
+  __shared__ uint64_t s_key[kTile];
+  __shared__ uint32_t s_id[kTile];
+  __shared__ uint32_t cnt[kW][kRadix];     // keys of a digit in the wave's rounds so far, then those before the wave
+  __shared__ uint32_t local[kRadix];       // a digit's first place in the ordered tile
+  __shared__ uint32_t to_global[kRadix];   // ... and what a place of it adds to give the output position
+  __shared__ uint32_t tmp[kW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  running[tid] = offsets[int64_t(tid) * nblocks + blockIdx.x];
-  for (int w = 0; w < kBlock / 64; ++w) wave_cnt[w][tid] = 0;
+  const int64_t base = int64_t(blockIdx.x) * kTile;
+  const int count = int(min(int64_t(kTile), n - base));
+  for (int w = 0; w < kW; ++w) cnt[w][tid] = 0;
+  uint64_t key[ITEMS];
+  uint32_t id[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int at = wave * 64 * ITEMS + k * 64 + lane;
+    key[k] = at < count ? keys_in[base + at] : 0;
+    id[k] = at < count ? ids_in[base + at] : 0;
+  }
   __syncthreads();
-  int64_t base = int64_t(blockIdx.x) * kSortTile;
-  for (int k = 0; k < kSortItems; ++k) {
-    int64_t i = base + int64_t(k) * kBlock + tid;
-    bool valid = i < n;
-    uint64_t key = valid ? keys_in[i] : 0;
-    uint32_t id = valid ? ids_in[i] : 0;
-    uint32_t digit = uint32_t((key >> shift) & (kRadix - 1));
-    // lanes of this wave holding the same digit
-    uint64_t peers = __ballot(valid);
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const bool valid = wave * 64 * ITEMS + k * 64 + lane < count;
+    const uint32_t digit = uint32_t(key[k] >> shift) & (kRadix - 1);
+    uint64_t peers = __ballot(valid);  // lanes of this wave holding the same digit
 #pragma unroll
     for (int b = 0; b < kRadixBits; ++b) {
-      uint64_t bal = __ballot((digit >> b) & 1u);
+      const uint64_t bal = __ballot((digit >> b) & 1u);
       peers &= ((digit >> b) & 1u) ? bal : ~bal;
     }
-    uint32_t rank = __popcll(peers & lanemask_lt());
-    bool leader = valid && rank == 0;
-    if (leader) wave_cnt[wave][digit] = __popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = running[digit] + rank;
-      for (int w = 0; w < wave; ++w) pos += wave_cnt[w][digit];
-      if (pos < uint64_t(n)) {
-        keys_out[pos] = key;
-        ids_out[pos] = id;
-      }
-    }
-    __syncthreads();
-    uint32_t add = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
-      add += wave_cnt[w][tid];
-      wave_cnt[w][tid] = 0;
-    }
-    running[tid] += add;
-    __syncthreads();
+    const uint32_t below = __popcll(peers & lanemask_lt());
+    // a wave's LDS operations keep their order: every lane reads before the digit's first lane adds
+    const uint32_t before = valid ? __hip_atomic_load(&cnt[wave][digit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
+    if (valid && below == 0)
+      __hip_atomic_store(&cnt[wave][digit], before + uint32_t(__popcll(peers)), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    rank[k] = before + below;
   }
+  __syncthreads();
+  uint32_t mine = 0, total;
+  for (int w = 0; w < kW; ++w) {
+    const uint32_t c = cnt[w][tid];
+    cnt[w][tid] = mine;
+    mine += c;
+  }
+  const uint32_t place = block_scan(mine, tmp, &total);
+  uint32_t digit_total, before_block;  // digit tid: its keys in all blocks, and in the blocks before this one
+  if (SCAN) {
+    digit_total = before_block = 0;
+    for (int64_t b = 0; b < nblocks; ++b) {
+      const uint32_t c = hist[int64_t(tid) * nblocks + b];
+      if (b < int64_t(blockIdx.x)) before_block += c;
+      digit_total += c;
+    }
+  } else {
+    digit_total = totals[tid];
+    before_block = hist[int64_t(tid) * nblocks + blockIdx.x];
+  }
+  const uint32_t digit_base = block_scan(digit_total, tmp, &total);
+  local[tid] = place;
+  to_global[tid] = digit_base + before_block - place;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (wave * 64 * ITEMS + k * 64 + lane < count) {
+      const uint32_t digit = uint32_t(key[k] >> shift) & (kRadix - 1);
+      const uint32_t at = local[digit] + cnt[wave][digit] + rank[k];
+      s_key[at] = key[k];
+      s_id[at] = id[k];
+    }
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int i = tid; i < count; i += kBlock) {
+    const uint64_t v = s_key[i];
+    const uint32_t pos = to_global[uint32_t(v >> shift) & (kRadix - 1)] + uint32_t(i);
+    if (int64_t(pos) < n) {
+      keys_out[pos] = v;
+      ids_out[pos] = s_id[i];
+    }
+  }
+}
+
+// One stable pass by the digit at `shift`.
+template <int ITEMS>
+hipError_t sort_pass(const uint64_t* k0, const uint32_t* i0, int64_t n, int shift, uint32_t* hist, uint32_t* totals,
+                     uint64_t* k1, uint32_t* i1, hipStream_t s) {
+  const int64_t nb = (n + ITEMS * kBlock - 1) / (ITEMS * kBlock);
+  k_digit_hist<ITEMS><<<unsigned(nb), kBlock, 0, s>>>(k0, n, shift, hist, nb);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (nb <= kScanInScatter) {
+    k_scatter<ITEMS, true><<<unsigned(nb), kBlock, 0, s>>>(k0, i0, n, shift, hist, totals, nb, k1, i1);
+    return hipGetLastError();
+  }
+  k_digit_scan<<<kRadix, kBlock, 0, s>>>(hist, nb, totals);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_scatter<ITEMS, false><<<unsigned(nb), kBlock, 0, s>>>(k0, i0, n, shift, hist, totals, nb, k1, i1);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1238,22 +1268,6 @@ inline unsigned blocks_for(int64_t n, int b = kBlock) { return unsigned((n + b -
 
 }  // namespace
 
-// In-place exclusive scan of data[0, m); the total goes to *total_out if it is not null.  `tmp`
-// holds scan_tmp_entries(m) words.
-int64_t scan_tmp_entries(int64_t m) { return m / kScanTile + 2; }
-
-hipError_t scan_exclusive(uint32_t* data, int64_t m, uint32_t* total_out, uint32_t* tmp, hipStream_t s) {
-  if (m <= 2 * kScanTile) {
-    k_scan_exclusive<<<1, 1024, 0, s>>>(data, m, total_out);
-    return hipGetLastError();
-  }
-  const int64_t nb = (m + kScanTile - 1) / kScanTile;
-  k_tile_sums<<<unsigned(nb), kScanThreads, 0, s>>>(data, m, tmp);
-  k_scan_exclusive<<<1, 1024, 0, s>>>(tmp, nb, total_out);
-  k_tile_scan<<<unsigned(nb), kScanThreads, 0, s>>>(data, m, tmp);
-  return hipGetLastError();
-}
-
 BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool bvh, bool ploc) {
   BuildPlan p{};
   p.T = T;
@@ -1278,7 +1292,8 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
 
   off = 0;
   p.num_blocks_prep = (T + kBlock - 1) / kBlock;
-  p.num_sort_blocks = (T + kSortTile - 1) / kSortTile;
+  const int64_t sort_tile = int64_t(kBlock) * (T < kSortFew ? kSortItemsFew : kSortItems);
+  p.num_sort_blocks = (T + sort_tile - 1) / sort_tile;
   p.status_off = take(256);
   p.partial_off = take(size_t(p.num_blocks_prep > 0 ? p.num_blocks_prep : 1) * sizeof(Bounds6));
   if (T > 0) {
@@ -1303,7 +1318,7 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
     p.frontier_off[0] = take(size_t(T) * 8);
     p.frontier_off[1] = take(size_t(T) * 8);
     p.sel_off = take(size_t(T) * 16);
-    p.scan_tmp_off = take(size_t(scan_tmp_entries(p.num_sort_blocks * kRadix)) * 4);
+    p.digit_totals_off = take(size_t(kRadix) * 4);
     p.counts_off = take(size_t(std::max(kPlocBlocks, kWideBlocks)) * 8);
     if (ploc) {
       for (int k = 0; k < 2; ++k) {
@@ -1407,17 +1422,13 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       uint32_t* i0 = reinterpret_cast<uint32_t*>(scratch + plan.ids0_off);
       uint32_t* i1 = reinterpret_cast<uint32_t*>(scratch + plan.ids1_off);
       uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + plan.hist_off);
-      uint32_t* scan_tmp = reinterpret_cast<uint32_t*>(scratch + plan.scan_tmp_off);
+      uint32_t* totals = reinterpret_cast<uint32_t*>(scratch + plan.digit_totals_off);
       k_morton<<<blocks_for(T), kBlock, 0, stream>>>(lo, hi, &state->bounds, T, k0, i0);
       SRT_LAUNCH_CHECK();
-      const int64_t nb = plan.num_sort_blocks;
       for (int pass = 0; pass < 8; ++pass) {
-        int shift = pass * kRadixBits;
-        k_digit_hist<<<unsigned(nb), kBlock, 0, stream>>>(k0, T, shift, hist, nb);
-        SRT_LAUNCH_CHECK();
-        SRT_CHECK(scan_exclusive(hist, nb * kRadix, nullptr, scan_tmp, stream));
-        k_scatter<<<unsigned(nb), kBlock, 0, stream>>>(k0, i0, T, shift, hist, nb, k1, i1);
-        SRT_LAUNCH_CHECK();
+        const int shift = pass * kRadixBits;
+        SRT_CHECK(T < kSortFew ? sort_pass<kSortItemsFew>(k0, i0, T, shift, hist, totals, k1, i1, stream)
+                               : sort_pass<kSortItems>(k0, i0, T, shift, hist, totals, k1, i1, stream));
         std::swap(k0, k1);
         std::swap(i0, i1);
       }

@@ -131,7 +131,7 @@ struct BuildPlan {
       parent_off, flags_off, nodebox_off, status_off, range_off, frontier_off[2], sel_off, counts_off;
   size_t ploc_lo_off[2], ploc_hi_off[2], ploc_ext_off[2], ploc_partner_off;
   size_t dp_cost_off, dp_choice_off;
-  size_t scan_tmp_off;
+  size_t digit_totals_off;
   size_t scratch_bytes;
   int64_t num_blocks_prep, num_sort_blocks;
   bool bvh;

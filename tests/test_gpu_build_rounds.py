@@ -102,3 +102,18 @@ def test_refused_triangles_stay_refused(torch_cuda, n, bad):
             with pytest.raises(rt.RtError) as e:
                 GpuScene(scene, accel=accel)
             assert e.value.status == rt.RT_ERR_INVALID_ARGUMENT
+
+
+@pytest.mark.parametrize("n", [255, 1024, 1025, 32768, 32769, 262143, 262144, 300001])
+def test_sort_at_the_edges_of_its_tiles(torch_cuda, n):
+    """The record order is a stable sort of the Morton codes where the sort's tile size and its prefix change (262,144
+    triangles; 32 blocks), with a tenth of the triangles duplicated (equal codes keep their order)."""
+    from paper_1702_01530_amd.stereo import GpuScene
+    from tests.test_gpu_render import _morton_keys, _record_ids
+    scene = _soup(n, "uniform")
+    r = np.random.default_rng(n + 1)
+    scene.triangles[r.integers(0, n, n // 10)] = scene.triangles[r.integers(0, n, n // 10)]
+    print(f"[build] sort {n}", flush=True)
+    gs = GpuScene(scene)
+    assert np.array_equal(_record_ids(gs, n), np.argsort(_morton_keys(scene.triangles), kind="stable"))
+    gs.close()
