@@ -447,8 +447,7 @@ __global__ __launch_bounds__(kBlock) void k_karras(const uint64_t* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 
 __device__ inline float half_area(float4 lo, float4 hi) {
-  const float dx = hi.x - lo.x, dy = hi.y - lo.y, dz = hi.z - lo.z;
-  return dx * dy + dy * dz + dz * dx;
+  return half_area_of(hi.x - lo.x, hi.y - lo.y, hi.z - lo.z);
 }
 
 #ifndef SRT_DP_TRI_COST
@@ -625,11 +624,12 @@ __global__ __launch_bounds__(kBlock) void k_ploc_init(const uint32_t* __restrict
   c.ext[0][i] = make_float4(cost, cost, __int_as_float(~int(i)), 0.f);
 }
 
-constexpr int kPlocBlock = 512;    // threads of a search block
+constexpr int kPlocBlock = 512;    // threads of a search block ...
+constexpr int kPlocLanes = 4;      // ... which share a position's search this many at a time
 constexpr int kPlocBlocks = 1024;  // most blocks of a round: each sums the others' counts
+constexpr int kPlocFew = 65536;    // below this many, tiles of kPairOwn positions leave most of the chip idle
 constexpr int kPlocTail = 1024;    // clusters that one workgroup takes over
 constexpr int kPackBlocks = 1024;  // workgroups that pack triangles beside it
-static_assert(kPlocBlock >= 4 * kPlocRadius, "a search block needs positions of its own");
 
 // The positions that block `b` of `blocks` handles in a round of n clusters: whole tiles of `own`.
 __device__ inline void ploc_range(uint32_t n, uint32_t own, uint32_t b, uint32_t blocks, uint32_t* begin,
@@ -652,12 +652,11 @@ __device__ inline uint32_t block_sum(uint32_t v, uint32_t* tmp) {
 
 // partner[i] = the position cluster i merges with this round, or -1; counts[block] = (merges, absorbed
 // clusters) of the block's positions.  A tile's mutual pairs need the choices of kPlocRadius positions on
-// either side too, so a block makes those as well (kPlocBlock choices for kPlocBlock - 2 kPlocRadius
-// positions).  LANES lanes share one position's search where a round has too few positions to fill the chip.
-template <int LANES>
+// either side too, so a block makes those as well.  This is the search of a round with too few clusters to
+// fill the chip: kPlocLanes lanes share a position's candidates.
 __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* state, int slot,
                                                         int32_t* __restrict__ partner, uint2* __restrict__ counts) {
-  constexpr int R = kPlocRadius, kPos = kPlocBlock / LANES, kOwn = kPos - 2 * R;
+  constexpr int R = kPlocRadius, LANES = kPlocLanes, kPos = kPlocBlock / LANES, kOwn = kPos - 2 * R;
   static_assert(kOwn > 0 && 2 * R % LANES == 0, "search split");
   __shared__ float4 s_lo[kPos + 2 * R], s_hi[kPos + 2 * R];
   __shared__ int s_nn[kPos];
@@ -714,6 +713,127 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* 
       const int j = s_nn[p];
       const bool mutual = s_nn[j] == p;  // j lies within R of p
       partner[g] = mutual ? int32_t(g + j - p) : -1;
+      merges += (mutual && j > p) ? 1u : 0u;    // the lower position of a mutual pair makes the node
+      absorbed += (mutual && j < p) ? 1u : 0u;  // the higher one goes
+    }
+  }
+  merges = block_sum(merges, tmp);
+  absorbed = block_sum(absorbed, tmp);
+  if (threadIdx.x == 0) counts[blockIdx.x] = make_uint2(merges, absorbed);
+}
+
+// max and min without the instructions that quiet a signalling NaN first (12 of 87 in the search's loop; boxes of
+// accepted input hold no NaN, and those of refused input are only ever written to the scratch).
+__device__ inline float raw_max(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ inline float raw_min(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// merged_area for two boxes known to be no NaN
+__device__ inline float merged_area_raw(float3 alo, float3 ahi, float3 blo, float3 bhi) {
+  return half_area_of(raw_max(ahi.x, bhi.x) - raw_min(alo.x, blo.x), raw_max(ahi.y, bhi.y) - raw_min(alo.y, blo.y),
+                      raw_max(ahi.z, bhi.z) - raw_min(alo.z, blo.z));
+}
+
+// The search of a round with many clusters, bound by the VALU (18 instructions a candidate, 64 candidates a
+// position).  An area is the same from both sides, so it is computed once: a thread holds two neighbouring
+// positions and walks the kPlocRadius positions above them; the better of its two areas with each goes to that
+// position's word in LDS, (area bits << 32 | position), whose minimum is the best partner below, ties to the
+// smaller position.  Even and odd positions lie in arrays of their own, so a wave's reads are consecutive.
+// First round of 3.4M triangles: 166 us with all of a position's candidates in one thread, 86 us this way.
+constexpr int kPairBlock = 256;
+constexpr int kPairOwn = 2 * kPairBlock - 3 * kPlocRadius;
+
+__global__ __launch_bounds__(kPairBlock) void k_ploc_nn_pairs(Clusters c, BuildState* state, int slot,
+                                                              int32_t* __restrict__ partner,
+                                                              uint2* __restrict__ counts) {
+  constexpr int R = kPlocRadius, H = R / 2, kPos = 2 * kPairBlock, kHalf = kPairBlock + H;
+  static_assert(R % 2 == 0 && kPairOwn > 0 && kPairOwn % 2 == 0, "positions come in pairs");
+  __shared__ float4 s_lo[2][kHalf], s_hi[2][kHalf];  // position base - 2R + k at [k & 1][k / 2]
+  __shared__ unsigned long long s_below[2][kHalf];   // its best partner below
+  __shared__ int s_nn[kPos];
+  __shared__ uint32_t tmp[kPairBlock / 64];
+  const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
+  if (n <= kPlocTail) return;
+  const float4* __restrict__ lo = buf ? c.lo[1] : c.lo[0];
+  const float4* __restrict__ hi = buf ? c.hi[1] : c.hi[0];
+  uint32_t begin, end, merges = 0, absorbed = 0;
+  ploc_range(n, kPairOwn, blockIdx.x, gridDim.x, &begin, &end);
+  const int q = threadIdx.x;
+  for (uint32_t base = begin; base < end; base += kPairOwn) {
+    __syncthreads();
+    for (int k = threadIdx.x; k < 2 * kHalf; k += kPairBlock) {
+      const int64_t g = int64_t(base) - 2 * R + k;
+      const bool in = g >= 0 && g < int64_t(n);
+      // a box at +inf: any merge with it has an infinite area and is never chosen
+      s_lo[k & 1][k >> 1] = in ? lo[g] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+      s_hi[k & 1][k >> 1] = in ? hi[g] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+      s_below[k & 1][k >> 1] = ~0ull;
+    }
+    __syncthreads();
+    const int64_t g0 = int64_t(base) - 2 * R + 2 * q;  // even, as tiles and R are; its parity partner is g0 + 1
+    auto f3 = [](float4 v) { return make_float3(v.x, v.y, v.z); };
+    const float3 lo0 = f3(s_lo[0][q]), hi0 = f3(s_hi[0][q]), lo1 = f3(s_lo[1][q]), hi1 = f3(s_hi[1][q]);
+    float best0 = INFINITY, best1 = INFINITY;  // over the positions above
+    int bk0 = 0, bk1 = 0;
+    auto tell = [&](unsigned long long* word, float ar, int from) {
+      __hip_atomic_fetch_min(word, (static_cast<unsigned long long>(__float_as_uint(ar)) << 32) | uint32_t(from),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // the box at LDS position j = 2q + k with both of the thread's
+    auto both = [&](int odd, int at, int k) {
+      const float3 l = f3(s_lo[odd][at]), h = f3(s_hi[odd][at]);
+      const float a0 = merged_area_raw(lo0, hi0, l, h), a1 = merged_area_raw(lo1, hi1, l, h);
+      if (a0 < best0) best0 = a0, bk0 = k;
+      if (a1 < best1) best1 = a1, bk1 = k - 1;
+      tell(&s_below[odd][at], a1 < a0 ? a1 : a0, a1 < a0 ? 2 * q + 1 : 2 * q);
+    };
+    {
+      const float ar = merged_area_raw(lo0, hi0, lo1, hi1);
+      best0 = ar, bk0 = 1;
+      tell(&s_below[1][q], ar, 2 * q);
+    }
+#pragma unroll 3
+    for (int kk = 1; kk < H; ++kk) {
+      both(0, q + kk, 2 * kk);
+      both(1, q + kk, 2 * kk + 1);
+    }
+    both(0, q + H, R);
+    {  // R + 1 above the lower position: only the upper one reaches it
+      const float ar = merged_area_raw(lo1, hi1, f3(s_lo[1][q + H]), f3(s_hi[1][q + H]));
+      if (ar < best1) best1 = ar, bk1 = R;
+      tell(&s_below[1][q + H], ar, 2 * q + 1);
+    }
+    __syncthreads();
+    const bool v0 = g0 >= 0 && g0 < int64_t(n), v1 = g0 + 1 >= 0 && g0 + 1 < int64_t(n);
+    auto choose = [&](int odd, float best, int bk, int64_t g) {
+      const int p = 2 * q + odd;
+      const unsigned long long w = s_below[odd][q];
+      const float below = __uint_as_float(uint32_t(w >> 32));
+      if (below < INFINITY && below <= best) {  // the partner below is the smaller position
+        best = below;
+        bk = int(uint32_t(w)) - p;
+      }
+      if (!(best < INFINITY)) bk = g > 0 ? -1 : 1;  // boxes of refused input only: keep the rounds well formed
+      const float4 lo4 = s_lo[odd][q], hi4 = s_hi[odd][q], olo = s_lo[odd ^ 1][q], ohi = s_hi[odd ^ 1][q];
+      if (v0 && v1 && ploc_takes_parity(best, lo4, hi4, olo, ohi)) bk = odd ? -1 : 1;
+      return p + bk;
+    };
+    s_nn[2 * q] = v0 ? choose(0, best0, bk0, g0) : -1;
+    s_nn[2 * q + 1] = v1 ? choose(1, best1, bk1, g0 + 1) : -1;
+    __syncthreads();
+    for (int k = 0; k < 2; ++k) {
+      // positions from 2R to kPos - R are the tile's own; those from R on have seen every candidate
+      const int p = 2 * q + k;
+      if (p < 2 * R || p >= kPos - R || !(k ? v1 : v0)) continue;
+      const int j = s_nn[p];
+      const bool mutual = s_nn[j] == p;  // j lies within R of p
+      partner[g0 + k] = mutual ? int32_t(g0 + k + j - p) : -1;
       merges += (mutual && j > p) ? 1u : 0u;    // the lower position of a mutual pair makes the node
       absorbed += (mutual && j < p) ? 1u : 0u;  // the higher one goes
     }
@@ -1456,13 +1576,13 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       // finds at most kPlocTail clusters does nothing.
       auto cluster = [&](int rounds) -> hipError_t {
         for (int k = 0; k < rounds; ++k, ++round) {
-          const bool few = expected < 65536;  // tiles of one lane a position would leave most of the chip idle
-          const unsigned own = kPlocBlock / (few ? 4 : 1) - 2 * kPlocRadius;
+          const bool few = expected < kPlocFew;
+          const unsigned own = few ? kPlocBlock / kPlocLanes - 2 * kPlocRadius : kPairOwn;
           const unsigned grid = unsigned(std::min<double>(kPlocBlocks, std::max(1.0, std::ceil(expected / own))));
           if (few)
-            k_ploc_nn<4><<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
+            k_ploc_nn<<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
           else
-            k_ploc_nn<1><<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
+            k_ploc_nn_pairs<<<grid, kPairBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
           if ((e = hipGetLastError()) != hipSuccess) return e;
           k_ploc_compact<<<grid, kBlock, 0, stream>>>(cl, state, round & 1, partner, counts, own, made);
           if ((e = hipGetLastError()) != hipSuccess) return e;

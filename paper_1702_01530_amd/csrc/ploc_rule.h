@@ -15,6 +15,10 @@
 
 namespace srt {
 
+// Half the surface area of a box, with the roundings written out: every kernel (and the host) gets the same
+// value for the same box, however its compiler would contract the sum.
+SRT_HD inline float half_area_of(float dx, float dy, float dz) { return fmaf(dx, dz, fmaf(dx, dy, dy * dz)); }
+
 // Surface area (up to the factor 2) of the union of boxes a and b.  Symmetric in a and b, and never
 // below either box's own area (max/min are exact and correctly rounded sums and products of
 // non-negative values are monotone), which the mutual-pair argument below relies on.
@@ -23,7 +27,7 @@ SRT_HD inline float merged_area(V alo, V ahi, V blo, V bhi) {
   const float dx = fmaxf(ahi.x, bhi.x) - fminf(alo.x, blo.x);
   const float dy = fmaxf(ahi.y, bhi.y) - fminf(alo.y, blo.y);
   const float dz = fmaxf(ahi.z, bhi.z) - fminf(alo.z, blo.z);
-  return dx * dy + dy * dz + dz * dx;
+  return half_area_of(dx, dy, dz);
 }
 
 // Merge partner of cluster i among positions i-R .. i+R of n clusters (n >= 2): the one whose
