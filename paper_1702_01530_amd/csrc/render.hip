@@ -205,24 +205,52 @@ __device__ inline void primary_ray(const DevCamera& c, int eye, int x, int y, fl
 // Ray-primitive tests (FP32)
 // ---------------------------------------------------------------------------------------------
 
-// Moller-Trumbore; closed triangle; only det == 0 rejected.  Returns t or +inf.
+// Moller-Trumbore with its roundings written out, so that every kernel gets the same answer for the same ray
+// and triangle however its compiler would contract the sums.
+struct TriTest {
+  float3 T, P, Q;
+  float det, un, vn;
+
+  __device__ static inline float3 cross_fma(float3 a, float3 b) {
+    return make_float3(fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x)));
+  }
+  __device__ static inline float dot_yxz(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
+  __device__ static inline float dot_xyz(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)); }
+
+  // the determinant and the first barycentric coordinate times it
+  __device__ inline void first(float3 o, float3 d, float3 v0, float3 e1, float3 e2) {
+    P = cross_fma(d, e2);
+    det = dot_yxz(e1, P);
+    T = o - v0;
+    un = dot_xyz(T, P);
+  }
+  // the second one times the determinant
+  __device__ inline void second(float3 d, float3 e1) {
+    Q = cross_fma(T, e1);
+    vn = dot_yxz(d, Q);
+  }
+  // t, or +inf outside the triangle or (tmin, tmax); det != 0
+  __device__ inline float t(float3 e2, float inv, float u, float tmin, float tmax) const {
+    if (!(vn * inv >= 0.0f && fmaf(vn, inv, u) <= 1.0f)) return INFINITY;
+    const float t = dot_yxz(e2, Q) * inv;
+    return (t > tmin && t < tmax) ? t : INFINITY;
+  }
+};
+
+// Closed triangle; only det == 0 rejected.  Returns t or +inf.
 __device__ inline float tri_t(const float4* __restrict__ recs, int r, float3 o, float3 d, float tmin, float tmax,
                               int* id_out) {
   const float4 a = recs[3 * r], b = recs[3 * r + 1], c = recs[3 * r + 2];
   *id_out = __float_as_int(a.w);
   const float3 e1 = f3(b), e2 = f3(c);
-  const float3 T = o - f3(a);
-  const float3 P = cross(d, e2);
-  const float det = dot(e1, P);
-  if (det == 0.0f) return INFINITY;
-  const float inv = 1.0f / det;
-  const float u = dot(T, P) * inv;
+  TriTest m;
+  m.first(o, d, f3(a), e1, e2);
+  if (m.det == 0.0f) return INFINITY;
+  const float inv = 1.0f / m.det;
+  const float u = m.un * inv;
   if (!(u >= 0.0f && u <= 1.0f)) return INFINITY;
-  const float3 Q = cross(T, e1);
-  const float v = dot(d, Q) * inv;
-  if (!(v >= 0.0f && u + v <= 1.0f)) return INFINITY;
-  const float t = dot(e2, Q) * inv;
-  return (t > tmin && t < tmax) ? t : INFINITY;
+  m.second(d, e1);
+  return m.t(e2, inv, u, tmin, tmax);
 }
 
 // Sphere with unit d: b = -oc.d, h^2 = |oc + b d|^2, disc = r^2 - h^2, roots b -+ sqrt(disc).
@@ -454,6 +482,7 @@ __device__ inline int shfl_i(int v, int src) { return __builtin_amdgcn_ds_bpermu
 // Traverses the rays of one wave (all lanes call it together; `mine` marks the lanes that hold a ray).
 // ANY = false: closest hit, minimum t, exact ties to the smaller original id; the limit starts at +inf.
 // ANY = true : occlusion, stops at the first primitive with t in (tmin, limit).
+// FLAT: scenes without a tree (or RT_FLAG_BRUTE_FORCE) may come too; k_trace_flat takes them otherwise.
 // commit(key, t) is called once for every lane with a ray: the hit's key (-1: none) and distance.
 // Closest-hit candidates are tested against the next float above the best t, so that an exact tie in t
 // reaches the (t, id) comparison, and boxes entered exactly at the best t are not culled.
@@ -468,7 +497,7 @@ __device__ inline int shfl_i(int v, int src) { return __builtin_amdgcn_ds_bpermu
 // 4 lights: the six launches took 538, 1324, 300, 166, 222 and 135 us and take 455, 1130, 230, 81, 53 and
 // 31; the frame went from 2844 to 2121 us.  kCoopRays 8 / 16 / 24 / 32 / 48 / 64: 2463 / 2376 / 2322 / 2278
 // / 2258 / 2310 us (at 7 waves).
-template <bool ANY, bool COUNT, class Commit>
+template <bool ANY, bool COUNT, bool FLAT, class Commit>
 __device__ __attribute__((always_inline)) inline void traverse(const DevScene& sc, bool mine, Ray r,
                                                                bool brute, Stack& st, const Share& share,
                                                                uint32_t& nnodes, uint32_t& ntris, Commit commit) {
@@ -509,14 +538,14 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
       const int key = sc.T + sc.S + p;
       accept(plane_t(sc.planes[p], r.o, r.d, r.tmin, r.limit), key, key);
     }
-    if (brute || !sc.has_bvh) {
+    if (FLAT && (brute || !sc.has_bvh)) {
       for (int k = 0; k < sc.T && !(ANY && found); ++k) {
         int id;
         const float t = tri_t(sc.tris, k, r.o, r.d, r.tmin, r.limit, &id);
         if (COUNT) ++ntris;
         accept(t, k, id);
       }
-    } else if (sc.T > 0 && !(ANY && found)) {
+    } else if (sc.T > 0 && sc.has_bvh && !(ANY && found)) {
       node = sc.root;
     }
   }
@@ -719,7 +748,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
   // rays instead of 8 are within 1%.
   const uint32_t nwaves = gridDim.x * uint32_t(kWaves);
   int blog = 6;
-  if (!COUNT && kCoopRays > 0 && !a.brute && (MULTI || a.one.sc.has_bvh))
+  if (!COUNT && kCoopRays > 0 && !a.brute)
     while (blog > kMinRaysLog2 && (rays >> (blog - 1)) < nwaves) --blog;
   const uint32_t nc_pad = round_up(nc, blog);
   uint32_t total = nc_pad;
@@ -727,9 +756,10 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
     for (int l = 0; l < LS; ++l) total += round_up(a.ctr->shadow_count[depth - 1][l], blog);
   uint32_t c_nodes = 0, c_tris = 0, s_nodes = 0, s_tris = 0;
   // Larger grabs than one batch unbalance the launch's end, and refilling single lanes stalls the wave on
-  // every refill.  Device-scope atomics on one address serialise, so: wave w's first batch is batch w, with no atomic (a launch whose work fits in
-  // the first round takes none); later batches b = nwaves + c + K k come from counter c = w mod K
-  // of K = min(kWorkCounters, nwaves) interleaved counters, so K atomics proceed at once.
+  // every refill.  Device-scope atomics on one address serialise, so: wave w's first batch is batch w, with
+  // no atomic (a launch whose work fits in the first round takes none); later batches b = nwaves + c + K k
+  // come from counter c = w mod K of K = min(kWorkCounters, nwaves) interleaved counters, so K atomics
+  // proceed at once.
   const uint32_t wid = blockIdx.x * uint32_t(kWaves) + uint32_t(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   const uint32_t nbatches = total >> blog;
   const uint32_t ncounters = nwaves < uint32_t(kWorkCounters) ? nwaves : uint32_t(kWorkCounters);  // each served
@@ -776,7 +806,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
             r.exclude = __float_as_int(rd.w);
           }
         }
-        traverse<false, COUNT>(it.sc, mine, r, a.brute != 0, st, share, c_nodes, c_tris,
+        traverse<false, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, c_nodes, c_tris,
                                      [&](int key, float t) {
                                        const uint32_t entry = e;
                                        global_scalar(a.hit)[entry] = make_float2(t, __int_as_float(key));
@@ -808,7 +838,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
           r.limit = sqrtf(dot(Lv, Lv));
           r.d = (1.0f / r.limit) * Lv;
         }
-        traverse<true, COUNT>(it.sc, mine, r, a.brute != 0, st, share, s_nodes, s_tris,
+        traverse<true, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, s_nodes, s_tris,
                                     [&](int key, float) {
                                       uint32_t o = owner;
                                       asm volatile("" : "+v"(o));  // the address is formed here, not before the loop
@@ -823,6 +853,192 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
     add_work(a.ctr, 1, c_tris);
     add_work(a.ctr, 2, s_nodes);
     add_work(a.ctr, 3, s_tris);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// k_trace_flat: the same rays of a single scene without a tree (spheres and planes only, RT_ACCEL_NONE, one
+// triangle) or under RT_FLAG_BRUTE_FORCE: every ray against every primitive.
+//
+// Primitives are the same for the whole wave, so they are scalar loads and a test is bound by the VALU: 45
+// instructions a triangle, half of them behind the division.  Most waves find that no lane is inside a
+// triangle's first edge pair long before that (24 instructions on average).  With many triangles, SEGS waves
+// share a batch of 64 rays, each over its part of the triangles: a frame of 131,072 paths is 2,048 batches, a
+// quarter of the waves the chip holds, and a launch of few rays would last as long as one wave's walk over
+// all triangles (0.26 us each, a dependent load, before).  256x256, 2,432 triangles, depth 1, 1 light: 1815 us
+// with the walk inside k_trace, 357 this way (390 with records loaded two at a time, 420 one at a time; 4 or
+// 16 waves a batch: 463).
+// ---------------------------------------------------------------------------------------------
+
+#ifndef SRT_FLAT_STEP
+#define SRT_FLAT_STEP 4
+#endif
+constexpr int kFlatSegs = 8;        // waves that share a batch's triangles ...
+constexpr int kFlatSplit = 512;     // ... from this many on
+constexpr int kFlatWaves = 8192;    // waves of a full grid
+template <int SEGS>
+constexpr int kFlatBlock = SEGS > 1 ? 64 * SEGS : kBlock;
+
+// True where the triangle test certainly rejects a barycentric coordinate num / det (signs and sizes only,
+// before the division): below 0 by more than an underflow can hide, or above 1 by more than rounding can.
+__device__ inline bool outside(float num_signed, float det_abs) {
+  return num_signed < -1e-30f * det_abs || num_signed > 1.0001f * det_abs;
+}
+
+// Tests a wave's rays against triangle records first .. last - 1, all lanes together; accept(t, record, id)
+// for the lanes with a candidate in (tmin, limit()).
+template <class Limit, class Accept>
+__device__ __attribute__((always_inline)) inline void flat_triangles(const float4* tris, int first, int last, float3 o,
+                                                                     float3 d, float tmin, Limit limit, Accept accept) {
+  typedef __attribute__((address_space(4))) const float4 const_float4;  // written by an earlier launch only
+  auto test = [&](float4 a, float4 b, float4 c, int k) {
+    const float3 e1 = f3(b), e2 = f3(c);
+    TriTest m;
+    m.first(o, d, f3(a), e1, e2);
+    const uint32_t sign = __float_as_uint(m.det) & 0x80000000u;
+    const float ad = fabsf(m.det);
+    if (outside(__uint_as_float(__float_as_uint(m.un) ^ sign), ad)) return;
+    m.second(d, e1);
+    if (outside(__uint_as_float(__float_as_uint(m.vn) ^ sign), ad)) return;
+    if (m.det == 0.0f) return;
+    const float inv = 1.0f / m.det;
+    const float u = m.un * inv;
+    if (!(u >= 0.0f && u <= 1.0f)) return;
+    const float t = m.t(e2, inv, u, tmin, limit());
+    if (t < INFINITY) accept(t, k, __float_as_int(a.w));
+  };
+  // kStep records are loaded at a time, so a wave waits once for all of them
+  constexpr int kStep = SRT_FLAT_STEP;
+  const const_float4* recs = (const const_float4*)tris;
+  int k = first;
+  for (; k + kStep <= last; k += kStep) {
+    float4 r[3 * kStep];
+#pragma unroll
+    for (int j = 0; j < 3 * kStep; ++j) r[j] = ((const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k)))[j];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) test(r[3 * j], r[3 * j + 1], r[3 * j + 2], k + j);
+  }
+  for (; k < last; ++k) {
+    const float4* r = (const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k));
+    test(r[0], r[1], r[2], k);
+  }
+}
+
+template <int SEGS>
+__global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int depth) {
+  __shared__ float s_t[SEGS > 1 ? SEGS * 64 : 1];
+  __shared__ int s_key[SEGS > 1 ? SEGS * 64 : 1], s_id[SEGS > 1 ? SEGS * 64 : 1];
+  __shared__ unsigned long long s_hit[SEGS > 1 ? SEGS : 1];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int seg = SEGS > 1 ? wave : 0;
+  const DevScene& sc = a.one.sc;
+  const int LS = a.lstride;
+  const int q = depth & 1, sq = (depth + 1) & 1;
+  const uint32_t nc = depth > a.dmax ? 0u : (depth == 0 ? uint32_t(a.path_count) : a.ctr->refl_count[depth]);
+  const uint32_t nc_pad = round_up(nc, 6);
+  uint32_t total = nc_pad;
+  if (depth >= 1)
+    for (int l = 0; l < LS; ++l) total += round_up(a.ctr->shadow_count[depth - 1][l], 6);
+  const int first = int(int64_t(sc.T) * seg / SEGS), last = int(int64_t(sc.T) * (seg + 1) / SEGS);
+  constexpr uint32_t kPer = SEGS > 1 ? 1 : kFlatBlock<SEGS> / 64;  // batches a block holds at a time
+  const uint32_t mine = blockIdx.x * kPer + (SEGS > 1 ? 0u : uint32_t(wave));
+  for (uint32_t base = mine * 64u; base < total; base += gridDim.x * kPer * 64u) {  // block-uniform with SEGS > 1
+    if (base < nc_pad) {
+      // ---- closest-hit batch
+      const uint32_t e = base + lane;
+      bool valid = e < nc;
+      float3 o = make_float3(0.f, 0.f, 0.f), d = o;
+      int exclude = -1;
+      if (valid) {
+        if (depth == 0) {
+          int eye, x, y;
+          valid = path_pixel(a.one.cam, a.path_begin + e, &eye, &x, &y);
+          if (valid) {
+            primary_ray(a.one.cam, eye, x, y, &o, &d);
+            if (seg == 0) {
+              a.ro[q][e] = make_float4(o.x, o.y, o.z, __int_as_float(int(e)));
+              a.rd[q][e] = make_float4(d.x, d.y, d.z, __int_as_float(-1));
+            }
+          } else if (seg == 0) {
+            a.ro[q][e].w = __int_as_float(-1);  // outside the image
+          }
+        } else {
+          const float4 ro = a.ro[q][e], rd = a.rd[q][e];
+          o = f3(ro);
+          d = f3(rd);
+          exclude = __float_as_int(rd.w);
+        }
+      }
+      const float tmin = depth == 0 ? 0.0f : kSecondaryTmin;
+      Best best{INFINITY, -1, 0x7fffffff};
+      if (valid) {
+        auto accept = [&](float t, int key, int id) {
+          if (key != exclude && (t < best.t || (t == best.t && id < best.id))) best = Best{t, key, id};
+        };
+        if (seg == 0) {
+          for (int k = 0; k < sc.S; ++k) accept(sphere_t(sc.spheres[k], o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
+          for (int k = 0; k < sc.P; ++k) {
+            const int key = sc.T + sc.S + k;
+            accept(plane_t(sc.planes[k], o, d, tmin, next_up(best.t)), key, key);
+          }
+          if (!(best.t < INFINITY)) best = Best{INFINITY, -1, 0x7fffffff};
+        }
+        flat_triangles(sc.tris, first, last, o, d, tmin, [&] { return next_up(best.t); }, accept);
+      }
+      if (SEGS > 1) {
+        s_t[wave * 64 + lane] = best.t;
+        s_id[wave * 64 + lane] = best.id;
+        s_key[wave * 64 + lane] = best.key;
+        __syncthreads();
+        if (wave == 0) {
+          for (int w = 1; w < SEGS; ++w) {
+            const float t = s_t[w * 64 + lane];
+            const int id = s_id[w * 64 + lane];
+            if (t < best.t || (t == best.t && id < best.id)) best = Best{t, s_key[w * 64 + lane], id};
+          }
+        }
+      }
+      if (valid && seg == 0) a.hit[e] = make_float2(best.t, __int_as_float(best.key));
+    } else {
+      // ---- shadow batch: find the light whose (padded) range holds this batch
+      uint32_t start = nc_pad;
+      int l = 0;
+      uint32_t cnt = a.ctr->shadow_count[depth - 1][0];
+      while (l + 1 < LS && base >= start + round_up(cnt, 6)) {
+        start += round_up(cnt, 6);
+        ++l;
+        cnt = a.ctr->shadow_count[depth - 1][l];
+      }
+      const uint32_t i = base - start + lane;
+      const bool valid = i < cnt;
+      bool found = false;
+      if (valid) {
+        const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
+        const float3 P = f3(rec);
+        const int exclude = __float_as_int(rec.w);
+        const float3 Lv = f3(sc.lights[2 * l]) - P;
+        const float dist = sqrtf(dot(Lv, Lv));
+        const float3 d = (1.0f / dist) * Lv;
+        auto accept = [&](float t, int key, int) { found = found || (key != exclude && t < INFINITY); };
+        if (seg == 0) {
+          for (int k = 0; k < sc.S; ++k) accept(sphere_t(sc.spheres[k], P, d, kSecondaryTmin, dist), sc.T + k, 0);
+          for (int k = 0; k < sc.P; ++k)
+            accept(plane_t(sc.planes[k], P, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
+        }
+        // in steps, so that a wave whose rays are all answered stops
+        for (int k = first; k < last && !__all(found); k += 64)
+          flat_triangles(sc.tris, k, min(k + 64, last), P, d, kSecondaryTmin, [&] { return dist; }, accept);
+      }
+      uint64_t hits = __ballot(found);
+      if (SEGS > 1) {
+        if (lane == 0) s_hit[wave] = hits;
+        __syncthreads();
+        if (wave == 0)
+          for (int w = 1; w < SEGS; ++w) hits |= s_hit[w];
+      }
+      if (valid && seg == 0) a.vis[sq][size_t(a.sowner[sq][size_t(l) * a.cap + i]) * LS + l] = (hits >> lane) & 1 ? 0 : 1;
+    }
+    if (SEGS > 1) __syncthreads();  // the LDS results are reused by the next batch
   }
 }
 
@@ -1213,12 +1429,12 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
 
   // The persistent grid, cut where the launch cannot hold that many batches (small frames: a workgroup
   // without work still costs its dispatch).
-  const bool trees = multi || (ra.one.sc.has_bvh && !a.brute);
-  auto gtrace = [&](int d) {
+  auto gtrace = [&](int d, int64_t rays_per_block, int64_t most) {
     const int64_t rays = ra.path_count * ((d <= ra.max_depth ? 1 : 0) + (d >= 1 ? ra.max_lights : 0));
-    const int64_t per_block = int64_t(kWaves) << (trees ? kMinRaysLog2 : 6);
-    return unsigned(std::max<int64_t>(1, std::min<int64_t>(p.grid_trace, (rays + per_block - 1) / per_block)));
+    return unsigned(std::max<int64_t>(1, std::min<int64_t>(most, (rays + rays_per_block - 1) / rays_per_block)));
   };
+  // Single scenes without a tree to walk have kernels of their own (the work counters are k_trace's).
+  const bool flat = !multi && !count && (a.brute || !ra.one.sc.has_bvh);
   const unsigned gstream =
       unsigned(std::max<int64_t>(1, std::min<int64_t>((ra.path_count + kBlock - 1) / kBlock, ra.stream_blocks)));
   const unsigned gshade = unsigned(std::max<int64_t>(
@@ -1231,12 +1447,22 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   if (e != hipSuccess) return e;
   const int D = a.dmax;
   for (int d = 0; d <= D + 1; ++d) {
-    if (multi)
-      e = count ? launch(k_trace<true, true>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE)
-                : launch(k_trace<false, true>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE);
-    else
-      e = count ? launch(k_trace<true, false>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE)
-                : launch(k_trace<false, false>, gtrace(d), a, d, s, timer, RT_STAGE_TRACE);
+    if (flat) {
+      if (ra.one.sc.T >= kFlatSplit)
+        e = launch(k_trace_flat<kFlatSegs>, gtrace(d, 64, kFlatWaves / kFlatSegs), a, d, s, timer, RT_STAGE_TRACE,
+                   kFlatBlock<kFlatSegs>);
+      else
+        e = launch(k_trace_flat<1>, gtrace(d, kFlatBlock<1>, kFlatWaves * 64 / kFlatBlock<1>), a, d, s, timer,
+                   RT_STAGE_TRACE, kFlatBlock<1>);
+    } else {
+      const unsigned grid = gtrace(d, int64_t(kWaves) << kMinRaysLog2, p.grid_trace);
+      if (multi)
+        e = count ? launch(k_trace<true, true>, grid, a, d, s, timer, RT_STAGE_TRACE)
+                  : launch(k_trace<false, true>, grid, a, d, s, timer, RT_STAGE_TRACE);
+      else
+        e = count ? launch(k_trace<true, false>, grid, a, d, s, timer, RT_STAGE_TRACE)
+                  : launch(k_trace<false, false>, grid, a, d, s, timer, RT_STAGE_TRACE);
+    }
     if (e != hipSuccess) return e;
     if (d <= D) {
       if (multi)

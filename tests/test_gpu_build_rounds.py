@@ -117,3 +117,27 @@ def test_sort_at_the_edges_of_its_tiles(torch_cuda, n):
     gs = GpuScene(scene)
     assert np.array_equal(_record_ids(gs, n), np.argsort(_morton_keys(scene.triangles), kind="stable"))
     gs.close()
+
+
+@pytest.mark.parametrize("n", [1, 3, 5, 511, 512, 519, 1030])
+@pytest.mark.parametrize("size", [(1, 1), (33, 21), (150, 140)])
+def test_scenes_without_a_tree(torch_cuda, n, size):
+    """RT_ACCEL_NONE around the sizes where eight waves share a batch's triangles (512) and where a wave's records, taken
+    four at a time, leave a rest: equal to the tree's render and to brute force on the tree's records, byte for byte."""
+    torch = torch_cuda
+    from dataclasses import replace
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    scene = replace(_soup(n, "grid"), spheres=np.asarray([[0.5, 0.3, 4, 0.4], [-1, 0, 9, 1.5]], np.float32),
+                    sphere_material=np.zeros(2, np.uint32), planes=np.asarray([[0, 1, 0, -3]], np.float32),
+                    plane_material=np.zeros(1, np.uint32))
+    cam = mono_camera(center=(0, 0.5, 0), width=size[0], height=size[1], depth=2, baseline=0.065, convergence=5.0)
+    print(f"[flat] {n} {size}", flush=True)
+    a, b = GpuScene(scene, accel="none"), GpuScene(scene)
+    outs = [render_stereo(a, cam, path_ids=True), render_stereo(b, cam, path_ids=True),
+            render_stereo(b, cam, path_ids=True, brute_force=True), render_stereo(a, cam, path_ids=True, count_work=True)]
+    torch.cuda.synchronize()
+    for o in outs[1:]:
+        for k in ("radiance", "hit_t", "hit_prim", "path_prims", "shadow_state"):
+            assert torch.equal(outs[0][k], o[k]), k
+    a.close()
+    b.close()
