@@ -924,6 +924,13 @@ __device__ __attribute__((always_inline)) inline void flat_triangles(const float
   }
 }
 
+// Element k of a scene array, as a scalar load: k is the same for the wave, and the array was written by an
+// earlier launch.
+__device__ inline float4 scalar_load(const float4* p, int k) {
+  typedef __attribute__((address_space(4))) const float4 const_float4;
+  return *(const float4*)((const_float4*)p + __builtin_amdgcn_readfirstlane(k));
+}
+
 template <int SEGS>
 __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int depth) {
   __shared__ float s_t[SEGS > 1 ? SEGS * 64 : 1];
@@ -976,10 +983,10 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
           if (key != exclude && (t < best.t || (t == best.t && id < best.id))) best = Best{t, key, id};
         };
         if (seg == 0) {
-          for (int k = 0; k < sc.S; ++k) accept(sphere_t(sc.spheres[k], o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
+          for (int k = 0; k < sc.S; ++k) accept(sphere_t(scalar_load(sc.spheres, k), o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
           for (int k = 0; k < sc.P; ++k) {
             const int key = sc.T + sc.S + k;
-            accept(plane_t(sc.planes[k], o, d, tmin, next_up(best.t)), key, key);
+            accept(plane_t(scalar_load(sc.planes, k), o, d, tmin, next_up(best.t)), key, key);
           }
           if (!(best.t < INFINITY)) best = Best{INFINITY, -1, 0x7fffffff};
         }
@@ -1021,9 +1028,9 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
         const float3 d = (1.0f / dist) * Lv;
         auto accept = [&](float t, int key, int) { found = found || (key != exclude && t < INFINITY); };
         if (seg == 0) {
-          for (int k = 0; k < sc.S; ++k) accept(sphere_t(sc.spheres[k], P, d, kSecondaryTmin, dist), sc.T + k, 0);
+          for (int k = 0; k < sc.S; ++k) accept(sphere_t(scalar_load(sc.spheres, k), P, d, kSecondaryTmin, dist), sc.T + k, 0);
           for (int k = 0; k < sc.P; ++k)
-            accept(plane_t(sc.planes[k], P, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
+            accept(plane_t(scalar_load(sc.planes, k), P, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
         }
         // in steps, so that a wave whose rays are all answered stops
         for (int k = first; k < last && !__all(found); k += 64)
