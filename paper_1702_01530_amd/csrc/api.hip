@@ -320,6 +320,7 @@ rt_status render_passes(const rt_scene_s* scene, const rt_stereo_camera* cam, co
   ra.flags = flags;
   ra.ws = ws;
   ra.plan = plan;
+  ra.frame_paths = total;
   for (int64_t begin = 0; begin < total; begin += chunk) {
     ra.path_begin = begin;
     ra.path_count = std::min(chunk, total - begin);

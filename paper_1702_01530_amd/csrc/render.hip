@@ -76,11 +76,22 @@ __device__ inline float3 operator+(float3 a, float3 b) { return make_float3(a.x 
 __device__ inline float3 operator-(float3 a, float3 b) { return make_float3(a.x - b.x, a.y - b.y, a.z - b.z); }
 __device__ inline float3 operator*(float s, float3 a) { return make_float3(s * a.x, s * a.y, s * a.z); }
 __device__ inline float3 mul(float3 a, float3 b) { return make_float3(a.x * b.x, a.y * b.y, a.z * b.z); }
-__device__ inline float dot(float3 a, float3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
-__device__ inline float3 cross(float3 a, float3 b) {
-  return make_float3(a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x);
+// Sums of products with their roundings written out: kernels that compute the same value get the same bits,
+// however the compiler would contract each.
+__device__ inline float fdot(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
+__device__ inline float3 fcross(float3 a, float3 b) {
+  return make_float3(fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x)));
 }
-__device__ inline float3 normalize(float3 a) { return (1.0f / sqrtf(dot(a, a))) * a; }
+// a + b rounded by itself, also where a or b is a product
+__device__ inline float3 add_rn(float3 a, float3 b) {
+#pragma clang fp contract(off)
+  return make_float3(a.x + b.x, a.y + b.y, a.z + b.z);
+}
+// s * a + b
+__device__ inline float3 fmad(float s, float3 a, float3 b) {
+  return make_float3(fmaf(s, a.x, b.x), fmaf(s, a.y, b.y), fmaf(s, a.z, b.z));
+}
+__device__ inline float3 normalize(float3 a) { return (1.0f / sqrtf(fdot(a, a))) * a; }
 
 // 1/d with exact zeros replaced by a tiny same-signed value, so that the slab
 // products stay finite (no 0 * inf) for axis-parallel rays.
@@ -211,28 +222,24 @@ struct TriTest {
   float3 T, P, Q;
   float det, un, vn;
 
-  __device__ static inline float3 cross_fma(float3 a, float3 b) {
-    return make_float3(fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x)));
-  }
-  __device__ static inline float dot_yxz(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
   __device__ static inline float dot_xyz(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)); }
 
   // the determinant and the first barycentric coordinate times it
   __device__ inline void first(float3 o, float3 d, float3 v0, float3 e1, float3 e2) {
-    P = cross_fma(d, e2);
-    det = dot_yxz(e1, P);
+    P = fcross(d, e2);
+    det = fdot(e1, P);
     T = o - v0;
     un = dot_xyz(T, P);
   }
   // the second one times the determinant
   __device__ inline void second(float3 d, float3 e1) {
-    Q = cross_fma(T, e1);
-    vn = dot_yxz(d, Q);
+    Q = fcross(T, e1);
+    vn = fdot(d, Q);
   }
   // t, or +inf outside the triangle or (tmin, tmax); det != 0
   __device__ inline float t(float3 e2, float inv, float u, float tmin, float tmax) const {
     if (!(vn * inv >= 0.0f && fmaf(vn, inv, u) <= 1.0f)) return INFINITY;
-    const float t = dot_yxz(e2, Q) * inv;
+    const float t = fdot(e2, Q) * inv;
     return (t > tmin && t < tmax) ? t : INFINITY;
   }
 };
@@ -256,9 +263,9 @@ __device__ inline float tri_t(const float4* __restrict__ recs, int r, float3 o, 
 // Sphere with unit d: b = -oc.d, h^2 = |oc + b d|^2, disc = r^2 - h^2, roots b -+ sqrt(disc).
 __device__ inline float sphere_t(float4 s, float3 o, float3 d, float tmin, float tmax) {
   const float3 oc = o - f3(s);
-  const float b = -dot(oc, d);
-  const float3 foot = oc + b * d;
-  const float disc = s.w * s.w - dot(foot, foot);
+  const float b = -fdot(oc, d);
+  const float3 foot = fmad(b, d, oc);
+  const float disc = fmaf(s.w, s.w, -fdot(foot, foot));
   if (disc < 0.0f) return INFINITY;
   const float q = sqrtf(disc);
   const float t0 = b - q, t1 = b + q;
@@ -268,10 +275,17 @@ __device__ inline float sphere_t(float4 s, float3 o, float3 d, float tmin, float
 }
 
 __device__ inline float plane_t(float4 p, float3 o, float3 d, float tmin, float tmax) {
-  const float nd = p.x * d.x + p.y * d.y + p.z * d.z;
+  const float nd = fdot(f3(p), d);
   if (nd == 0.0f) return INFINITY;
-  const float t = (p.w - (p.x * o.x + p.y * o.y + p.z * o.z)) / nd;
+  const float t = (p.w - fdot(f3(p), o)) / nd;
   return (t > tmin && t < tmax) ? t : INFINITY;
+}
+
+// The shadow ray from P to light l: its direction, and its length as the distance to stop at.
+__device__ inline float3 shadow_dir(const float4* lights, int l, float3 P, float* dist) {
+  const float3 Lv = f3(lights[2 * l]) - P;
+  *dist = sqrtf(fdot(Lv, Lv));
+  return (1.0f / *dist) * Lv;
 }
 
 // Slab test of one child box; returns the entry distance, or +inf when missed.
@@ -432,36 +446,34 @@ struct Best {
   int id;
 };
 
+// A wave's own LDS words, written by one of its lanes and read by another: within a wave LDS operations take
+// effect in program order, and the atomic access keeps the compiler from caching the value.
+template <class T>
+__device__ inline T lds_get(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+template <class T>
+__device__ inline void lds_put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
 // The best hits of the rays a wave shares between its lanes, one slot per ray (LDS, this wave's part).
 // A slot's word is (limit bits << 32 | id): as an integer it orders hits by (t, id), limit being the next
-// float above t.  Within a wave LDS operations take effect in program order.
+// float above t.
 struct Share {
   unsigned long long* word;
   int* key;
 
   __device__ inline void open(int slot, uint32_t limit_bits, int id, int k) const {
-    __hip_atomic_store(&word[slot], (static_cast<unsigned long long>(limit_bits) << 32) | uint32_t(id),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_store(&key[slot], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    lds_put(&word[slot], (static_cast<unsigned long long>(limit_bits) << 32) | uint32_t(id));
+    lds_put(&key[slot], k);
   }
-  __device__ inline float limit(int slot) const {
-    return __uint_as_float(
-        uint32_t(__hip_atomic_load(&word[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32));
-  }
-  __device__ inline int key_of(int slot) const {
-    return __hip_atomic_load(&key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
+  __device__ inline float limit(int slot) const { return __uint_as_float(uint32_t(lds_get(&word[slot]) >> 32)); }
+  __device__ inline int key_of(int slot) const { return lds_get(&key[slot]); }
   // Takes a hit if it is the ray's best; no other lane offers the same (t, id).
   __device__ inline void offer(int slot, uint32_t limit_bits, int id, int k) const {
     const unsigned long long w = (static_cast<unsigned long long>(limit_bits) << 32) | uint32_t(id);
     __hip_atomic_fetch_min(&word[slot], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (__hip_atomic_load(&word[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == w)
-      __hip_atomic_store(&key[slot], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (lds_get(&word[slot]) == w) lds_put(&key[slot], k);
   }
   // An occlusion query is answered: no candidate lies below a limit of 0.
-  __device__ inline void close(int slot) const {
-    __hip_atomic_store(&word[slot], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
+  __device__ inline void close(int slot) const { lds_put(&word[slot], 0ull); }
 };
 
 // A wave's working set of one kind of ray: lane l starts with ray l of the wave's batch (or none).
@@ -834,9 +846,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
           const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
           r.o = f3(rec);
           r.exclude = __float_as_int(rec.w);
-          const float3 Lv = f3(it.sc.lights[2 * l]) - r.o;
-          r.limit = sqrtf(dot(Lv, Lv));
-          r.d = (1.0f / r.limit) * Lv;
+          r.d = shadow_dir(it.sc.lights, l, r.o, &r.limit);
         }
         traverse<true, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, s_nodes, s_tris,
                                     [&](int key, float) {
@@ -931,6 +941,41 @@ __device__ inline float4 scalar_load(const float4* p, int k) {
   return *(const float4*)((const_float4*)p + __builtin_amdgcn_readfirstlane(k));
 }
 
+// The nearest hit among triangles first .. last - 1 and, with `rest`, the spheres and planes.
+__device__ __attribute__((always_inline)) inline Best flat_closest(const DevScene& sc, bool rest, int first, int last,
+                                                                   float3 o, float3 d, float tmin, int exclude) {
+  Best best{INFINITY, -1, 0x7fffffff};
+  auto accept = [&](float t, int key, int id) {
+    if (key != exclude && t < INFINITY && (t < best.t || (t == best.t && id < best.id))) best = Best{t, key, id};
+  };
+  if (rest) {
+    for (int k = 0; k < sc.S; ++k)
+      accept(sphere_t(scalar_load(sc.spheres, k), o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
+    for (int k = 0; k < sc.P; ++k) {
+      const int key = sc.T + sc.S + k;
+      accept(plane_t(scalar_load(sc.planes, k), o, d, tmin, next_up(best.t)), key, key);
+    }
+  }
+  flat_triangles(sc.tris, first, last, o, d, tmin, [&] { return next_up(best.t); }, accept);
+  return best;
+}
+
+// Whether any of them lies in (kSecondaryTmin, dist); in steps, so that a wave whose rays are all answered stops.
+__device__ __attribute__((always_inline)) inline bool flat_occluded(const DevScene& sc, bool rest, int first, int last,
+                                                                    float3 o, float3 d, float dist, int exclude) {
+  bool found = false;
+  auto accept = [&](float t, int key, int) { found = found || (key != exclude && t < INFINITY); };
+  if (rest) {
+    for (int k = 0; k < sc.S; ++k)
+      accept(sphere_t(scalar_load(sc.spheres, k), o, d, kSecondaryTmin, dist), sc.T + k, 0);
+    for (int k = 0; k < sc.P; ++k)
+      accept(plane_t(scalar_load(sc.planes, k), o, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
+  }
+  for (int k = first; k < last && !__all(found); k += 64)
+    flat_triangles(sc.tris, k, min(k + 64, last), o, d, kSecondaryTmin, [&] { return dist; }, accept);
+  return found;
+}
+
 template <int SEGS>
 __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int depth) {
   __shared__ float s_t[SEGS > 1 ? SEGS * 64 : 1];
@@ -976,22 +1021,9 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
           exclude = __float_as_int(rd.w);
         }
       }
-      const float tmin = depth == 0 ? 0.0f : kSecondaryTmin;
       Best best{INFINITY, -1, 0x7fffffff};
-      if (valid) {
-        auto accept = [&](float t, int key, int id) {
-          if (key != exclude && (t < best.t || (t == best.t && id < best.id))) best = Best{t, key, id};
-        };
-        if (seg == 0) {
-          for (int k = 0; k < sc.S; ++k) accept(sphere_t(scalar_load(sc.spheres, k), o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
-          for (int k = 0; k < sc.P; ++k) {
-            const int key = sc.T + sc.S + k;
-            accept(plane_t(scalar_load(sc.planes, k), o, d, tmin, next_up(best.t)), key, key);
-          }
-          if (!(best.t < INFINITY)) best = Best{INFINITY, -1, 0x7fffffff};
-        }
-        flat_triangles(sc.tris, first, last, o, d, tmin, [&] { return next_up(best.t); }, accept);
-      }
+      if (valid)
+        best = flat_closest(sc, seg == 0, first, last, o, d, depth == 0 ? 0.0f : kSecondaryTmin, exclude);
       if (SEGS > 1) {
         s_t[wave * 64 + lane] = best.t;
         s_id[wave * 64 + lane] = best.id;
@@ -1022,19 +1054,9 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
       if (valid) {
         const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
         const float3 P = f3(rec);
-        const int exclude = __float_as_int(rec.w);
-        const float3 Lv = f3(sc.lights[2 * l]) - P;
-        const float dist = sqrtf(dot(Lv, Lv));
-        const float3 d = (1.0f / dist) * Lv;
-        auto accept = [&](float t, int key, int) { found = found || (key != exclude && t < INFINITY); };
-        if (seg == 0) {
-          for (int k = 0; k < sc.S; ++k) accept(sphere_t(scalar_load(sc.spheres, k), P, d, kSecondaryTmin, dist), sc.T + k, 0);
-          for (int k = 0; k < sc.P; ++k)
-            accept(plane_t(scalar_load(sc.planes, k), P, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
-        }
-        // in steps, so that a wave whose rays are all answered stops
-        for (int k = first; k < last && !__all(found); k += 64)
-          flat_triangles(sc.tris, k, min(k + 64, last), P, d, kSecondaryTmin, [&] { return dist; }, accept);
+        float dist;
+        const float3 d = shadow_dir(sc.lights, l, P, &dist);
+        found = flat_occluded(sc, seg == 0, first, last, P, d, dist, __float_as_int(rec.w));
       }
       uint64_t hits = __ballot(found);
       if (SEGS > 1) {
@@ -1066,7 +1088,7 @@ __device__ inline void material_of(const DevScene& sc, int key, float4* m0, floa
 __device__ inline float3 geometric_normal(const DevScene& sc, int key, float3 P) {
   if (key < sc.T) {
     const float3 e1 = f3(sc.tris[3 * key + 1]), e2 = f3(sc.tris[3 * key + 2]);
-    return normalize(cross(e1, e2));
+    return normalize(fcross(e1, e2));
   }
   if (key < sc.T + sc.S) {
     const float4 s = sc.spheres[key - sc.T];
@@ -1081,6 +1103,35 @@ __device__ inline int32_t out_id(const DevScene& sc, int key) {
   if (key < sc.T) return __float_as_int(sc.tris[3 * key].w);
   return key;
 }
+
+// The pieces of the shading, shared by the kernels that shade.
+
+// The unit normal at P, turned towards the ray of direction d.
+__device__ inline float3 facing_normal(const DevScene& sc, int key, float3 P, float3 d) {
+  const float3 n = geometric_normal(sc, key, P);
+  return fdot(n, d) > 0.0f ? -1.0f * n : n;
+}
+
+// The direction and distance from P to light l, and the cosine at the surface.
+__device__ inline float light_at(const float4* lights, int l, float3 P, float3 N, float3* Ld, float* dist) {
+  *Ld = shadow_dir(lights, l, P, dist);
+  return fdot(N, *Ld);
+}
+
+// Light l's term at P times the path's throughput, for a surface of material (m0, m1) seen along d.
+__device__ inline float3 light_term(const float4* lights, int l, float3 P, float3 N, float3 d, float4 m0, float4 m1,
+                                    float3 thr) {
+  float3 Ld;
+  float dist;
+  const float ndl = light_at(lights, l, P, N, &Ld, &dist);
+  const float3 R = fmad(2.0f * ndl, N, -1.0f * Ld);
+  const float spec = powf(fmaxf(0.0f, fdot(R, -1.0f * d)), m0.w);
+  const float3 I = f3(lights[2 * l + 1]);
+  return mul(mul(I, fmad(ndl, f3(m0), spec * f3(m1))), thr);
+}
+
+// The mirror direction of d at a surface of normal N.
+__device__ inline float3 mirror_of(float3 d, float3 N) { return normalize(fmad(-(2.0f * fdot(d, N)), N, d)); }
 
 // ---------------------------------------------------------------------------------------------
 // k_shade: one thread per hit of depth `depth`.  Each block takes 256 consecutive entries per
@@ -1116,7 +1167,7 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
     }
     uint32_t mask = 0;
     bool spawn = false;
-    float3 P = make_float3(0.f, 0.f, 0.f), N = P, V = P, rdir = P, kr3 = P;
+    float3 P = make_float3(0.f, 0.f, 0.f), N = P, rdir = P, kr3 = P;
     float4 m0 = make_float4(0.f, 0.f, 0.f, 0.f), m1 = m0;
     const float4* lights = nullptr;
     const int key = __float_as_int(hit.y);
@@ -1146,23 +1197,21 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
       if (key < 0) {
         add = mul(thr, make_float3(sc.background[0], sc.background[1], sc.background[2]));
       } else {
-        P = o + hit.x * d;
-        const float3 Ng = geometric_normal(sc, key, P);
-        N = dot(Ng, d) > 0.0f ? -1.0f * Ng : Ng;
-        V = -1.0f * d;
+        P = fmad(hit.x, d, o);
+        N = facing_normal(sc, key, P, d);
         float4 m2;
         material_of(sc, key, &m0, &m1, &m2);
         add = mul(thr, mul(make_float3(sc.ambient[0], sc.ambient[1], sc.ambient[2]), f3(m0)));
         for (int l = 0; l < L; ++l) {
-          const float3 Lv = f3(lights[2 * l]) - P;
-          const float dist = sqrtf(dot(Lv, Lv));
-          const float ndl = dot(N, (1.0f / dist) * Lv);
+          float3 Ld;
+          float dist;
+          const float ndl = light_at(lights, l, P, N, &Ld, &dist);
           if (dist > kSecondaryTmin && ndl > 0.0f) mask |= 1u << l;
         }
         kr3 = f3(m2);
         if (depth < it.cam.D && (m2.x != 0.0f || m2.y != 0.0f || m2.z != 0.0f)) {
           spawn = true;
-          rdir = normalize(d - (2.0f * dot(d, N)) * N);
+          rdir = mirror_of(d, N);
         }
       }
       if (depth == 0) {
@@ -1170,9 +1219,10 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
         rad[1] = add.y;
         rad[2] = add.z;
       } else {
-        rad[0] += add.x;
-        rad[1] += add.y;
-        rad[2] += add.z;
+        const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), add);
+        rad[0] = r.x;
+        rad[1] = r.y;
+        rad[2] = r.z;
       }
       a.resinfo[q][e] = make_uint2(lp, mask);
     }
@@ -1200,19 +1250,11 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
       const uint64_t bal = __ballot(mine);
       if (mine) {
         const uint32_t slot = bbase[l] + wcnt[wave][l] + uint32_t(lanes_below(bal));
-        const float3 Lv = f3(lights[2 * l]) - P;
-        const float dist = sqrtf(dot(Lv, Lv));
-        const float3 Ld = (1.0f / dist) * Lv;
-        const float ndl = dot(N, Ld);
-        const float3 R = (2.0f * ndl) * N - Ld;
-        const float rv = fmaxf(0.0f, dot(R, V));
-        const float spec = powf(rv, m0.w);
-        const float3 I = f3(lights[2 * l + 1]);
-        const float3 term = mul(I, ndl * f3(m0) + spec * f3(m1));
+        const float3 term = light_term(lights, l, P, N, f3(rd), m0, m1, thr);
         const size_t s = size_t(l) * a.cap + slot;
         a.srec[q][s] = make_float4(P.x, P.y, P.z, __int_as_float(key));
         a.sowner[q][s] = e;
-        a.contrib[q][size_t(e) * LS + l] = make_float4(term.x * thr.x, term.y * thr.y, term.z * thr.z, 0.f);
+        a.contrib[q][size_t(e) * LS + l] = make_float4(term.x, term.y, term.z, 0.f);
       }
     }
     {
@@ -1221,7 +1263,8 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
         const uint32_t slot = bbase[LS] + wcnt[wave][LS] + uint32_t(lanes_below(bal));
         a.ro[nq][slot] = make_float4(P.x, P.y, P.z, ro.w);
         a.rd[nq][slot] = make_float4(rdir.x, rdir.y, rdir.z, __int_as_float(key));
-        a.thr[nq][slot] = make_float4(thr.x * kr3.x, thr.y * kr3.y, thr.z * kr3.z, 0.f);
+        const float3 next = mul(thr, kr3);
+        a.thr[nq][slot] = make_float4(next.x, next.y, next.z, 0.f);
       }
     }
     __syncthreads();  // wcnt / bbase are reused by the next iteration
@@ -1235,6 +1278,210 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
       for (int w = 0; w < kShadeWaves; ++w) sum += wcnt[w][0];
       if (sum) atomicAdd(&a.ctr->primary, sum);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// k_path: a small frame in one launch.  A wave takes its paths through the whole recursion -- closest hit,
+// shading, each light's shadow rays, the mirror ray -- with the pieces of the queue kernels, so each pixel
+// gets the same operations in the same order and the same bits.  A small frame is bound by its launches: the
+// queues cost 2 + 3 (D + 1) of them, each waiting for the last ray of the one before.  Here a wave waits only
+// for its own rays, its idle lanes share them (see traverse), and nothing passes through memory but the
+// result.  Larger frames gain more from the queues, which fill every wave with live rays.
+// A hit's shadow rays are packed over the lights, so a wave makes as many rounds as its rays need and not one a
+// light (641x479, 13k triangles, depth 4, 2 lights: 280 us a light at a time, 257 packed, 317 by queues).
+// 256x256, depth 1, 1 light: spheres 46.3 -> 18.4 us, 100 triangles 68.4 -> 52.0.  5 waves per SIMD with 6
+// spilled registers: 257 us; 4 without spills 264, 6 (35 spilled) 298 for that frame.
+// ---------------------------------------------------------------------------------------------
+
+// Which frames k_path takes.  Without a tree: at most kPathFlat triangles (1920x1080, depth 4, 2 lights: 42
+// triangles 367 vs 547 us through the queues, 148: 939 vs 1045, 262: 1695 vs 1698, 472: 2833 vs 2809).  With
+// one: as long as the rays, counted as paths x (1 + lights), are few for the tree's size.  640x480 with 4
+// lights is 3.1 M: 17k triangles 291 vs 304 us, 160k 449 vs 420, 3.4M 566 vs 548; 1024x768 with 2 lights is
+// 4.7 M: 17k triangles 414 vs 457, 160k 693 vs 669; 640x480 with 2 lights is 1.8 M: 362 vs 436 and 450 vs 564.
+constexpr int kPathFlat = 256;
+constexpr int kPathSmallTree = 32768;  // triangles; the nodes fit an XCD's L2 several times
+inline bool path_wins(const DevScene& sc, bool flat, int64_t paths) {
+  if (flat) return sc.T <= kPathFlat;
+  return paths * (1 + sc.L) <= (sc.T <= kPathSmallTree ? 5000000 : 2500000);
+}
+
+#ifndef SRT_PATH_WAVES
+#define SRT_PATH_WAVES 5
+#endif
+
+template <bool TREE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH_WAVES))) void k_path(KArgs a, int blog) {
+  __shared__ uint32_t lstack[TREE ? kStackLds * kBlock : 1];
+  __shared__ unsigned long long share_word[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
+  __shared__ int share_key[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
+  __shared__ uint32_t s_cnt[3][kWaves];
+  __shared__ uint16_t s_ray[kWaves][64 * RT_MAX_LIGHTS];              // lane | light << 6
+  __shared__ unsigned long long s_visible[kWaves][RT_MAX_LIGHTS];     // a bit a ray
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Share share{&share_word[TREE ? wave * kCoopRays : 0], &share_key[TREE ? wave * kCoopRays : 0]};
+  Stack st{&lstack[TREE ? threadIdx.x : 0], global_scalar(a.gstack), blockIdx.x * uint32_t(kBlock),
+           uint32_t(a.trace_threads), a.gstack_entries, 0, false};
+  const DevScene& sc = a.one.sc;
+  const uint32_t count = uint32_t(a.path_count), nwaves = gridDim.x * uint32_t(kWaves);
+  uint32_t n_refl = 0, n_shadow = 0, unused = 0;
+  for (uint32_t batch = blockIdx.x * uint32_t(kWaves) + wave; (batch << blog) < count; batch += nwaves) {
+    const uint32_t e = (batch << blog) + lane;
+    float3 o = make_float3(0.f, 0.f, 0.f), d = o;
+    int eye = 0, x = 0, y = 0;
+    bool alive = lane < (1 << blog) && e < count && path_pixel(a.one.cam, e, &eye, &x, &y);
+    const bool inside = alive;
+    if (alive) primary_ray(a.one.cam, eye, x, y, &o, &d);
+    float3 thr = make_float3(1.f, 1.f, 1.f), rad = make_float3(0.f, 0.f, 0.f), sum = rad;
+    bool lit = false;  // `sum` holds the lights' terms of the hit before, still to be added
+    int exclude = -1;
+    for (int depth = 0; __ballot(alive) != 0; ++depth) {
+      const float tmin = depth == 0 ? 0.0f : kSecondaryTmin;
+      float t = INFINITY;
+      int key = -1;
+      if (TREE) {
+        Ray r{o, d, tmin, INFINITY, exclude};
+        traverse<false, false, false>(sc, alive, r, false, st, share, unused, unused, [&](int k, float tk) {
+          key = k;
+          t = tk;
+        });
+      } else if (alive) {
+        const Best b = flat_closest(sc, true, 0, sc.T, o, d, tmin, exclude);
+        key = b.key;
+        t = b.t;
+      }
+      float3 P = o, N = o;
+      uint32_t mask = 0;
+      bool spawn = false;
+      if (alive) {
+        if (depth == 0) {
+          const int64_t pix = int64_t(y) * a.one.cam.W + x;
+          if (a.one.out.hit_t[eye]) a.one.out.hit_t[eye][pix] = t;
+          if (a.one.out.hit_prim[eye]) a.one.out.hit_prim[eye][pix] = out_id(sc, key);
+        }
+        float3 add;
+        if (key < 0) {
+          add = mul(thr, make_float3(sc.background[0], sc.background[1], sc.background[2]));
+        } else {
+          P = fmad(t, d, o);
+          N = facing_normal(sc, key, P, d);
+          float4 m0, m1, m2;
+          material_of(sc, key, &m0, &m1, &m2);
+          add = mul(thr, mul(make_float3(sc.ambient[0], sc.ambient[1], sc.ambient[2]), f3(m0)));
+          for (int l = 0; l < sc.L; ++l) {
+            float3 Ld;
+            float dist;
+            const float ndl = light_at(sc.lights, l, P, N, &Ld, &dist);
+            if (dist > kSecondaryTmin && ndl > 0.0f) mask |= 1u << l;
+          }
+          spawn = depth < a.one.cam.D && (m2.x != 0.0f || m2.y != 0.0f || m2.z != 0.0f);
+        }
+        // the queue kernels' order: this depth's term, then the lights of the depth before
+        rad = depth == 0 ? add : add_rn(rad, add);
+        if (lit) rad = add_rn(rad, sum);
+        sum = make_float3(0.f, 0.f, 0.f);
+        lit = mask != 0;
+      }
+      // The shadow rays of all lights, packed: a wave traces them 64 at a time, whichever light they head for.
+      uint32_t rays = 0;
+      for (int l = 0; l < sc.L; ++l) {
+        const bool cast = ((mask >> l) & 1u) != 0;
+        const uint64_t b = __ballot(cast);
+        if (cast) lds_put(&s_ray[wave][rays + lanes_below(b)], uint16_t(lane | (l << 6)));
+        rays += uint32_t(__popcll(b));
+      }
+      for (uint32_t first = 0; first < rays; first += 64) {
+        const bool cast = first + lane < rays;
+        const uint32_t r = cast ? uint32_t(lds_get(&s_ray[wave][first + lane])) : uint32_t(lane);
+        const int from = int(r & 63u);
+        const float3 from_P = make_float3(shfl_f(P.x, from), shfl_f(P.y, from), shfl_f(P.z, from));
+        const int from_key = shfl_i(key, from);
+        bool visible = false;
+        float dist = 0.0f;
+        float3 Ld = from_P;
+        if (cast) Ld = shadow_dir(sc.lights, int(r >> 6), from_P, &dist);
+        if (TREE) {
+          traverse<true, false, false>(sc, cast, Ray{from_P, Ld, kSecondaryTmin, dist, from_key}, false, st, share,
+                                       unused, unused, [&](int k, float) { visible = k < 0; });
+        } else if (cast) {
+          visible = !flat_occluded(sc, true, 0, sc.T, from_P, Ld, dist, from_key);
+        }
+        const uint64_t v = __ballot(visible);
+        if (lane == 0) lds_put(&s_visible[wave][first >> 6], static_cast<unsigned long long>(v));
+      }
+      n_shadow += lane == 0 ? rays : 0u;
+      rays = 0;
+      for (int l = 0; l < sc.L; ++l) {
+        const bool cast = ((mask >> l) & 1u) != 0;
+        const uint64_t b = __ballot(cast);
+        const uint32_t r = rays + lanes_below(b);
+        rays += uint32_t(__popcll(b));
+        if (cast && ((lds_get(&s_visible[wave][r >> 6]) >> (r & 63u)) & 1u)) {
+          float4 m0, m1, m2;
+          material_of(sc, key, &m0, &m1, &m2);
+          sum = add_rn(sum, light_term(sc.lights, l, P, N, d, m0, m1, thr));
+        }
+      }
+      if (spawn) {
+        float4 m0, m1, m2;
+        material_of(sc, key, &m0, &m1, &m2);
+        d = mirror_of(d, N);
+        o = P;
+        thr = mul(thr, f3(m2));
+        exclude = key;
+        ++n_refl;
+      }
+      alive = spawn;
+    }
+    if (inside) {
+      if (lit) rad = add_rn(rad, sum);
+      path_pixel(a.one.cam, e, &eye, &x, &y);
+      float* out = a.one.out.radiance[eye] + 3 * (int64_t(y) * a.one.cam.W + x);
+      out[0] = rad.x;
+      out[1] = rad.y;
+      out[2] = rad.z;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    n_refl += __shfl_xor(n_refl, off);
+    n_shadow += __shfl_xor(n_shadow, off);
+  }
+  const uint32_t broken = __ballot(st.overflow) != 0 ? 1u : 0u;
+  if (lane == 0) s_cnt[0][wave] = n_refl, s_cnt[1][wave] = n_shadow, s_cnt[2][wave] = broken;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint4 c = make_uint4(0u, 0u, 0u, 0u);
+    for (int w = 0; w < kWaves; ++w) c.x += s_cnt[0][w], c.y += s_cnt[1][w], c.z |= s_cnt[2][w];
+    reinterpret_cast<uint4*>(a.ctr)[blockIdx.x] = c;  // k_path's launches use the counters' bytes for this
+  }
+}
+static_assert(sizeof(Counters) >= kMaxTraceBlocks * sizeof(uint4), "a block's counts");
+
+// Adds the counts of k_path's blocks.
+__global__ __launch_bounds__(kBlock) void k_path_finish(const uint4* counts, int blocks, int64_t primary, int64_t* out) {
+  __shared__ unsigned long long s_sum[2];
+  __shared__ uint32_t s_err;
+  if (threadIdx.x == 0) s_sum[0] = s_sum[1] = 0, s_err = 0;
+  __syncthreads();
+  unsigned long long refl = 0, shadow = 0;
+  uint32_t err = 0;
+  for (int i = threadIdx.x; i < blocks; i += kBlock) refl += counts[i].x, shadow += counts[i].y, err |= counts[i].z;
+  for (int off = 32; off > 0; off >>= 1) {
+    refl += __shfl_xor(refl, off);
+    shadow += __shfl_xor(shadow, off);
+    err |= __shfl_xor(err, off);
+  }
+  if (lane_id() == 0) {
+    atomicAdd(&s_sum[0], refl);
+    atomicAdd(&s_sum[1], shadow);
+    atomicOr(&s_err, err);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[RT_COUNT_PRIMARY] += primary;
+    out[RT_COUNT_REFLECTION] += int64_t(s_sum[0]);
+    out[RT_COUNT_SHADOW] += int64_t(s_sum[1]);
+    out[RT_COUNT_ERRORS] += s_err;
   }
 }
 
@@ -1258,13 +1505,14 @@ __global__ __launch_bounds__(kBlock) void k_resolve(KArgs a, int depth) {
       if (!((ri.y >> l) & 1u)) continue;
       const size_t k = size_t(e) * LS + l;
       const bool v = a.vis[q][k] != 0;
-      if (v) sum = sum + f3(a.contrib[q][k]);
+      if (v) sum = add_rn(sum, f3(a.contrib[q][k]));
       if (PATH_IDS) it.out.shadow_state[eye][(pix * D1 + depth) * L + l] = v ? 2 : 1;
     }
     float* rad = it.out.radiance[eye] + 3 * pix;
-    rad[0] += sum.x;
-    rad[1] += sum.y;
-    rad[2] += sum.z;
+    const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), sum);
+    rad[0] = r.x;
+    rad[1] = r.y;
+    rad[2] = r.z;
   }
 }
 
@@ -1447,6 +1695,22 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   const unsigned gshade = unsigned(std::max<int64_t>(
       1, std::min<int64_t>((ra.path_count + kShadeBlock - 1) / kShadeBlock, ra.stream_blocks * kBlock / kShadeBlock)));
   hipError_t e;
+  // A small frame in one launch: whole frames only (the ray counts take the pixels as traced), and neither ray-tree
+  // signatures nor the timer, whose stages are the queue kernels'.
+  const bool whole = ra.path_begin == 0 && ra.path_count == ra.frame_paths;
+  if (!multi && !count && !ids && !timer && whole && path_wins(ra.one.sc, flat, ra.path_count)) {
+    int blog = 6;
+    if (!flat && kCoopRays > 0)
+      while (blog > kMinRaysLog2 && (ra.path_count >> (blog - 1)) < int64_t(p.grid_trace) * kWaves) --blog;
+    const int64_t per_block = int64_t(kWaves) << blog;
+    const unsigned grid = unsigned(std::min<int64_t>(p.grid_trace, (ra.path_count + per_block - 1) / per_block));
+    e = flat ? launch(k_path<false>, grid, a, blog, s, nullptr, RT_STAGE_TRACE)
+             : launch(k_path<true>, grid, a, blog, s, nullptr, RT_STAGE_TRACE);
+    if (e != hipSuccess || !ra.ray_counts) return e;
+    k_path_finish<<<1, kBlock, 0, s>>>(reinterpret_cast<const uint4*>(a.ctr), int(grid),
+                                       2 * int64_t(ra.one.cam.W) * ra.one.cam.H, ra.ray_counts);
+    return hipGetLastError();
+  }
   if (timer) timer_begin(timer, RT_STAGE_SETUP, s);
   k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
   e = hipGetLastError();

@@ -190,6 +190,7 @@ struct RenderArgs {
   char* ws;
   RenderPlan plan;
   int64_t path_begin, path_count;  // this pass's range of the (batch's) path space
+  int64_t frame_paths;             // single render: the paths of the whole frame
   int64_t stream_blocks;           // workgroups of the shading / resolve launches
 };
 

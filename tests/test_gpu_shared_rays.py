@@ -84,3 +84,36 @@ def test_waves_that_hold_several_items(torch_cuda):
             assert torch.equal(one[k], outs[i][k]), (i, k)
     for gs in built:
         gs.close()
+
+
+def _flat(n):
+    """n triangles and no tree."""
+    scene, cam = sg.make_small_terrain(seed=50, grid=18, n_spheres=2, level=1, lights=2, depth=3)
+    from dataclasses import replace
+    return replace(scene, triangles=scene.triangles[-n:], tri_material=scene.tri_material[-n:]), cam
+
+
+# Frames that one launch takes through the whole recursion against the queue kernels (which frames with ray-tree
+# signatures take): sizes around every batch width, no light to eight, no mirror to eight, no tree and no triangle.
+@pytest.mark.parametrize("size", [(1, 1), (3, 2), (17, 9), (181, 181), (255, 257), (420, 400)])
+@pytest.mark.parametrize("lights,depth", [(0, 2), (1, 0), (4, 4), (8, 8)])
+@pytest.mark.parametrize("what", ["tree", "spheres", "flat256", "flat257"])
+def test_whole_paths_equal_the_queues(torch_cuda, what, lights, depth, size):
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    if what == "tree":
+        scene, cam = sg.make_small_terrain(seed=33, grid=18, n_spheres=5, level=1)
+    elif what == "spheres":
+        scene, cam = sg.make_spheres_scene(seed=3)
+    else:
+        scene, cam = _flat(int(what[4:]))
+    all_lights = [[-6, 8, 2], [6, 6, 12], [-3, 9, 9], [5, 7, 3], [0, 8, 5], [-7, 5, 11], [3, 4, 14], [0.5, 3, -2]]
+    scene = scene.with_lights([p + [0.4, 0.4, 0.4] for p in all_lights[:lights]])
+    cam = cam.resized(*size).with_(max_depth=depth)
+    print(f"[whole paths] {what} L={lights} D={depth} {size}", flush=True)
+    gs = GpuScene(scene, accel="none" if what.startswith("flat") else "ploc")
+    one, queues = render_stereo(gs, cam), render_stereo(gs, cam, path_ids=True)
+    torch.cuda.synchronize()
+    for k in ("radiance", "hit_t", "hit_prim", "ray_counts"):
+        assert torch.equal(one[k], queues[k]), k
+    gs.close()
