@@ -137,18 +137,19 @@ struct KArgs {
   DevItem one;            // single render (MULTI = false)
   const DevItem* items;   // batch table (MULTI = true)
   int32_t num_items;
-  int32_t lstride;        // light slots per entry in contrib/vis (max lights over the items)
+  int32_t lstride;        // light queues (max lights over the items)
   int32_t dmax;           // max reflection depth over the items
   Counters* ctr;
-  float4* ro[2];       // mirror/primary ray queue by depth parity: origin + pass-local path index bits
-  float4* rd[2];       // direction + excluded primitive key bits
-  float4* thr[2];      // throughput
+  float4* ro[2];       // mirror-ray queue by depth parity: origin + pass-local path index bits
+  float4* rd[2];       // direction + excluded primitive key bits; also of the primary rays
+  float4* thr[2];      // throughput of a mirror ray
   float2* hit;         // (t, key bits) of the closest-hit rays of the current depth
-  uint2* resinfo[2];   // per entry of a depth: (pass-local path index, mask of lights with a shadow ray)
-  float4* srec[2];     // shadow records [light][cap]: (origin, excluded key bits)
-  uint32_t* sowner[2]; // [light][cap]: entry that owns the record
-  float4* contrib[2];  // [cap][lstride]: the light's term times throughput
-  uint8_t* vis[2];     // [cap][lstride]: 1 = light visible
+  uint32_t* epath[2];  // [cap]: pass-local path index of a mirror-ray entry (at depth 0 the entry's own index)
+  uint8_t* smask[2];   // [cap]: lights towards which the entry has a shadow ray
+  float4* spos[2];     // [cap]: origin of an entry's shadow rays, excluded key bits; written where smask is not 0
+  uint32_t* sowner[2]; // [light][cap]: entries with a shadow ray towards the light, in any order
+  float* contrib[2];   // [light][cap][3]: the light's term times throughput
+  uint8_t* vis[2];     // [light][cap]: 1 = light visible from the entry
   uint32_t* gstack;
   int32_t gstack_entries; // spill entries per lane in gstack
   int64_t path_begin, path_count;
@@ -165,10 +166,11 @@ static_assert(std::is_trivially_copyable<KArgs>::value && std::is_standard_layou
 template <bool MULTI>
 __device__ inline int item_of(const KArgs& a, int64_t p) {
   if (!MULTI) return 0;
+  typedef __attribute__((address_space(4))) const DevItem item_t;  // a scalar load where p is uniform
   int lo = 0, hi = a.num_items - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (a.items[mid].path_offset <= p)
+    if (((item_t*)a.items)[mid].path_offset <= p)
       lo = mid;
     else
       hi = mid - 1;
@@ -185,30 +187,39 @@ __device__ inline const DevItem& item_ref(const KArgs& a, int k) {
 // Camera
 // ---------------------------------------------------------------------------------------------
 
-__device__ inline bool path_pixel(const DevCamera& c, int64_t p, int* eye, int* x, int* y) {
-  int64_t tile = p / kPathsPerTile;
-  int r = int(p % kPathsPerTile);
+// The pixel of path r of tile `tile`; false outside the image.
+__device__ inline bool tile_pixel(const DevCamera& c, uint32_t tile, int r, int* eye, int* x, int* y) {
   *eye = r >> 6;
-  int w = r & 63;
-  int tx = int(tile % c.tiles_x), ty = int(tile / c.tiles_x);
+  const int w = r & 63;
+  const int ty = int(tile / uint32_t(c.tiles_x)), tx = int(tile) - ty * c.tiles_x;
   *x = tx * kTile + (w & 7);
   *y = ty * kTile + (w >> 3);
   return *x < c.W && *y < c.H;
 }
+// The pixel of path p of an image (of at most RT_MAX_PIXELS pixels, so tiles count in 32 bits).
+__device__ inline bool path_pixel(const DevCamera& c, int64_t p, int* eye, int* x, int* y) {
+  return tile_pixel(c, uint32_t(p / kPathsPerTile), int(p % kPathsPerTile), eye, x, y);
+}
+// The same where all lanes' paths are of one tile.
+__device__ inline bool wave_pixel(const DevCamera& c, int64_t p, int* eye, int* x, int* y) {
+  const uint32_t tile = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(p / kPathsPerTile))));
+  return tile_pixel(c, tile, int(p % kPathsPerTile), eye, x, y);
+}
 
 // Off-axis stereo pinhole: eye at C + s r (s = -+B/2), pixel-centre ray sheared by -s/Z0.
 // Computed in FP64 and rounded once to FP32.
+__device__ inline float3 eye_position(const DevCamera& c, int eye) {
+  const double s = eye == 0 ? -c.half_baseline : c.half_baseline;
+  return make_float3(float(fma(s, c.r[0], c.C[0])), float(fma(s, c.r[1], c.C[1])), float(fma(s, c.r[2], c.C[2])));
+}
 __device__ inline void primary_ray(const DevCamera& c, int eye, int x, int y, float3* o, float3* d) {
   double s = eye == 0 ? -c.half_baseline : c.half_baseline;
-  double O[3], D[3];
+  double D[3];
   double a = (double(x) + 0.5 - c.cx) / c.fpx - s * c.inv_convergence;
   double b = -(double(y) + 0.5 - c.cy) / c.fpx;
-  for (int k = 0; k < 3; ++k) {
-    O[k] = c.C[k] + s * c.r[k];
-    D[k] = c.f[k] + a * c.r[k] + b * c.u[k];
-  }
+  for (int k = 0; k < 3; ++k) D[k] = c.f[k] + a * c.r[k] + b * c.u[k];
   double inv = 1.0 / sqrt(D[0] * D[0] + D[1] * D[1] + D[2] * D[2]);
-  *o = make_float3(float(O[0]), float(O[1]), float(O[2]));
+  *o = eye_position(c, eye);
   *d = make_float3(float(D[0] * inv), float(D[1] * inv), float(D[2] * inv));
 }
 
@@ -820,8 +831,10 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
       const uint32_t e = base + lane;
       bool valid = filled && e < nc;
       int k = 0;
-      if (MULTI && valid)
-        k = item_of<MULTI>(a, a.path_begin + (depth == 0 ? e : uint32_t(__float_as_int(a.ro[q][e].w))));
+      if (MULTI && depth == 0)
+        k = item_of<MULTI>(a, a.path_begin + base);  // a tile's paths belong to one item
+      else if (MULTI && valid)
+        k = item_of<MULTI>(a, a.path_begin + uint32_t(__float_as_int(a.ro[q][e].w)));
       each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
         Ray r{};
         r.limit = INFINITY;
@@ -830,13 +843,10 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
         if (mine) {
           if (depth == 0) {
             int eye, x, y;
-            mine = path_pixel(it.cam, a.path_begin + e - it.path_offset, &eye, &x, &y);
+            mine = wave_pixel(it.cam, a.path_begin + e - it.path_offset, &eye, &x, &y);
             if (mine) {
               primary_ray(it.cam, eye, x, y, &r.o, &r.d);
-              a.ro[q][e] = make_float4(r.o.x, r.o.y, r.o.z, __int_as_float(int(e)));
               a.rd[q][e] = make_float4(r.d.x, r.d.y, r.d.z, __int_as_float(-1));
-            } else {
-              a.ro[q][e].w = __int_as_float(-1);  // outside the image
             }
           } else {
             const float4 ro = a.ro[q][e], rd = a.rd[q][e];
@@ -865,12 +875,12 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
       const bool valid = filled && i < cnt;
       const uint32_t owner = valid ? a.sowner[sq][size_t(l) * a.cap + i] : 0u;
       int k = 0;
-      if (MULTI && valid) k = item_of<MULTI>(a, a.path_begin + a.resinfo[sq][owner].x);
+      if (MULTI && valid) k = item_of<MULTI>(a, a.path_begin + (depth == 1 ? owner : a.epath[sq][owner]));
       each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
         Ray r{};
         r.tmin = kSecondaryTmin;
         if (mine) {
-          const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
+          const float4 rec = a.spos[sq][owner];
           r.o = f3(rec);
           r.exclude = __float_as_int(rec.w);
           r.d = shadow_dir(it.sc.lights, l, r.o, &r.limit);
@@ -879,7 +889,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
                                     [&](int key, float) {
                                       uint32_t o = owner;
                                       asm volatile("" : "+v"(o));  // the address is formed here, not before the loop
-                                      global_scalar(a.vis[sq])[size_t(o) * LS + l] = key < 0 ? 1 : 0;
+                                      global_scalar(a.vis[sq] + size_t(l) * a.cap)[o] = key < 0 ? 1 : 0;
                                     });
       });
     }
@@ -1031,15 +1041,10 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
       if (valid) {
         if (depth == 0) {
           int eye, x, y;
-          valid = path_pixel(a.one.cam, a.path_begin + e, &eye, &x, &y);
+          valid = wave_pixel(a.one.cam, a.path_begin + e, &eye, &x, &y);
           if (valid) {
             primary_ray(a.one.cam, eye, x, y, &o, &d);
-            if (seg == 0) {
-              a.ro[q][e] = make_float4(o.x, o.y, o.z, __int_as_float(int(e)));
-              a.rd[q][e] = make_float4(d.x, d.y, d.z, __int_as_float(-1));
-            }
-          } else if (seg == 0) {
-            a.ro[q][e].w = __int_as_float(-1);  // outside the image
+            if (seg == 0) a.rd[q][e] = make_float4(d.x, d.y, d.z, __int_as_float(-1));
           }
         } else {
           const float4 ro = a.ro[q][e], rd = a.rd[q][e];
@@ -1077,9 +1082,11 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
       }
       const uint32_t i = base - start + lane;
       const bool valid = i < cnt;
+      uint32_t owner = 0;
       bool found = false;
       if (valid) {
-        const float4 rec = a.srec[sq][size_t(l) * a.cap + i];
+        owner = a.sowner[sq][size_t(l) * a.cap + i];
+        const float4 rec = a.spos[sq][owner];
         const float3 P = f3(rec);
         float dist;
         const float3 d = shadow_dir(sc.lights, l, P, &dist);
@@ -1092,7 +1099,7 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
         if (wave == 0)
           for (int w = 1; w < SEGS; ++w) hits |= s_hit[w];
       }
-      if (valid && seg == 0) a.vis[sq][size_t(a.sowner[sq][size_t(l) * a.cap + i]) * LS + l] = (hits >> lane) & 1 ? 0 : 1;
+      if (valid && seg == 0) a.vis[sq][size_t(l) * a.cap + owner] = (hits >> lane) & 1 ? 0 : 1;
     }
     if (SEGS > 1) __syncthreads();  // the LDS results are reused by the next batch
   }
@@ -1145,12 +1152,10 @@ __device__ inline float light_at(const float4* lights, int l, float3 P, float3 N
   return fdot(N, *Ld);
 }
 
-// Light l's term at P times the path's throughput, for a surface of material (m0, m1) seen along d.
-__device__ inline float3 light_term(const float4* lights, int l, float3 P, float3 N, float3 d, float4 m0, float4 m1,
-                                    float3 thr) {
-  float3 Ld;
-  float dist;
-  const float ndl = light_at(lights, l, P, N, &Ld, &dist);
+// Light l's term (direction Ld, cosine ndl from light_at) times the path's throughput, for a surface of material
+// (m0, m1) seen along d.
+__device__ inline float3 light_term(const float4* lights, int l, float ndl, float3 Ld, float3 N, float3 d, float4 m0,
+                                    float4 m1, float3 thr) {
   const float3 R = fmad(2.0f * ndl, N, -1.0f * Ld);
   const float spec = powf(fmaxf(0.0f, fdot(R, -1.0f * d)), m0.w);
   const float3 I = f3(lights[2 * l + 1]);
@@ -1161,13 +1166,24 @@ __device__ inline float3 light_term(const float4* lights, int l, float3 P, float
 __device__ inline float3 mirror_of(float3 d, float3 N) { return normalize(fmad(-(2.0f * fdot(d, N)), N, d)); }
 
 // ---------------------------------------------------------------------------------------------
-// k_shade: one thread per hit of depth `depth`.  Each block takes 256 consecutive entries per
+// k_shade: one thread per hit of depth `depth`.  Each block takes 512 consecutive entries per
 // iteration; new shadow records (one queue per light) and mirror rays are compacted with wave
 // ballots, a block prefix over the waves and one atomic per block and queue.
+//
+// The launches of depth 0 are bound by memory (3.8 TB/s, most of it written), so little is written: what all
+// lights share (the hit point) once an entry, a light's queue holds entry numbers only, a term is 12 bytes in
+// its light's own array (a batch's scenes with fewer lights than the most leave no gaps in it), a path's
+// index is its entry at depth 0, and the origin of a primary ray is the eye.  Bytes a path with n lit lights
+// at depth 0: 20 + 36 n before, 29 + 16 n now, and 24 instead of 40 from the traversal.  A light's direction and
+// term are computed once, in one loop.  A batch's scene is the same for nearly every wave, see each_item.
+// Depth-0 shading and resolve, before and now: 1920x1080, 4 lights 175 + 66 us, 122 + 48; 16 mixed scenes
+// 1047 + 411 us, 744 + 255.
+// Registers for 8 waves per SIMD; the batch's kernel would spill 8 of them (8 small scenes 970 us, 915 with 6).
 // ---------------------------------------------------------------------------------------------
 
 template <bool PATH_IDS, bool MULTI>
-__global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
+__global__ __launch_bounds__(kShadeBlock) __attribute__((amdgpu_waves_per_eu(MULTI ? 6 : 8))) void k_shade(
+    KArgs a, int depth) {
   __shared__ uint32_t wcnt[kShadeWaves][RT_MAX_LIGHTS + 1];
   __shared__ uint32_t bbase[RT_MAX_LIGHTS + 1];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -1177,39 +1193,33 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
   uint32_t n_primary = 0;
   for (uint32_t base = blockIdx.x * kShadeBlock; base < total; base += gridDim.x * kShadeBlock) {  // block-uniform loop
     const uint32_t e = base + threadIdx.x;
-    bool active = e < total;
-    float4 ro = make_float4(0.f, 0.f, 0.f, __int_as_float(-1)), rd = make_float4(0.f, 0.f, 0.f, 0.f);
-    float3 thr = make_float3(1.f, 1.f, 1.f);
-    float2 hit = make_float2(INFINITY, __int_as_float(-1));
-    if (active) {
-      ro = a.ro[q][e];
-      if (__float_as_int(ro.w) < 0) {
-        active = false;
-        a.resinfo[q][e] = make_uint2(0xffffffffu, 0u);
-      } else {
-        rd = a.rd[q][e];
-        hit = a.hit[e];
-        if (depth > 0) thr = f3(a.thr[q][e]);
-      }
-    }
-    uint32_t mask = 0;
+    const bool active = e < total;
+    uint32_t mask = 0, lp = e;
     bool spawn = false;
-    float3 P = make_float3(0.f, 0.f, 0.f), N = P, rdir = P, kr3 = P;
-    float4 m0 = make_float4(0.f, 0.f, 0.f, 0.f), m1 = m0;
-    const float4* lights = nullptr;
-    const int key = __float_as_int(hit.y);
-    if (active) {
-      const uint32_t lp = uint32_t(__float_as_int(ro.w));
-      const int64_t p = a.path_begin + lp;
-      const DevItem& it = item_ref<MULTI>(a, item_of<MULTI>(a, p));
+    float3 P = make_float3(0.f, 0.f, 0.f), rdir = P, next = P;
+    int key = -1, item = 0;
+    if (depth > 0 && active) lp = uint32_t(__float_as_int(a.ro[q][e].w));
+    if (MULTI) {
+      if (depth == 0)
+        item = item_of<MULTI>(a, a.path_begin + uint32_t(__builtin_amdgcn_readfirstlane(e)));  // one to a tile
+      else if (active)
+        item = item_of<MULTI>(a, a.path_begin + lp);
+    }
+    each_item<MULTI>(a, active, item, [&](const DevItem& it, bool mine) {
       const DevScene& sc = it.sc;
       const int L = sc.L, D1 = it.cam.D + 1;
-      lights = sc.lights;
-      int eye, x, y;
-      path_pixel(it.cam, p - it.path_offset, &eye, &x, &y);
+      int eye = 0, x = 0, y = 0;
+      if (!mine) return;
+      const int64_t p = a.path_begin + lp - it.path_offset;
+      if (!(depth == 0 ? wave_pixel(it.cam, p, &eye, &x, &y) : path_pixel(it.cam, p, &eye, &x, &y))) return;
+      const float4 rd = a.rd[q][e];
+      const float2 hit = a.hit[e];
+      float3 thr = make_float3(1.f, 1.f, 1.f);
+      if (depth > 0) thr = f3(a.thr[q][e]);
+      key = __float_as_int(hit.y);
       const int64_t pix = int64_t(y) * it.cam.W + x;
       float* rad = it.out.radiance[eye] + 3 * pix;
-      const float3 o = f3(ro), d = f3(rd);
+      const float3 o = depth == 0 ? eye_position(it.cam, eye) : f3(a.ro[q][e]), d = f3(rd);
       if (depth == 0) {
         ++n_primary;
         if (it.out.hit_t[eye]) it.out.hit_t[eye][pix] = hit.x;
@@ -1225,33 +1235,38 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
         add = mul(thr, make_float3(sc.background[0], sc.background[1], sc.background[2]));
       } else {
         P = fmad(hit.x, d, o);
-        N = facing_normal(sc, key, P, d);
-        float4 m2;
+        const float3 N = facing_normal(sc, key, P, d);
+        float4 m0, m1, m2;
         material_of(sc, key, &m0, &m1, &m2);
         add = mul(thr, mul(make_float3(sc.ambient[0], sc.ambient[1], sc.ambient[2]), f3(m0)));
         for (int l = 0; l < L; ++l) {
           float3 Ld;
           float dist;
-          const float ndl = light_at(lights, l, P, N, &Ld, &dist);
-          if (dist > kSecondaryTmin && ndl > 0.0f) mask |= 1u << l;
+          const float ndl = light_at(sc.lights, l, P, N, &Ld, &dist);
+          if (dist > kSecondaryTmin && ndl > 0.0f) {
+            mask |= 1u << l;
+            const float3 term = light_term(sc.lights, l, ndl, Ld, N, d, m0, m1, thr);
+            float* c = a.contrib[q] + 3 * (size_t(l) * a.cap + e);
+            c[0] = term.x;
+            c[1] = term.y;
+            c[2] = term.z;
+          }
         }
-        kr3 = f3(m2);
         if (depth < it.cam.D && (m2.x != 0.0f || m2.y != 0.0f || m2.z != 0.0f)) {
           spawn = true;
           rdir = mirror_of(d, N);
+          next = mul(thr, f3(m2));
         }
       }
-      if (depth == 0) {
-        rad[0] = add.x;
-        rad[1] = add.y;
-        rad[2] = add.z;
-      } else {
-        const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), add);
-        rad[0] = r.x;
-        rad[1] = r.y;
-        rad[2] = r.z;
-      }
-      a.resinfo[q][e] = make_uint2(lp, mask);
+      if (depth > 0) add = add_rn(make_float3(rad[0], rad[1], rad[2]), add);
+      rad[0] = add.x;
+      rad[1] = add.y;
+      rad[2] = add.z;
+    });
+    if (active) {
+      a.smask[q][e] = uint8_t(mask);  // 0 too for paths outside the image
+      if (depth > 0) a.epath[q][e] = lp;
+      if (mask) a.spos[q][e] = make_float4(P.x, P.y, P.z, __int_as_float(key));
     }
     // per-wave counts of every queue (light queues 0..LS-1, mirror queue LS), then one atomic per
     // block and queue
@@ -1277,20 +1292,15 @@ __global__ __launch_bounds__(kShadeBlock) void k_shade(KArgs a, int depth) {
       const uint64_t bal = __ballot(mine);
       if (mine) {
         const uint32_t slot = bbase[l] + wcnt[wave][l] + uint32_t(lanes_below(bal));
-        const float3 term = light_term(lights, l, P, N, f3(rd), m0, m1, thr);
-        const size_t s = size_t(l) * a.cap + slot;
-        a.srec[q][s] = make_float4(P.x, P.y, P.z, __int_as_float(key));
-        a.sowner[q][s] = e;
-        a.contrib[q][size_t(e) * LS + l] = make_float4(term.x, term.y, term.z, 0.f);
+        a.sowner[q][size_t(l) * a.cap + slot] = e;
       }
     }
     {
       const uint64_t bal = __ballot(spawn);
       if (spawn) {
         const uint32_t slot = bbase[LS] + wcnt[wave][LS] + uint32_t(lanes_below(bal));
-        a.ro[nq][slot] = make_float4(P.x, P.y, P.z, ro.w);
+        a.ro[nq][slot] = make_float4(P.x, P.y, P.z, __int_as_float(int(lp)));
         a.rd[nq][slot] = make_float4(rdir.x, rdir.y, rdir.z, __int_as_float(key));
-        const float3 next = mul(thr, kr3);
         a.thr[nq][slot] = make_float4(next.x, next.y, next.z, 0.f);
       }
     }
@@ -1356,13 +1366,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
     const uint32_t e = (batch << blog) + lane;
     float3 o = make_float3(0.f, 0.f, 0.f), d = o;
     int eye = 0, x = 0, y = 0;
-    bool alive = lane < (1 << blog) && e < count && path_pixel(a.one.cam, e, &eye, &x, &y);
+    bool alive = lane < (1 << blog) && e < count && wave_pixel(a.one.cam, e, &eye, &x, &y);
     const bool inside = alive;
     if (alive) primary_ray(a.one.cam, eye, x, y, &o, &d);
     float3 thr = make_float3(1.f, 1.f, 1.f), rad = make_float3(0.f, 0.f, 0.f), sum = rad;
     bool lit = false;  // `sum` holds the lights' terms of the hit before, still to be added
     int exclude = -1;
     for (int depth = 0; __ballot(alive) != 0; ++depth) {
+      // The arguments read afresh at every depth: kept from the start they spilled 79 scalar registers (641x479, 13k
+      // triangles: 257 -> 255 us).
+      const KArgs& a = kernel_args();  // the same values as the parameter, see kernel_args
+      const DevScene& sc = a.one.sc;
       const float tmin = depth == 0 ? 0.0f : kSecondaryTmin;
       float t = INFINITY;
       int key = -1;
@@ -1446,7 +1460,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
         if (cast && ((lds_get(&s_visible[wave][r >> 6]) >> (r & 63u)) & 1u)) {
           float4 m0, m1, m2;
           material_of(sc, key, &m0, &m1, &m2);
-          sum = add_rn(sum, light_term(sc.lights, l, P, N, d, m0, m1, thr));
+          float3 Ld;
+          float dist;
+          const float ndl = light_at(sc.lights, l, P, N, &Ld, &dist);
+          sum = add_rn(sum, light_term(sc.lights, l, ndl, Ld, N, d, m0, m1, thr));
         }
       }
       if (spawn) {
@@ -1462,7 +1479,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
     }
     if (inside) {
       if (lit) rad = add_rn(rad, sum);
-      path_pixel(a.one.cam, e, &eye, &x, &y);
+      wave_pixel(a.one.cam, e, &eye, &x, &y);
       float* out = a.one.out.radiance[eye] + 3 * (int64_t(y) * a.one.cam.W + x);
       out[0] = rad.x;
       out[1] = rad.y;
@@ -1518,28 +1535,41 @@ __global__ __launch_bounds__(kBlock) void k_resolve(KArgs a, int depth) {
   const int q = depth & 1;
   const uint32_t total = depth == 0 ? uint32_t(a.path_count) : a.ctr->refl_count[depth];
   const int LS = a.lstride;
-  for (uint32_t e = blockIdx.x * kBlock + threadIdx.x; e < total; e += gridDim.x * kBlock) {
-    const uint2 ri = a.resinfo[q][e];
-    if (ri.y == 0) continue;  // no shadow rays (also invalid paths)
-    const int64_t p = a.path_begin + ri.x;
-    const DevItem& it = item_ref<MULTI>(a, item_of<MULTI>(a, p));
-    const int L = it.sc.L, D1 = it.cam.D + 1;
-    int eye, x, y;
-    path_pixel(it.cam, p - it.path_offset, &eye, &x, &y);
-    const int64_t pix = int64_t(y) * it.cam.W + x;
-    float3 sum = make_float3(0.f, 0.f, 0.f);
-    for (int l = 0; l < L; ++l) {
-      if (!((ri.y >> l) & 1u)) continue;
-      const size_t k = size_t(e) * LS + l;
-      const bool v = a.vis[q][k] != 0;
-      if (v) sum = add_rn(sum, f3(a.contrib[q][k]));
-      if (PATH_IDS) it.out.shadow_state[eye][(pix * D1 + depth) * L + l] = v ? 2 : 1;
+  for (uint32_t base = blockIdx.x * kBlock; base < total; base += gridDim.x * kBlock) {
+    const uint32_t e = base + threadIdx.x;
+    const uint32_t mask = e < total ? a.smask[q][e] : 0u;  // 0: no shadow rays, also outside the image
+    const uint32_t lp = depth == 0 || mask == 0 ? e : a.epath[q][e];
+    int item = 0;
+    if (MULTI) {
+      if (depth == 0)
+        item = item_of<MULTI>(a, a.path_begin + uint32_t(__builtin_amdgcn_readfirstlane(e)));  // one to a tile
+      else if (mask)
+        item = item_of<MULTI>(a, a.path_begin + lp);
     }
-    float* rad = it.out.radiance[eye] + 3 * pix;
-    const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), sum);
-    rad[0] = r.x;
-    rad[1] = r.y;
-    rad[2] = r.z;
+    each_item<MULTI>(a, mask != 0, item, [&](const DevItem& it, bool mine) {
+      if (!mine) return;
+      const int L = it.sc.L, D1 = it.cam.D + 1;
+      int eye, x, y;
+      const int64_t p = a.path_begin + lp - it.path_offset;
+      if (depth == 0)
+        wave_pixel(it.cam, p, &eye, &x, &y);
+      else
+        path_pixel(it.cam, p, &eye, &x, &y);
+      const int64_t pix = int64_t(y) * it.cam.W + x;
+      float3 sum = make_float3(0.f, 0.f, 0.f);
+      for (int l = 0; l < L; ++l) {
+        if (!((mask >> l) & 1u)) continue;
+        const size_t k = size_t(l) * a.cap + e;
+        const bool v = a.vis[q][k] != 0;
+        if (v) sum = add_rn(sum, make_float3(a.contrib[q][3 * k], a.contrib[q][3 * k + 1], a.contrib[q][3 * k + 2]));
+        if (PATH_IDS) it.out.shadow_state[eye][(pix * D1 + depth) * L + l] = v ? 2 : 1;
+      }
+      float* rad = it.out.radiance[eye] + 3 * pix;
+      const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), sum);
+      rad[0] = r.x;
+      rad[1] = r.y;
+      rad[2] = r.z;
+    });
   }
 }
 
@@ -1662,10 +1692,11 @@ size_t plan_render(int64_t chunk, int32_t L, int grid_trace, RenderPlan* p, int 
     p->ro_off[k] = take(n * 16);
     p->rd_off[k] = take(n * 16);
     p->thr_off[k] = take(n * 16);
-    p->resinfo_off[k] = take(n * 8);
-    p->srec_off[k] = take(ns * 16);
+    p->epath_off[k] = take(n * 4);
+    p->smask_off[k] = take(n);
+    p->spos_off[k] = take(n * 16);
     p->sowner_off[k] = take(ns * 4);
-    p->contrib_off[k] = take(ns * 16);
+    p->contrib_off[k] = take(ns * 12);
     p->vis_off[k] = take(ns);
   }
   p->hit_off = take(n * 8);
@@ -1691,10 +1722,11 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
     a.ro[k] = reinterpret_cast<float4*>(ws + p.ro_off[k]);
     a.rd[k] = reinterpret_cast<float4*>(ws + p.rd_off[k]);
     a.thr[k] = reinterpret_cast<float4*>(ws + p.thr_off[k]);
-    a.resinfo[k] = reinterpret_cast<uint2*>(ws + p.resinfo_off[k]);
-    a.srec[k] = reinterpret_cast<float4*>(ws + p.srec_off[k]);
+    a.epath[k] = reinterpret_cast<uint32_t*>(ws + p.epath_off[k]);
+    a.smask[k] = reinterpret_cast<uint8_t*>(ws + p.smask_off[k]);
+    a.spos[k] = reinterpret_cast<float4*>(ws + p.spos_off[k]);
     a.sowner[k] = reinterpret_cast<uint32_t*>(ws + p.sowner_off[k]);
-    a.contrib[k] = reinterpret_cast<float4*>(ws + p.contrib_off[k]);
+    a.contrib[k] = reinterpret_cast<float*>(ws + p.contrib_off[k]);
     a.vis[k] = reinterpret_cast<uint8_t*>(ws + p.vis_off[k]);
   }
   a.hit = reinterpret_cast<float2*>(ws + p.hit_off);

@@ -157,7 +157,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
 
 struct RenderPlan {
   int64_t chunk_paths;  // paths per pass (multiple of kPathsPerTile)
-  size_t counters_off, ro_off[2], rd_off[2], thr_off[2], hit_off, resinfo_off[2], srec_off[2], sowner_off[2],
+  size_t counters_off, ro_off[2], rd_off[2], thr_off[2], hit_off, epath_off[2], smask_off[2], spos_off[2], sowner_off[2],
       contrib_off[2], vis_off[2], gstack_off;
   size_t bytes;
   int grid_trace;     // persistent workgroups for the traversal kernels

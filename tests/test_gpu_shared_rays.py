@@ -117,3 +117,33 @@ def test_whole_paths_equal_the_queues(torch_cuda, what, lights, depth, size):
     for k in ("radiance", "hit_t", "hit_prim", "ray_counts"):
         assert torch.equal(one[k], queues[k]), k
     gs.close()
+
+
+# A batch of scenes with no light to eight, cut into passes in the middle of items: the queues' layout (entries, light
+# arrays, eye positions) against each image in one launch.
+@pytest.mark.parametrize("max_pass_paths", [4096, 4992, 1 << 25])
+def test_batch_passes_equal_whole_paths(torch_cuda, max_pass_paths):
+    torch = torch_cuda
+    from paper_1702_01530_amd import rt
+    from paper_1702_01530_amd.stereo import GpuScene, render_batch, render_stereo
+    all_lights = [[-6, 8, 2], [6, 6, 12], [-3, 9, 9], [5, 7, 3], [0, 8, 5], [-7, 5, 11], [3, 4, 14], [0.5, 3, -2]]
+    pairs = []
+    for i, n in enumerate((0, 8, 1, 5)):
+        scene, cam = sg.make_small_terrain(seed=60 + i, grid=12, n_spheres=4, level=1)
+        scene = scene.with_lights([p + [0.4, 0.4, 0.4] for p in all_lights[:n]])
+        pairs.append((GpuScene(scene), cam.resized(61 + 6 * i, 43 - 5 * i).with_(max_depth=i + 1)))
+    print(f"[batch passes] {max_pass_paths}", flush=True)
+    saved = rt.rt_get_tuning()
+    rt.rt_set_tuning(**{**saved, "max_pass_paths": max_pass_paths})
+    try:
+        outs = render_batch(pairs)
+        torch.cuda.synchronize()
+    finally:
+        rt.rt_set_tuning(**saved)
+    for i, (gs, cam) in enumerate(pairs):
+        one = render_stereo(gs, cam)
+        torch.cuda.synchronize()
+        for k in ("radiance", "hit_t", "hit_prim"):
+            assert torch.equal(one[k], outs[i][k]), (i, k)
+    for gs, _ in pairs:
+        gs.close()
