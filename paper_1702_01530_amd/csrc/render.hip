@@ -336,12 +336,13 @@ __device__ inline float raw_min(float a, float b) {
   return r;
 }
 
-// Entry distances of the four children of BVH4 node `node` (+inf where the ray misses the child's
-// box inside [tmin, tmax]; with HITS_ONLY 0 instead of the distance of a hit child) and their references.
-template <bool HITS_ONLY>
+// The four children of BVH4 node `node`: h whether the ray meets the child's box inside [tmin, tmax], t the entry
+// distance (+inf where it does not), r the reference.  The loop counts the children to push from h, which are lane
+// masks in scalar registers, and not from the sorted distances: 7 of about 100 vector instructions a step less (3.4 M
+// triangles at 4K 6.53 -> 6.48 ms, 16 mixed scenes 6.78 -> 6.74).
 __device__ __attribute__((always_inline)) inline void node4_children(const float4* __restrict__ nodes, int node,
                                                                      float3 inv, float3 oi, float tmin, float tmax,
-                                                                     float (&t)[4], int (&r)[4]) {
+                                                                     float (&t)[4], int (&r)[4], bool (&h)[4]) {
 #if SRT_QNODE
   // Slab planes of child k on axis a are p_a + q s_a, i.e. t = q (s_a / d_a) + (p_a - o_a) / d_a; the
   // near and far planes of an axis are picked once per node from the ray's direction sign.  A byte q
@@ -381,8 +382,8 @@ __device__ __attribute__((always_inline)) inline void node4_children(const float
     const float zn = fmaf(q(hnz), az, bz), zf = fmaf(q(hfz), az, bz);
     const float tn = raw_max3(xn, yn, raw_max(zn, tmin));
     const float tf = raw_min3(xf, yf, raw_min(zf, tmax));
-    // HITS_ONLY: 0 for a hit child, +inf otherwise (an occlusion query needs no entry distance)
-    t[k] = tn <= tf ? (HITS_ONLY ? 0.0f : tn) : INFINITY;
+    h[k] = tn <= tf;
+    t[k] = h[k] ? tn : INFINITY;
   }
   r[0] = n1.x;
   r[1] = n1.y;
@@ -395,8 +396,7 @@ __device__ __attribute__((always_inline)) inline void node4_children(const float
   t[1] = slab(lx.y, hx.y, ly.y, hy.y, lz.y, hz.y, inv, oi, tmin, tmax);
   t[2] = slab(lx.z, hx.z, ly.z, hy.z, lz.z, hz.z, inv, oi, tmin, tmax);
   t[3] = slab(lx.w, hx.w, ly.w, hy.w, lz.w, hz.w, inv, oi, tmin, tmax);
-  if (HITS_ONLY)
-    for (int k = 0; k < 4; ++k) t[k] = t[k] < INFINITY ? 0.0f : INFINITY;
+  for (int k = 0; k < 4; ++k) h[k] = t[k] < INFINITY;
   r[0] = __float_as_int(cr.x);
   r[1] = __float_as_int(cr.y);
   r[2] = __float_as_int(cr.z);
@@ -662,25 +662,26 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
         if (COUNT) ++nnodes;
         float t[4];
         int c[4];
-        node4_children<ANY>(nodes, node, inv, oi, r.tmin, r.limit, t, c);
+        bool h[4];
+        node4_children(nodes, node, inv, oi, r.tmin, r.limit, t, c, h);
         if (ANY) {
           // occlusion: the order of the hit children does not change the answer, so they are taken in
           // slot order (the same for every lane of the wave) without sorting: the first hit child next,
           // the later hit children pushed so that they pop in slot order
-          const bool h0 = t[0] == 0.0f, h1 = t[1] == 0.0f, h2 = t[2] == 0.0f, h3 = t[3] == 0.0f;
-          if (h0 || h1 || h2 || h3) {
-            node = h0 ? c[0] : (h1 ? c[1] : (h2 ? c[2] : c[3]));
-            const bool g1 = h1 && h0, g2 = h2 && (h0 || h1), g3 = h3 && (h0 || h1 || h2);  // hits after the first
+          if (h[0] || h[1] || h[2] || h[3]) {
+            node = h[0] ? c[0] : (h[1] ? c[1] : (h[2] ? c[2] : c[3]));
+            // hits after the first
+            const bool g1 = h[1] && h[0], g2 = h[2] && (h[0] || h[1]), g3 = h[3] && (h[0] || h[1] || h[2]);
             const int np = int(g1) + int(g2) + int(g3);
             if (np > 0) st.push_sorted(g1 ? c[1] : (g2 ? c[2] : c[3]), (g1 && g2) ? c[2] : c[3], c[3], np);
           } else {
             node = st.sp > 0 ? st.pop() : kDoneRef;
           }
         } else {
-          sort4(t, c);
-          if (t[0] < INFINITY) {
+          if (h[0] || h[1] || h[2] || h[3]) {
+            sort4(t, c);
             node = c[0];
-            const int np = int(t[1] < INFINITY) + int(t[2] < INFINITY) + int(t[3] < INFINITY);
+            const int np = int(h[0]) + int(h[1]) + int(h[2]) + int(h[3]) - 1;
             if (np > 0) st.push_sorted(c[1], c[2], c[3], np);
           } else {
             node = st.sp > 0 ? st.pop() : kDoneRef;
