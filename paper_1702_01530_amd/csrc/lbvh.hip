@@ -961,13 +961,60 @@ __global__ __launch_bounds__(kBlock) void k_pack(PackArgs a) {
   pack_scene(a, int64_t(blockIdx.x) * kBlock + threadIdx.x, int64_t(gridDim.x) * kBlock);
 }
 
+// A workgroup's barrier for what passes through LDS.  __syncthreads also waits until memory has taken the
+// stores so far, which nothing in the launch reads back.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// v of another lane of the group of 2^(S + 1), of which each half holds one value throughout: with S = 0, 1, .. in turn
+// a reduction over groups of up to 32 lanes, without the address and the trip through LDS of a shuffle.
+template <int S>
+__device__ inline uint32_t other_half(uint32_t v) {
+  // pairs and quads exchanged, then mirrors of 8 and 16 lanes, then 16 lanes swapped
+  constexpr int kDpp[4] = {0xb1, 0x4e, 0x141, 0x140};
+  if (S < 4) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), kDpp[S & 3], 0xf, 0xf, false));
+  return uint32_t(__builtin_amdgcn_ds_swizzle(int(v), 0x401f));
+}
+template <int S>
+__device__ inline void nearer_half(float* best, int* bk) {
+  const float ob = __uint_as_float(other_half<S>(__float_as_uint(*best)));
+  const int ok = int(other_half<S>(uint32_t(*bk)));
+  if (ob < *best || (ob == *best && ok < *bk)) *best = ob, *bk = ok;
+}
+
+// Lane `sub` of the 2^LOG2 that share the search of position i: every 2^LOG2-th of its 2 R neighbours, in ascending
+// order, ties to the first.
+template <int LOG2>
+__device__ __attribute__((always_inline)) inline void search_share(const float4* lo, const float4* hi, int i, int sub,
+                                                                   float* best, int* bk) {
+  constexpr int R = kPlocRadius, kHalf = R >> LOG2;
+  auto f3 = [](float4 v) { return make_float3(v.x, v.y, v.z); };
+  const float3 alo = f3(lo[i]), ahi = f3(hi[i]);
+  auto half = [&](int first) {
+#pragma unroll 4
+    for (int k = 0; k < kHalf; ++k) {
+      const int d = first + (k << LOG2);
+      const float ar = merged_area_raw(alo, ahi, f3(lo[i + d]), f3(hi[i + d]));
+      if (ar < *best) *best = ar, *bk = d;
+    }
+  };
+  half(sub - R);
+  half(sub + 1);
+}
+
 // The remaining rounds of at most kPlocTail clusters, in one workgroup: a round costs a search whose 64
-// candidates are split over as many lanes as there are to spare, and three barriers (about 30 rounds, 116 us).
+// candidates are split over as many lanes as there are to spare, and three barriers.  It is bound by the search,
+// three quarters of the time (2.4 us a round of 30, the first rounds 10), with one CU's VALU: 20 instructions a
+// candidate and loads four candidates ahead.  10k triangles: 136 us with a bounds check and a wait a candidate, shuffles
+// through LDS and barriers that wait for stores, 115 this way.
 // The launch's other workgroups pack the triangles meanwhile (77 us as a launch of its own, for 3.4M).
 __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState* state, int slot, PlocNodes out,
                                                          PackArgs pack) {
   constexpr int R = kPlocRadius, kW = kPlocTail / 64;
-  __shared__ float4 s_lo[kPlocTail], s_hi[kPlocTail], s_ext[kPlocTail];
+  __shared__ float4 p_lo[kPlocTail + 2 * R], p_hi[kPlocTail + 2 * R], s_ext[kPlocTail];
   __shared__ int s_nn[kPlocTail];
   __shared__ uint32_t wkeep[kW], wmerge[kW];
   if (blockIdx.x > 0) {
@@ -977,6 +1024,10 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
   BuildState::Ploc st = state->ploc[slot];
   if (st.n > kPlocTail || st.n < 2) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // Boxes at +inf before the first cluster and after the last: any merge with them has an infinite area.
+  const float4 nowhere = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+  float4 *const s_lo = p_lo + R, *const s_hi = p_hi + R;
+  if (tid < R) p_lo[tid] = p_hi[tid] = s_lo[st.n + tid] = s_hi[st.n + tid] = nowhere;
   if (tid < int(st.n)) {
     s_lo[tid] = st.buf ? c.lo[1][tid] : c.lo[0][tid];
     s_hi[tid] = st.buf ? c.hi[1][tid] : c.hi[0][tid];
@@ -992,25 +1043,27 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
     float best = INFINITY;
     int bk = 0;
     if (i < n) {
-      const float4 alo = s_lo[i], ahi = s_hi[i];
-      const int first = max(-R, -i), last = min(R, n - 1 - i);
-      for (int k = first + sub; k <= last; k += lanes) {
-        const float ar = merged_area(alo, ahi, s_lo[i + k], s_hi[i + k]);
-        if (k != 0 && ar < best) best = ar, bk = k;
+      switch (log2l) {
+        case 0: search_share<0>(s_lo, s_hi, i, sub, &best, &bk); break;
+        case 1: search_share<1>(s_lo, s_hi, i, sub, &best, &bk); break;
+        case 2: search_share<2>(s_lo, s_hi, i, sub, &best, &bk); break;
+        case 3: search_share<3>(s_lo, s_hi, i, sub, &best, &bk); break;
+        case 4: search_share<4>(s_lo, s_hi, i, sub, &best, &bk); break;
+        default: search_share<5>(s_lo, s_hi, i, sub, &best, &bk); break;
       }
     }
-    for (int off = 1; off < lanes; off <<= 1) {
-      const float ob = __shfl_xor(best, off);
-      const int ok = __shfl_xor(bk, off);
-      if (ob < best || (ob == best && ok < bk)) best = ob, bk = ok;
-    }
+    if (log2l > 0) nearer_half<0>(&best, &bk);
+    if (log2l > 1) nearer_half<1>(&best, &bk);
+    if (log2l > 2) nearer_half<2>(&best, &bk);
+    if (log2l > 3) nearer_half<3>(&best, &bk);
+    if (log2l > 4) nearer_half<4>(&best, &bk);
     if (i < n && sub == 0) {
       if (!(best < INFINITY)) bk = i > 0 ? -1 : 1;
       const int p = i ^ 1;
       if (p < n && ploc_takes_parity(best, s_lo[i], s_hi[i], s_lo[p], s_hi[p])) bk = p - i;
       s_nn[i] = i + bk;
     }
-    __syncthreads();
+    lds_barrier();
     const int j = tid < n ? s_nn[tid] : -1;
     const bool mutual = tid < n && s_nn[j] == tid;
     const bool merge = mutual && j > tid, keep = tid < n && !(mutual && j < tid);
@@ -1019,7 +1072,7 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
     float4 lo, hi, ext, blo, bhi, bext;
     if (keep) lo = s_lo[tid], hi = s_hi[tid], ext = s_ext[tid];
     if (merge) blo = s_lo[j], bhi = s_hi[j], bext = s_ext[j];
-    __syncthreads();
+    lds_barrier();
     int kb = 0, mb = 0, mt = 0;
     for (int w = 0; w < kW; ++w) {
       const int x = int(wkeep[w]), y = int(wmerge[w]);
@@ -1040,7 +1093,8 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
       s_hi[pos] = hi;
       s_ext[pos] = ext;
     }
-    __syncthreads();
+    if (tid < R) s_lo[n + tid] = s_hi[n + tid] = nowhere;
+    lds_barrier();
   }
   if (tid == 0) {
     bad = bad || next != 0;
