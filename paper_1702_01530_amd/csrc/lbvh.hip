@@ -410,10 +410,10 @@ __device__ inline int delta(const uint64_t* __restrict__ k, int64_t n, int64_t i
   return 64 + __clz(uint32_t(i) ^ uint32_t(j));
 }
 
-// children[i] = (left, right) references, parents of internal nodes at parent[0..T-2],
+// made[i] = (left, right) references (and later the choice bits), parents of internal nodes at parent[0..T-2],
 // parents of leaves at parent[T-1 + leaf]; range[i] = (first, last) sorted leaf indices.
 __global__ __launch_bounds__(kBlock) void k_karras(const uint64_t* __restrict__ keys, int64_t n,
-                                                   int2* __restrict__ children, int32_t* __restrict__ parent,
+                                                   int4* __restrict__ made, int32_t* __restrict__ parent,
                                                    int2* __restrict__ range) {
   int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (i >= n - 1) return;
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kBlock) void k_karras(const uint64_t* __restrict__ 
   int64_t first = i < j ? i : j, last = i < j ? j : i;
   int left = (first == gamma) ? ~int(gamma) : int(gamma);           // leaf refs as ~index here
   int right = (last == gamma + 1) ? ~int(gamma + 1) : int(gamma + 1);
-  children[i] = make_int2(left, right);
+  made[i] = make_int4(left, right, 0, 0);
   range[i] = make_int2(int(first), int(last));
   if (gamma < 0 || gamma + 1 >= n) return;  // cannot happen for a valid split; never write out of bounds
   if (left < 0) parent[n - 1 + ~left] = int(i); else parent[left] = int(i);
@@ -453,6 +453,12 @@ __device__ inline float half_area(float4 lo, float4 hi) {
 #ifndef SRT_DP_TRI_COST
 #define SRT_DP_TRI_COST 0.5f
 #endif
+// The cost of a leaf, rounded by itself
+__device__ inline float leaf_cost(float4 lo, float4 hi) {
+#pragma clang fp contract(off)
+  return SRT_DP_TRI_COST * half_area(lo, hi);
+}
+
 // Cost-optimal cut of the binary tree into the 4-wide tree (surface-area model, as in Ylitie et al.
 // 2017): C(n, j) is the least expected cost of binary subtree n when it may take j slots of its BVH4
 // parent.  C(n, 1) = A(n) + D_n(4) (n becomes a BVH4 node whose four slots its two children share),
@@ -464,7 +470,7 @@ __device__ inline void dp_child_costs(int r, const float4* dp_cost, const float4
                                       const uint32_t* sorted_ids, float (&c)[4]) {
   if (r < 0) {
     const uint32_t id = sorted_ids[~r];
-    const float a = SRT_DP_TRI_COST * half_area(leaf_lo[id], leaf_hi[id]);
+    const float a = leaf_cost(leaf_lo[id], leaf_hi[id]);
     c[0] = c[1] = c[2] = c[3] = a;
   } else {
     const float4 v = dp_cost[r];
@@ -495,23 +501,22 @@ __device__ inline float4 dp_costs(float area, const float (&ca)[4], const float 
 }
 
 // Fills the cost table entry of binary node n, whose box and children's entries are final.
-__device__ inline void dp_node(int64_t n, const int2* children, const float4* nodebox, const float4* leaf_lo,
-                               const float4* leaf_hi, const uint32_t* sorted_ids, float4* dp_cost,
-                               uint32_t* dp_choice) {
-  const int2 ch = children[n];
+__device__ inline void dp_node(int64_t n, int4* made, const float4* nodebox, const float4* leaf_lo,
+                               const float4* leaf_hi, const uint32_t* sorted_ids, float4* dp_cost) {
+  const int4 ch = made[n];
   float ca[4], cb[4];
   dp_child_costs(ch.x, dp_cost, leaf_lo, leaf_hi, sorted_ids, ca);
   dp_child_costs(ch.y, dp_cost, leaf_lo, leaf_hi, sorted_ids, cb);
-  dp_cost[n] = dp_costs(half_area(nodebox[2 * n], nodebox[2 * n + 1]), ca, cb, &dp_choice[n]);
+  uint32_t choice;
+  dp_cost[n] = dp_costs(half_area(nodebox[2 * n], nodebox[2 * n + 1]), ca, cb, &choice);
+  made[n].z = int(choice);
 }
 
-__global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ children,
-                                                  const int32_t* __restrict__ parent,
+__global__ __launch_bounds__(kBlock) void k_refit(int4* made, const int32_t* __restrict__ parent,
                                                   const float4* __restrict__ leaf_lo, const float4* __restrict__ leaf_hi,
                                                   const uint32_t* __restrict__ sorted_ids, float4* nodebox,
                                                   uint32_t* flags, int64_t n, int32_t* __restrict__ max_depth,
-                                                  uint32_t* __restrict__ status, float4* dp_cost,
-                                                  uint32_t* dp_choice) {
+                                                  uint32_t* __restrict__ status, float4* dp_cost) {
   int64_t leaf = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (leaf >= n) return;
   int node = parent[n - 1 + leaf];
@@ -523,7 +528,7 @@ __global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ child
     }
     uint32_t old = __hip_atomic_fetch_add(&flags[node], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     if (old == 0) break;  // the sibling subtree is still being built; its thread climbs on
-    int2 ch = children[node];
+    const int4 ch = made[node];
     float4 lo[2], hi[2];
     int c[2] = {ch.x, ch.y};
 #pragma unroll
@@ -540,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void k_refit(const int2* __restrict__ child
     nodebox[2 * node] = make_float4(fminf(lo[0].x, lo[1].x), fminf(lo[0].y, lo[1].y), fminf(lo[0].z, lo[1].z), 0.f);
     nodebox[2 * node + 1] =
         make_float4(fmaxf(hi[0].x, hi[1].x), fmaxf(hi[0].y, hi[1].y), fmaxf(hi[0].z, hi[1].z), 0.f);
-    dp_node(node, children, nodebox, leaf_lo, leaf_hi, sorted_ids, dp_cost, dp_choice);
+    dp_node(node, made, nodebox, leaf_lo, leaf_hi, sorted_ids, dp_cost);
     if (node == 0) break;
     node = parent[node];
   }
@@ -604,12 +609,21 @@ struct BuildState {
 };
 static_assert(sizeof(BuildState) <= 256, "the plan sets 256 bytes aside");
 
-// Clusters in struct-of-arrays form: box corners with C(1) and C(2) beside them, then (C(3), C(4), reference).
+// Clusters: the corners of the box, the reference (node, or ~position of a leaf) beside the lower one.  Buffer 0 holds
+// the leaves and is kept: the collapse reads their boxes from it in leaf order.  The rounds write buffers 1 and 2 in
+// turn.  What a cluster costs lies with its node and a leaf's follows from its box, so a round moves 32 bytes a cluster
+// (with the costs carried along it was 48; 3.4M triangles, all rounds: 463 us of compaction then, 396 now).
 struct Clusters {
-  float4* lo[2];
-  float4* hi[2];
-  float4* ext[2];
+  float4 *lo0, *lo1, *lo2, *hi0, *hi1, *hi2;
 };
+__device__ inline float4* buffer_of(uint32_t buf, float4* b0, float4* b1, float4* b2) {
+  float4* b = b0;
+  if (buf == 1) b = b1;
+  if (buf == 2) b = b2;
+  return b;
+}
+__device__ inline float4* lo_of(const Clusters& c, uint32_t buf) { return buffer_of(buf, c.lo0, c.lo1, c.lo2); }
+__device__ inline float4* hi_of(const Clusters& c, uint32_t buf) { return buffer_of(buf, c.hi0, c.hi1, c.hi2); }
 
 __global__ __launch_bounds__(kBlock) void k_ploc_init(const uint32_t* __restrict__ sorted_ids,
                                                       const float4* __restrict__ leaf_lo,
@@ -618,10 +632,8 @@ __global__ __launch_bounds__(kBlock) void k_ploc_init(const uint32_t* __restrict
   if (i >= n) return;
   const uint32_t id = sorted_ids[i];
   const float4 lo = leaf_lo[id], hi = leaf_hi[id];
-  const float cost = SRT_DP_TRI_COST * half_area(lo, hi);
-  c.lo[0][i] = make_float4(lo.x, lo.y, lo.z, cost);
-  c.hi[0][i] = make_float4(hi.x, hi.y, hi.z, cost);
-  c.ext[0][i] = make_float4(cost, cost, __int_as_float(~int(i)), 0.f);
+  c.lo0[i] = make_float4(lo.x, lo.y, lo.z, __int_as_float(~int(i)));
+  c.hi0[i] = make_float4(hi.x, hi.y, hi.z, 0.f);
 }
 
 constexpr int kPlocBlock = 512;    // threads of a search block ...
@@ -663,8 +675,7 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* 
   __shared__ uint32_t tmp[kPlocBlock / 64];
   const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
   if (n <= kPlocTail) return;
-  const float4* __restrict__ lo = buf ? c.lo[1] : c.lo[0];
-  const float4* __restrict__ hi = buf ? c.hi[1] : c.hi[0];
+  const float4 *__restrict__ lo = lo_of(c, buf), *__restrict__ hi = hi_of(c, buf);
   uint32_t begin, end, merges = 0, absorbed = 0;
   ploc_range(n, kOwn, blockIdx.x, gridDim.x, &begin, &end);
   const int p = threadIdx.x / LANES, sub = threadIdx.x % LANES;
@@ -760,8 +771,7 @@ __global__ __launch_bounds__(kPairBlock) void k_ploc_nn_pairs(Clusters c, BuildS
   __shared__ uint32_t tmp[kPairBlock / 64];
   const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
   if (n <= kPlocTail) return;
-  const float4* __restrict__ lo = buf ? c.lo[1] : c.lo[0];
-  const float4* __restrict__ hi = buf ? c.hi[1] : c.hi[0];
+  const float4 *__restrict__ lo = lo_of(c, buf), *__restrict__ hi = hi_of(c, buf);
   uint32_t begin, end, merges = 0, absorbed = 0;
   ploc_range(n, kPairOwn, blockIdx.x, gridDim.x, &begin, &end);
   const int q = threadIdx.x;
@@ -844,89 +854,114 @@ __global__ __launch_bounds__(kPairBlock) void k_ploc_nn_pairs(Clusters c, BuildS
 }
 
 struct PlocNodes {
-  int2* children;
+  int4* made;      // (children, choice bits, 0)
   float4* nodebox;
-  uint32_t* dp_choice;
+  float4* cost;    // C(1..4)
 };
 
-// Merges clusters a (lower position) and b into node `node`.
-__device__ inline void ploc_merge(const PlocNodes& out, int node, float4 alo, float4 ahi, float4 aext, float4 blo,
-                                  float4 bhi, float4 bext, float4* lo, float4* hi, float4* ext) {
+__device__ inline float4 ploc_cost(const PlocNodes& out, float4 lo, float4 hi) {
+  const int ref = __float_as_int(lo.w);
+  if (ref >= 0) return out.cost[ref];
+  const float c = leaf_cost(lo, hi);
+  return make_float4(c, c, c, c);
+}
+
+// Merges clusters a (lower position) and b, which cost ca and cb, into node `node`.
+__device__ inline float4 ploc_merge(const PlocNodes& out, int node, float4 alo, float4 ahi, float4 ca4, float4 blo,
+                                    float4 bhi, float4 cb4, float4* lo, float4* hi) {
   const float4 ulo = make_float4(fminf(alo.x, blo.x), fminf(alo.y, blo.y), fminf(alo.z, blo.z), 0.f);
   const float4 uhi = make_float4(fmaxf(ahi.x, bhi.x), fmaxf(ahi.y, bhi.y), fmaxf(ahi.z, bhi.z), 0.f);
-  const float ca[4] = {alo.w, ahi.w, aext.x, aext.y}, cb[4] = {blo.w, bhi.w, bext.x, bext.y};
+  const float ca[4] = {ca4.x, ca4.y, ca4.z, ca4.w}, cb[4] = {cb4.x, cb4.y, cb4.z, cb4.w};
   uint32_t choice;
   const float4 cost = dp_costs(half_area(ulo, uhi), ca, cb, &choice);
-  out.children[node] = make_int2(__float_as_int(aext.z), __float_as_int(bext.z));
+  out.made[node] = make_int4(__float_as_int(alo.w), __float_as_int(blo.w), int(choice), 0);
   out.nodebox[2 * int64_t(node)] = ulo;
   out.nodebox[2 * int64_t(node) + 1] = uhi;
-  out.dp_choice[node] = choice;
-  *lo = make_float4(ulo.x, ulo.y, ulo.z, cost.x);
-  *hi = make_float4(uhi.x, uhi.y, uhi.z, cost.y);
-  *ext = make_float4(cost.z, cost.w, __int_as_float(node), 0.f);
+  *lo = make_float4(ulo.x, ulo.y, ulo.z, __int_as_float(node));
+  *hi = uhi;
+  return cost;
 }
 
 // Makes the round's nodes and compacts the survivors into the other buffer.  `own` and the grid are those of
-// the round's search, whose counts place each block's output.
+// the round's search, whose counts place each block's output.  A tile's loads are issued before the tile ahead of it
+// is stored, and the first tile's before the counts are summed: a round is a chain of such waits.
 __global__ __launch_bounds__(kBlock) void k_ploc_compact(Clusters c, BuildState* state, int slot,
                                                          const int32_t* __restrict__ partner,
                                                          const uint2* __restrict__ counts, uint32_t own,
                                                          PlocNodes out) {
-  __shared__ uint32_t tmp[kBlock / 64];
-  __shared__ uint32_t wkeep[2][kBlock / 64], wmerge[2][kBlock / 64];
+  constexpr int kW = kBlock / 64;
+  __shared__ uint4 wsum[kW];
+  __shared__ uint32_t wkeep[2][kW], wmerge[2][kW];
   const BuildState::Ploc st = state->ploc[slot];
   BuildState::Ploc* next = &state->ploc[slot ^ 1];
   if (st.n <= kPlocTail) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *next = st;
     return;
   }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t dst = st.buf == 1 ? 2u : 1u;
+  const float4 *ilo = lo_of(c, st.buf), *ihi = hi_of(c, st.buf);
+  float4 *olo = lo_of(c, dst), *ohi = hi_of(c, dst);
   uint32_t begin, end;
   ploc_range(st.n, own, blockIdx.x, gridDim.x, &begin, &end);
-  uint32_t m0 = 0, a0 = 0, mall = 0, aall = 0;
+  int32_t j = -1;
+  float4 lo, hi;
+  auto fetch = [&](uint32_t i) {
+    j = -1;
+    if (i < end) j = partner[i], lo = ilo[i], hi = ihi[i];
+  };
+  fetch(begin + threadIdx.x);
+  uint4 sum = make_uint4(0u, 0u, 0u, 0u);  // merges and absorbed clusters, of the blocks before and of all
   for (uint32_t k = threadIdx.x; k < gridDim.x; k += kBlock) {
     const uint2 v = counts[k];
-    mall += v.x, aall += v.y;
-    if (k < blockIdx.x) m0 += v.x, a0 += v.y;
+    sum.z += v.x, sum.w += v.y;
+    if (k < blockIdx.x) sum.x += v.x, sum.y += v.y;
   }
-  m0 = block_sum(m0, tmp), a0 = block_sum(a0, tmp), mall = block_sum(mall, tmp), aall = block_sum(aall, tmp);
+  for (int off = 32; off > 0; off >>= 1) {
+    sum.x += __shfl_xor(sum.x, off), sum.y += __shfl_xor(sum.y, off);
+    sum.z += __shfl_xor(sum.z, off), sum.w += __shfl_xor(sum.w, off);
+  }
+  if (lane == 0) wsum[wave] = sum;
+  __syncthreads();
+  uint32_t m0 = 0, a0 = 0, mall = 0, aall = 0;
+  for (int w = 0; w < kW; ++w) m0 += wsum[w].x, a0 += wsum[w].y, mall += wsum[w].z, aall += wsum[w].w;
   // every round merges a pair, each pair absorbs one cluster, and T - 1 nodes are made in all
   const bool bad = mall == 0 || mall != aall || mall > st.next;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (bad) atomicOr(&state->error, 1u);
-    *next = BuildState::Ploc{bad ? 0u : st.n - mall, bad ? 0u : st.next - mall, st.buf ^ 1u, 0u};
+    *next = BuildState::Ploc{bad ? 0u : st.n - mall, bad ? 0u : st.next - mall, dst, 0u};
   }
   if (bad) return;
-  const int src = int(st.buf), dst = src ^ 1;
-  const float4 *ilo = src ? c.lo[1] : c.lo[0], *ihi = src ? c.hi[1] : c.hi[0], *iext = src ? c.ext[1] : c.ext[0];
-  float4 *olo = dst ? c.lo[1] : c.lo[0], *ohi = dst ? c.hi[1] : c.hi[0], *oext = dst ? c.ext[1] : c.ext[0];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t pos0 = begin - a0, node0 = st.next - mall + m0;
   int par = 0;
   for (uint32_t base = begin; base < end; base += kBlock, par ^= 1) {
     const uint32_t i = base + threadIdx.x;
-    const bool valid = i < end;
-    const int32_t j = valid ? partner[i] : -1;
-    const bool merge = valid && j > int32_t(i), keep = valid && (j < 0 || merge);
+    const bool merge = j > int32_t(i), keep = i < end && (j < 0 || merge);
     const uint64_t bk = __ballot(keep), bm = __ballot(merge);
     if (lane == 0) wkeep[par][wave] = uint32_t(__popcll(bk)), wmerge[par][wave] = uint32_t(__popcll(bm));
+    float4 tlo = lo, thi = hi, blo, bhi, ca, cb;
+    if (merge) {
+      blo = ilo[j], bhi = ihi[j];
+      ca = ploc_cost(out, tlo, thi);
+      cb = ploc_cost(out, blo, bhi);
+    }
+    fetch(i + kBlock);
     __syncthreads();
     uint32_t kb = 0, mb = 0, kt = 0, mt = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
+    for (int w = 0; w < kW; ++w) {
       const uint32_t x = wkeep[par][w], y = wmerge[par][w];
       if (w < wave) kb += x, mb += y;
       kt += x, mt += y;
     }
     const uint64_t lt = lanemask_lt();
-    const uint32_t pos = pos0 + kb + uint32_t(__popcll(bk & lt));
+    if (merge) {
+      const uint32_t node = node0 + mb + uint32_t(__popcll(bm & lt));
+      out.cost[node] = ploc_merge(out, int(node), tlo, thi, ca, blo, bhi, cb, &tlo, &thi);
+    }
     if (keep) {
-      float4 lo = ilo[i], hi = ihi[i], ext = iext[i];
-      if (merge) {
-        const uint32_t node = node0 + mb + uint32_t(__popcll(bm & lt));
-        ploc_merge(out, int(node), lo, hi, ext, ilo[j], ihi[j], iext[j], &lo, &hi, &ext);
-      }
-      olo[pos] = lo;
-      ohi[pos] = hi;
-      oext[pos] = ext;
+      const uint32_t pos = pos0 + kb + uint32_t(__popcll(bk & lt));
+      olo[pos] = tlo;
+      ohi[pos] = thi;
     }
     pos0 += kt;
     node0 += mt;
@@ -1014,7 +1049,7 @@ __device__ __attribute__((always_inline)) inline void search_share(const float4*
 __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState* state, int slot, PlocNodes out,
                                                          PackArgs pack) {
   constexpr int R = kPlocRadius, kW = kPlocTail / 64;
-  __shared__ float4 p_lo[kPlocTail + 2 * R], p_hi[kPlocTail + 2 * R], s_ext[kPlocTail];
+  __shared__ float4 p_lo[kPlocTail + 2 * R], p_hi[kPlocTail + 2 * R], s_cost[kPlocTail];
   __shared__ int s_nn[kPlocTail];
   __shared__ uint32_t wkeep[kW], wmerge[kW];
   if (blockIdx.x > 0) {
@@ -1029,9 +1064,10 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
   float4 *const s_lo = p_lo + R, *const s_hi = p_hi + R;
   if (tid < R) p_lo[tid] = p_hi[tid] = s_lo[st.n + tid] = s_hi[st.n + tid] = nowhere;
   if (tid < int(st.n)) {
-    s_lo[tid] = st.buf ? c.lo[1][tid] : c.lo[0][tid];
-    s_hi[tid] = st.buf ? c.hi[1][tid] : c.hi[0][tid];
-    s_ext[tid] = st.buf ? c.ext[1][tid] : c.ext[0][tid];
+    const float4 lo = lo_of(c, st.buf)[tid], hi = hi_of(c, st.buf)[tid];
+    s_lo[tid] = lo;
+    s_hi[tid] = hi;
+    s_cost[tid] = ploc_cost(out, lo, hi);
   }
   __syncthreads();
   bool bad = false;
@@ -1069,9 +1105,9 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
     const bool merge = mutual && j > tid, keep = tid < n && !(mutual && j < tid);
     const uint64_t bkeep = __ballot(keep), bmerge = __ballot(merge);
     if (lane == 0) wkeep[wave] = uint32_t(__popcll(bkeep)), wmerge[wave] = uint32_t(__popcll(bmerge));
-    float4 lo, hi, ext, blo, bhi, bext;
-    if (keep) lo = s_lo[tid], hi = s_hi[tid], ext = s_ext[tid];
-    if (merge) blo = s_lo[j], bhi = s_hi[j], bext = s_ext[j];
+    float4 lo, hi, cost, blo, bhi, bcost;
+    if (keep) lo = s_lo[tid], hi = s_hi[tid], cost = s_cost[tid];
+    if (merge) blo = s_lo[j], bhi = s_hi[j], bcost = s_cost[j];
     lds_barrier();
     int kb = 0, mb = 0, mt = 0;
     for (int w = 0; w < kW; ++w) {
@@ -1086,12 +1122,12 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
     next -= mt;
     n -= mt;
     const uint64_t lt = lanemask_lt();
-    if (merge) ploc_merge(out, next + mb + __popcll(bmerge & lt), lo, hi, ext, blo, bhi, bext, &lo, &hi, &ext);
+    if (merge) cost = ploc_merge(out, next + mb + __popcll(bmerge & lt), lo, hi, cost, blo, bhi, bcost, &lo, &hi);
     if (keep) {
       const int pos = kb + __popcll(bkeep & lt);
       s_lo[pos] = lo;
       s_hi[pos] = hi;
-      s_ext[pos] = ext;
+      s_cost[pos] = cost;
     }
     if (tid < R) s_lo[n + tid] = s_hi[n + tid] = nowhere;
     lds_barrier();
@@ -1117,12 +1153,11 @@ constexpr int kWideBlocks = 1024;  // most blocks of a level: each sums the othe
 constexpr int kWideTail = 1024;    // a level of at most this many nodes is done by the one-workgroup kernel
 
 struct WideArgs {
-  const int2* children;
+  const int4* made;           // per binary node: children and the cost-optimal cut
   const float4* nodebox;
   const float4* leaf_lo;
   const float4* leaf_hi;
-  const uint32_t* sorted_ids;
-  const uint32_t* dp_choice;  // per binary node: the cost-optimal cut
+  const uint32_t* sorted_ids; // null: the leaf boxes are in leaf order
   int2* frontier[2];          // (binary node, BVH4 index) of level l's nodes in frontier[l & 1]
   int4* sel;                  // chosen binary-tree references per frontier item
   uint32_t* counts;           // internal children of a block's items
@@ -1134,37 +1169,50 @@ struct WideArgs {
 // The up to four binary-tree references that BVH4 node of binary node `bin` holds; returns how many are
 // internal.
 __device__ inline uint32_t wide_select(const WideArgs& a, int bin, int (&out)[4]) {
-  const int2 ch = a.children[bin];
+  const int4 ch = a.made[bin];
   int r[4] = {ch.x, ch.y, kWideEmpty, kWideEmpty};
   int cnt = 2;
   // follow the cost-optimal cut: the node's four slots split k : 4 - k between its children, and a
   // child with j > 1 slots is opened when that is cheaper
-  int js[4] = {int((a.dp_choice[bin] >> 6) & 3u), 0, 0, 0};
+  int js[4] = {int((uint32_t(ch.z) >> 6) & 3u), 0, 0, 0};
   js[1] = 4 - js[0];
+  // (children, choice bits) of a reference that has slots to open into, read when it gets them: the reads of both
+  // children overlap, and an opened one's children are there already
+  auto record = [&](int ref, int slots) {
+    return ref >= 0 && slots > 1 ? a.made[ref] : make_int4(0, 0, 0, 0);
+  };
+  int4 m[4] = {record(r[0], js[0]), record(r[1], js[1]), make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)};
   for (int step = 0; step < 2; ++step) {
     int p = -1;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (p < 0 && k < cnt && r[k] >= 0 && js[k] > 1 && ((a.dp_choice[r[k]] >> (3 * (js[k] - 2) + 2)) & 1u)) p = k;
+      if (p < 0 && k < cnt && r[k] >= 0 && js[k] > 1 && ((uint32_t(m[k].z) >> (3 * (js[k] - 2) + 2)) & 1u)) p = k;
     if (p < 0) break;
-    const int2 c = a.children[r[p]];
-    const int kk = int((a.dp_choice[r[p]] >> (3 * (js[p] - 2))) & 3u);
-    const int jj = js[p];
+    int4 c = m[0];
+    int jj = js[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k)
+      if (k == p) c = m[k], jj = js[k];
+    const int kk = int((uint32_t(c.z) >> (3 * (jj - 2))) & 3u);
+    const int4 mx = step == 0 ? record(c.x, kk) : c, my = step == 0 ? record(c.y, jj - kk) : c;
 #pragma unroll
     for (int k = 3; k > 0; --k)
       if (k > p + 1 && k <= cnt) {
         r[k] = r[k - 1];
         js[k] = js[k - 1];
+        m[k] = m[k - 1];
       }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (k == p) {
         r[k] = c.x;
         js[k] = kk;
+        m[k] = mx;
       }
       if (k == p + 1) {
         r[k] = c.y;
         js[k] = jj - kk;
+        m[k] = my;
       }
     }
     ++cnt;
@@ -1210,7 +1258,7 @@ __device__ inline void wide_emit(const WideArgs& a, float p, int b4, const int (
       h = l;
       ref[k] = 0;
     } else if (r[k] < 0) {
-      const uint32_t id = a.sorted_ids[~r[k]];
+      const uint32_t id = a.sorted_ids ? a.sorted_ids[~r[k]] : uint32_t(~r[k]);
       l = a.leaf_lo[id];
       h = a.leaf_hi[id];
       l = make_float4(l.x - p, l.y - p, l.z - p, 0.f);
@@ -1480,18 +1528,17 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
     p.ids0_off = take(size_t(T) * 4);
     p.ids1_off = take(size_t(T) * 4);
     p.hist_off = take(size_t(p.num_sort_blocks) * kRadix * 4);
-    p.children_off = take(size_t(T) * 8);
+    p.made_off = take(size_t(T) * 16);
     p.nodebox_off = take(size_t(T) * 32);
     if (!ploc) {
       p.range_off = take(size_t(T) * 8);
       p.parent_off = take(size_t(2 * T) * 4);
       p.flags_off = take(size_t(T) * 4);
     }
-    if (!ploc) p.dp_cost_off = take(size_t(T) * 16);
-    p.dp_choice_off = take(size_t(T) * 4);
     p.frontier_off[0] = take(size_t(T) * 8);
     p.frontier_off[1] = take(size_t(T) * 8);
     p.sel_off = take(size_t(T) * 16);
+    p.dp_cost_off = p.sel_off;  // the costs are of no use to the collapse
     p.digit_totals_off = take(size_t(kRadix) * 4);
     p.counts_off = take(size_t(std::max(kPlocBlocks, kWideBlocks)) * 8);
     if (ploc) {
@@ -1499,8 +1546,6 @@ BuildPlan plan_build(int64_t T, int64_t S, int64_t P, int64_t M, int64_t L, bool
         p.ploc_lo_off[k] = take(size_t(T) * 16);
         p.ploc_hi_off[k] = take(size_t(T) * 16);
       }
-      p.ploc_ext_off[0] = p.sel_off;  // free until the collapse
-      p.ploc_ext_off[1] = take(size_t(T) * 16);
       p.ploc_partner_off = take(size_t(T) * 4);
     }
   }
@@ -1612,16 +1657,16 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       const size_t zero_from = plan.nodes_off + size_t((T - 1) / 3) * kNodeBytes;
       pack.nodes = reinterpret_cast<float4*>(storage + zero_from);
       pack.node_float4 = int64_t((plan.tris_off - zero_from) / 16);
-      int2* children = reinterpret_cast<int2*>(scratch + plan.children_off);
+      int4* tree = reinterpret_cast<int4*>(scratch + plan.made_off);
       int2* range = reinterpret_cast<int2*>(scratch + plan.range_off);
       int32_t* parent = reinterpret_cast<int32_t*>(scratch + plan.parent_off);
       uint32_t* flags = reinterpret_cast<uint32_t*>(scratch + plan.flags_off);
       float4* nodebox = reinterpret_cast<float4*>(scratch + plan.nodebox_off);
-      uint32_t* dp_choice = reinterpret_cast<uint32_t*>(scratch + plan.dp_choice_off);
+      float4* dp_cost = reinterpret_cast<float4*>(scratch + plan.dp_cost_off);
       uint2* counts = reinterpret_cast<uint2*>(scratch + plan.counts_off);
       Clusters cl{};
       int32_t* partner = nullptr;
-      const PlocNodes made{children, nodebox, dp_choice};
+      const PlocNodes made{tree, nodebox, dp_cost};
       bool packed = false;
       int round = 0;
       double expected = double(T);  // clusters left, were every round to leave the usual share
@@ -1648,11 +1693,12 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         return hipGetLastError();
       };
       if (plan.ploc) {
-        for (int k = 0; k < 2; ++k) {
-          cl.lo[k] = reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[k]);
-          cl.hi[k] = reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[k]);
-          cl.ext[k] = reinterpret_cast<float4*>(scratch + plan.ploc_ext_off[k]);
-        }
+        cl.lo0 = reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[0]);
+        cl.hi0 = reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[0]);
+        cl.lo1 = reinterpret_cast<float4*>(scratch + plan.ploc_lo_off[1]);
+        cl.hi1 = reinterpret_cast<float4*>(scratch + plan.ploc_hi_off[1]);
+        cl.lo2 = lo;  // the boxes in input order, free once the leaves are in theirs
+        cl.hi2 = hi;
         partner = reinterpret_cast<int32_t*>(scratch + plan.ploc_partner_off);
         k_ploc_init<<<blocks_for(T), kBlock, 0, stream>>>(i0, lo, hi, T, cl);
         SRT_LAUNCH_CHECK();
@@ -1660,22 +1706,20 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       } else {
         k_pack<<<blocks_for(T), kBlock, 0, stream>>>(pack);
         SRT_LAUNCH_CHECK();
-        float4* dp_cost = reinterpret_cast<float4*>(scratch + plan.dp_cost_off);
-        k_karras<<<blocks_for(T - 1), kBlock, 0, stream>>>(k0, T, children, parent, range);
+        k_karras<<<blocks_for(T - 1), kBlock, 0, stream>>>(k0, T, tree, parent, range);
         SRT_LAUNCH_CHECK();
         k_fill<uint32_t><<<blocks_for(T - 1), kBlock, 0, stream>>>(flags, 0u, T - 1);
         SRT_LAUNCH_CHECK();
-        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(children, parent, lo, hi, i0, nodebox, flags, T,
-                                                      &state->max_depth, status, dp_cost, dp_choice);
+        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(tree, parent, lo, hi, i0, nodebox, flags, T,
+                                                      &state->max_depth, status, dp_cost);
         SRT_LAUNCH_CHECK();
       }
       WideArgs wa{};
-      wa.children = children;
+      wa.made = tree;
       wa.nodebox = nodebox;
-      wa.leaf_lo = lo;
-      wa.leaf_hi = hi;
-      wa.sorted_ids = i0;
-      wa.dp_choice = dp_choice;
+      wa.leaf_lo = plan.ploc ? cl.lo0 : lo;
+      wa.leaf_hi = plan.ploc ? cl.hi0 : hi;
+      wa.sorted_ids = plan.ploc ? nullptr : i0;
       wa.sel = reinterpret_cast<int4*>(scratch + plan.sel_off);
       wa.counts = reinterpret_cast<uint32_t*>(counts);
       wa.nodes = reinterpret_cast<float4*>(storage + plan.nodes_off);

@@ -127,10 +127,10 @@ struct BuildPlan {
   size_t nodes_off, tris_off, spheres_off, sphere_mat_off, planes_off, plane_mat_off, mats_off, lights_off;
   size_t storage_bytes;
   // scratch
-  size_t keys0_off, keys1_off, ids0_off, ids1_off, lo_off, hi_off, partial_off, hist_off, children_off,
+  size_t keys0_off, keys1_off, ids0_off, ids1_off, lo_off, hi_off, partial_off, hist_off, made_off,
       parent_off, flags_off, nodebox_off, status_off, range_off, frontier_off[2], sel_off, counts_off;
-  size_t ploc_lo_off[2], ploc_hi_off[2], ploc_ext_off[2], ploc_partner_off;
-  size_t dp_cost_off, dp_choice_off;
+  size_t ploc_lo_off[2], ploc_hi_off[2], ploc_partner_off;
+  size_t dp_cost_off;
   size_t digit_totals_off;
   size_t scratch_bytes;
   int64_t num_blocks_prep, num_sort_blocks;
