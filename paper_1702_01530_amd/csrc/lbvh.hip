@@ -662,6 +662,49 @@ __device__ inline uint32_t block_sum(uint32_t v, uint32_t* tmp) {
   return t;
 }
 
+// max and min without the instructions that quiet a signalling NaN first (12 of 87 in the search's loop; boxes of
+// accepted input hold no NaN, and those of refused input are only ever written to the scratch).
+__device__ inline float raw_max(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ inline float raw_min(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// merged_area for two boxes known to be no NaN
+__device__ inline float merged_area_raw(float3 alo, float3 ahi, float3 blo, float3 bhi) {
+  return half_area_of(raw_max(ahi.x, bhi.x) - raw_min(alo.x, blo.x), raw_max(ahi.y, bhi.y) - raw_min(alo.y, blo.y),
+                      raw_max(ahi.z, bhi.z) - raw_min(alo.z, blo.z));
+}
+
+// v of another lane of the group of 2^(S + 1), of which each half holds one value throughout: with S = 0, 1, .. in turn
+// a reduction over groups of up to 32 lanes, without the address and the trip through LDS of a shuffle.
+template <int S>
+__device__ inline uint32_t other_half(uint32_t v) {
+  // pairs and quads exchanged, then mirrors of 8 and 16 lanes, then 16 lanes swapped
+  constexpr int kDpp[4] = {0xb1, 0x4e, 0x141, 0x140};
+  if (S < 4) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), kDpp[S & 3], 0xf, 0xf, false));
+  return uint32_t(__builtin_amdgcn_ds_swizzle(int(v), 0x401f));
+}
+template <int S>
+__device__ inline void nearer_half(float* best, int* bk) {
+  const float ob = __uint_as_float(other_half<S>(__float_as_uint(*best)));
+  const int ok = int(other_half<S>(uint32_t(*bk)));
+  if (ob < *best || (ob == *best && ok < *bk)) *best = ob, *bk = ok;
+}
+
+// counts[block] = (merges, absorbed) of a search block; `merges` and `absorbed` are each wave's own.
+__device__ inline void store_counts(uint32_t merges, uint32_t absorbed, uint2* tmp, uint2* counts) {
+  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = make_uint2(merges, absorbed);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < int(blockDim.x) / 64; ++w) merges += tmp[w].x, absorbed += tmp[w].y;
+  counts[blockIdx.x] = make_uint2(merges, absorbed);
+}
+
 // partner[i] = the position cluster i merges with this round, or -1; counts[block] = (merges, absorbed
 // clusters) of the block's positions.  A tile's mutual pairs need the choices of kPlocRadius positions on
 // either side too, so a block makes those as well.  This is the search of a round with too few clusters to
@@ -672,7 +715,7 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* 
   static_assert(kOwn > 0 && 2 * R % LANES == 0, "search split");
   __shared__ float4 s_lo[kPos + 2 * R], s_hi[kPos + 2 * R];
   __shared__ int s_nn[kPos];
-  __shared__ uint32_t tmp[kPlocBlock / 64];
+  __shared__ uint2 tmp[kPlocBlock / 64];
   const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
   if (n <= kPlocTail) return;
   const float4 *__restrict__ lo = lo_of(c, buf), *__restrict__ hi = hi_of(c, buf);
@@ -692,26 +735,28 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* 
     const int64_t g = int64_t(base) - R + p;  // this thread's position, at p + R in LDS
     const bool valid = g >= 0 && g < int64_t(n);
     const float4 alo = s_lo[p + R], ahi = s_hi[p + R];
+    auto area = [&](int k) {
+      auto f3 = [](float4 v) { return make_float3(v.x, v.y, v.z); };
+      return merged_area_raw(f3(alo), f3(ahi), f3(s_lo[p + R + k]), f3(s_hi[p + R + k]));
+    };
     float best = INFINITY;
     int bk = 0;
     // ascending positions: ties keep the smaller one
 #pragma unroll 8
     for (int q = 0; q < R / LANES; ++q) {
       const int k = -R + q * LANES + sub;
-      const float ar = merged_area(alo, ahi, s_lo[p + R + k], s_hi[p + R + k]);
+      const float ar = area(k);
       if (ar < best) best = ar, bk = k;
     }
 #pragma unroll 8
     for (int q = 0; q < R / LANES; ++q) {
       const int k = 1 + q * LANES + sub;
-      const float ar = merged_area(alo, ahi, s_lo[p + R + k], s_hi[p + R + k]);
+      const float ar = area(k);
       if (ar < best) best = ar, bk = k;
     }
-    for (int off = 1; off < LANES; off <<= 1) {
-      const float ob = __shfl_xor(best, off);
-      const int ok = __shfl_xor(bk, off);
-      if (ob < best || (ob == best && ok < bk)) best = ob, bk = ok;
-    }
+    static_assert(LANES == 4, "two halvings");
+    nearer_half<0>(&best, &bk);
+    nearer_half<1>(&best, &bk);
     if (valid) {
       if (!(best < INFINITY)) bk = g > 0 ? -1 : 1;  // boxes of refused input only: keep the rounds well formed
       const int toward = (g & 1) ? -1 : 1;  // g ^ 1
@@ -720,35 +765,17 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(Clusters c, BuildState* 
     }
     if (sub == 0) s_nn[p] = valid ? p + bk : -1;
     __syncthreads();
+    int j = p;
     if (sub == 0 && p >= R && p < kPos - R && valid) {
-      const int j = s_nn[p];
+      j = s_nn[p];
       const bool mutual = s_nn[j] == p;  // j lies within R of p
       partner[g] = mutual ? int32_t(g + j - p) : -1;
-      merges += (mutual && j > p) ? 1u : 0u;    // the lower position of a mutual pair makes the node
-      absorbed += (mutual && j < p) ? 1u : 0u;  // the higher one goes
+      if (!mutual) j = p;
     }
+    merges += uint32_t(__popcll(__ballot(j > p)));    // the lower position of a mutual pair makes the node
+    absorbed += uint32_t(__popcll(__ballot(j < p)));  // the higher one goes
   }
-  merges = block_sum(merges, tmp);
-  absorbed = block_sum(absorbed, tmp);
-  if (threadIdx.x == 0) counts[blockIdx.x] = make_uint2(merges, absorbed);
-}
-
-// max and min without the instructions that quiet a signalling NaN first (12 of 87 in the search's loop; boxes of
-// accepted input hold no NaN, and those of refused input are only ever written to the scratch).
-__device__ inline float raw_max(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ inline float raw_min(float a, float b) {
-  float r;
-  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-// merged_area for two boxes known to be no NaN
-__device__ inline float merged_area_raw(float3 alo, float3 ahi, float3 blo, float3 bhi) {
-  return half_area_of(raw_max(ahi.x, bhi.x) - raw_min(alo.x, blo.x), raw_max(ahi.y, bhi.y) - raw_min(alo.y, blo.y),
-                      raw_max(ahi.z, bhi.z) - raw_min(alo.z, blo.z));
+  store_counts(merges, absorbed, tmp, counts);
 }
 
 // The search of a round with many clusters, bound by the VALU (18 instructions a candidate, 64 candidates a
@@ -768,7 +795,7 @@ __global__ __launch_bounds__(kPairBlock) void k_ploc_nn_pairs(Clusters c, BuildS
   __shared__ float4 s_lo[2][kHalf], s_hi[2][kHalf];  // position base - 2R + k at [k & 1][k / 2]
   __shared__ unsigned long long s_below[2][kHalf];   // its best partner below
   __shared__ int s_nn[kPos];
-  __shared__ uint32_t tmp[kPairBlock / 64];
+  __shared__ uint2 tmp[kPairBlock / 64];
   const uint32_t n = state->ploc[slot].n, buf = state->ploc[slot].buf;
   if (n <= kPlocTail) return;
   const float4 *__restrict__ lo = lo_of(c, buf), *__restrict__ hi = hi_of(c, buf);
@@ -840,17 +867,18 @@ __global__ __launch_bounds__(kPairBlock) void k_ploc_nn_pairs(Clusters c, BuildS
     for (int k = 0; k < 2; ++k) {
       // positions from 2R to kPos - R are the tile's own; those from R on have seen every candidate
       const int p = 2 * q + k;
-      if (p < 2 * R || p >= kPos - R || !(k ? v1 : v0)) continue;
-      const int j = s_nn[p];
-      const bool mutual = s_nn[j] == p;  // j lies within R of p
-      partner[g0 + k] = mutual ? int32_t(g0 + k + j - p) : -1;
-      merges += (mutual && j > p) ? 1u : 0u;    // the lower position of a mutual pair makes the node
-      absorbed += (mutual && j < p) ? 1u : 0u;  // the higher one goes
+      int j = p;
+      if (p >= 2 * R && p < kPos - R && (k ? v1 : v0)) {
+        j = s_nn[p];
+        const bool mutual = s_nn[j] == p;  // j lies within R of p
+        partner[g0 + k] = mutual ? int32_t(g0 + k + j - p) : -1;
+        if (!mutual) j = p;
+      }
+      merges += uint32_t(__popcll(__ballot(j > p)));    // the lower position of a mutual pair makes the node
+      absorbed += uint32_t(__popcll(__ballot(j < p)));  // the higher one goes
     }
   }
-  merges = block_sum(merges, tmp);
-  absorbed = block_sum(absorbed, tmp);
-  if (threadIdx.x == 0) counts[blockIdx.x] = make_uint2(merges, absorbed);
+  store_counts(merges, absorbed, tmp, counts);
 }
 
 struct PlocNodes {
@@ -1002,22 +1030,6 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// v of another lane of the group of 2^(S + 1), of which each half holds one value throughout: with S = 0, 1, .. in turn
-// a reduction over groups of up to 32 lanes, without the address and the trip through LDS of a shuffle.
-template <int S>
-__device__ inline uint32_t other_half(uint32_t v) {
-  // pairs and quads exchanged, then mirrors of 8 and 16 lanes, then 16 lanes swapped
-  constexpr int kDpp[4] = {0xb1, 0x4e, 0x141, 0x140};
-  if (S < 4) return uint32_t(__builtin_amdgcn_mov_dpp(int(v), kDpp[S & 3], 0xf, 0xf, false));
-  return uint32_t(__builtin_amdgcn_ds_swizzle(int(v), 0x401f));
-}
-template <int S>
-__device__ inline void nearer_half(float* best, int* bk) {
-  const float ob = __uint_as_float(other_half<S>(__float_as_uint(*best)));
-  const int ok = int(other_half<S>(uint32_t(*bk)));
-  if (ob < *best || (ob == *best && ok < *bk)) *best = ob, *bk = ok;
 }
 
 // Lane `sub` of the 2^LOG2 that share the search of position i: every 2^LOG2-th of its 2 R neighbours, in ascending
