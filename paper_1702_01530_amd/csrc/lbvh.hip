@@ -1162,7 +1162,10 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
 
 constexpr int kWideEmpty = INT32_MIN;
 constexpr int kWideBlocks = 1024;  // most blocks of a level: each sums the others' counts
-constexpr int kWideTail = 1024;    // a level of at most this many nodes is done by the one-workgroup kernel
+constexpr int kWideTail = 1024;    // a level of at most this many nodes is done by the one-workgroup kernel,
+constexpr int kWideSmall = 4096;   // of at most this many in a tree of at most kWideSmallTree triangles (2k / 10k /
+                                   // 15k triangles: 499 / 587 / 615 us with launches a level, 478 / 573 / 620 without)
+constexpr int64_t kWideSmallTree = 12288;
 
 struct WideArgs {
   const int4* made;           // per binary node: children and the cost-optimal cut
@@ -1175,6 +1178,7 @@ struct WideArgs {
   uint32_t* counts;           // internal children of a block's items
   float4* nodes;
   uint32_t max_nodes;         // T - 1
+  uint32_t tail;              // kWideTail or kWideSmall
   BuildState* state;
 };
 
@@ -1254,9 +1258,10 @@ __device__ inline int grid_exponent(double ext) {
 }
 
 // Writes BVH4 node `b4` with children r; its internal children are BVH4 nodes first, first + 1, ... and
-// entries slot, slot + 1, ... of the next level.
+// entries slot, slot + 1, ... of the next level, which put(entry, (binary node, BVH4 index)) takes.
+template <class Put>
 __device__ inline void wide_emit(const WideArgs& a, float p, int b4, const int (&r)[4], uint32_t first, uint32_t slot,
-                                 int2* next) {
+                                 Put put) {
   float lo[3][4], hi[3][4];
   int ref[4];
   uint32_t k_int = 0;
@@ -1282,7 +1287,7 @@ __device__ inline void wide_emit(const WideArgs& a, float p, int b4, const int (
       l = make_float4(l.x - p, l.y - p, l.z - p, 0.f);
       h = make_float4(h.x + p, h.y + p, h.z + p, 0.f);
       const int idx = int(first + k_int);
-      next[slot + k_int] = make_int2(r[k], idx);
+      put(slot + k_int, make_int2(r[k], idx));
       ++k_int;
       ref[k] = idx;
     }
@@ -1355,7 +1360,7 @@ __device__ inline float wide_pad(const Bounds6& b) {
 __global__ __launch_bounds__(kBlock) void k_wide_select(WideArgs a, int slot) {
   __shared__ uint32_t tmp[kBlock / 64];
   const BuildState::Wide st = a.state->wide[slot];
-  if (st.m <= kWideTail) return;
+  if (st.m <= a.tail) return;
   const int2* frontier = (st.level & 1) ? a.frontier[1] : a.frontier[0];
   uint32_t begin, end, n = 0;
   ploc_range(st.m, kBlock, blockIdx.x, gridDim.x, &begin, &end);
@@ -1374,7 +1379,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a, int slot) {
   __shared__ uint32_t wcnt[2][kBlock / 64];
   const BuildState::Wide st = a.state->wide[slot];
   BuildState::Wide* out = &a.state->wide[slot ^ 1];
-  if (st.m <= kWideTail) {
+  if (st.m <= a.tail) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *out = st;
     return;
   }
@@ -1420,54 +1425,68 @@ __global__ __launch_bounds__(kBlock) void k_wide_emit(WideArgs a, int slot) {
       all += wcnt[par][w];
     }
     const uint32_t off = before + wb + scan - n;
-    if (valid) wide_emit(a, pad, frontier[i].y, r, st.allocated + off, off, next);
+    if (valid)
+      wide_emit(a, pad, frontier[i].y, r, st.allocated + off, off, [&](uint32_t e, int2 v) { next[e] = v; });
     before += all;
   }
 }
 
-// Every level of at most kWideTail nodes from the state's level on, in one workgroup: the top of the tree
-// before the wide levels, and what is left after them.
+// Every level of at most a.tail nodes from the state's level on, in one workgroup: the top of the tree before the wide
+// levels, and what is left after them.  A level is a chain of dependent reads (a node's record, its children's, the
+// chosen children's boxes); its entries pass to the next one through LDS, also written to memory for the launch that
+// takes over, and no barrier waits for a store.
 __global__ __launch_bounds__(kWideTail) void k_wide_levels(WideArgs a, int slot) {
   constexpr int kW = kWideTail / 64;
+  __shared__ int2 entries[2][kWideSmall];
   __shared__ uint32_t wcnt[kW];
   BuildState::Wide st = a.state->wide[slot];
   if (a.state->ploc[0].n != 1 || a.state->ploc[1].n != 1) return;  // the binary tree is not complete yet
   const float pad = wide_pad(a.state->bounds);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   bool bad = false;
-  while (st.m > 0 && st.m <= kWideTail) {  // allocated grows with every level and is bounded
+  if (st.m <= a.tail) {
     const int2* frontier = (st.level & 1) ? a.frontier[1] : a.frontier[0];
+    for (uint32_t i = threadIdx.x; i < st.m; i += kWideTail) entries[st.level & 1][i] = frontier[i];
+  }
+  __syncthreads();
+  while (st.m > 0 && st.m <= a.tail && !bad) {  // allocated grows with every level and is bounded
     int2* next = (st.level & 1) ? a.frontier[0] : a.frontier[1];
-    const bool valid = threadIdx.x < st.m;
-    int r[4] = {kWideEmpty, kWideEmpty, kWideEmpty, kWideEmpty};
-    int2 item = make_int2(0, 0);
-    uint32_t n = 0;
-    if (valid) {
-      item = frontier[threadIdx.x];
-      n = wide_select(a, item.x, r);
+    int2* next_lds = entries[(st.level & 1) ^ 1];
+    uint32_t total = 0;
+    for (uint32_t base = 0; base < st.m && !bad; base += kWideTail) {
+      const bool valid = base + threadIdx.x < st.m;
+      int r[4] = {kWideEmpty, kWideEmpty, kWideEmpty, kWideEmpty};
+      int2 item = make_int2(0, 0);
+      uint32_t n = 0;
+      if (valid) {
+        item = entries[st.level & 1][base + threadIdx.x];
+        n = wide_select(a, item.x, r);
+      }
+      uint32_t scan = n;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(scan, off);
+        if (lane >= off) scan += u;
+      }
+      if (lane == 63) wcnt[wave] = scan;
+      lds_barrier();
+      uint32_t before = total;
+      for (int w = 0; w < kW; ++w) {
+        if (w < wave) before += wcnt[w];
+        total += wcnt[w];
+      }
+      bad = total > a.max_nodes - st.allocated;
+      const uint32_t off = before + scan - n;
+      if (valid && !bad)
+        wide_emit(a, pad, item.y, r, st.allocated + off, off, [&](uint32_t e, int2 v) {
+          next[e] = v;
+          if (e < uint32_t(kWideSmall)) next_lds[e] = v;
+        });
+      lds_barrier();  // the next level's entries are written, wcnt is free
     }
-    uint32_t scan = n;
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t u = __shfl_up(scan, off);
-      if (lane >= off) scan += u;
-    }
-    if (lane == 63) wcnt[wave] = scan;
-    __syncthreads();
-    uint32_t wb = 0, total = 0;
-    for (int w = 0; w < kW; ++w) {
-      if (w < wave) wb += wcnt[w];
-      total += wcnt[w];
-    }
-    if (total > a.max_nodes - st.allocated) {
-      bad = true;
-      break;
-    }
-    const uint32_t off = wb + scan - n;
-    if (valid) wide_emit(a, pad, item.y, r, st.allocated + off, off, next);
+    if (bad) break;
     st.m = total;
     st.allocated += total;
     ++st.level;
-    __syncthreads();  // the next level's entries are written, wcnt is free
   }
   if (threadIdx.x == 0) {
     if (bad) {
@@ -1736,6 +1755,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       wa.counts = reinterpret_cast<uint32_t*>(counts);
       wa.nodes = reinterpret_cast<float4*>(storage + plan.nodes_off);
       wa.max_nodes = uint32_t(T - 1);
+      wa.tail = T <= kWideSmallTree ? kWideSmall : kWideTail;
       wa.state = state;
       for (int k = 0; k < 2; ++k) wa.frontier[k] = reinterpret_cast<int2*>(scratch + plan.frontier_off[k]);
       int level = 0;
@@ -1754,7 +1774,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         return hipGetLastError();
       };
       // levels of more than kWideTail nodes: none for a small tree, 10 of 17 for 3.4M triangles
-      const int wide_levels = T <= kWideTail ? 0 : 4 + int(std::ceil(std::log2(double(T) / kWideTail) / 2));
+      const int wide_levels = T <= kWideSmallTree ? 0 : 4 + int(std::ceil(std::log2(double(T) / kWideTail) / 2));
       SRT_CHECK(collapse(wide_levels));
       for (;;) {
         SRT_CHECK(hipMemcpyAsync(&done, state, sizeof(done), hipMemcpyDeviceToHost, stream));

@@ -141,3 +141,17 @@ def test_scenes_without_a_tree(torch_cuda, n, size):
             assert torch.equal(outs[0][k], o[k]), k
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("accel", ["ploc", "karras"])
+@pytest.mark.parametrize("n,kind", [(12288, "uniform"), (12288, "line"), (12288, "same"), (12289, "uniform"),
+                                    (12289, "grow")])
+def test_small_trees_level_by_level(torch_cuda, n, kind, accel):
+    """Trees of at most 12,288 triangles are collapsed by one workgroup, several nodes a thread; larger ones by a launch
+    a level where a level is wide."""
+    from paper_1702_01530_amd.stereo import GpuScene
+    scene = _soup(n, kind)
+    print(f"[build] levels {n} {kind} {accel}", flush=True)
+    gs = GpuScene(scene, accel=accel)
+    _walk(gs, n, scene.triangles)
+    gs.close()
