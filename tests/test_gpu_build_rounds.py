@@ -143,6 +143,20 @@ def test_scenes_without_a_tree(torch_cuda, n, size):
     b.close()
 
 
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 127, 1087, 1088, 16384, 16385])
+@pytest.mark.parametrize("kind", ["uniform", "grid", "same"])
+def test_sort_of_few_keys(torch_cuda, n, kind):
+    """Small builds place each key by counting the keys before it, in tiles of 64 and shares of 64 a wave: the record order
+    is a stable sort of the Morton codes, with few distinct codes and with one."""
+    from paper_1702_01530_amd.stereo import GpuScene
+    from tests.test_gpu_render import _morton_keys, _record_ids
+    scene = _soup(n, kind)
+    print(f"[build] sort {n} {kind}", flush=True)
+    gs = GpuScene(scene)
+    assert np.array_equal(_record_ids(gs, n), np.argsort(_morton_keys(scene.triangles), kind="stable"))
+    gs.close()
+
+
 @pytest.mark.parametrize("accel", ["ploc", "karras"])
 @pytest.mark.parametrize("n,kind", [(12288, "uniform"), (12288, "line"), (12288, "same"), (12289, "uniform"),
                                     (12289, "grow")])
