@@ -1348,8 +1348,11 @@ inline bool path_wins(const DevScene& sc, bool flat, int64_t paths) {
 #define SRT_PATH_WAVES 5
 #endif
 
+constexpr int kFlatPathWaves = 6;  // waves per SIMD that k_path<false>'s registers allow
+
 template <bool TREE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH_WAVES))) void k_path(KArgs a, int blog) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH_WAVES))) void k_path(
+    KArgs a, int blog, int dynamic) {
   __shared__ uint32_t lstack[TREE ? kStackLds * kBlock : 1];
   __shared__ unsigned long long share_word[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
   __shared__ int share_key[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
@@ -1363,7 +1366,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
   const DevScene& sc = a.one.sc;
   const uint32_t count = uint32_t(a.path_count), nwaves = gridDim.x * uint32_t(kWaves);
   uint32_t n_refl = 0, n_shadow = 0, unused = 0;
-  for (uint32_t batch = blockIdx.x * uint32_t(kWaves) + wave; (batch << blog) < count; batch += nwaves) {
+  // A wave takes its first batch by its number and, in a dynamic launch (whose counters were set to zero before), later
+  // ones from interleaved counters, as k_trace does.
+  const uint32_t wid = blockIdx.x * uint32_t(kWaves) + wave, ncounters = min(nwaves, uint32_t(kWorkCounters));
+  auto later = [&] {
+    uint32_t k = 0;
+    if (lane == 0) k = atomicAdd(&kernel_args().ctr->trace_work[RT_MAX_DEPTH + 1][wid % ncounters][0], 1u);
+    return nwaves + wid % ncounters + ncounters * uint32_t(__builtin_amdgcn_readfirstlane(int(k)));
+  };
+  for (uint32_t batch = wid; (uint64_t(batch) << blog) < count; batch = later()) {
     const uint32_t e = (batch << blog) + lane;
     float3 o = make_float3(0.f, 0.f, 0.f), d = o;
     int eye = 0, x = 0, y = 0;
@@ -1486,6 +1497,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
       out[1] = rad.y;
       out[2] = rad.z;
     }
+    if (!dynamic) break;
   }
   for (int off = 32; off > 0; off >>= 1) {
     n_refl += __shfl_xor(n_refl, off);
@@ -1500,7 +1512,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
     reinterpret_cast<uint4*>(a.ctr)[blockIdx.x] = c;  // k_path's launches use the counters' bytes for this
   }
 }
-static_assert(sizeof(Counters) >= kMaxTraceBlocks * sizeof(uint4), "a block's counts");
+static_assert(offsetof(Counters, trace_work) + sizeof(Counters::trace_work) / (RT_MAX_DEPTH + 2) * (RT_MAX_DEPTH + 1) >=
+                  kMaxTraceBlocks * sizeof(uint4),
+              "the blocks' counts end before the work counters in use");
 
 // Adds the counts of k_path's blocks.
 __global__ __launch_bounds__(kBlock) void k_path_finish(const uint4* counts, int blocks, int64_t primary, int64_t* out) {
@@ -1759,13 +1773,31 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   // signatures nor the timer, whose stages are the queue kernels'.
   const bool whole = ra.path_begin == 0 && ra.path_count == ra.frame_paths;
   if (!multi && !count && !ids && !timer && whole && path_wins(ra.one.sc, flat, ra.path_count)) {
+    // A batch of 64 paths a wave, or of fewer where that still leaves every wave of the full grid at most one.  With more
+    // batches than waves run at once (k_path's registers allow resident blocks), those take them one by one: in fixed
+    // shares, or left to the dispatcher, the last ones decide (641x479, 13k triangles: 251 us in fixed shares, 235 so;
+    // spheres at 1080p 134 and 106).  Where each wave gets one batch of 64 and a few get two, batches of 32 are evener
+    // (480x360: 212 and 183 us); from 1.5 batches a wave on they no longer are (640x480: 222 and 239).
     int blog = 6;
-    if (!flat && kCoopRays > 0)
+    const int resident = std::max(1, p.grid_trace * (flat ? kFlatPathWaves : SRT_PATH_WAVES) / kTraceWaves);
+    auto blocks_of = [&](int log2n) {
+      return (ra.path_count + (int64_t(kWaves) << log2n) - 1) / (int64_t(kWaves) << log2n);
+    };
+    if (!flat && kCoopRays > 0) {
       while (blog > kMinRaysLog2 && (ra.path_count >> (blog - 1)) < int64_t(p.grid_trace) * kWaves) --blog;
-    const int64_t per_block = int64_t(kWaves) << blog;
-    const unsigned grid = unsigned(std::min<int64_t>(p.grid_trace, (ra.path_count + per_block - 1) / per_block));
-    e = flat ? launch(k_path<false>, grid, a, blog, s, nullptr, RT_STAGE_TRACE)
-             : launch(k_path<true>, grid, a, blog, s, nullptr, RT_STAGE_TRACE);
+      if (blog == 6 && blocks_of(6) > resident && 2 * blocks_of(6) < 3 * resident) blog = 5;
+    }
+    const int dynamic = blocks_of(blog) > p.grid_trace || (blog >= 5 && blocks_of(blog) > resident) ? 1 : 0;
+    const unsigned grid = unsigned(std::min<int64_t>(dynamic ? resident : p.grid_trace, blocks_of(blog)));
+    if (dynamic) {
+      k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (flat)
+      k_path<false><<<grid, kBlock, 0, s>>>(a, blog, dynamic);
+    else
+      k_path<true><<<grid, kBlock, 0, s>>>(a, blog, dynamic);
+    e = hipGetLastError();
     if (e != hipSuccess || !ra.ray_counts) return e;
     k_path_finish<<<1, kBlock, 0, s>>>(reinterpret_cast<const uint4*>(a.ctr), int(grid),
                                        2 * int64_t(ra.one.cam.W) * ra.one.cam.H, ra.ray_counts);

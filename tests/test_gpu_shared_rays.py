@@ -147,3 +147,22 @@ def test_batch_passes_equal_whole_paths(torch_cuda, max_pass_paths):
             assert torch.equal(one[k], outs[i][k]), (i, k)
     for gs, _ in pairs:
         gs.close()
+
+
+@pytest.mark.parametrize("size", [(480, 360), (720, 560)])
+@pytest.mark.parametrize("what", ["tree", "flat256"])
+def test_whole_paths_in_several_batches_equal_the_queues(torch_cuda, what, size):
+    """Frames of more batches than waves run at once, which take them one by one: of 32 paths and of 64."""
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    scene, cam = sg.make_small_terrain(seed=33, grid=18, n_spheres=5, level=1, lights=2) if what == "tree" else _flat(256)
+    cam = cam.resized(*size).with_(max_depth=3)
+    print(f"[whole paths] {what} {size}", flush=True)
+    gs = GpuScene(scene, accel="ploc" if what == "tree" else "none")
+    queues = render_stereo(gs, cam, path_ids=True)
+    for _ in range(2):  # the counters of the first launch are no concern of the second
+        one = render_stereo(gs, cam)
+        torch.cuda.synchronize()
+        for k in ("radiance", "hit_t", "hit_prim", "ray_counts"):
+            assert torch.equal(one[k], queues[k]), k
+    gs.close()
