@@ -241,6 +241,18 @@ srt::DevOutputs dev_outputs(const rt_stereo_output* o, uint32_t flags) {
   return d;
 }
 
+// Whether [p, p + bytes) lies in the allocation that p points into, as far as the runtime knows it.
+bool one_allocation(void* p, size_t bytes) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const uintptr_t a = reinterpret_cast<uintptr_t>(base), b = reinterpret_cast<uintptr_t>(p);
+  return a <= b && b - a <= size && bytes <= size - (b - a);
+}
+
 // Copies both eyes' radiance into the pinned host buffers of `out`, ordered after `stream`.
 rt_status readback(const rt_stereo_camera* cam, const rt_stereo_output* out, uint32_t flags, hipStream_t stream,
                    hipStream_t copy_stream, srt::TimerImpl* timer) {
@@ -267,7 +279,13 @@ rt_status readback(const rt_stereo_camera* cam, const rt_stereo_output* out, uin
       use_kernel = false;
     }
   if (timer) srt::timer_begin(timer, RT_STAGE_READBACK, cs);
-  for (int eye = 0; eye < 2 && e == hipSuccess; ++eye)
+  // Eyes that lie side by side on both ends are one copy: a second one starts 10 us after the first has ended
+  // (256x256 with a tree of 100 triangles, 2 x 14.5 us of copies: 106 and 96 us for the call).
+  const bool side_by_side = !use_kernel && out->radiance[1] == out->radiance[0] + bytes / 4 &&
+                            out->host_radiance[1] == out->host_radiance[0] + bytes / 4 &&
+                            one_allocation(out->radiance[0], 2 * bytes) && one_allocation(out->host_radiance[0], 2 * bytes);
+  if (side_by_side) e = hipMemcpyAsync(out->host_radiance[0], out->radiance[0], 2 * bytes, hipMemcpyDeviceToHost, cs);
+  for (int eye = side_by_side ? 2 : 0; eye < 2 && e == hipSuccess; ++eye)
     e = use_kernel ? srt::copy_to_host(out->radiance[eye], dview[eye], bytes, kReadbackBlocks, cs)
                    : hipMemcpyAsync(out->host_radiance[eye], out->radiance[eye], bytes, hipMemcpyDeviceToHost, cs);
   if (timer) srt::timer_end(timer, RT_STAGE_READBACK, cs);
