@@ -156,6 +156,7 @@ struct KArgs {
   uint32_t cap;           // entries per queue
   int32_t brute;
   int32_t trace_threads;  // threads in the persistent traversal grid (gstack stride)
+  int32_t resolve;        // k_trace of depth d also adds the lights' terms of depth d - 2
 };
 // Kernels take KArgs by value as their first argument, so its bytes start the kernel-argument
 // segment (kernel_args reads them there).
@@ -775,6 +776,53 @@ __device__ __attribute__((always_inline)) inline void each_item(const KArgs& a, 
   }
 }
 
+// 64 << kResolveLog2 entries make a batch of k_trace's.  As launches of their own the resolves of a 1080p frame of
+// 3.4M triangles, depth 4, took 48 + 16 + 8 + 7 + 6 us; with all but the last in the traversal the frame went from 2056
+// to 1999 us, 16 mixed scenes from 6738 to 6605, 8 small ones from 911 to 875 (64 entries a batch: 2001, 6795 and 888;
+// 256: 1996, 6643 and 880).
+constexpr int kResolveLog2 = 1;
+
+// Adds the unoccluded lights' terms of entry e of depth `depth` to its path's pixel, in light order.  All lanes of a
+// wave call it, with consecutive entries from a multiple of 64 on.
+template <bool PATH_IDS, bool MULTI>
+__device__ __attribute__((always_inline)) inline void resolve_entry(const KArgs& a, int depth, uint32_t e,
+                                                                    uint32_t total) {
+  const int q = depth & 1;
+  const uint32_t mask = e < total ? a.smask[q][e] : 0u;  // 0: no shadow rays, also outside the image
+  const uint32_t lp = depth == 0 || mask == 0 ? e : a.epath[q][e];
+  int item = 0;
+  if (MULTI) {
+    if (depth == 0)
+      item = item_of<MULTI>(a, a.path_begin + uint32_t(__builtin_amdgcn_readfirstlane(e)));  // one to a tile
+    else if (mask)
+      item = item_of<MULTI>(a, a.path_begin + lp);
+  }
+  each_item<MULTI>(a, mask != 0, item, [&](const DevItem& it, bool mine) {
+    if (!mine) return;
+    const int L = it.sc.L, D1 = it.cam.D + 1;
+    int eye, x, y;
+    const int64_t p = a.path_begin + lp - it.path_offset;
+    if (depth == 0)
+      wave_pixel(it.cam, p, &eye, &x, &y);
+    else
+      path_pixel(it.cam, p, &eye, &x, &y);
+    const int64_t pix = int64_t(y) * it.cam.W + x;
+    float3 sum = make_float3(0.f, 0.f, 0.f);
+    for (int l = 0; l < L; ++l) {
+      if (!((mask >> l) & 1u)) continue;
+      const size_t k = size_t(l) * a.cap + e;
+      const bool v = a.vis[q][k] != 0;
+      if (v) sum = add_rn(sum, make_float3(a.contrib[q][3 * k], a.contrib[q][3 * k + 1], a.contrib[q][3 * k + 2]));
+      if (PATH_IDS) it.out.shadow_state[eye][(pix * D1 + depth) * L + l] = v ? 2 : 1;
+    }
+    float* rad = it.out.radiance[eye] + 3 * pix;
+    const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), sum);
+    rad[0] = r.x;
+    rad[1] = r.y;
+    rad[2] = r.z;
+  });
+}
+
 template <bool COUNT, bool MULTI>
 __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int depth) {
   __shared__ uint32_t lstack[kStackLds * kBlock];
@@ -813,18 +861,29 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
   // proceed at once.
   const uint32_t wid = blockIdx.x * uint32_t(kWaves) + uint32_t(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   const uint32_t nbatches = total >> blog;
+  // Last come the entries of depth - 2, whose lights' terms are still to be added: work that waits for memory, for
+  // waves that would otherwise wait for the launch's last rays.
+  const uint32_t nres = !COUNT && a.resolve && depth >= 2
+                            ? (depth == 2 ? uint32_t(a.path_count) : a.ctr->refl_count[depth - 2])
+                            : 0u;
+  const uint32_t nall = nbatches + ((nres + (64u << kResolveLog2) - 1u) >> (6 + kResolveLog2));
   const uint32_t ncounters = nwaves < uint32_t(kWorkCounters) ? nwaves : uint32_t(kWorkCounters);  // each served
   const uint32_t home = wid % ncounters;
   uint32_t batch = wid;
   for (bool first = true;; first = false) {
     if (!first) {
-      if (nwaves + home >= nbatches) break;  // no batch left for this counter
+      if (nwaves + home >= nall) break;  // no batch left for this counter
       uint32_t k = 0;
       if (lane == 0) k = atomicAdd(&a.ctr->trace_work[depth][home][0], 1u);
       batch = nwaves + home + ncounters * uint32_t(__builtin_amdgcn_readfirstlane(int(k)));
     }
-    if (batch >= nbatches) break;
+    if (batch >= nall) break;
     const KArgs& a = kernel_args();  // the same values as the parameter, see kernel_args
+    if (!COUNT && batch >= nbatches) {
+      for (int k = 0; k < (1 << kResolveLog2); ++k)
+        resolve_entry<false, MULTI>(a, depth - 2, ((((batch - nbatches) << kResolveLog2) + k) << 6) + lane, nres);
+      continue;
+    }
     const uint32_t base = batch << blog;
     const bool filled = lane < (1 << blog);
     if (base < nc_pad) {
@@ -1544,48 +1603,12 @@ __global__ __launch_bounds__(kBlock) void k_path_finish(const uint4* counts, int
   }
 }
 
-// k_resolve: adds the unoccluded lights' terms of depth `depth` to each path's pixel, in light order.
+// k_resolve: the lights' terms of one depth, see resolve_entry.
 template <bool PATH_IDS, bool MULTI>
 __global__ __launch_bounds__(kBlock) void k_resolve(KArgs a, int depth) {
-  const int q = depth & 1;
   const uint32_t total = depth == 0 ? uint32_t(a.path_count) : a.ctr->refl_count[depth];
-  const int LS = a.lstride;
-  for (uint32_t base = blockIdx.x * kBlock; base < total; base += gridDim.x * kBlock) {
-    const uint32_t e = base + threadIdx.x;
-    const uint32_t mask = e < total ? a.smask[q][e] : 0u;  // 0: no shadow rays, also outside the image
-    const uint32_t lp = depth == 0 || mask == 0 ? e : a.epath[q][e];
-    int item = 0;
-    if (MULTI) {
-      if (depth == 0)
-        item = item_of<MULTI>(a, a.path_begin + uint32_t(__builtin_amdgcn_readfirstlane(e)));  // one to a tile
-      else if (mask)
-        item = item_of<MULTI>(a, a.path_begin + lp);
-    }
-    each_item<MULTI>(a, mask != 0, item, [&](const DevItem& it, bool mine) {
-      if (!mine) return;
-      const int L = it.sc.L, D1 = it.cam.D + 1;
-      int eye, x, y;
-      const int64_t p = a.path_begin + lp - it.path_offset;
-      if (depth == 0)
-        wave_pixel(it.cam, p, &eye, &x, &y);
-      else
-        path_pixel(it.cam, p, &eye, &x, &y);
-      const int64_t pix = int64_t(y) * it.cam.W + x;
-      float3 sum = make_float3(0.f, 0.f, 0.f);
-      for (int l = 0; l < L; ++l) {
-        if (!((mask >> l) & 1u)) continue;
-        const size_t k = size_t(l) * a.cap + e;
-        const bool v = a.vis[q][k] != 0;
-        if (v) sum = add_rn(sum, make_float3(a.contrib[q][3 * k], a.contrib[q][3 * k + 1], a.contrib[q][3 * k + 2]));
-        if (PATH_IDS) it.out.shadow_state[eye][(pix * D1 + depth) * L + l] = v ? 2 : 1;
-      }
-      float* rad = it.out.radiance[eye] + 3 * pix;
-      const float3 r = add_rn(make_float3(rad[0], rad[1], rad[2]), sum);
-      rad[0] = r.x;
-      rad[1] = r.y;
-      rad[2] = r.z;
-    });
-  }
+  for (uint32_t base = blockIdx.x * kBlock; base < total; base += gridDim.x * kBlock)
+    resolve_entry<PATH_IDS, MULTI>(a, depth, base + threadIdx.x, total);
 }
 
 // One workgroup clears the counters (41 KB, most of it the spaced work cursors), 16 bytes a store.
@@ -1759,7 +1782,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   // The persistent grid, cut where the launch cannot hold that many batches (small frames: a workgroup
   // without work still costs its dispatch).
   auto gtrace = [&](int d, int64_t rays_per_block, int64_t most) {
-    const int64_t rays = ra.path_count * ((d <= ra.max_depth ? 1 : 0) + (d >= 1 ? ra.max_lights : 0));
+    const int64_t rays = ra.path_count * ((d <= ra.max_depth ? 1 : 0) + (d >= 1 ? ra.max_lights : 0) + (d >= 2 ? 1 : 0));
     return unsigned(std::max<int64_t>(1, std::min<int64_t>(most, (rays + rays_per_block - 1) / rays_per_block)));
   };
   // Single scenes without a tree to walk have kernels of their own (the work counters are k_trace's).
@@ -1808,6 +1831,9 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   e = hipGetLastError();
   if (timer) timer_end(timer, RT_STAGE_SETUP, s);
   if (e != hipSuccess) return e;
+  // The traversal takes the resolve of two depths before along, but for the ray-tree signatures, which k_resolve writes,
+  // and the timer, whose stages are apart.
+  a.resolve = !flat && !count && !ids && !timer ? 1 : 0;
   const int D = a.dmax;
   for (int d = 0; d <= D + 1; ++d) {
     if (flat) {
@@ -1836,7 +1862,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
                 : launch(k_shade<false, false>, gshade, a, d, s, timer, RT_STAGE_SHADE, kShadeBlock);
       if (e != hipSuccess) return e;
     }
-    if (d >= 1) {
+    if (d >= 1 && (!a.resolve || d == D + 1)) {
       if (multi)
         e = ids ? launch(k_resolve<true, true>, gstream, a, d - 1, s, timer, RT_STAGE_RESOLVE)
                 : launch(k_resolve<false, true>, gstream, a, d - 1, s, timer, RT_STAGE_RESOLVE);

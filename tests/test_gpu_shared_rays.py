@@ -166,3 +166,23 @@ def test_whole_paths_in_several_batches_equal_the_queues(torch_cuda, what, size)
         for k in ("radiance", "hit_t", "hit_prim", "ray_counts"):
             assert torch.equal(one[k], queues[k]), k
     gs.close()
+
+
+@pytest.mark.parametrize("lights,depth", [(1, 0), (4, 1), (8, 2), (2, 5)])
+def test_terms_added_by_the_traversal_equal_the_launches(torch_cuda, lights, depth):
+    """Frames by queues: the traversal of depth d adds the lights' terms of depth d - 2, but not with ray-tree signatures
+    or the timer, whose frames take launches of their own for them."""
+    torch = torch_cuda
+    from paper_1702_01530_amd.stereo import GpuScene, render_stereo
+    scene, cam = sg.make_small_terrain(seed=33, grid=18, n_spheres=5, level=1)
+    all_lights = [[-6, 8, 2], [6, 6, 12], [-3, 9, 9], [5, 7, 3], [0, 8, 5], [-7, 5, 11], [3, 4, 14], [0.5, 3, -2]]
+    scene = scene.with_lights([p + [0.4, 0.4, 0.4] for p in all_lights[:lights]])
+    cam = cam.resized(1700, 1021).with_(max_depth=depth)
+    print(f"[queues] L={lights} D={depth}", flush=True)
+    gs = GpuScene(scene)
+    one, ids, counted = (render_stereo(gs, cam, **kw) for kw in ({}, {"path_ids": True}, {"count_work": True}))
+    torch.cuda.synchronize()
+    for k in ("radiance", "hit_t", "hit_prim"):
+        assert torch.equal(one[k], ids[k]) and torch.equal(one[k], counted[k]), k
+    assert torch.equal(one["ray_counts"][:3], ids["ray_counts"][:3])
+    gs.close()
