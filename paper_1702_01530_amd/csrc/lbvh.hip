@@ -5,7 +5,8 @@
 //   1. per triangle: bounding box and centroid, input validation;
 //   2. reduction of the centroid and scene bounds;
 //   3. 63-bit Morton code of the centroid quantised to 2^21 cells per axis;
-//   4. stable LSD radix sort of (code, triangle id), 8 passes of 8 bits;
+//   4. stable sort of (code, triangle id): LSD radix, 8 passes of 8 bits, or for
+//      few triangles one launch that counts the codes before each;
 //   5. binary tree over the sorted leaves: by default locally-ordered clustering
 //      (PLOC: neighbours in the Morton order merge by smallest surface area, so
 //      node boxes come with the merges); with RT_ACCEL_KARRAS, Karras (2012)
@@ -13,11 +14,12 @@
 //   6. a bottom-up box refit (an atomic arrival counter per node, the second
 //      child to arrive unions both boxes and climbs on);
 //   7. a bottom-up surface-area cost table that picks the cheapest way to cut the
-//      binary tree into a 4-wide one (filled during the refit, or one launch per
-//      clustering round);
-//   8. top-down collapse into that 4-wide tree, one level per launch, with the
-//      children's boxes quantised to 8 bits on each node's own grid (64-byte
-//      nodes), and 48-byte triangle records in leaf order.
+//      binary tree into a 4-wide one (filled during the refit or as the clustering
+//      makes the nodes);
+//   8. top-down collapse into that 4-wide tree, level by level (the narrow levels
+//      in one workgroup, two launches for each wide one), with the children's
+//      boxes quantised to 8 bits on each node's own grid (64-byte nodes), and
+//      48-byte triangle records in leaf order.
 // Every step is deterministic, so a scene always builds the same tree.
 
 #include <hip/hip_runtime.h>
@@ -615,9 +617,9 @@ __global__ __launch_bounds__(kBlock) void k_refit(int4* made, const int32_t* __r
 // bound by the cost of a round that has little to do.  The number of clusters stays on the device: the
 // host launches as many rounds as the decay suggests, two kernels each, without waiting for any of them,
 // and one workgroup does every round from kPlocTail clusters down (about 30 of them) with the clusters in
-// LDS.  A cluster carries its row of the cost table, so a node's entry is made with the node.  With a host
-// read, two prefix sums and five launches a round, and a launch a round for the cost table, building and
-// showing a scene of 10k triangles took 2.99 ms and takes 0.80 (3.4M triangles: 8.2 and 3.3 ms).
+// LDS.  A node's row of the cost table is made with the node.  With a host read, two prefix sums and five
+// launches a round, and a launch a round for the cost table, building and showing a scene of 10k triangles took
+// 2.99 ms and took 0.80 this way (3.4M triangles: 8.2 and 3.3 ms); 0.51 and 2.55 with the steps since.
 // ---------------------------------------------------------------------------------------------
 
 // Search radius: with the cost-table collapse, 32 gives the fewest node visits per frame on the
@@ -1072,36 +1074,42 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Lane `sub` of the 2^LOG2 that share the search of position i: every 2^LOG2-th of its 2 R neighbours, in ascending
-// order, ties to the first.
+// The searches of positions i0 and i0 + 1 among the kPlocRadius positions above each, by lane `sub` of the 2^LOG2 that
+// share them, ties to the first; `below` takes what they find for those positions (see k_ploc_nn_pairs).
 template <int LOG2>
-__device__ __attribute__((always_inline)) inline void search_share(const float4* lo, const float4* hi, int i, int sub,
-                                                                   float* best, int* bk) {
-  constexpr int R = kPlocRadius, kHalf = R >> LOG2;
+__device__ __attribute__((always_inline)) inline void search_pair(const float4* lo, const float4* hi,
+                                                                  unsigned long long* below, int i0, int sub, float* best0,
+                                                                  int* bk0, float* best1, int* bk1) {
+  constexpr int R = kPlocRadius, kSteps = (R + 1 + (1 << LOG2) - 1) >> LOG2;
   auto f3 = [](float4 v) { return make_float3(v.x, v.y, v.z); };
-  const float3 alo = f3(lo[i]), ahi = f3(hi[i]);
-  auto half = [&](int first) {
+  const float3 lo0 = f3(lo[i0]), hi0 = f3(hi[i0]), lo1 = f3(lo[i0 + 1]), hi1 = f3(hi[i0 + 1]);
 #pragma unroll 4
-    for (int k = 0; k < kHalf; ++k) {
-      const int d = first + (k << LOG2);
-      const float ar = merged_area_raw(alo, ahi, f3(lo[i + d]), f3(hi[i + d]));
-      if (ar < *best) *best = ar, *bk = d;
-    }
-  };
-  half(sub - R);
-  half(sub + 1);
+  for (int k = 0; k < kSteps; ++k) {
+    const int d = 1 + sub + (k << LOG2);
+    if (d > R + 1) break;
+    const float3 l = f3(lo[i0 + d]), h = f3(hi[i0 + d]);
+    // i0 reaches d = 1 .. R, i0 + 1 reaches d = 2 .. R + 1
+    const float a0 = d <= R ? merged_area_raw(lo0, hi0, l, h) : INFINITY;
+    const float a1 = d >= 2 ? merged_area_raw(lo1, hi1, l, h) : INFINITY;
+    if (a0 < *best0) *best0 = a0, *bk0 = d;
+    if (a1 < *best1) *best1 = a1, *bk1 = d - 1;
+    const unsigned long long word = (static_cast<unsigned long long>(__float_as_uint(a1 < a0 ? a1 : a0)) << 32) |
+                                    uint32_t(a1 < a0 ? i0 + 1 : i0);
+    __hip_atomic_fetch_min(&below[i0 + d], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
 }
 
-// The remaining rounds of at most kPlocTail clusters, in one workgroup: a round costs a search whose 64
-// candidates are split over as many lanes as there are to spare, and three barriers.  It is bound by the search,
-// three quarters of the time (2.4 us a round of 30, the first rounds 10), with one CU's VALU: 20 instructions a
-// candidate and loads four candidates ahead.  10k triangles: 136 us with a bounds check and a wait a candidate, shuffles
-// through LDS and barriers that wait for stores, 115 this way.
+// The remaining rounds of at most kPlocTail clusters, in one workgroup: a round costs a search whose candidates are
+// split over as many lanes as there are to spare, and four barriers.  It is bound by the search, with one CU's VALU: each
+// area is computed once, for both of its clusters, by lanes that hold two neighbours, with loads four candidates
+// ahead.  10k triangles, 30 rounds: 136 us with a bounds check and a wait a candidate, shuffles through LDS and barriers
+// that wait for stores; 115 without those; 101 with the areas shared.
 // The launch's other workgroups pack the triangles meanwhile (77 us as a launch of its own, for 3.4M).
 __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState* state, int slot, PlocNodes out,
                                                          PackArgs pack) {
   constexpr int R = kPlocRadius, kW = kPlocTail / 64;
   __shared__ float4 p_lo[kPlocTail + 2 * R], p_hi[kPlocTail + 2 * R], s_cost[kPlocTail];
+  __shared__ unsigned long long s_below[kPlocTail + 2 * R];  // a position's best partner below
   __shared__ int s_nn[kPlocTail];
   __shared__ uint32_t wkeep[kW], wmerge[kW];
   if (blockIdx.x > 0) {
@@ -1115,6 +1123,7 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
   const float4 nowhere = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
   float4 *const s_lo = p_lo + R, *const s_hi = p_hi + R;
   if (tid < R) p_lo[tid] = p_hi[tid] = s_lo[st.n + tid] = s_hi[st.n + tid] = nowhere;
+  s_below[tid] = ~0ull;
   if (tid < int(st.n)) {
     const float4 lo = lo_of(c, st.buf)[tid], hi = hi_of(c, st.buf)[tid];
     s_lo[tid] = lo;
@@ -1125,27 +1134,33 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
   bool bad = false;
   int n = int(st.n), next = int(st.next);
   while (n > 1) {  // every round merges a pair, or ends the loop
-    int log2l = 0;
-    while (log2l < 5 && (n << (log2l + 1)) <= kPlocTail) ++log2l;
-    const int lanes = 1 << log2l, i = tid >> log2l, sub = tid & (lanes - 1);
-    float best = INFINITY;
-    int bk = 0;
-    if (i < n) {
+    int log2l = 1;  // lanes to a pair of positions
+    while (log2l < 5 && (n + 1) << log2l <= kPlocTail) ++log2l;
+    const int sub = tid & ((1 << log2l) - 1), i0 = (tid >> log2l) * 2;
+    float best0 = INFINITY, best1 = INFINITY;
+    int bk0 = 0, bk1 = 0;
+    if (i0 < n) {
       switch (log2l) {
-        case 0: search_share<0>(s_lo, s_hi, i, sub, &best, &bk); break;
-        case 1: search_share<1>(s_lo, s_hi, i, sub, &best, &bk); break;
-        case 2: search_share<2>(s_lo, s_hi, i, sub, &best, &bk); break;
-        case 3: search_share<3>(s_lo, s_hi, i, sub, &best, &bk); break;
-        case 4: search_share<4>(s_lo, s_hi, i, sub, &best, &bk); break;
-        default: search_share<5>(s_lo, s_hi, i, sub, &best, &bk); break;
+        case 1: search_pair<1>(s_lo, s_hi, s_below, i0, sub, &best0, &bk0, &best1, &bk1); break;
+        case 2: search_pair<2>(s_lo, s_hi, s_below, i0, sub, &best0, &bk0, &best1, &bk1); break;
+        case 3: search_pair<3>(s_lo, s_hi, s_below, i0, sub, &best0, &bk0, &best1, &bk1); break;
+        case 4: search_pair<4>(s_lo, s_hi, s_below, i0, sub, &best0, &bk0, &best1, &bk1); break;
+        default: search_pair<5>(s_lo, s_hi, s_below, i0, sub, &best0, &bk0, &best1, &bk1); break;
       }
     }
-    if (log2l > 0) nearer_half<0>(&best, &bk);
-    if (log2l > 1) nearer_half<1>(&best, &bk);
-    if (log2l > 2) nearer_half<2>(&best, &bk);
-    if (log2l > 3) nearer_half<3>(&best, &bk);
-    if (log2l > 4) nearer_half<4>(&best, &bk);
-    if (i < n && sub == 0) {
+    nearer_half<0>(&best0, &bk0), nearer_half<0>(&best1, &bk1);
+    if (log2l > 1) nearer_half<1>(&best0, &bk0), nearer_half<1>(&best1, &bk1);
+    if (log2l > 2) nearer_half<2>(&best0, &bk0), nearer_half<2>(&best1, &bk1);
+    if (log2l > 3) nearer_half<3>(&best0, &bk0), nearer_half<3>(&best1, &bk1);
+    if (log2l > 4) nearer_half<4>(&best0, &bk0), nearer_half<4>(&best1, &bk1);
+    lds_barrier();
+    const int i = i0 + sub;
+    if (sub < 2 && i < n) {
+      float best = sub == 0 ? best0 : best1;
+      int bk = sub == 0 ? bk0 : bk1;
+      const unsigned long long w = s_below[i];
+      const float area = __uint_as_float(uint32_t(w >> 32));
+      if (area < INFINITY && area <= best) best = area, bk = int(uint32_t(w)) - i;  // the smaller position
       if (!(best < INFINITY)) bk = i > 0 ? -1 : 1;
       const int p = i ^ 1;
       if (p < n && ploc_takes_parity(best, s_lo[i], s_hi[i], s_lo[p], s_hi[p])) bk = p - i;
@@ -1182,6 +1197,7 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters c, BuildState*
       s_cost[pos] = cost;
     }
     if (tid < R) s_lo[n + tid] = s_hi[n + tid] = nowhere;
+    s_below[tid] = ~0ull;
     lds_barrier();
   }
   if (tid == 0) {

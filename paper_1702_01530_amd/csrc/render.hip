@@ -7,13 +7,18 @@
 //   k_trace(d)    persistent BVH traversal of the closest-hit rays of depth d
 //                 (primary rays generated in-register, FP64 rounded once to
 //                 FP32) together with the shadow rays spawned at depth d-1;
-//                 the two ray kinds fill one grid, so neither leaves a tail
+//                 the two ray kinds fill one grid, so neither leaves a tail.
+//                 Its last batches add the unoccluded lights' terms of depth
+//                 d-2 in light order
 //   k_shade(d)    Phong shading of the depth-d hits: adds the ambient (or
 //                 background) term, spawns one shadow ray per light with
 //                 N.L > 0 into that light's queue and a mirror ray into the
 //                 next depth's queue; queues are compacted with wave ballots
 //                 and one atomic per block and queue
-//   k_resolve(d-1) adds the unoccluded lights' terms of depth d-1 in light order
+//   k_resolve(D)  adds the terms of the last depth (of every depth, with
+//                 ray-tree signatures or the timer)
+// Single scenes without a tree have a traversal kernel of their own
+// (k_trace_flat), and small whole frames are one launch (k_path).
 // Queues and per-depth buffers are double-buffered by depth parity.  Every
 // pixel's radiance is accumulated by one thread at a time in a fixed order,
 // so results do not depend on queue order, pass size or concurrent work.
@@ -742,7 +747,7 @@ __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
 
 // Traversal occupancy: the traversal kernels are held to kTraceWaves waves per SIMD, a budget of
 // 64 VGPRs and 20 KB of LDS a block.  The single-scene kernel meets it without spilling, the batch kernel
-// with 8 registers spilled outside the node step.  7 waves: 2258 vs 2187 us for a 1080p frame of 3.4M
+// with 6 registers spilled outside the node step.  7 waves: 2258 vs 2187 us for a 1080p frame of 3.4M
 // triangles, 7.68 vs 7.47 ms for 16 mixed pairs.  The instrumented kernels are left free.
 constexpr int kTraceWaves = SRT_TRACE_WAVES_PER_EU;
 #define SRT_TRACE_ATTR __attribute__((amdgpu_waves_per_eu(COUNT || kTraceWaves <= 0 ? 1 : kTraceWaves)))
