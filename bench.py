@@ -779,7 +779,7 @@ def main():
                    "dram_gbs": traffic / (avg_launch_ms * 1e-3) / 1e9 if traffic else None,
                    "dram_frac_of_peak": traffic / (avg_launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if traffic else None,
                    "hbm_peak_gbs": HBM_PEAK_GBS, "copy_peak_gbs": copy_gbs,
-                   "note": "algorithmic bytes count every node visit as a fetch; most are served by LDS, L2 and "
+                   "note": "algorithmic bytes count every node visit as a fetch; most are served by the L2 and "
                            "the Infinity Cache, so they are not quoted against the HBM peak"},
     }
     log(f"[bench] k_trace: {achieved:.2f} T algorithmic lane-ops/s = {achieved / VALU_PEAK_TOPS:.3f} of the VALU "
