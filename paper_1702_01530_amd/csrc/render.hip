@@ -1392,8 +1392,8 @@ __global__ __launch_bounds__(kShadeBlock) __attribute__((amdgpu_waves_per_eu(MUL
 // result.  Larger frames gain more from the queues, which fill every wave with live rays.
 // A hit's shadow rays are packed over the lights, so a wave makes as many rounds as its rays need and not one a
 // light (641x479, 13k triangles, depth 4, 2 lights: 280 us a light at a time, 257 packed, 317 by queues).
-// 256x256, depth 1, 1 light: spheres 46.3 -> 18.4 us, 100 triangles 68.4 -> 52.0.  5 waves per SIMD with 6
-// spilled registers: 257 us; 4 without spills 264, 6 (35 spilled) 298 for that frame.
+// 256x256, depth 1, 1 light: spheres 46.3 -> 16.5 us, 100 triangles 68.4 -> 48.2.  5 waves per SIMD with 10
+// spilled registers; 4 without spills or 6 with 37 take 5% longer on that frame, which now takes 235 us.
 // ---------------------------------------------------------------------------------------------
 
 // Which frames k_path takes.  Without a tree: at most kPathFlat triangles (1920x1080, depth 4, 2 lights: 42
@@ -1416,7 +1416,7 @@ constexpr int kFlatPathWaves = 6;  // waves per SIMD that k_path<false>'s regist
 
 template <bool TREE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH_WAVES))) void k_path(
-    KArgs a, int blog, int dynamic) {
+    KArgs a, int blog, int dynamic, int64_t* out) {
   __shared__ uint32_t lstack[TREE ? kStackLds * kBlock : 1];
   __shared__ unsigned long long share_word[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
   __shared__ int share_key[TREE ? kWaves * std::max(kCoopRays, 1) : 1];
@@ -1556,10 +1556,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
     if (inside) {
       if (lit) rad = add_rn(rad, sum);
       wave_pixel(a.one.cam, e, &eye, &x, &y);
-      float* out = a.one.out.radiance[eye] + 3 * (int64_t(y) * a.one.cam.W + x);
-      out[0] = rad.x;
-      out[1] = rad.y;
-      out[2] = rad.z;
+      float* pixel = a.one.out.radiance[eye] + 3 * (int64_t(y) * a.one.cam.W + x);
+      pixel[0] = rad.x;
+      pixel[1] = rad.y;
+      pixel[2] = rad.z;
     }
     if (!dynamic) break;
   }
@@ -1573,14 +1573,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
   if (threadIdx.x == 0) {
     uint4 c = make_uint4(0u, 0u, 0u, 0u);
     for (int w = 0; w < kWaves; ++w) c.x += s_cnt[0][w], c.y += s_cnt[1][w], c.z |= s_cnt[2][w];
-    reinterpret_cast<uint4*>(a.ctr)[blockIdx.x] = c;  // k_path's launches use the counters' bytes for this
+    if (out) {
+      unsigned long long* sum = reinterpret_cast<unsigned long long*>(out);
+      if (blockIdx.x == 0) atomicAdd(&sum[RT_COUNT_PRIMARY], 2ull * a.one.cam.W * a.one.cam.H);
+      if (c.x) atomicAdd(&sum[RT_COUNT_REFLECTION], c.x);
+      if (c.y) atomicAdd(&sum[RT_COUNT_SHADOW], c.y);
+      if (c.z) atomicAdd(&sum[RT_COUNT_ERRORS], 1ull);
+    } else {
+      reinterpret_cast<uint4*>(a.ctr)[blockIdx.x] = c;  // for k_path_finish, in the counters' bytes
+    }
   }
 }
 static_assert(offsetof(Counters, trace_work) + sizeof(Counters::trace_work) / (RT_MAX_DEPTH + 2) * (RT_MAX_DEPTH + 1) >=
                   kMaxTraceBlocks * sizeof(uint4),
               "the blocks' counts end before the work counters in use");
 
-// Adds the counts of k_path's blocks.
+// Adds the counts of k_path's blocks where they do not do it themselves.
 __global__ __launch_bounds__(kBlock) void k_path_finish(const uint4* counts, int blocks, int64_t primary, int64_t* out) {
   __shared__ unsigned long long s_sum[2];
   __shared__ uint32_t s_err;
@@ -1821,12 +1829,16 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
       k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    // The blocks add their ray counts to the caller's by themselves (256x256: spheres 18.7 us with a launch for it, 16.5
+    // so; 100 triangles 51.9, 48.2; 641x479, 13k triangles 237, 234), but where all of them end at once and would wait
+    // for each other's atomics: without a tree, one batch after another (spheres at 1080p 107 and 131 us).
+    int64_t* direct = flat && dynamic ? nullptr : ra.ray_counts;
     if (flat)
-      k_path<false><<<grid, kBlock, 0, s>>>(a, blog, dynamic);
+      k_path<false><<<grid, kBlock, 0, s>>>(a, blog, dynamic, direct);
     else
-      k_path<true><<<grid, kBlock, 0, s>>>(a, blog, dynamic);
+      k_path<true><<<grid, kBlock, 0, s>>>(a, blog, dynamic, direct);
     e = hipGetLastError();
-    if (e != hipSuccess || !ra.ray_counts) return e;
+    if (e != hipSuccess || !ra.ray_counts || direct) return e;
     k_path_finish<<<1, kBlock, 0, s>>>(reinterpret_cast<const uint4*>(a.ctr), int(grid),
                                        2 * int64_t(ra.one.cam.W) * ra.one.cam.H, ra.ray_counts);
     return hipGetLastError();
