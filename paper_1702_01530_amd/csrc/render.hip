@@ -113,11 +113,6 @@ __device__ inline int lanes_below(uint64_t mask) {
   return int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
 }
 
-// The lane id, computed where it is called (its inputs are no registers, so it need not be kept until then).
-__device__ inline uint32_t fresh_lane() {
-  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-}
-
 // A pointer to global memory held in scalar registers.  The empty asm hides where it came from, so that it
 // is not loaded again, and the cast around it keeps accesses through it global ones (not flat).
 template <class T>
@@ -182,11 +177,6 @@ __device__ inline int item_of(const KArgs& a, int64_t p) {
       hi = mid - 1;
   }
   return lo;
-}
-
-template <bool MULTI>
-__device__ inline const DevItem& item_ref(const KArgs& a, int k) {
-  return MULTI ? a.items[k] : a.one;
 }
 
 // ---------------------------------------------------------------------------------------------
