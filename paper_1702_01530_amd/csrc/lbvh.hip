@@ -32,6 +32,7 @@
 #include <utility>
 #include <vector>
 
+#include "cluster_plan.h"
 #include "rt_internal.h"
 #define SRT_HD __host__ __device__
 #include "ploc_rule.h"
@@ -680,9 +681,7 @@ __global__ __launch_bounds__(kBlock) void k_ploc_init(const uint32_t* __restrict
 
 constexpr int kPlocBlock = 512;    // threads of a search block ...
 constexpr int kPlocLanes = 4;      // ... which share a position's search this many at a time
-constexpr int kPlocBlocks = 1024;  // most blocks of a round: each sums the others' counts
 constexpr int kPlocFew = 65536;    // below this many, tiles of kPairOwn positions leave most of the chip idle
-constexpr int kPlocTail = 1024;    // clusters that one workgroup takes over
 constexpr int kPackBlocks = 1024;  // workgroups that pack triangles beside it
 
 // The positions that block `b` of `blocks` handles in a round of n clusters: whole tiles of `own`.
@@ -1760,16 +1759,15 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
       int32_t* partner = nullptr;
       const PlocNodes made{tree, nodebox, dp_cost};
       bool packed = false;
-      int round = 0;
-      double expected = double(T);  // clusters left, were every round to leave the usual share
-      // `rounds` clustering rounds and the one-workgroup rest.  A round leaves 0.57 of the clusters at first
-      // and 0.81 to 0.83 later; a grid made for too few clusters takes more tiles a block, and a round that
-      // finds at most kPlocTail clusters does nothing.
-      auto cluster = [&](int rounds) -> hipError_t {
-        for (int k = 0; k < rounds; ++k, ++round) {
-          const bool few = expected < kPlocFew;
+      ClusterPlan rounds(T);
+      const int& round = rounds.rounds;
+      // `count` clustering rounds and the one-workgroup rest.  A grid made for too few clusters takes more tiles a
+      // block, and a round that finds at most kPlocTail clusters does nothing.
+      auto cluster = [&](int count) -> hipError_t {
+        for (int k = 0; k < count; ++k, rounds.next()) {
+          const bool few = rounds.expected < kPlocFew;
           const unsigned own = few ? kPlocBlock / kPlocLanes - 2 * kPlocRadius : kPairOwn;
-          const unsigned grid = unsigned(std::min<double>(kPlocBlocks, std::max(1.0, std::ceil(expected / own))));
+          const unsigned grid = unsigned(rounds.blocks(own));
           if (few)
             k_ploc_nn<<<grid, kPlocBlock, 0, stream>>>(cl, state, round & 1, partner, counts);
           else
@@ -1777,7 +1775,6 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
           if ((e = hipGetLastError()) != hipSuccess) return e;
           k_ploc_compact<<<grid, kBlock, 0, stream>>>(cl, state, round & 1, partner, counts, own, made);
           if ((e = hipGetLastError()) != hipSuccess) return e;
-          expected = std::max(double(kPlocTail), expected * (round == 0 ? 0.6 : 0.83));
         }
         const int64_t blocks = packed ? 0 : std::min<int64_t>(kPackBlocks, (T + kPlocTail - 1) / kPlocTail);
         packed = true;
@@ -1794,7 +1791,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         partner = reinterpret_cast<int32_t*>(scratch + plan.ploc_partner_off);
         k_ploc_init<<<blocks_for(T), kBlock, 0, stream>>>(i0, lo, hi, T, cl);
         SRT_LAUNCH_CHECK();
-        SRT_CHECK(cluster(T <= kPlocTail ? 0 : 2 + int(std::ceil(std::log(double(T) / kPlocTail) / 0.2))));
+        SRT_CHECK(cluster(rounds.first()));
       } else {
         k_pack<<<blocks_for(T), kBlock, 0, stream>>>(pack);
         SRT_LAUNCH_CHECK();
@@ -1846,7 +1843,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         if (tree && done.wide[level & 1].m == 0) break;
         // an unusual tree: more rounds or levels than the launches above.  Every round merges a pair and
         // every level adds a node, so this ends.
-        if (!tree) SRT_CHECK(cluster(16));
+        if (!tree) SRT_CHECK(cluster(rounds.look(int64_t(done.ploc[round & 1].n))));
         SRT_CHECK(collapse(std::max(wide_levels, 4)));
       }
       result->num_nodes = done.wide[level & 1].allocated;
