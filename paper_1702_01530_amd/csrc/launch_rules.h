@@ -1,0 +1,49 @@
+// Which launches a render takes, from the sizes of its scene and image.  Plain C++: a host check runs it too.
+// Results never depend on these rules.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace srt {
+
+struct SceneSize {
+  int32_t T, S, P, L;
+  bool flat;  // without a tree, or rendered as if it had none
+};
+
+// Primitives that every ray of the scene is tested against.
+inline int64_t walked(const SceneSize& s) { return int64_t(s.S) + s.P + (s.flat ? s.T : 0); }
+
+// Whether the waves of a workgroup share a batch's walk (k_trace_flat).  A launch of few rays lasts as long as one walk;
+// a full one gains nothing from the shares and pays for joining them.  64x48, depth 0, 1 light: 120 triangles 75 us
+// alone and 51 shared, 511: 160 and 63; 1920x1080: 394 and 646, 1371 and 1647.  256x256, depth 4, 4 lights: 256 spheres
+// 336 and 307, 1024: 823 and 663.
+constexpr int kFlatSplit = 512;
+inline bool flat_splits(const SceneSize& s) { return walked(s) >= kFlatSplit; }
+
+// Whether a whole frame goes through k_path.
+//
+// Without a tree: at most kPathFlat triangles (1920x1080, depth 8, 1 light: 120 triangles 354 us and 527 through the
+// queues, 255: 840 and 1037; 64x48: 255 triangles 255 and 270, 400: 474 and 413).  Shadow rays wait for the walks before
+// theirs, so a small frame takes few spheres and planes, the fewer the more lights there are: 256x256, depth 4, 64
+// spheres: 104 and 159 us with 1 light, 167 and 188 with 4; 256: 285 and 304, 467 and 339; 1024: 996 and 439 with 1.  A
+// large one has waves to run meanwhile (1920x1080, depth 4: 256 spheres 2188 and 2420, 3351 and 3968; 1024: 9882 and
+// 9986 with 1 light, 2029 and 3233 at depth 0).
+//
+// With a tree: as long as the rays, counted as paths x (1 + lights), are few for the tree's size.  Terrains, depth 4:
+// 800x600 with 4 lights is 4.8 M: 13k triangles 453 us and 476 through the queues; 640x480 with 8 lights 5.5 M: 531 and
+// 511; 212k triangles: 640x480 with 2 lights is 1.8 M: 407 and 453, with 4 3.1 M: 520 and 524.  Scattered triangles that
+// are all mirrors cross earlier (depth 3, 4 lights: 30k triangles at 640x480 1166 and 911, 100k at 320x240 767 and 673),
+// large images of few lights later (212k, 1280x960, 1 light, 4.9 M: 648 and 699).
+constexpr int kPathFlat = 256;
+constexpr int kPathWalk = 512;
+constexpr int64_t kPathMany = int64_t(1) << 21;
+constexpr int kPathSmallTree = 32768;  // triangles; the nodes fit an XCD's L2 several times
+inline bool path_wins(const SceneSize& s, int64_t paths) {
+  const int64_t analytic = int64_t(s.S) + s.P;
+  if (s.flat) return s.T <= kPathFlat && (paths >= kPathMany || analytic * std::max(s.L, 1) <= kPathWalk);
+  return paths * (1 + s.L) <= (s.T <= kPathSmallTree ? 5000000 : 2500000);
+}
+
+}  // namespace srt

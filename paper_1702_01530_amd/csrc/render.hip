@@ -964,19 +964,20 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
 //
 // Primitives are the same for the whole wave, so they are scalar loads and a test is bound by the VALU: 45
 // instructions a triangle, half of them behind the division.  Most waves find that no lane is inside a
-// triangle's first edge pair long before that (24 instructions on average).  With many triangles, SEGS waves
-// share a batch of 64 rays, each over its part of the triangles: a frame of 131,072 paths is 2,048 batches, a
-// quarter of the waves the chip holds, and a launch of few rays would last as long as one wave's walk over
-// all triangles (0.26 us each, a dependent load, before).  256x256, 2,432 triangles, depth 1, 1 light: 1815 us
-// with the walk inside k_trace, 357 this way (390 with records loaded two at a time, 420 one at a time; 4 or
-// 16 waves a batch: 463).
+// triangle's first edge pair long before that (24 instructions on average).  With many primitives, SEGS waves
+// share a batch of 64 rays, each over its part of the spheres, planes and triangles: a frame of 131,072 paths is
+// 2,048 batches, a quarter of the waves the chip holds, and a launch of few rays would last as long as one wave's
+// walk over all of them (0.26 us a triangle, a dependent load, before).  256x256, 2,432 triangles, depth 1, 1
+// light: 1815 us with the walk inside k_trace, 357 this way (390 with records loaded two at a time, 420 one at a
+// time; 4 or 16 waves a batch: 463).  640x480, depth 4, 2 lights, 4,000 spheres and 520 triangles: 66.7 ms with all
+// spheres in the first part, loaded one at a time, 9.1 this way; 256x256, 4 lights, 1,024 spheres: 2390 us through
+// k_path, 663.
 // ---------------------------------------------------------------------------------------------
 
 #ifndef SRT_FLAT_STEP
 #define SRT_FLAT_STEP 4
 #endif
-constexpr int kFlatSegs = 8;        // waves that share a batch's triangles ...
-constexpr int kFlatSplit = 512;     // ... from this many on
+constexpr int kFlatSegs = 8;        // waves that share a batch's walk
 constexpr int kFlatWaves = 8192;    // waves of a full grid
 template <int SEGS>
 constexpr int kFlatBlock = SEGS > 1 ? 64 * SEGS : kBlock;
@@ -1026,45 +1027,67 @@ __device__ __attribute__((always_inline)) inline void flat_triangles(const float
   }
 }
 
-// Element k of a scene array, as a scalar load: k is the same for the wave, and the array was written by an
-// earlier launch.
-__device__ inline float4 scalar_load(const float4* p, int k) {
+// test(value, k) for elements first .. last - 1 of a scene array, loaded as the triangles' records are.
+template <class Test>
+__device__ __attribute__((always_inline)) inline void flat_each(const float4* p, int first, int last, Test test) {
   typedef __attribute__((address_space(4))) const float4 const_float4;
-  return *(const float4*)((const_float4*)p + __builtin_amdgcn_readfirstlane(k));
+  constexpr int kStep = SRT_FLAT_STEP;
+  const const_float4* v = (const const_float4*)p;
+  int k = first;
+  for (; k + kStep <= last; k += kStep) {
+    float4 r[kStep];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) r[j] = ((const float4*)(v + __builtin_amdgcn_readfirstlane(k)))[j];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) test(r[j], k + j);
+  }
+  for (; k < last; ++k) test(*(const float4*)(v + __builtin_amdgcn_readfirstlane(k)), k);
 }
 
-// The nearest hit among triangles first .. last - 1 and, with `rest`, the spheres and planes.
-__device__ __attribute__((always_inline)) inline Best flat_closest(const DevScene& sc, bool rest, int first, int last,
-                                                                   float3 o, float3 d, float tmin, int exclude) {
+// One of `of` equal shares of a scene's primitives.
+struct Part {
+  int k, of;
+  __device__ inline int first(int n) const { return int(int64_t(n) * k / of); }
+  __device__ inline int last(int n) const { return int(int64_t(n) * (k + 1) / of); }
+};
+
+// The nearest hit among the primitives of a share.
+__device__ __attribute__((always_inline)) inline Best flat_closest(const DevScene& sc, Part part, float3 o, float3 d,
+                                                                   float tmin, int exclude) {
   Best best{INFINITY, -1, 0x7fffffff};
   auto accept = [&](float t, int key, int id) {
     if (key != exclude && t < INFINITY && (t < best.t || (t == best.t && id < best.id))) best = Best{t, key, id};
   };
-  if (rest) {
-    for (int k = 0; k < sc.S; ++k)
-      accept(sphere_t(scalar_load(sc.spheres, k), o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k);
-    for (int k = 0; k < sc.P; ++k) {
-      const int key = sc.T + sc.S + k;
-      accept(plane_t(scalar_load(sc.planes, k), o, d, tmin, next_up(best.t)), key, key);
-    }
-  }
-  flat_triangles(sc.tris, first, last, o, d, tmin, [&] { return next_up(best.t); }, accept);
+  flat_each(sc.spheres, part.first(sc.S), part.last(sc.S),
+            [&](float4 s, int k) { accept(sphere_t(s, o, d, tmin, next_up(best.t)), sc.T + k, sc.T + k); });
+  flat_each(sc.planes, part.first(sc.P), part.last(sc.P), [&](float4 p, int k) {
+    const int key = sc.T + sc.S + k;
+    accept(plane_t(p, o, d, tmin, next_up(best.t)), key, key);
+  });
+  flat_triangles(sc.tris, part.first(sc.T), part.last(sc.T), o, d, tmin, [&] { return next_up(best.t); }, accept);
   return best;
 }
 
 // Whether any of them lies in (kSecondaryTmin, dist); in steps, so that a wave whose rays are all answered stops.
-__device__ __attribute__((always_inline)) inline bool flat_occluded(const DevScene& sc, bool rest, int first, int last,
-                                                                    float3 o, float3 d, float dist, int exclude) {
+__device__ __attribute__((always_inline)) inline bool flat_occluded(const DevScene& sc, Part part, float3 o, float3 d,
+                                                                    float dist, int exclude) {
   bool found = false;
   auto accept = [&](float t, int key, int) { found = found || (key != exclude && t < INFINITY); };
-  if (rest) {
-    for (int k = 0; k < sc.S; ++k)
-      accept(sphere_t(scalar_load(sc.spheres, k), o, d, kSecondaryTmin, dist), sc.T + k, 0);
-    for (int k = 0; k < sc.P; ++k)
-      accept(plane_t(scalar_load(sc.planes, k), o, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0);
-  }
-  for (int k = first; k < last && !__all(found); k += 64)
-    flat_triangles(sc.tris, k, min(k + 64, last), o, d, kSecondaryTmin, [&] { return dist; }, accept);
+  auto steps = [&](int n, auto range) {
+    const int last = part.last(n);
+    for (int k = part.first(n); k < last && !__all(found); k += 64) range(k, min(k + 64, last));
+  };
+  steps(sc.S, [&](int first, int last) {
+    flat_each(sc.spheres, first, last,
+              [&](float4 s, int k) { accept(sphere_t(s, o, d, kSecondaryTmin, dist), sc.T + k, 0); });
+  });
+  steps(sc.P, [&](int first, int last) {
+    flat_each(sc.planes, first, last,
+              [&](float4 p, int k) { accept(plane_t(p, o, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0); });
+  });
+  steps(sc.T, [&](int first, int last) {
+    flat_triangles(sc.tris, first, last, o, d, kSecondaryTmin, [&] { return dist; }, accept);
+  });
   return found;
 }
 
@@ -1083,7 +1106,7 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
   uint32_t total = nc_pad;
   if (depth >= 1)
     for (int l = 0; l < LS; ++l) total += round_up(a.ctr->shadow_count[depth - 1][l], 6);
-  const int first = int(int64_t(sc.T) * seg / SEGS), last = int(int64_t(sc.T) * (seg + 1) / SEGS);
+  const Part part{seg, SEGS};
   constexpr uint32_t kPer = SEGS > 1 ? 1 : kFlatBlock<SEGS> / 64;  // batches a block holds at a time
   const uint32_t mine = blockIdx.x * kPer + (SEGS > 1 ? 0u : uint32_t(wave));
   for (uint32_t base = mine * 64u; base < total; base += gridDim.x * kPer * 64u) {  // block-uniform with SEGS > 1
@@ -1110,7 +1133,7 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
       }
       Best best{INFINITY, -1, 0x7fffffff};
       if (valid)
-        best = flat_closest(sc, seg == 0, first, last, o, d, depth == 0 ? 0.0f : kSecondaryTmin, exclude);
+        best = flat_closest(sc, part, o, d, depth == 0 ? 0.0f : kSecondaryTmin, exclude);
       if (SEGS > 1) {
         s_t[wave * 64 + lane] = best.t;
         s_id[wave * 64 + lane] = best.id;
@@ -1145,7 +1168,7 @@ __global__ __launch_bounds__(kFlatBlock<SEGS>) void k_trace_flat(KArgs a, int de
         const float3 P = f3(rec);
         float dist;
         const float3 d = shadow_dir(sc.lights, l, P, &dist);
-        found = flat_occluded(sc, seg == 0, first, last, P, d, dist, __float_as_int(rec.w));
+        found = flat_occluded(sc, part, P, d, dist, __float_as_int(rec.w));
       }
       uint64_t hits = __ballot(found);
       if (SEGS > 1) {
@@ -1386,18 +1409,6 @@ __global__ __launch_bounds__(kShadeBlock) __attribute__((amdgpu_waves_per_eu(MUL
 // spilled registers; 4 without spills or 6 with 37 take 5% longer on that frame, which now takes 235 us.
 // ---------------------------------------------------------------------------------------------
 
-// Which frames k_path takes.  Without a tree: at most kPathFlat triangles (1920x1080, depth 4, 2 lights: 42
-// triangles 367 vs 547 us through the queues, 148: 939 vs 1045, 262: 1695 vs 1698, 472: 2833 vs 2809).  With
-// one: as long as the rays, counted as paths x (1 + lights), are few for the tree's size.  640x480 with 4
-// lights is 3.1 M: 17k triangles 291 vs 304 us, 160k 449 vs 420, 3.4M 566 vs 548; 1024x768 with 2 lights is
-// 4.7 M: 17k triangles 414 vs 457, 160k 693 vs 669; 640x480 with 2 lights is 1.8 M: 362 vs 436 and 450 vs 564.
-constexpr int kPathFlat = 256;
-constexpr int kPathSmallTree = 32768;  // triangles; the nodes fit an XCD's L2 several times
-inline bool path_wins(const DevScene& sc, bool flat, int64_t paths) {
-  if (flat) return sc.T <= kPathFlat;
-  return paths * (1 + sc.L) <= (sc.T <= kPathSmallTree ? 5000000 : 2500000);
-}
-
 #ifndef SRT_PATH_WAVES
 #define SRT_PATH_WAVES 5
 #endif
@@ -1453,7 +1464,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
           t = tk;
         });
       } else if (alive) {
-        const Best b = flat_closest(sc, true, 0, sc.T, o, d, tmin, exclude);
+        const Best b = flat_closest(sc, Part{0, 1}, o, d, tmin, exclude);
         key = b.key;
         t = b.t;
       }
@@ -1511,7 +1522,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
           traverse<true, false, false>(sc, cast, Ray{from_P, Ld, kSecondaryTmin, dist, from_key}, false, st, share,
                                        unused, unused, [&](int k, float) { visible = k < 0; });
         } else if (cast) {
-          visible = !flat_occluded(sc, true, 0, sc.T, from_P, Ld, dist, from_key);
+          visible = !flat_occluded(sc, Part{0, 1}, from_P, Ld, dist, from_key);
         }
         const uint64_t v = __ballot(visible);
         if (lane == 0) lds_put(&s_visible[wave][first >> 6], static_cast<unsigned long long>(v));
@@ -1790,6 +1801,8 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   };
   // Single scenes without a tree to walk have kernels of their own (the work counters are k_trace's).
   const bool flat = !multi && !count && (a.brute || !ra.one.sc.has_bvh);
+  SceneSize size = scene_size(ra.one.sc);
+  size.flat = flat;
   const unsigned gstream =
       unsigned(std::max<int64_t>(1, std::min<int64_t>((ra.path_count + kBlock - 1) / kBlock, ra.stream_blocks)));
   const unsigned gshade = unsigned(std::max<int64_t>(
@@ -1798,7 +1811,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   // A small frame in one launch: whole frames only (the ray counts take the pixels as traced), and neither ray-tree
   // signatures nor the timer, whose stages are the queue kernels'.
   const bool whole = ra.path_begin == 0 && ra.path_count == ra.frame_paths;
-  if (!multi && !count && !ids && !timer && whole && path_wins(ra.one.sc, flat, ra.path_count)) {
+  if (!multi && !count && !ids && !timer && whole && path_wins(size, ra.path_count)) {
     // A batch of 64 paths a wave, or of fewer where that still leaves every wave of the full grid at most one.  With more
     // batches than waves run at once (k_path's registers allow resident blocks), those take them one by one: in fixed
     // shares, or left to the dispatcher, the last ones decide (641x479, 13k triangles: 251 us in fixed shares, 235 so;
@@ -1844,7 +1857,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   const int D = a.dmax;
   for (int d = 0; d <= D + 1; ++d) {
     if (flat) {
-      if (ra.one.sc.T >= kFlatSplit)
+      if (flat_splits(size))
         e = launch(k_trace_flat<kFlatSegs>, gtrace(d, 64, kFlatWaves / kFlatSegs), a, d, s, timer, RT_STAGE_TRACE,
                    kFlatBlock<kFlatSegs>);
       else

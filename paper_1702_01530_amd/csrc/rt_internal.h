@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "../../include/stereort.h"
+#include "launch_rules.h"
 
 namespace srt {
 
@@ -121,6 +122,8 @@ struct Scene;  // host handle body
 // ---------------------------------------------------------------------------------------------
 // Host-side entry points of the translation units
 // ---------------------------------------------------------------------------------------------
+
+inline SceneSize scene_size(const DevScene& sc) { return SceneSize{sc.T, sc.S, sc.P, sc.L, sc.has_bvh == 0}; }
 
 struct BuildPlan {
   int64_t T;

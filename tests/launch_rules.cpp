@@ -1,0 +1,32 @@
+// Host-side check of paper_1702_01530_amd/csrc/launch_rules.h.  Prints one line per claim and exits non-zero on a failure.
+#include <cstdio>
+
+#include "../paper_1702_01530_amd/csrc/launch_rules.h"
+
+using namespace srt;
+
+static int failures = 0;
+static void claim(bool ok, const char* what) {
+  std::printf("%s %s\n", ok ? "OK" : "FAIL", what);
+  if (!ok) ++failures;
+}
+
+static void spheres_are_work() {
+  const int64_t small = 2 * 256 * 256, large = 2 * 1920 * 1080;
+  claim(path_wins({0, 8, 1, 1, true}, small), "a few spheres go through k_path");
+  claim(path_wins({0, 8, 1, 8, true}, small), "with any lights");
+  claim(!path_wins({0, 4096, 1, 1, true}, small), "a small frame of many spheres does not");
+  claim(!path_wins({0, 1, 4096, 1, true}, small), "nor one of many planes");
+  claim(!path_wins({100, 500, 0, 2, true}, small), "nor one of triangles and many spheres");
+  claim(path_wins({0, 256, 1, 1, true}, small) && !path_wins({0, 256, 1, 4, true}, small), "lights count");
+  claim(path_wins({0, 1024, 1, 4, true}, large), "a large frame has waves to run meanwhile");
+  claim(path_wins({256, 0, 0, 8, true}, small) && !path_wins({257, 0, 0, 1, true}, large), "triangles as before");
+  claim(!flat_splits({511, 0, 0, 1, true}) && flat_splits({512, 0, 0, 1, true}), "triangles split as before");
+  claim(!flat_splits({0, 510, 1, 1, true}) && flat_splits({0, 511, 1, 1, true}), "spheres and planes split too");
+  claim(flat_splits({100, 412, 0, 1, true}) && flat_splits({0, 1 << 20, 1 << 16, 1, true}), "all together");
+}
+
+int main() {
+  spheres_are_work();
+  return failures ? 1 : 0;
+}

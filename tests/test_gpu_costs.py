@@ -1,0 +1,65 @@
+"""What renders cost beside others of the same work: a path that falls out of its kernel's shape costs several times as
+much.  The limits lie a factor of two or more from both sides (see each test)."""
+import numpy as np
+import pytest
+
+from tests.helpers import make_scene, material, mono_camera
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1702_01530_amd import rt
+    rt.lib()
+    return torch
+
+
+def _time(torch, call, repeats=9):
+    """The shortest of several calls, in microseconds of the device."""
+    for _ in range(2):
+        call()
+    best = float("inf")
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(repeats):
+        torch.cuda.synchronize()
+        start.record()
+        call()
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(end) * 1e3)
+    return best
+
+
+def _scene(spheres=0, tris=0, seed=3, lights=2):
+    r = np.random.default_rng(seed)
+    size = min(1.0, 8 / np.cbrt(max(spheres + tris, 1)))
+    balls = np.concatenate([r.uniform((-5, 0, 3), (5, 5, 13), (spheres, 3)), r.uniform(0.1, 0.5, (spheres, 1)) * size], 1)
+    t = r.uniform((-5, 0, 3), (5, 5, 13), (tris, 1, 3)) + r.uniform(-0.4, 0.4, (tris, 3, 3)) * size
+    return make_scene(tris=t, spheres=balls, lights=[[-6, 8, 2, 0.5, 0.5, 0.5], [6, 6, 12, 0.5, 0.5, 0.5]][:lights],
+                      materials=[material(ks=(0.3,) * 3, kr=(0.5,) * 3)], ambient=(0.05,) * 3)
+
+
+def _camera(width, height, depth):
+    return mono_camera(center=(0, 1.5, -3), width=width, height=height, depth=depth, baseline=0.065, convergence=5.0)
+
+
+def _frame(torch, scene, cam, **kw):
+    from paper_1702_01530_amd.stereo import GpuScene, Workspace, alloc_outputs, render_stereo
+    gs = GpuScene(scene, **kw)
+    ws, outs = Workspace.for_camera(cam, gs.num_lights), alloc_outputs(cam, gs.num_lights, gs.device)
+    us = _time(torch, lambda: render_stereo(gs, cam, workspace=ws, outputs=outs))
+    gs.close()
+    return us
+
+
+def test_spheres_beside_triangles(torch_cuda):
+    """4,000 spheres and 520 triangles against 20 and 4,500, without a tree: 3.3 and 2.7 ms; with all spheres in one of
+    the waves that share the walk 24.3."""
+    cam = _camera(640, 480, 1)
+    spheres, tris = (_frame(torch_cuda, _scene(s, t), cam, accel="none") for s, t in ((4000, 520), (20, 4500)))
+    print(f"[cost] spheres {spheres:.0f} triangles {tris:.0f} us", flush=True)
+    assert spheres < 4 * tris
