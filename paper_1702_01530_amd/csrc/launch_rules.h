@@ -35,14 +35,18 @@ inline bool flat_splits(const SceneSize& s) { return walked(s) >= kFlatSplit; }
 // 800x600 with 4 lights is 4.8 M: 13k triangles 453 us and 476 through the queues; 640x480 with 8 lights 5.5 M: 531 and
 // 511; 212k triangles: 640x480 with 2 lights is 1.8 M: 407 and 453, with 4 3.1 M: 520 and 524.  Scattered triangles that
 // are all mirrors cross earlier (depth 3, 4 lights: 30k triangles at 640x480 1166 and 911, 100k at 320x240 767 and 673),
-// large images of few lights later (212k, 1280x960, 1 light, 4.9 M: 648 and 699).
+// large images of few lights later (212k, 1280x960, 1 light, 4.9 M: 648 and 699).  Spheres and planes beside the tree
+// count as without one (5k triangles, depth 3, 640x480: 63 spheres 493 and 507 with 1 light, 886 and 706 with 4; 255
+// spheres 811 and 714, 1355 and 985; 1,023: 2216 and 1536; 64x48, 1,023 spheres: 1160 and 864).
 constexpr int kPathFlat = 256;
 constexpr int kPathWalk = 512;
+constexpr int kPathTreeWalk = 128;
 constexpr int64_t kPathMany = int64_t(1) << 21;
 constexpr int kPathSmallTree = 32768;  // triangles; the nodes fit an XCD's L2 several times
 inline bool path_wins(const SceneSize& s, int64_t paths) {
   const int64_t analytic = int64_t(s.S) + s.P;
   if (s.flat) return s.T <= kPathFlat && (paths >= kPathMany || analytic * std::max(s.L, 1) <= kPathWalk);
+  if (analytic > kPathTreeWalk) return false;
   return paths * (1 + s.L) <= (s.T <= kPathSmallTree ? 5000000 : 2500000);
 }
 

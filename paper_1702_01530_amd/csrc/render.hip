@@ -39,6 +39,10 @@
 #define SRT_TRACE_WAVES_PER_EU 8
 #endif
 
+#ifndef SRT_FLAT_STEP
+#define SRT_FLAT_STEP 4
+#endif
+
 namespace srt {
 namespace {
 
@@ -525,6 +529,24 @@ __device__ inline float shfl_f(float v, int src) {
 }
 __device__ inline int shfl_i(int v, int src) { return __builtin_amdgcn_ds_bpermute(src << 2, v); }
 
+// test(value, k) for elements first .. last - 1 of a scene array, which are the same for the whole wave and were written
+// by an earlier launch: scalar loads, kStep at a time, so that a wave waits once for all of them.
+template <class Test>
+__device__ __attribute__((always_inline)) inline void flat_each(const float4* p, int first, int last, Test test) {
+  typedef __attribute__((address_space(4))) const float4 const_float4;
+  constexpr int kStep = SRT_FLAT_STEP;
+  const const_float4* v = (const const_float4*)p;
+  int k = first;
+  for (; k + kStep <= last; k += kStep) {
+    float4 r[kStep];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) r[j] = ((const float4*)(v + __builtin_amdgcn_readfirstlane(k)))[j];
+#pragma unroll
+    for (int j = 0; j < kStep; ++j) test(r[j], k + j);
+  }
+  for (; k < last; ++k) test(*(const float4*)(v + __builtin_amdgcn_readfirstlane(k)), k);
+}
+
 // Traverses the rays of one wave (all lanes call it together; `mine` marks the lanes that hold a ray).
 // ANY = false: closest hit, minimum t, exact ties to the smaller original id; the limit starts at +inf.
 // ANY = true : occlusion, stops at the first primitive with t in (tmin, limit).
@@ -576,14 +598,16 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
   int node = kDoneRef;
   st.sp = 0;
   if (mine) {
-    for (int s = 0; s < sc.S && !(ANY && found); ++s) {
-      const int key = sc.T + s;
-      accept(sphere_t(sc.spheres[s], r.o, r.d, r.tmin, r.limit), key, key);
-    }
-    for (int p = 0; p < sc.P && !(ANY && found); ++p) {
-      const int key = sc.T + sc.S + p;
-      accept(plane_t(sc.planes[p], r.o, r.d, r.tmin, r.limit), key, key);
-    }
+    // Spheres and planes are the same for the whole wave.  Loaded one at a time by each lane, 2,000 of them beside a tree
+    // of 5,000 triangles, 256x256, 2 lights, depth 3: 3030 us, 1670 this way.
+    for (int k = 0; k < sc.S && !(ANY && __all(found)); k += 64)
+      flat_each(sc.spheres, k, min(k + 64, sc.S),
+                [&](float4 s, int i) { accept(sphere_t(s, r.o, r.d, r.tmin, r.limit), sc.T + i, sc.T + i); });
+    for (int k = 0; k < sc.P && !(ANY && __all(found)); k += 64)
+      flat_each(sc.planes, k, min(k + 64, sc.P), [&](float4 p, int i) {
+        const int key = sc.T + sc.S + i;
+        accept(plane_t(p, r.o, r.d, r.tmin, r.limit), key, key);
+      });
     if (FLAT && (brute || !sc.has_bvh)) {
       for (int k = 0; k < sc.T && !(ANY && found); ++k) {
         int id;
@@ -974,9 +998,6 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
 // k_path, 663.
 // ---------------------------------------------------------------------------------------------
 
-#ifndef SRT_FLAT_STEP
-#define SRT_FLAT_STEP 4
-#endif
 constexpr int kFlatSegs = 8;        // waves that share a batch's walk
 constexpr int kFlatWaves = 8192;    // waves of a full grid
 template <int SEGS>
@@ -1025,23 +1046,6 @@ __device__ __attribute__((always_inline)) inline void flat_triangles(const float
     const float4* r = (const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k));
     test(r[0], r[1], r[2], k);
   }
-}
-
-// test(value, k) for elements first .. last - 1 of a scene array, loaded as the triangles' records are.
-template <class Test>
-__device__ __attribute__((always_inline)) inline void flat_each(const float4* p, int first, int last, Test test) {
-  typedef __attribute__((address_space(4))) const float4 const_float4;
-  constexpr int kStep = SRT_FLAT_STEP;
-  const const_float4* v = (const const_float4*)p;
-  int k = first;
-  for (; k + kStep <= last; k += kStep) {
-    float4 r[kStep];
-#pragma unroll
-    for (int j = 0; j < kStep; ++j) r[j] = ((const float4*)(v + __builtin_amdgcn_readfirstlane(k)))[j];
-#pragma unroll
-    for (int j = 0; j < kStep; ++j) test(r[j], k + j);
-  }
-  for (; k < last; ++k) test(*(const float4*)(v + __builtin_amdgcn_readfirstlane(k)), k);
 }
 
 // One of `of` equal shares of a scene's primitives.

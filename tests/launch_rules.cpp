@@ -26,7 +26,17 @@ static void spheres_are_work() {
   claim(flat_splits({100, 412, 0, 1, true}) && flat_splits({0, 1 << 20, 1 << 16, 1, true}), "all together");
 }
 
+static void spheres_beside_a_tree() {
+  const int64_t paths = 2 * 640 * 480;
+  claim(path_wins({13000, 0, 0, 2, false}, paths), "a small frame of a tree goes through k_path");
+  claim(path_wins({13000, 8, 1, 2, false}, paths), "with a few spheres too");
+  claim(!path_wins({5000, 2000, 1, 2, false}, paths), "not with many");
+  claim(!path_wins({100, 0, 1024, 1, false}, paths), "nor with many planes");
+  claim(!path_wins({13000, 0, 0, 8, false}, paths), "rays count as before");
+}
+
 int main() {
   spheres_are_work();
+  spheres_beside_a_tree();
   return failures ? 1 : 0;
 }

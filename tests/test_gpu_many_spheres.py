@@ -62,3 +62,17 @@ def test_walks_without_a_tree(torch_cuda, S, P, T, size):
     _same(torch_cuda, gs, mono_camera(center=(0, 2, 0), width=size[0], height=size[1], depth=3, baseline=0.065,
                                       convergence=5.0), (S, P, T, size))
     gs.close()
+
+
+# beside a tree: around the limit of the frames in one launch (128 in all) and the steps of 64; 180x130 has batches of 8
+# rays a wave, 420x400 of 32
+@pytest.mark.parametrize("S,P,T", [(1, 0, 2), (5, 4, 40), (64, 0, 40), (65, 63, 300), (66, 63, 300), (300, 70, 2000)])
+@pytest.mark.parametrize("size", [(1, 1), (180, 130), (420, 400)])
+@pytest.mark.parametrize("accel", ["ploc", "karras"])
+def test_walks_beside_a_tree(torch_cuda, S, P, T, size, accel):
+    from paper_1702_01530_amd.stereo import GpuScene
+    print(f"[spheres] {S} {P} {T} {size} {accel}", flush=True)
+    gs = GpuScene(_scene(S, P, T), accel=accel)
+    _same(torch_cuda, gs, mono_camera(center=(0, 2, 0), width=size[0], height=size[1], depth=3, baseline=0.065,
+                                      convergence=5.0), (S, P, T, size))
+    gs.close()
