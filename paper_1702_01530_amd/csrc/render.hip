@@ -47,6 +47,8 @@ namespace srt {
 namespace {
 
 constexpr int kBlock = kTraceBlock;
+constexpr int kFlatStep = SRT_FLAT_STEP;  // primitives that the kernels for scenes without a tree load at a time
+constexpr int kWalkStep = 2;              // triangles that a batch's traversal does: 4 spill 8 more registers
 constexpr int kWaves = kBlock / 64;
 constexpr int kStackLds = SRT_STACK_LDS;       // traversal stack entries per lane kept in LDS (power of two)
 constexpr int kStackGlobal = kStackMax - kStackLds;  // older entries spill to the workspace
@@ -529,20 +531,63 @@ __device__ inline float shfl_f(float v, int src) {
 }
 __device__ inline int shfl_i(int v, int src) { return __builtin_amdgcn_ds_bpermute(src << 2, v); }
 
+// True where the triangle test certainly rejects a barycentric coordinate num / det (signs and sizes only,
+// before the division): below 0 by more than an underflow can hide, or above 1 by more than rounding can.
+__device__ inline bool outside(float num_signed, float det_abs) {
+  return num_signed < -1e-30f * det_abs || num_signed > 1.0001f * det_abs;
+}
+
+// Tests a wave's rays against triangle records first .. last - 1, all lanes together; accept(t, record, id)
+// for the lanes with a candidate in (tmin, limit()).  STEP records are loaded at a time, so a wave waits once for
+// all of them.
+template <int STEP, class Limit, class Accept>
+__device__ __attribute__((always_inline)) inline void flat_triangles(const float4* tris, int first, int last, float3 o,
+                                                                     float3 d, float tmin, Limit limit, Accept accept) {
+  typedef __attribute__((address_space(4))) const float4 const_float4;  // written by an earlier launch only
+  auto test = [&](float4 a, float4 b, float4 c, int k) {
+    const float3 e1 = f3(b), e2 = f3(c);
+    TriTest m;
+    m.first(o, d, f3(a), e1, e2);
+    const uint32_t sign = __float_as_uint(m.det) & 0x80000000u;
+    const float ad = fabsf(m.det);
+    if (outside(__uint_as_float(__float_as_uint(m.un) ^ sign), ad)) return;
+    m.second(d, e1);
+    if (outside(__uint_as_float(__float_as_uint(m.vn) ^ sign), ad)) return;
+    if (m.det == 0.0f) return;
+    const float inv = 1.0f / m.det;
+    const float u = m.un * inv;
+    if (!(u >= 0.0f && u <= 1.0f)) return;
+    const float t = m.t(e2, inv, u, tmin, limit());
+    if (t < INFINITY) accept(t, k, __float_as_int(a.w));
+  };
+  const const_float4* recs = (const const_float4*)tris;
+  int k = first;
+  for (; k + STEP <= last; k += STEP) {
+    float4 r[3 * STEP];
+#pragma unroll
+    for (int j = 0; j < 3 * STEP; ++j) r[j] = ((const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k)))[j];
+#pragma unroll
+    for (int j = 0; j < STEP; ++j) test(r[3 * j], r[3 * j + 1], r[3 * j + 2], k + j);
+  }
+  for (; k < last; ++k) {
+    const float4* r = (const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k));
+    test(r[0], r[1], r[2], k);
+  }
+}
+
 // test(value, k) for elements first .. last - 1 of a scene array, which are the same for the whole wave and were written
-// by an earlier launch: scalar loads, kStep at a time, so that a wave waits once for all of them.
+// by an earlier launch: scalar loads, kFlatStep at a time, so that a wave waits once for all of them.
 template <class Test>
 __device__ __attribute__((always_inline)) inline void flat_each(const float4* p, int first, int last, Test test) {
   typedef __attribute__((address_space(4))) const float4 const_float4;
-  constexpr int kStep = SRT_FLAT_STEP;
   const const_float4* v = (const const_float4*)p;
   int k = first;
-  for (; k + kStep <= last; k += kStep) {
-    float4 r[kStep];
+  for (; k + kFlatStep <= last; k += kFlatStep) {
+    float4 r[kFlatStep];
 #pragma unroll
-    for (int j = 0; j < kStep; ++j) r[j] = ((const float4*)(v + __builtin_amdgcn_readfirstlane(k)))[j];
+    for (int j = 0; j < kFlatStep; ++j) r[j] = ((const float4*)(v + __builtin_amdgcn_readfirstlane(k)))[j];
 #pragma unroll
-    for (int j = 0; j < kStep; ++j) test(r[j], k + j);
+    for (int j = 0; j < kFlatStep; ++j) test(r[j], k + j);
   }
   for (; k < last; ++k) test(*(const float4*)(v + __builtin_amdgcn_readfirstlane(k)), k);
 }
@@ -609,11 +654,16 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
         accept(plane_t(p, r.o, r.d, r.tmin, r.limit), key, key);
       });
     if (FLAT && (brute || !sc.has_bvh)) {
-      for (int k = 0; k < sc.T && !(ANY && found); ++k) {
-        int id;
-        const float t = tri_t(sc.tris, k, r.o, r.d, r.tmin, r.limit, &id);
-        if (COUNT) ++ntris;
-        accept(t, k, id);
+      if (COUNT) {
+        for (int k = 0; k < sc.T && !(ANY && found); ++k) {
+          int id;
+          const float t = tri_t(sc.tris, k, r.o, r.d, r.tmin, r.limit, &id);
+          ++ntris;
+          accept(t, k, id);
+        }
+      } else {  // 16 images of 256x256, 2,000 triangles each, depth 2, 2 lights: 18.8 ms with the loop above, 7.6 this way
+        for (int k = 0; k < sc.T && !(ANY && __all(found)); k += 64)
+          flat_triangles<kWalkStep>(sc.tris, k, min(k + 64, sc.T), r.o, r.d, r.tmin, [&] { return r.limit; }, accept);
       }
     } else if (sc.T > 0 && sc.has_bvh && !(ANY && found)) {
       node = sc.root;
@@ -1003,51 +1053,6 @@ constexpr int kFlatWaves = 8192;    // waves of a full grid
 template <int SEGS>
 constexpr int kFlatBlock = SEGS > 1 ? 64 * SEGS : kBlock;
 
-// True where the triangle test certainly rejects a barycentric coordinate num / det (signs and sizes only,
-// before the division): below 0 by more than an underflow can hide, or above 1 by more than rounding can.
-__device__ inline bool outside(float num_signed, float det_abs) {
-  return num_signed < -1e-30f * det_abs || num_signed > 1.0001f * det_abs;
-}
-
-// Tests a wave's rays against triangle records first .. last - 1, all lanes together; accept(t, record, id)
-// for the lanes with a candidate in (tmin, limit()).
-template <class Limit, class Accept>
-__device__ __attribute__((always_inline)) inline void flat_triangles(const float4* tris, int first, int last, float3 o,
-                                                                     float3 d, float tmin, Limit limit, Accept accept) {
-  typedef __attribute__((address_space(4))) const float4 const_float4;  // written by an earlier launch only
-  auto test = [&](float4 a, float4 b, float4 c, int k) {
-    const float3 e1 = f3(b), e2 = f3(c);
-    TriTest m;
-    m.first(o, d, f3(a), e1, e2);
-    const uint32_t sign = __float_as_uint(m.det) & 0x80000000u;
-    const float ad = fabsf(m.det);
-    if (outside(__uint_as_float(__float_as_uint(m.un) ^ sign), ad)) return;
-    m.second(d, e1);
-    if (outside(__uint_as_float(__float_as_uint(m.vn) ^ sign), ad)) return;
-    if (m.det == 0.0f) return;
-    const float inv = 1.0f / m.det;
-    const float u = m.un * inv;
-    if (!(u >= 0.0f && u <= 1.0f)) return;
-    const float t = m.t(e2, inv, u, tmin, limit());
-    if (t < INFINITY) accept(t, k, __float_as_int(a.w));
-  };
-  // kStep records are loaded at a time, so a wave waits once for all of them
-  constexpr int kStep = SRT_FLAT_STEP;
-  const const_float4* recs = (const const_float4*)tris;
-  int k = first;
-  for (; k + kStep <= last; k += kStep) {
-    float4 r[3 * kStep];
-#pragma unroll
-    for (int j = 0; j < 3 * kStep; ++j) r[j] = ((const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k)))[j];
-#pragma unroll
-    for (int j = 0; j < kStep; ++j) test(r[3 * j], r[3 * j + 1], r[3 * j + 2], k + j);
-  }
-  for (; k < last; ++k) {
-    const float4* r = (const float4*)(recs + 3 * __builtin_amdgcn_readfirstlane(k));
-    test(r[0], r[1], r[2], k);
-  }
-}
-
 // One of `of` equal shares of a scene's primitives.
 struct Part {
   int k, of;
@@ -1068,7 +1073,7 @@ __device__ __attribute__((always_inline)) inline Best flat_closest(const DevScen
     const int key = sc.T + sc.S + k;
     accept(plane_t(p, o, d, tmin, next_up(best.t)), key, key);
   });
-  flat_triangles(sc.tris, part.first(sc.T), part.last(sc.T), o, d, tmin, [&] { return next_up(best.t); }, accept);
+  flat_triangles<kFlatStep>(sc.tris, part.first(sc.T), part.last(sc.T), o, d, tmin, [&] { return next_up(best.t); }, accept);
   return best;
 }
 
@@ -1090,7 +1095,7 @@ __device__ __attribute__((always_inline)) inline bool flat_occluded(const DevSce
               [&](float4 p, int k) { accept(plane_t(p, o, d, kSecondaryTmin, dist), sc.T + sc.S + k, 0); });
   });
   steps(sc.T, [&](int first, int last) {
-    flat_triangles(sc.tris, first, last, o, d, kSecondaryTmin, [&] { return dist; }, accept);
+    flat_triangles<kFlatStep>(sc.tris, first, last, o, d, kSecondaryTmin, [&] { return dist; }, accept);
   });
   return found;
 }

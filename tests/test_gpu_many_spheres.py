@@ -76,3 +76,25 @@ def test_walks_beside_a_tree(torch_cuda, S, P, T, size, accel):
     _same(torch_cuda, gs, mono_camera(center=(0, 2, 0), width=size[0], height=size[1], depth=3, baseline=0.065,
                                       convergence=5.0), (S, P, T, size))
     gs.close()
+
+
+# batches of scenes without a tree, and of both kinds: a batch walks in the traversal's own kernel
+@pytest.mark.parametrize("sizes", [[(40, 30)] * 4, [(8, 8)] * 9, [(1, 1), (70, 51), (5, 3), (16, 16)]])
+@pytest.mark.parametrize("brute", [False, True])
+def test_batches_of_scenes_without_a_tree(torch_cuda, sizes, brute):
+    from paper_1702_01530_amd.stereo import GpuScene, render_batch, render_stereo
+    torch = torch_cuda
+    kinds = [(3, 1, 130, "none"), (70, 2, 0, "none"), (0, 0, 67, "none"), (4, 5, 300, "ploc")]
+    scenes = [GpuScene(_scene(*k[:3]), accel=k[3]) for k in kinds]
+    pairs = [(scenes[i % 4], mono_camera(center=(0, 2, 0.1 * i), width=w, height=h, depth=i % 4, baseline=0.065,
+                                         convergence=5.0)) for i, (w, h) in enumerate(sizes)]
+    print(f"[spheres] batch {sizes[:4]} brute={brute}", flush=True)
+    outs = render_batch(pairs, brute_force=brute)
+    torch.cuda.synchronize()
+    for i, (gs, cam) in enumerate(pairs):
+        one = render_stereo(gs, cam, path_ids=True, count_work=True)
+        torch.cuda.synchronize()
+        for k in ("radiance", "hit_t", "hit_prim"):
+            assert torch.equal(one[k], outs[i][k]), (i, k)
+    for gs in scenes:
+        gs.close()
