@@ -15,6 +15,9 @@ struct SceneSize {
 // Primitives that every ray of the scene is tested against.
 inline int64_t walked(const SceneSize& s) { return int64_t(s.S) + s.P + (s.flat ? s.T : 0); }
 
+// The fewest rays a traversal wave starts with, as a power of two: one image, or a batch of them.
+constexpr int min_rays_log2(bool batch) { return batch ? 0 : 3; }
+
 // Whether the waves of a workgroup share a batch's walk (k_trace_flat).  A launch of few rays lasts as long as one walk;
 // a full one gains nothing from the shares and pays for joining them.  64x48, depth 0, 1 light: 120 triangles 75 us
 // alone and 51 shared, 511: 160 and 63; 1920x1080: 394 and 646, 1371 and 1647.  256x256, depth 4, 4 lights: 256 spheres

@@ -71,10 +71,6 @@ static_assert(kCoopRays >= 0 && kCoopRays <= 64, "one slot per lane at most");
 #define SRT_COOP_SHARE 8
 #endif
 constexpr int kCoopShare = SRT_COOP_SHARE;  // a hand-over needs at least 1/kCoopShare of the busy lanes in pairs
-#ifndef SRT_MIN_RAYS_LOG2
-#define SRT_MIN_RAYS_LOG2 3
-#endif
-constexpr int kMinRaysLog2 = SRT_MIN_RAYS_LOG2;  // smallest batch of rays a wave starts with
 
 // ---------------------------------------------------------------------------------------------
 // Small vector helpers
@@ -661,7 +657,7 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
           ++ntris;
           accept(t, k, id);
         }
-      } else {  // 16 images of 256x256, 2,000 triangles each, depth 2, 2 lights: 18.8 ms with the loop above, 7.6 this way
+      } else {  // 16 images of 256x256, 2,000 triangles each, depth 2, 2 lights: 18.8 ms with the loop above, 5.7 this way
         for (int k = 0; k < sc.T && !(ANY && __all(found)); k += 64)
           flat_triangles<kWalkStep>(sc.tris, k, min(k + 64, sc.T), r.o, r.d, r.tmin, [&] { return r.limit; }, accept);
       }
@@ -797,6 +793,32 @@ __device__ __attribute__((always_inline)) inline void traverse(const DevScene& s
   }
 }
 
+// The same for one lane's ray in a scene without a tree, where the wave's rays are of several scenes: each walk would
+// wait for the ones before it (4 images of 64x64 over scenes of 200 spheres, depth 2: 306 us that way, 282 so).
+template <bool ANY, bool COUNT, class Commit>
+__device__ __attribute__((always_inline)) inline void walk_alone(const DevScene& sc, Ray r, uint32_t& ntris,
+                                                                 Commit commit) {
+  Best best{INFINITY, -1, 0x7fffffff};
+  auto accept = [&](float t, int key, int id) {
+    if (key == r.exclude || !(t < INFINITY)) return false;
+    if (ANY || t < best.t || (t == best.t && id < best.id)) best = Best{t, key, id};
+    if (!ANY) r.limit = next_up(best.t);
+    return ANY;
+  };
+  bool found = false;
+  for (int k = 0; k < sc.S && !found; ++k)
+    found = accept(sphere_t(sc.spheres[k], r.o, r.d, r.tmin, r.limit), sc.T + k, sc.T + k);
+  for (int k = 0; k < sc.P && !found; ++k)
+    found = accept(plane_t(sc.planes[k], r.o, r.d, r.tmin, r.limit), sc.T + sc.S + k, sc.T + sc.S + k);
+  for (int k = 0; k < sc.T && !found; ++k) {
+    int id;
+    const float t = tri_t(sc.tris, k, r.o, r.d, r.tmin, r.limit, &id);
+    if (COUNT) ++ntris;
+    found = accept(t, k, id);
+  }
+  commit(best.key, best.t);
+}
+
 __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
   // wave reduction, one 64-bit atomic per wave
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -806,7 +828,7 @@ __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
 // ---------------------------------------------------------------------------------------------
 // k_trace: closest-hit rays of depth `depth` and shadow rays of depth `depth - 1` in one
 // persistent grid.  The work space is [closest rays | shadow rays of light 0 | light 1 | ...],
-// each range padded to a multiple of 64 so that every wave batch is one kind of ray.
+// each range padded to whole batches so that every wave batch is one kind of ray.
 // ---------------------------------------------------------------------------------------------
 
 // Traversal occupancy: the traversal kernels are held to kTraceWaves waves per SIMD, a budget of
@@ -827,9 +849,47 @@ __device__ __attribute__((always_inline)) inline const KArgs& kernel_args() {
   return *(const KArgs*)p;
 }
 
-// Calls body(item, mine) for each item that lanes of this wave hold, with `mine` marking its lanes; every
-// lane makes the call.  The item is the same for the whole wave, so its fields are scalar loads.  Queue
-// entries are in path order within a shading block's run, so nearly every wave holds one item.
+// Calls body(item, mine) for each scene that lanes of this wave hold, with an item of it and `mine` marking its
+// lanes; every lane makes the call.  The item is the same for the whole wave, so its fields are scalar loads.  Queue
+// entries are in path order within a shading block's run, so nearly every wave holds one item.  In a wave that holds
+// several, lanes whose scene has no tree call alone(item) instead, all at once.
+template <bool MULTI, class Body, class Alone>
+__device__ __attribute__((always_inline)) inline void each_scene(const KArgs& a, bool valid, int k, Body body,
+                                                                 Alone alone) {
+  if (!MULTI) {
+    body(a.one, valid);
+    return;
+  }
+  typedef __attribute__((address_space(4))) const DevItem item_t;
+  uint64_t todo = __ballot(valid);
+  if (todo == 0) return;
+  if (__ballot(valid && k == __builtin_amdgcn_readlane(k, __builtin_ctzll(todo))) != todo) {
+    if (valid && (a.brute || !a.items[k].sc.has_bvh)) {
+      alone(a.items[k]);
+      valid = false;
+    }
+    todo = __ballot(valid);
+    const uintptr_t scene = valid ? reinterpret_cast<uintptr_t>(a.items[k].sc.materials) : 0;  // in its own storage
+    const int lo = int(uint32_t(scene)), hi = int(uint32_t(scene >> 32));
+    for (uint64_t left = todo; left != 0;) {  // the lanes of a scene take one item's number
+      const int from = __builtin_ctzll(left);
+      const bool same = valid && lo == __builtin_amdgcn_readlane(lo, from) && hi == __builtin_amdgcn_readlane(hi, from);
+      if (same) k = __builtin_amdgcn_readlane(k, from);
+      left &= ~__ballot(same);
+    }
+  }
+  while (todo != 0) {
+    const int k0 = __builtin_amdgcn_readlane(k, __builtin_ctzll(todo));
+    const bool mine = valid && k == k0;
+    body(*(const DevItem*)((const item_t*)a.items + k0), mine);
+    todo &= ~__ballot(mine);
+  }
+}
+
+// Calls body(item, valid) once, with the item the lane holds: its fields are scalar loads where the wave holds one item,
+// vector loads where it holds several.  One item after the other, as the traversal takes them, the entries of a batch of
+// small images took up to 64 turns (64 images of 16x16, depth 4: 68 + 56 us for the shading of depths 2 and 3, 13 this
+// way).
 template <bool MULTI, class Body>
 __device__ __attribute__((always_inline)) inline void each_item(const KArgs& a, bool valid, int k, Body body) {
   if (!MULTI) {
@@ -837,12 +897,13 @@ __device__ __attribute__((always_inline)) inline void each_item(const KArgs& a, 
     return;
   }
   typedef __attribute__((address_space(4))) const DevItem item_t;
-  for (uint64_t todo = __ballot(valid); todo != 0;) {
-    const int k0 = __builtin_amdgcn_readlane(k, __builtin_ctzll(todo));
-    const bool mine = valid && k == k0;
-    body(*(const DevItem*)((const item_t*)a.items + k0), mine);
-    todo &= ~__ballot(mine);
-  }
+  const uint64_t all = __ballot(valid);
+  if (all == 0) return;
+  const int k0 = __builtin_amdgcn_readlane(k, __builtin_ctzll(all));
+  if (__ballot(valid && k == k0) == all)
+    body(*(const DevItem*)((const item_t*)a.items + k0), valid);
+  else
+    body(a.items[valid ? k : k0], valid);
 }
 
 // 64 << kResolveLog2 entries make a batch of k_trace's.  As launches of their own the resolves of a 1080p frame of
@@ -913,11 +974,13 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
   // Work comes in batches of 64 rays, one per lane, or fewer where that still gives every wave of the grid
   // at most one batch: the wave's other lanes then share its rays from the start (see traverse).  A 641x479
   // frame of 13k triangles takes 329 us that way and 436 us in batches of 64; batches of at least 4 or 16
-  // rays instead of 8 are within 1%.
+  // rays instead of 8 are within 1%.  A batch of images goes down to one ray a wave: its last rays are of as many images,
+  // whose traversals would wait for each other (256 images of 32x32 over 32 scenes, depth 4: 553 us with 8 rays at least,
+  // 479 with one).
   const uint32_t nwaves = gridDim.x * uint32_t(kWaves);
   int blog = 6;
   if (!COUNT && kCoopRays > 0 && !a.brute)
-    while (blog > kMinRaysLog2 && (rays >> (blog - 1)) < nwaves) --blog;
+    while (blog > min_rays_log2(MULTI) && (rays >> (blog - 1)) < nwaves) --blog;
   const uint32_t nc_pad = round_up(nc, blog);
   uint32_t total = nc_pad;
   if (shadows)
@@ -964,7 +1027,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
         k = item_of<MULTI>(a, a.path_begin + base);  // a tile's paths belong to one item
       else if (MULTI && valid)
         k = item_of<MULTI>(a, a.path_begin + uint32_t(__float_as_int(a.ro[q][e].w)));
-      each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
+      auto ray = [&](const DevItem& it, bool& mine) {
         Ray r{};
         r.limit = INFINITY;
         r.tmin = depth == 0 ? 0.0f : kSecondaryTmin;
@@ -984,12 +1047,22 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
             r.exclude = __float_as_int(rd.w);
           }
         }
-        traverse<false, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, c_nodes, c_tris,
-                                     [&](int key, float t) {
-                                       const uint32_t entry = e;
-                                       global_scalar(a.hit)[entry] = make_float2(t, __int_as_float(key));
-                                     });
-      });
+        return r;
+      };
+      auto commit = [&](int key, float t) {
+        const uint32_t entry = e;
+        global_scalar(a.hit)[entry] = make_float2(t, __int_as_float(key));
+      };
+      each_scene<MULTI>(
+          a, valid, k,
+          [&](const DevItem& it, bool mine) {
+            const Ray r = ray(it, mine);
+            traverse<false, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, c_nodes, c_tris, commit);
+          },
+          [&](const DevItem& it) {
+            bool mine = true;
+            walk_alone<false, COUNT>(it.sc, ray(it, mine), c_tris, commit);
+          });
     } else {
       // ---- shadow batch: find the light whose (padded) range holds this batch
       uint32_t start = nc_pad;
@@ -1005,7 +1078,7 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
       const uint32_t owner = valid ? a.sowner[sq][size_t(l) * a.cap + i] : 0u;
       int k = 0;
       if (MULTI && valid) k = item_of<MULTI>(a, a.path_begin + (depth == 1 ? owner : a.epath[sq][owner]));
-      each_item<MULTI>(a, valid, k, [&](const DevItem& it, bool mine) {
+      auto ray = [&](const DevItem& it, bool mine) {
         Ray r{};
         r.tmin = kSecondaryTmin;
         if (mine) {
@@ -1014,13 +1087,20 @@ __global__ __launch_bounds__(kBlock) SRT_TRACE_ATTR void k_trace(KArgs a, int de
           r.exclude = __float_as_int(rec.w);
           r.d = shadow_dir(it.sc.lights, l, r.o, &r.limit);
         }
-        traverse<true, COUNT, COUNT || MULTI>(it.sc, mine, r, a.brute != 0, st, share, s_nodes, s_tris,
-                                    [&](int key, float) {
-                                      uint32_t o = owner;
-                                      asm volatile("" : "+v"(o));  // the address is formed here, not before the loop
-                                      global_scalar(a.vis[sq] + size_t(l) * a.cap)[o] = key < 0 ? 1 : 0;
-                                    });
-      });
+        return r;
+      };
+      auto commit = [&](int key, float) {
+        uint32_t o = owner;
+        asm volatile("" : "+v"(o));  // the address is formed here, not before the loop
+        global_scalar(a.vis[sq] + size_t(l) * a.cap)[o] = key < 0 ? 1 : 0;
+      };
+      each_scene<MULTI>(
+          a, valid, k,
+          [&](const DevItem& it, bool mine) {
+            traverse<true, COUNT, COUNT || MULTI>(it.sc, mine, ray(it, mine), a.brute != 0, st, share, s_nodes, s_tris,
+                                                  commit);
+          },
+          [&](const DevItem& it) { walk_alone<true, COUNT>(it.sc, ray(it, true), s_tris, commit); });
     }
   }
   if (st.overflow) atomicOr(&a.ctr->error, 1u);
@@ -1832,7 +1912,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
       return (ra.path_count + (int64_t(kWaves) << log2n) - 1) / (int64_t(kWaves) << log2n);
     };
     if (!flat && kCoopRays > 0) {
-      while (blog > kMinRaysLog2 && (ra.path_count >> (blog - 1)) < int64_t(p.grid_trace) * kWaves) --blog;
+      while (blog > min_rays_log2(false) && (ra.path_count >> (blog - 1)) < int64_t(p.grid_trace) * kWaves) --blog;
       if (blog == 6 && blocks_of(6) > resident && 2 * blocks_of(6) < 3 * resident) blog = 5;
     }
     const int dynamic = blocks_of(blog) > p.grid_trace || (blog >= 5 && blocks_of(blog) > resident) ? 1 : 0;
@@ -1873,7 +1953,7 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
         e = launch(k_trace_flat<1>, gtrace(d, kFlatBlock<1>, kFlatWaves * 64 / kFlatBlock<1>), a, d, s, timer,
                    RT_STAGE_TRACE, kFlatBlock<1>);
     } else {
-      const unsigned grid = gtrace(d, int64_t(kWaves) << kMinRaysLog2, p.grid_trace);
+      const unsigned grid = gtrace(d, int64_t(kWaves) << min_rays_log2(multi), p.grid_trace);
       if (multi)
         e = count ? launch(k_trace<true, true>, grid, a, d, s, timer, RT_STAGE_TRACE)
                   : launch(k_trace<false, true>, grid, a, d, s, timer, RT_STAGE_TRACE);

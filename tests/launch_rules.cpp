@@ -35,7 +35,13 @@ static void spheres_beside_a_tree() {
   claim(!path_wins({13000, 0, 0, 8, false}, paths), "rays count as before");
 }
 
+static void batches() {
+  claim(min_rays_log2(false) == 3, "a wave of one image starts with eight rays or more");
+  claim(min_rays_log2(true) == 0, "of a batch with one or more: each may be of another scene");
+}
+
 int main() {
+  batches();
   spheres_are_work();
   spheres_beside_a_tree();
   return failures ? 1 : 0;
