@@ -319,6 +319,14 @@ rt_status current_device(int* dev) {
   return RT_OK;
 }
 
+// The grids of a single render.
+void set_grids(srt::RenderPlan* plan, int dev) {
+  const int per_cu = current_tuning().trace_blocks_per_cu;
+  plan->grid_trace = srt::resident_blocks(dev, per_cu, srt::GridOf::trace);
+  plan->grid_path[0] = srt::resident_blocks(dev, per_cu, srt::GridOf::path_flat);
+  plan->grid_path[1] = srt::resident_blocks(dev, per_cu, srt::GridOf::path_tree);
+}
+
 // Renders the frame in passes of `chunk` paths with the workspace laid out by `plan`.
 rt_status render_passes(const rt_scene_s* scene, const rt_stereo_camera* cam, const rt_stereo_output* out, char* ws,
                         const srt::RenderPlan& plan, int64_t chunk, uint32_t flags, hipStream_t stream,
@@ -369,7 +377,7 @@ rt_status render_one(const rt_scene_s* scene, const rt_stereo_camera* cam, const
   int dev = 0;
   rt_status st = check_scene_device(scene, &dev);
   if (st != RT_OK) return st;
-  plan.grid_trace = srt::trace_grid_size(dev, current_tuning().trace_blocks_per_cu, false);
+  set_grids(&plan, dev);
   return render_passes(scene, cam, out, ws, plan, chunk, flags, stream, copy_stream, timer);
 }
 
@@ -421,7 +429,7 @@ rt_status prepare_batch(const rt_batch_item* items, int32_t n, void* workspace, 
   const int64_t chunk = chunk_for(total, lmax, workspace_bytes - tbytes, &plan);
   if (chunk == 0) return fail(RT_ERR_BUFFER_TOO_SMALL, "workspace of %zu bytes is too small", workspace_bytes);
   const rt_tuning tune = current_tuning();
-  plan.grid_trace = srt::trace_grid_size(dev, tune.trace_blocks_per_cu, true);
+  plan.grid_trace = srt::resident_blocks(dev, tune.trace_blocks_per_cu, srt::GridOf::trace_batch);
   char* ws = static_cast<char*>(workspace);
   bp->dtable = reinterpret_cast<srt::DevItem*>(ws);
   srt::RenderArgs& ra = bp->ra;
@@ -665,13 +673,15 @@ rt_status rt_render_stereo_noalloc(rt_scene scene, const rt_stereo_camera* camer
   // The spill area is sized to this scene's tree and the traversal grid actually launched, so the
   // fixed scratch leaves the most room for the pass's queues.
   srt::RenderPlan plan;
-  const int grid = srt::trace_grid_size(dev, current_tuning().trace_blocks_per_cu, false);
+  srt::RenderPlan grids;
+  set_grids(&grids, dev);
   const int64_t chunk = chunk_for(total_paths(camera), scene->dev.L, RT_NOALLOC_SCRATCH_BYTES, &plan,
-                                  srt::spill_entries_for_depth(scene->info.bvh_depth), grid * srt::kTraceBlock);
+                                  srt::spill_entries_for_depth(scene->info.bvh_depth),
+                                  grids.grid_trace * srt::kTraceBlock);
   if (chunk == 0)
     return fail(RT_ERR_BUFFER_TOO_SMALL, "the smallest pass for %d lights and tree depth %d does not fit the %zu-byte "
                 "device scratch", scene->dev.L, scene->info.bvh_depth, size_t(RT_NOALLOC_SCRATCH_BYTES));
-  plan.grid_trace = grid;
+  set_grids(&plan, dev);
   s = render_passes(scene, camera, out, ws, plan, chunk, flags, static_cast<hipStream_t>(stream),
                     static_cast<hipStream_t>(copy_stream), nullptr);
   if (s != RT_OK) return s;

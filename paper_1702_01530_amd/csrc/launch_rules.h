@@ -53,4 +53,31 @@ inline bool path_wins(const SceneSize& s, int64_t paths) {
   return paths * (1 + s.L) <= (s.T <= kPathSmallTree ? 5000000 : 2500000);
 }
 
+// How k_path's waves take a frame's paths: a batch of 64 a wave, or of fewer where that still leaves every wave of the
+// full grid at most one.  With more batches than waves run at once, those take them one by one: in fixed shares, or left
+// to the dispatcher, the last ones decide (641x479, 13k triangles: 251 us in fixed shares, 235 so; spheres at 1080p 134
+// and 106).  Where each wave gets one batch of 64 and a few get two, batches of 32 are evener (480x360: 212 and 183 us);
+// from 1.5 batches a wave on they no longer are (640x480: 222 and 239).
+struct PathLaunch {
+  int log2n;     // a wave's batch is 2^log2n paths
+  bool dynamic;  // waves take one batch after another
+  int64_t grid;  // workgroups
+};
+
+// `full` bounds the grid (each of its threads has a part of the traversal's spill area); `resident` workgroups run at
+// once, by k_path's own occupancy and the limit of workgroups per CU.  Taken as 5/8 of the traversal's, that limit at 1
+// left 96 of 256 CUs without work (641x479, 13k triangles: 755 us, 543 so; spheres at 1080p 520 and 376).
+inline PathLaunch path_launch(bool flat, int64_t paths, int waves, int64_t full, int64_t resident) {
+  PathLaunch l{6, false, 0};
+  resident = std::max<int64_t>(1, std::min(resident, full));
+  auto blocks = [&](int log2n) { return (paths + (int64_t(waves) << log2n) - 1) / (int64_t(waves) << log2n); };
+  if (!flat) {
+    while (l.log2n > min_rays_log2(false) && (paths >> (l.log2n - 1)) < full * waves) --l.log2n;
+    if (l.log2n == 6 && blocks(6) > resident && 2 * blocks(6) < 3 * resident) l.log2n = 5;
+  }
+  l.dynamic = blocks(l.log2n) > full || (l.log2n >= 5 && blocks(l.log2n) > resident);
+  l.grid = std::min(l.dynamic ? resident : full, blocks(l.log2n));
+  return l;
+}
+
 }  // namespace srt

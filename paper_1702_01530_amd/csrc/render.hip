@@ -1502,8 +1502,6 @@ __global__ __launch_bounds__(kShadeBlock) __attribute__((amdgpu_waves_per_eu(MUL
 #define SRT_PATH_WAVES 5
 #endif
 
-constexpr int kFlatPathWaves = 6;  // waves per SIMD that k_path<false>'s registers allow
-
 template <bool TREE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH_WAVES))) void k_path(
     KArgs a, int blog, int dynamic, int64_t* out) {
@@ -1783,29 +1781,29 @@ hipError_t copy_to_host(const void* src, void* host_dst_device_view, size_t byte
   return hipGetLastError();
 }
 
-int trace_grid_size(int device, int blocks_per_cu, bool multi) {
-  // per device (the current one, which the occupancy query reads): CUs and workgroups per CU of the
-  // single-scene and batch traversal kernels, looked up once; renders may come from several threads
+int resident_blocks(int device, int blocks_per_cu, GridOf kernel) {
+  // per device (the current one, which the occupancy query reads): CUs and each kernel's workgroups per CU, looked up
+  // once; renders may come from several threads
   static std::mutex lock;
-  static int cached_cus[64] = {0}, cached_occ[64][2] = {{0}};
+  static int cached_cus[64] = {0}, cached_occ[64][4] = {{0}};
   if (device < 0 || device >= 64) return kMaxTraceBlocks;
   std::lock_guard<std::mutex> guard(lock);
   if (!cached_cus[device]) {
     hipDeviceProp_t prop;
     int cus = 256;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess) cus = prop.multiProcessorCount;
-    int occ[2] = {0, 0};
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[0], k_trace<false, false>, kBlock, 0) != hipSuccess ||
-        occ[0] <= 0)
-      occ[0] = 4;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], k_trace<false, true>, kBlock, 0) != hipSuccess ||
-        occ[1] <= 0)
-      occ[1] = 4;
-    cached_occ[device][0] = occ[0];
-    cached_occ[device][1] = occ[1];
+    auto look = [&](GridOf which, const void* f) {
+      int occ = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, kBlock, 0) != hipSuccess || occ <= 0) occ = 4;
+      cached_occ[device][int(which)] = occ;
+    };
+    look(GridOf::trace, reinterpret_cast<const void*>(k_trace<false, false>));
+    look(GridOf::trace_batch, reinterpret_cast<const void*>(k_trace<false, true>));
+    look(GridOf::path_flat, reinterpret_cast<const void*>(k_path<false>));
+    look(GridOf::path_tree, reinterpret_cast<const void*>(k_path<true>));
     cached_cus[device] = cus;
   }
-  int per_cu = cached_occ[device][multi ? 1 : 0];
+  int per_cu = cached_occ[device][int(kernel)];
   if (blocks_per_cu > 0) per_cu = std::min(per_cu, blocks_per_cu);
   return std::min(kMaxTraceBlocks, cached_cus[device] * per_cu);
 }
@@ -1901,22 +1899,9 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
   // signatures nor the timer, whose stages are the queue kernels'.
   const bool whole = ra.path_begin == 0 && ra.path_count == ra.frame_paths;
   if (!multi && !count && !ids && !timer && whole && path_wins(size, ra.path_count)) {
-    // A batch of 64 paths a wave, or of fewer where that still leaves every wave of the full grid at most one.  With more
-    // batches than waves run at once (k_path's registers allow resident blocks), those take them one by one: in fixed
-    // shares, or left to the dispatcher, the last ones decide (641x479, 13k triangles: 251 us in fixed shares, 235 so;
-    // spheres at 1080p 134 and 106).  Where each wave gets one batch of 64 and a few get two, batches of 32 are evener
-    // (480x360: 212 and 183 us); from 1.5 batches a wave on they no longer are (640x480: 222 and 239).
-    int blog = 6;
-    const int resident = std::max(1, p.grid_trace * (flat ? kFlatPathWaves : SRT_PATH_WAVES) / kTraceWaves);
-    auto blocks_of = [&](int log2n) {
-      return (ra.path_count + (int64_t(kWaves) << log2n) - 1) / (int64_t(kWaves) << log2n);
-    };
-    if (!flat && kCoopRays > 0) {
-      while (blog > min_rays_log2(false) && (ra.path_count >> (blog - 1)) < int64_t(p.grid_trace) * kWaves) --blog;
-      if (blog == 6 && blocks_of(6) > resident && 2 * blocks_of(6) < 3 * resident) blog = 5;
-    }
-    const int dynamic = blocks_of(blog) > p.grid_trace || (blog >= 5 && blocks_of(blog) > resident) ? 1 : 0;
-    const unsigned grid = unsigned(std::min<int64_t>(dynamic ? resident : p.grid_trace, blocks_of(blog)));
+    const PathLaunch l = path_launch(flat, ra.path_count, kWaves, p.grid_trace, p.grid_path[flat ? 0 : 1]);
+    const int blog = l.log2n, dynamic = l.dynamic ? 1 : 0;
+    const unsigned grid = unsigned(l.grid);
     if (dynamic) {
       k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
       if ((e = hipGetLastError()) != hipSuccess) return e;

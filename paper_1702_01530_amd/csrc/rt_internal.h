@@ -164,13 +164,15 @@ struct RenderPlan {
       contrib_off[2], vis_off[2], gstack_off;
   size_t bytes;
   int grid_trace;     // persistent workgroups for the traversal kernels
+  int grid_path[2];   // workgroups of a small frame's launch that run at once: without a tree, with one
   int stack_entries;  // traversal-stack spill entries per lane
   int stack_threads;  // traversal threads the spill area covers (at least grid_trace x 256)
 };
 
-// Persistent traversal workgroups: CUs x min(occupancy limit of the single or batch kernel,
-// blocks_per_cu if > 0).
-int trace_grid_size(int device, int blocks_per_cu, bool multi);
+// Workgroups of a kernel that run at once: CUs x min(its occupancy limit, blocks_per_cu if > 0).  The traversal
+// kernels' are their persistent grids.
+enum class GridOf { trace, trace_batch, path_flat, path_tree };
+int resident_blocks(int device, int blocks_per_cu, GridOf kernel);
 // stack_entries <= 0: the most any tree the build accepts needs; stack_threads <= 0: the largest grid.
 size_t plan_render(int64_t chunk_paths, int32_t num_lights, int grid_trace, RenderPlan* plan, int stack_entries = 0,
                    int stack_threads = 0);

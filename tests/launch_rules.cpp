@@ -40,7 +40,27 @@ static void batches() {
   claim(min_rays_log2(true) == 0, "of a batch with one or more: each may be of another scene");
 }
 
+static void small_frames() {
+  const int waves = 4;
+  bool covers = true, bounded = true;
+  for (bool flat : {false, true})
+    for (int64_t full : {1, 255, 256, 768, 2048})
+      for (int64_t resident : {0, 1, 256, 1280, 1536, 4096})
+        for (int64_t paths = 1; paths < 20000000; paths = paths * 5 / 4 + 127) {
+          const PathLaunch l = path_launch(flat, paths, waves, full, resident);
+          covers = covers && (l.dynamic || (l.grid * waves << l.log2n) >= paths);
+          bounded = bounded && l.grid >= 1 && l.grid <= full && l.log2n >= 3 && l.log2n <= 6;
+        }
+  claim(covers, "a launch that is not dynamic has a wave for every batch");
+  claim(bounded, "grids hold at least one workgroup and no more than the spill area has room for");
+  const int64_t frame = int64_t(81) * 60 * 128;  // 641x479
+  claim(path_launch(false, frame, waves, 256, 256).grid == 256, "one workgroup per CU is one on every CU");
+  claim(path_launch(false, frame, waves, 2048, 1280).grid == 1280 && path_launch(false, frame, waves, 2048, 1280).dynamic,
+        "a full grid has what is resident");
+}
+
 int main() {
+  small_frames();
   batches();
   spheres_are_work();
   spheres_beside_a_tree();
