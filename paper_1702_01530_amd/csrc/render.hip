@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -159,6 +161,7 @@ struct KArgs {
   int32_t brute;
   int32_t trace_threads;  // threads in the persistent traversal grid (gstack stride)
   int32_t resolve;        // k_trace of depth d also adds the lights' terms of depth d - 2
+  unsigned long long launch;  // k_path: the launch's number
 };
 // Kernels take KArgs by value as their first argument, so its bytes start the kernel-argument
 // segment (kernel_args reads them there).
@@ -1666,7 +1669,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
       if (blockIdx.x == 0) atomicAdd(&sum[RT_COUNT_PRIMARY], 2ull * a.one.cam.W * a.one.cam.H);
       if (c.x) atomicAdd(&sum[RT_COUNT_REFLECTION], c.x);
       if (c.y) atomicAdd(&sum[RT_COUNT_SHADOW], c.y);
-      if (c.z) atomicAdd(&sum[RT_COUNT_ERRORS], 1ull);
+      // one error a launch: the first block to leave the launch's number in the workspace adds it
+      const KArgs& a = kernel_args();
+      if (c.z && atomicExch(&a.ctr->stopped, a.launch) != a.launch) atomicAdd(&sum[RT_COUNT_ERRORS], 1ull);
     } else {
       reinterpret_cast<uint4*>(a.ctr)[blockIdx.x] = c;  // for k_path_finish, in the counters' bytes
     }
@@ -1675,6 +1680,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SRT_PATH
 static_assert(offsetof(Counters, trace_work) + sizeof(Counters::trace_work) / (RT_MAX_DEPTH + 2) * (RT_MAX_DEPTH + 1) >=
                   kMaxTraceBlocks * sizeof(uint4),
               "the blocks' counts end before the work counters in use");
+static_assert(offsetof(Counters, stopped) >= kMaxTraceBlocks * sizeof(uint4), "... and before the launch's number");
 
 // Adds the counts of k_path's blocks where they do not do it themselves.
 __global__ __launch_bounds__(kBlock) void k_path_finish(const uint4* counts, int blocks, int64_t primary, int64_t* out) {
@@ -1756,6 +1762,20 @@ __global__ __launch_bounds__(kBlock) void k_copy_to_host4(const uint32_t* __rest
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// A number that no other launch has, of this process or of one that used the memory before; never 0.
+unsigned long long launch_number() {
+  static std::atomic<unsigned long long> next{
+      static_cast<unsigned long long>(std::chrono::system_clock::now().time_since_epoch().count())};
+  return (2 * next.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
 
 template <typename K>
 hipError_t launch(K kernel, unsigned grid, const KArgs& a, int depth, hipStream_t s, TimerImpl* timer, int stage,
@@ -1902,7 +1922,10 @@ hipError_t render_chunk(const RenderArgs& ra, hipStream_t s, TimerImpl* timer) {
     const PathLaunch l = path_launch(flat, ra.path_count, kWaves, p.grid_trace, p.grid_path[flat ? 0 : 1]);
     const int blog = l.log2n, dynamic = l.dynamic ? 1 : 0;
     const unsigned grid = unsigned(l.grid);
-    if (dynamic) {
+    // The workspace holds anything before the launch, but not its number.  A captured launch has one number for all its
+    // replays, so those clear it.
+    a.launch = launch_number();
+    if (dynamic || (!flat && ra.ray_counts && capturing(s))) {
       k_reset<<<1, kResetBlock, 0, s>>>(a.ctr);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }

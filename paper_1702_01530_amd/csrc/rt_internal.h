@@ -111,6 +111,7 @@ struct Counters {
   uint32_t primary;                                        // valid primary paths
   uint32_t error;                                          // consistency-check hits
   unsigned long long work[4];                              // node visits / tri tests (closest, shadow)
+  unsigned long long stopped;                              // the number of the last k_path launch that stopped a ray
 };
 
 // Tile order of paths: a tile of 8x8 pixels of the left eye, then the same tile of the right eye.
