@@ -1,5 +1,8 @@
 // The merge-partner rule of the clustering tree builder (locally-ordered clustering over the Morton
-// order, Meister and Bittner 2018), shared by the build kernel and a host-side check of its rounds.
+// order, Meister and Bittner 2018).  ploc_partner states it.  The build kernels search in forms of
+// their own (a position's candidates split over lanes, or each area computed once for both of its
+// clusters) and share the area and the exception; whole trees made with ploc_partner on the host
+// are compared with theirs, and its rounds are checked to merge on inputs full of ties.
 //
 // Plain C++: the including translation unit defines SRT_HD (e.g. `__host__ __device__`) before the
 // include to make the functions callable from kernels; a host-only build leaves it empty.  V is any
