@@ -558,12 +558,11 @@ __device__ inline void dp_node(int64_t n, int4* made, const float4* nodebox, con
 __global__ __launch_bounds__(kBlock) void k_refit(int4* made, const int32_t* __restrict__ parent,
                                                   const float4* __restrict__ leaf_lo, const float4* __restrict__ leaf_hi,
                                                   const uint32_t* __restrict__ sorted_ids, float4* nodebox,
-                                                  uint32_t* flags, int64_t n, int32_t* __restrict__ max_depth,
-                                                  uint32_t* __restrict__ status, float4* dp_cost) {
+                                                  uint32_t* flags, int64_t n, uint32_t* __restrict__ status,
+                                                  float4* dp_cost) {
   int64_t leaf = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (leaf >= n) return;
   int node = parent[n - 1 + leaf];
-  int depth = 1;
   for (int guard = 0; guard < 256; ++guard) {
     if (node < 0 || node >= n - 1) {  // corrupt parent link: report instead of reading out of bounds
       atomicOr(status, 16u);
@@ -592,17 +591,6 @@ __global__ __launch_bounds__(kBlock) void k_refit(int4* made, const int32_t* __r
     if (node == 0) break;
     node = parent[node];
   }
-  // depth of this leaf: count ancestors (read-only walk over the parent links)
-  int nd = parent[n - 1 + leaf];
-  while (nd != 0 && depth < 256) {
-    nd = parent[nd];
-    if (nd < 0 || nd >= n - 1) {
-      atomicOr(status, 16u);
-      return;
-    }
-    ++depth;
-  }
-  atomicMax(max_depth, depth);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -633,9 +621,8 @@ constexpr int kPlocRadius = SRT_PLOC_RADIUS;
 // What the build's kernels tell each other and, at its end, the host (the scratch's first words).
 struct BuildState {
   uint32_t status;    // BuildResult::status_bits
-  int32_t max_depth;  // deepest leaf of the Karras tree
   uint32_t error;     // a step that cannot happen: no merge in a round, more nodes than leaves
-  uint32_t pad;
+  uint32_t pad[2];
   struct Ploc {
     uint32_t n;     // clusters left; 1 when the tree is complete, 0 after an error
     uint32_t next;  // internal nodes not yet made: the next round's take the indices below this
@@ -1556,7 +1543,6 @@ __global__ __launch_bounds__(kWideTail) void k_wide_levels(WideArgs a, int slot)
 __global__ void k_build_init(BuildState* s, uint32_t ploc_clusters, int2* frontier0) {
   if (threadIdx.x != 0) return;
   s->status = 0;
-  s->max_depth = 0;
   s->error = 0;
   for (int k = 0; k < 2; ++k) {
     s->ploc[k] = BuildState::Ploc{ploc_clusters, ploc_clusters - 1u, 0u, 0u};
@@ -1799,8 +1785,7 @@ hipError_t build_scene_device(const rt_scene_desc* desc, const BuildPlan& plan, 
         SRT_LAUNCH_CHECK();
         k_fill<uint32_t><<<blocks_for(T - 1), kBlock, 0, stream>>>(flags, 0u, T - 1);
         SRT_LAUNCH_CHECK();
-        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(tree, parent, lo, hi, i0, nodebox, flags, T,
-                                                      &state->max_depth, status, dp_cost);
+        k_refit<<<blocks_for(T), kBlock, 0, stream>>>(tree, parent, lo, hi, i0, nodebox, flags, T, status, dp_cost);
         SRT_LAUNCH_CHECK();
       }
       WideArgs wa{};
