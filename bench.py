@@ -40,10 +40,12 @@ OPS_PER_TRI_TEST = 38
 # node record (64 B four-wide quantised, 128 B four-wide FP32), a triangle test its 48 B record.
 NODE_VISIT_BYTES = {64: 64, 128: 128}  # node record size -> bytes one visit reads
 TRI_BYTES = 48       # one triangle record test
-CLOSEST_RAY_IO = 32 + 8   # ray in (origin+path, direction+exclude) + hit out (t, key)
-ANY_RAY_IO = 32 + 1       # shadow record in + visibility byte out
+PRIMARY_RAY_IO = 16 + 8       # direction + hit (t, key) out; the ray is made in the launch
+MIRROR_RAY_IO = 32 + 8        # ray in (origin+path, direction+exclude) + hit out
+SHADOW_RAY_IO = 4 + 16 + 1    # entry and its origin+exclude in, visibility byte out
 COUNTER_SOURCES = ["paper_1702_01530_amd/csrc/render.hip", "paper_1702_01530_amd/csrc/lbvh.hip",
-                   "paper_1702_01530_amd/csrc/rt_internal.h", "paper_1702_01530_amd/csrc/ploc_rule.h"]
+                   "paper_1702_01530_amd/csrc/rt_internal.h", "paper_1702_01530_amd/csrc/launch_rules.h",
+                   "paper_1702_01530_amd/csrc/ploc_rule.h"]
 
 
 def sources_sha256(sources) -> str:
@@ -599,8 +601,8 @@ def main():
     rays = int(cnt[0] + cnt[1] + cnt[2])
     closest_rays, any_rays = int(cnt[0] + cnt[1]), int(cnt[2])
     node_visit = NODE_VISIT_BYTES.get(info["node_bytes"] // max(info["num_nodes"], 1), 0)  # 0: no BVH
-    closest_bytes = node_visit * cnt[3] + TRI_BYTES * cnt[4] + CLOSEST_RAY_IO * closest_rays
-    any_bytes = node_visit * cnt[5] + TRI_BYTES * cnt[6] + ANY_RAY_IO * any_rays
+    closest_bytes = node_visit * cnt[3] + TRI_BYTES * cnt[4] + PRIMARY_RAY_IO * cnt[0] + MIRROR_RAY_IO * cnt[1]
+    any_bytes = node_visit * cnt[5] + TRI_BYTES * cnt[6] + SHADOW_RAY_IO * any_rays
     log(f"[bench] rays/frame {rays} (primary {cnt[0]}, mirror {cnt[1]}, shadow {cnt[2]}); "
         f"closest: {cnt[3] / max(closest_rays, 1):.1f} nodes + {cnt[4] / max(closest_rays, 1):.1f} tris per ray; "
         f"shadow: {cnt[5] / max(any_rays, 1):.1f} nodes + {cnt[6] / max(any_rays, 1):.1f} tris per ray")
@@ -653,7 +655,7 @@ def main():
         f"resolve {iso['resolve'][0] / args.steps:.3f}")
 
     # per-stage device time with F frames in flight (launches overlap): its own run, since the event pair
-    # around every launch costs time of its own
+    # around every launch costs time of its own, and a timed render resolves every depth in a launch of its own
     timer = Timer()
     run_frames(args.steps, F, timer=timer.handle)
     stages = timer.read()

@@ -229,7 +229,8 @@ typedef struct rt_timer_s* rt_timer;
  * host memory (hipHostMalloc) on `copy_stream` (NULL: on `stream`) once
  * rendering is done;
  * synchronise copy_stream before reading it.  `timer` (optional) records
- * per-kernel device time (see rt_timer_read).  The workspace must be 256-byte
+ * per-kernel device time (see rt_timer_read) and chooses the launches that its
+ * stages are made of, which take longer than a render without it.  The workspace must be 256-byte
  * aligned and must not be used by another render in flight. */
 rt_status rt_render_stereo(rt_scene scene, const rt_stereo_camera* camera, const rt_stereo_output* out,
                            void* workspace, size_t workspace_bytes, uint32_t flags, void* stream,
@@ -289,8 +290,8 @@ rt_status rt_batch_graph_launch(rt_batch_graph graph, const rt_batch_item* items
 rt_status rt_batch_graph_destroy(rt_batch_graph graph);
 
 /* Launch tuning (process-wide).  Results are identical for every setting; only
- * speed changes.  trace_blocks_per_cu: persistent traversal workgroups per CU
- * (0 = as many as fit); stream_blocks: grid of the streaming launches, in units
+ * speed changes.  trace_blocks_per_cu: persistent traversal workgroups per CU,
+ * and those of a small frame's launch (0 = as many as fit); stream_blocks: grid of the streaming launches, in units
  * of 256 threads (the shading kernel's 512-thread blocks take half as many);
  * max_pass_paths: largest number of paths per pass (>= 4096).  Defaults: 0, 8192,
  * 2^25. */
@@ -350,7 +351,12 @@ typedef struct {
 } rt_timing;
 
 /* A timer records a HIP event pair around every kernel (and copy) a render
- * enqueues.  rt_timer_read waits for the recorded events, adds their elapsed
+ * enqueues.  A render with a timer keeps the stages apart: a small frame goes
+ * through the traversal, shading and resolve launches of each depth, which one
+ * launch does without a timer, and in less time, and every depth's
+ * lights' terms are added by a resolve launch, where otherwise the traversal of
+ * two depths on adds them.  So the sum of the stages is not the time of a render
+ * without a timer; the images are the same to the bit.  rt_timer_read waits for the recorded events, adds their elapsed
  * times into *out (which it does not clear first) and forgets them. */
 rt_status rt_timer_create(rt_timer* out);
 rt_status rt_timer_destroy(rt_timer timer);

@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256) void k_compose(const float* __restrict__ left,
   }
 }
 
-// Four pixels a thread: three 16-byte loads an eye and one 16-byte store, with the row from the grid instead
-// of a 64-bit division a pixel.  Needs 16-byte aligned pointers and, side by side, rows of whole groups (the
+// Four pixels a thread: three 16-byte loads an eye and one 16-byte store, with one 64-bit division for four pixels
+// of both eyes where there was one a pixel (side by side; the anaglyph needs none).  Needs 16-byte aligned pointers and, side by side, rows of whole groups (the
 // output's and the eyes' groups then start together); other calls take k_compose.  Bound by memory: every
 // line of both eyes is read, also for the channels an anaglyph leaves out.  3840x2160: anaglyph 41.1 -> 38.9 us
 // (232 MB, 6.0 TB/s), side by side 57.5 -> 41.7; 2,048 or 4,096 workgroups 42.1 and 40.5, loads past the

@@ -836,7 +836,7 @@ __device__ inline void add_work(Counters* ctr, int slot, uint32_t v) {
 
 // Traversal occupancy: the traversal kernels are held to kTraceWaves waves per SIMD, a budget of
 // 64 VGPRs and 20 KB of LDS a block.  The single-scene kernel meets it without spilling, the batch kernel
-// with 6 registers spilled outside the node step.  7 waves: 2258 vs 2187 us for a 1080p frame of 3.4M
+// with 4 registers spilled outside the node step.  7 waves: 2258 vs 2187 us for a 1080p frame of 3.4M
 // triangles, 7.68 vs 7.47 ms for 16 mixed pairs.  The instrumented kernels are left free.
 constexpr int kTraceWaves = SRT_TRACE_WAVES_PER_EU;
 #define SRT_TRACE_ATTR __attribute__((amdgpu_waves_per_eu(COUNT || kTraceWaves <= 0 ? 1 : kTraceWaves)))
@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(kShadeBlock) __attribute__((amdgpu_waves_per_eu(MUL
 // result.  Larger frames gain more from the queues, which fill every wave with live rays.
 // A hit's shadow rays are packed over the lights, so a wave makes as many rounds as its rays need and not one a
 // light (641x479, 13k triangles, depth 4, 2 lights: 280 us a light at a time, 257 packed, 317 by queues).
-// 256x256, depth 1, 1 light: spheres 46.3 -> 16.5 us, 100 triangles 68.4 -> 48.2.  5 waves per SIMD with 10
+// 256x256, depth 1, 1 light: spheres 46.3 -> 16.5 us, 100 triangles 68.4 -> 48.2.  5 waves per SIMD with 8
 // spilled registers; 4 without spills or 6 with 37 take 5% longer on that frame, which now takes 235 us.
 // ---------------------------------------------------------------------------------------------
 
