@@ -356,7 +356,8 @@ typedef struct {
  * launch does without a timer, and in less time, and every depth's
  * lights' terms are added by a resolve launch, where otherwise the traversal of
  * two depths on adds them.  So the sum of the stages is not the time of a render
- * without a timer; the images are the same to the bit.  rt_timer_read waits for the recorded events, adds their elapsed
+ * without a timer; the images are the same to the bit.  rt_timer_read waits
+ * for the recorded events, adds their elapsed
  * times into *out (which it does not clear first) and forgets them. */
 rt_status rt_timer_create(rt_timer* out);
 rt_status rt_timer_destroy(rt_timer timer);
