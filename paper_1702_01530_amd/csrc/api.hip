@@ -671,7 +671,8 @@ rt_status rt_render_stereo_noalloc(rt_scene scene, const rt_stereo_camera* camer
   char* ws = nullptr;
   if ((s = scratch_on_device(dev, &ws)) != RT_OK) return s;
   // The spill area is sized to this scene's tree and the traversal grid actually launched, so the
-  // fixed scratch leaves the most room for the pass's queues.
+  // fixed scratch leaves the most room for the pass's queues.  The tuning is read once: another thread may set it
+  // meanwhile, and a larger grid would write past the area.
   srt::RenderPlan plan;
   srt::RenderPlan grids;
   set_grids(&grids, dev);
@@ -681,7 +682,8 @@ rt_status rt_render_stereo_noalloc(rt_scene scene, const rt_stereo_camera* camer
   if (chunk == 0)
     return fail(RT_ERR_BUFFER_TOO_SMALL, "the smallest pass for %d lights and tree depth %d does not fit the %zu-byte "
                 "device scratch", scene->dev.L, scene->info.bvh_depth, size_t(RT_NOALLOC_SCRATCH_BYTES));
-  set_grids(&plan, dev);
+  plan.grid_trace = grids.grid_trace;
+  std::copy(grids.grid_path, grids.grid_path + 2, plan.grid_path);
   s = render_passes(scene, camera, out, ws, plan, chunk, flags, static_cast<hipStream_t>(stream),
                     static_cast<hipStream_t>(copy_stream), nullptr);
   if (s != RT_OK) return s;
